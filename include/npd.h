@@ -124,7 +124,7 @@ int npd_version(void);
 const char* npd_status_string(npd_status st);
 
 /*
- * Name of the kernel family npd_kd_loss_fwd_bwd launches for `desc` when every row is 16-byte aligned and the
+ * Name of the kernel family npd_kd_loss_fwd_bwd launches for `desc` when every tensor is 16-byte aligned and the
  * workspace npd_workspace_bytes() asks for is given ("kd_gang_kernel", "kd_cached_kernel", "kd_rows_kernel",
  * "div_rows_kernel"; "" for an invalid desc): lets a benchmark or profile say what it measured.  Static string.
  */
@@ -194,9 +194,10 @@ size_t npd_workspace_bytes(const npd_kd_desc* desc);
  * value; all sums are accumulated in fp32.  A call's results are bitwise reproducible from
  * run to run (no floating-point atomics).  Two different calls on the same data (forward only
  * vs with gradient, other strides or alignment) may sum a row in another order: their scalar
- * outputs then agree to fp32 rounding, not bit for bit.  Rows that are 16-byte aligned with
- * strides that are multiples of 8 elements take the fast kernels; anything else is handled
- * element-wise, with the same results to rounding.
+ * outputs then agree to fp32 rounding, not bit for bit.  The fast kernels take rows that begin at the
+ * same offset from a 16-byte boundary in student, teacher and gradient (tensors that are themselves
+ * 16-byte aligned and share their row pitch modulo 8 elements, whatever the pitch); anything else is
+ * handled element-wise, with the same results to rounding.
  */
 npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logits, const void* teacher_dense,
                                const int32_t* teacher_idx, const float* teacher_val, const int32_t* labels,

@@ -38,6 +38,16 @@ bool misaligned(const void* p, uintptr_t elem) { return (reinterpret_cast<uintpt
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// two tensors whose rows 0 begin at the same offset from a 16-byte boundary (an absent one agrees with any)
+bool same_offset(const void* p, const void* q) {
+  return !q || ((reinterpret_cast<uintptr_t>(p) ^ reinterpret_cast<uintptr_t>(q)) & 15u) == 0;
+}
+
+// dense teacher: student and teacher rows drift from the 16-byte boundaries alike
+bool same_pitch_offset(const npd_kd_desc& d) {
+  return d.teacher_kind != NPD_TEACHER_DENSE_BF16 || (d.student_stride - d.teacher_stride) % 8 == 0;
+}
+
 npd_status check_desc(const npd_kd_desc* d) {
   if (!d) return NPD_ERR_NULL;
   if (d->n_tokens <= 0 || d->vocab <= 0) return NPD_ERR_SHAPE;
@@ -220,11 +230,12 @@ npd_status check_kd_call(const npd_kd_desc* desc, const void* student_logits, co
   a.t_stride = d.teacher_stride;
   a.V = V;
   a.k = d.teacher_kind == NPD_TEACHER_TOPK ? d.topk : 0;
-  // 128-bit accesses need 16-byte aligned rows in every dense tensor the kernel touches
-  bool vec = aligned16(student_logits) && d.student_stride % 8 == 0;
-  if (grad_out) vec = vec && aligned16(grad_out);
-  if (teacher_dense) vec = vec && aligned16(teacher_dense) && d.teacher_stride % 8 == 0;
+  // 128-bit accesses need every dense tensor the kernel touches to have the same offset from a 16-byte boundary in
+  // each row: bases alike and pitches alike modulo 16 bytes (16-byte aligned rows are the ordinary case)
+  const bool vec = same_offset(student_logits, grad_out) && same_offset(student_logits, teacher_dense) &&
+                   (!teacher_dense || same_pitch_offset(d));
   a.nvec_s = vec ? V / 8 : 0;
+  a.ragged = !aligned16(student_logits) || d.student_stride % 8 != 0;
   a.c = (float)(1.4426950408889634 / (double)d.tau);
   a.inv_tau = 1.0f / d.tau;
   a.gscale = (float)((double)d.grad_scale / (double)d.tau);
@@ -265,9 +276,8 @@ const char* npd_kd_kernel_name(const npd_kd_desc* desc) {
   npd::KdArgs a{};
   a.T = d.n_tokens;
   a.V = d.vocab;
-  a.nvec_s = (d.student_stride % 8 == 0 && (d.teacher_kind != NPD_TEACHER_DENSE_BF16 || d.teacher_stride % 8 == 0))
-                 ? d.vocab / 8
-                 : 0;
+  a.nvec_s = same_pitch_offset(d) ? d.vocab / 8 : 0;
+  a.ragged = d.student_stride % 8 != 0;
   a.cscale = d.ce_grad_scale;
   a.divergence = d.divergence;
   a.need_lse1 = d.tau != 1.0f;

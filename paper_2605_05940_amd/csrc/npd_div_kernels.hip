@@ -25,8 +25,10 @@ __global__ __launch_bounds__(BLOCK) void div_rows_kernel(const KdArgs a) {
   __shared__ float red[4 * 3 * (BLOCK / kWave)];
   const int tid = threadIdx.x;
   const int64_t row = blockIdx.x;
-  const int V = a.V, nvec = a.nvec_s;
+  const int V = a.V;
   uint16_t* grow = GRAD ? a.g + row * a.s_stride : nullptr;
+  const RowSplit sp = row_split(a.s + row * a.s_stride, V, a.nvec_s != 0);
+  const int nvec = sp.nvec, n_edge = V - nvec * 8;
 
   if (!a.mask[row]) {  // not scored: scalars 0, gradient row zero-filled, logits never read
     if (tid == 0) {
@@ -37,16 +39,16 @@ __global__ __launch_bounds__(BLOCK) void div_rows_kernel(const KdArgs a) {
     }
     if constexpr (GRAD) {
       const uint4 z = make_uint4(0, 0, 0, 0);
-      for (int i = tid; i < nvec; i += BLOCK) reinterpret_cast<uint4*>(grow)[i] = z;
-      for (int e = nvec * 8 + tid; e < V; e += BLOCK) grow[e] = 0;
+      for (int i = tid; i < nvec; i += BLOCK) reinterpret_cast<uint4*>(grow + sp.head)[i] = z;
+      for (int j = tid; j < n_edge; j += BLOCK) grow[sp.edge_elem(j)] = 0;
     }
     return;
   }
 
   const uint16_t* srow = a.s + row * a.s_stride;
   const uint16_t* trow = a.t + row * a.t_stride;
-  const uint4* svec = reinterpret_cast<const uint4*>(srow);
-  const uint4* tvec = reinterpret_cast<const uint4*>(trow);
+  const uint4* svec = reinterpret_cast<const uint4*>(srow + sp.head);
+  const uint4* tvec = reinterpret_cast<const uint4*>(trow + sp.head);
   const float c = a.c;
   const bool lse1 = a.need_lse1 != 0;  // uniform
   const bool lse1_t = lse1 && a.tnll != nullptr;
@@ -75,7 +77,8 @@ __global__ __launch_bounds__(BLOCK) void div_rows_kernel(const KdArgs a) {
     if (lse1) acc[2].add8(xs, kLog2e);
     if (lse1_t) acc[3].add8(xt, kLog2e);
   }
-  for (int e = nvec * 8 + tid; e < V; e += BLOCK) {
+  for (int j = tid; j < n_edge; j += BLOCK) {
+    const int e = sp.edge_elem(j);
     const float xs = bf16_one(srow[e]), xt = bf16_one(trow[e]);
     acc[0].add1_cross(xs, xs - xt, c);
     acc[1].add1(xt, c);
@@ -117,9 +120,11 @@ __global__ __launch_bounds__(BLOCK) void div_rows_kernel(const KdArgs a) {
       for (int j = 0; j < 8; ++j)
         skew_elem<DIV>(__builtin_fmaf(xs[j], c, -k.Ls), __builtin_fmaf(xt[j], c, -k.Lt), k.alpha, dsum, usum);
     }
-    for (int e = nvec * 8 + tid; e < V; e += BLOCK)
+    for (int j = tid; j < n_edge; j += BLOCK) {
+      const int e = sp.edge_elem(j);
       skew_elem<DIV>(__builtin_fmaf(bf16_one(srow[e]), c, -k.Ls), __builtin_fmaf(bf16_one(trow[e]), c, -k.Lt),
                      k.alpha, dsum, usum);
+    }
     kd = block_sum<BLOCK>(dsum, red);
     kd = kd < 0.0f ? 0.0f : kd;
     k.ubar = block_sum<BLOCK>(usum, red);
@@ -144,8 +149,10 @@ __global__ __launch_bounds__(BLOCK) void div_rows_kernel(const KdArgs a) {
       for (int e = tid; e < V; e += BLOCK) grow[e] = qnan;
       return;
     }
-    for (int e = nvec * 8 + tid; e < V; e += BLOCK)
+    for (int j = tid; j < n_edge; j += BLOCK) {
+      const int e = sp.edge_elem(j);
       grow[e] = one_bf16(div_grad_elem<DIV>(bf16_one(srow[e]), bf16_one(trow[e]), k));
+    }
     for (int i = nvec - 1 - tid; i >= 0; i -= BLOCK) {
       float xs[8], xt[8], gv[8];
       unpack8(svec[i], xs);
@@ -157,7 +164,7 @@ __global__ __launch_bounds__(BLOCK) void div_rows_kernel(const KdArgs a) {
       o.y = pack_bf16(gv[2], gv[3]);
       o.z = pack_bf16(gv[4], gv[5]);
       o.w = pack_bf16(gv[6], gv[7]);
-      reinterpret_cast<uint4*>(grow)[i] = o;
+      reinterpret_cast<uint4*>(grow + sp.head)[i] = o;
     }
     if (k.ce) {  // uniform
       // the label position gets its final value once the dense stores of the whole workgroup are ordered before it

@@ -26,7 +26,9 @@ struct KdArgs {
   int64_t T;
   int64_t s_stride, t_stride;
   int32_t V, k;
-  int32_t nvec_s;      // 8-element groups of a row that are moved with 128-bit accesses (0: unaligned)
+  int32_t nvec_s;      // V / 8 where rows are moved with 128-bit accesses (a row that begins inside a 16-byte group has
+                       // that many groups or one less, see RowSplit); 0: element by element
+  int32_t ragged;      // rows begin anywhere inside a 16-byte group (all dense tensors alike)
   float c;             // log2(e) / tau
   float inv_tau;
   float gscale;        // grad_scale / tau

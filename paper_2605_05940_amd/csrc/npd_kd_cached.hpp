@@ -219,15 +219,17 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
   constexpr int SL = TEACHER == kDense ? 0 : (CT < CS - CSR ? CT : CS - CSR);
   const int tid = threadIdx.x;
   const int voff = tid * 16;
-  const int V = a.V, nvec = a.nvec_s;  // only launched with 16-byte aligned rows: nvec = V / 8
+  const int V = a.V;
   const float c = a.c;
   const bool lse1_t = LSE1 && a.tnll != nullptr;
-  // without SHORT: launched only for rows of more than (CS - 1) * CB groups, so every one of the first CS groups
-  // per thread is full except, when the row has at most CS * CB groups, the last one
+  // without SHORT: launched only for V / 8 > (CS - 1) * CB (and a row has at most one group less than that), so every
+  // one of the first CS groups per thread is full except, when the row has at most CS * CB groups, the last one
+  const int64_t row = blockIdx.x;
+  const RowSplit sp = row_split(a.s + row * a.s_stride, V, true);  // only launched with student, teacher and gradient
+  const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;  // rows at the same offset from a 16-byte boundary
   const int nit = (nvec + CB - 1) / CB;  // 128-bit groups per thread
 
   // One workgroup per row.  A row that is not scored: scalars 0, gradient row zero-filled, logits never read.
-  const int64_t row = blockIdx.x;
   if (!a.mask[row]) {
     if (tid == 0) {
       if (a.kd) a.kd[row] = 0.0f;
@@ -238,8 +240,8 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
     if constexpr (GRAD) {
       uint16_t* grow0 = a.g + row * a.s_stride;
       const uint4 z = make_uint4(0, 0, 0, 0);
-      for (int i = tid; i < nvec; i += CB) st16_stream(grow0, i, z);
-      for (int e = nvec * 8 + tid; e < V; e += CB) grow0[e] = 0;
+      for (int i = tid; i < nvec; i += CB) st16_stream(grow0 + head, i, z);
+      if (tid < n_edge) grow0[sp.edge_elem(tid)] = 0;
     }
     return;
   }
@@ -255,8 +257,12 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
     const uint16_t* srow = a.s + row * a.s_stride;
     const uint16_t* trow = TEACHER == kDense ? a.t + row * a.t_stride : nullptr;
     uint16_t* grow = GRAD ? a.g + row * a.s_stride : nullptr;
-    const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow, nvec);
-    const __amdgpu_buffer_rsrc_t rt = row_rsrc(TEACHER == kDense ? trow : srow, nvec);
+    // the whole groups of the rows
+    const uint16_t* svec = srow + head;
+    const uint16_t* tvec = TEACHER == kDense ? trow + head : nullptr;
+    uint16_t* gvec = GRAD ? grow + head : nullptr;
+    const __amdgpu_buffer_rsrc_t rs = row_rsrc(svec, nvec);
+    const __amdgpu_buffer_rsrc_t rt = row_rsrc(TEACHER == kDense ? tvec : svec, nvec);
 
     int y = -1;
     float s_y = 0.0f, t_y = 0.0f;
@@ -298,13 +304,14 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
         if (it >= CSR && it < CSR + SL) lds_t[tid * LS + (it - CSR)] = vs;
       __builtin_amdgcn_sched_barrier(0);  // keep the instruction scheduler from piling all loads up front
     }
-    // ---- sweep 1, streamed part (rows longer than the cache) and the sub-group tail
+    // ---- sweep 1, streamed part (rows longer than the cache) and the edge elements
     for (int i = CS * CB + tid; i < nvec; i += CB) {
-      const uint4 vs = ld16(srow, i);
-      const uint4 vt = TEACHER == kDense ? ld16(trow, i) : make_uint4(0, 0, 0, 0);
+      const uint4 vs = ld16(svec, i);
+      const uint4 vt = TEACHER == kDense ? ld16(tvec, i) : make_uint4(0, 0, 0, 0);
       accum8<TEACHER, LSE1, REV>(vs, vt, c, lse1_t, acc);
     }
-    for (int e = nvec * 8 + tid; e < V; e += CB) {
+    if (tid < n_edge) {
+      const int e = sp.edge_elem(tid);
       const float xs = bf16_one(srow[e]);
       if constexpr (TEACHER == kDense) {
         const float xt = bf16_one(trow[e]);
@@ -388,6 +395,7 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
     const bool ce = GRAD && a.cscale != 0.0f;                       // uniform (tau = 1 here whenever it is set)
     const bool bad_label = a.labels && (unsigned)y >= (unsigned)V;  // uniform
     Sweep2Coef k = sweep2_coef(acc[0], acc[1], c, a.gscale, a.cscale, TEACHER != kNone, TEACHER == kDense);
+    k.folded = k.folded && !a.ragged;  // rows at any offset have always had the precise form
     if constexpr (REV) {
       const float inv_z = 1.0f / acc[0].z;
       k.ra = a.gscale * a.inv_tau * inv_z;
@@ -420,11 +428,13 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
         // every element's probabilities alive for it (in scratch memory)
         asm volatile("" : "+v"(dsum), "+v"(usum));
       };
-      for (int e = nvec * 8 + tid; e < V; e += CB)
+      if (tid < n_edge) {
+        const int e = sp.edge_elem(tid);
         skew_elem<DIVK>(__builtin_fmaf(bf16_one(srow[e]), c, -Ls), __builtin_fmaf(bf16_one(trow[e]), c, -Lt), a.alpha,
                         dsum, usum);
+      }
       for (int i = (nit - 1) * CB + tid; i >= CS * CB; i -= CB)
-        if (i < nvec) accum(ld16(srow, i), ld16(trow, i));
+        if (i < nvec) accum(ld16(svec, i), ld16(tvec, i));
       walk_back([&](int it, const uint4& vs, const uint4& vt) {
         if ((!SHORT && it < CS - 1) || it * CB + tid < nvec) accum(vs, vt);
       }, false);
@@ -482,8 +492,9 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
         const uint16_t qnan = 0x7fc0;
         for (int e = tid; e < V; e += CB) grow[e] = qnan;
       } else {
-        // sub-group tail and streamed part first (read most recently), then the first CS groups backwards
-        for (int e = nvec * 8 + tid; e < V; e += CB) {
+        // edge elements and streamed part first (read most recently), then the first CS groups backwards
+        if (tid < n_edge) {
+          const int e = sp.edge_elem(tid);
           const float xs = bf16_one(srow[e]);
           if constexpr (REV)
             grow[e] = one_bf16(grad_reverse_elem(xs, bf16_one(trow[e]), k));
@@ -495,9 +506,9 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
         }
         for (int i = (nit - 1) * CB + tid; i >= CS * CB; i -= CB) {
           if (i < nvec) {
-            const uint4 vs = ld16_last(srow, i);
-            const uint4 vt = TEACHER == kDense ? ld16_last(trow, i) : make_uint4(0, 0, 0, 0);
-            st16_stream(grow, i, grad8<TEACHER, false, DIVK>(vs, vt, k));
+            const uint4 vs = ld16_last(svec, i);
+            const uint4 vt = TEACHER == kDense ? ld16_last(tvec, i) : make_uint4(0, 0, 0, 0);
+            st16_stream(gvec, i, grad8<TEACHER, false, DIVK>(vs, vt, k));
           }
         }
         if (k.folded) {  // uniform
@@ -525,7 +536,7 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
             }
             {
               const uint4 gq = grad8<TEACHER, true, DIVK>(vs, vt, k);
-              if ((!SHORT && it < CS - 1) || it * CB + tid < nvec) st16_stream(grow, it * CB + tid, gq);
+              if ((!SHORT && it < CS - 1) || it * CB + tid < nvec) st16_stream(gvec, it * CB + tid, gq);
             }
             __builtin_amdgcn_sched_barrier(0);
           }
@@ -533,9 +544,9 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
           // rows whose reference exponents are in the thousands: precise form, plain loop over the row
           for (int i = (nit < CS ? nit : CS) * CB - CB + tid; i >= 0; i -= CB) {
             if (i < nvec) {
-              const uint4 vs = ld16(srow, i);
-              const uint4 vt = TEACHER == kDense ? ld16(trow, i) : make_uint4(0, 0, 0, 0);
-              st16_stream(grow, i, grad8<TEACHER, false, DIVK>(vs, vt, k));
+              const uint4 vs = ld16(svec, i);
+              const uint4 vt = TEACHER == kDense ? ld16(tvec, i) : make_uint4(0, 0, 0, 0);
+              st16_stream(gvec, i, grad8<TEACHER, false, DIVK>(vs, vt, k));
             }
           }
         }

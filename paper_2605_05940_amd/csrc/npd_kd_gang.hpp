@@ -221,13 +221,15 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   const int64_t row = blockIdx.x / (unsigned)G;
   const int slice = (int)(blockIdx.x - (unsigned)(row * G));
   const int tid = threadIdx.x;
-  const int V = a.V, nvec = a.nvec_s;
+  const int V = a.V;
   uint16_t* grow = a.g + row * a.s_stride;
-  // This workgroup owns groups [g0, g1) -- the last slice also the sub-group tail of the row.  Boundaries inside the row
+  const RowSplit sp = row_split(grow, V, true);  // every dense row at the same offset from a 16-byte boundary
+  const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;
+  // This workgroup owns groups [g0, g1) -- the last slice also the edge elements of the row.  Boundaries inside the row
   // are moved down to the next 128-byte boundary of the gradient row's address (by `shift` groups), so that no cache
   // line is shared by two workgroups of a row; a slice is at most 7 groups longer than a.gang_groups for it.
   const bool last = slice == G - 1;
-  const int shift = (int)((reinterpret_cast<uintptr_t>(grow) >> 4) & 7u);
+  const int shift = (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
   const int b0 = slice * a.gang_groups - shift, b1 = b0 + a.gang_groups;
   const int g0 = slice == 0 ? 0 : (b0 < nvec ? b0 : nvec);
   const int g1 = last ? nvec : (b1 < nvec ? b1 : nvec);
@@ -240,9 +242,8 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       if (a.tnll) a.tnll[row] = 0.0f;
       if (a.lse) a.lse[row] = 0.0f;
     }
-    gang_zero_slice<K>(grow, g0, ng, tid);
-    if (last)
-      for (int e = nvec * 8 + tid; e < V; e += TH) grow[e] = 0;
+    gang_zero_slice<K>(grow + head, g0, ng, tid);
+    if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
     return;
   }
 
@@ -255,8 +256,8 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   // The slice as a buffer: all of a thread's groups are requested at once, unconditionally (a predicate around a load
   // makes the compiler wait for it on the spot); groups past the slice's end read as zero and are never used.  Groups
   // k < q are whole for every thread, group q belongs to the first `part` threads.
-  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + (size_t)g0 * 8, ng);
-  const __amdgpu_buffer_rsrc_t rt = row_rsrc(trow + (size_t)g0 * 8, ng);
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
+  const __amdgpu_buffer_rsrc_t rt = row_rsrc(trow + head + (size_t)g0 * 8, ng);
   const int voff = tid * 16;
   const int q = ng / TH, part = ng - q * TH;  // uniform
   uint4 sreg[K], treg[K];
@@ -273,8 +274,8 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   if (a.labels) {
     y = a.labels[row];
     if ((unsigned)y < (unsigned)V) {
-      const int gy = y >> 3;
-      own_y = (gy >= g0 && gy < g1) || (last && gy >= nvec);
+      const int gy = sp.group_of(y);
+      own_y = gy >= 0 ? gy >= g0 && gy < g1 : last;
       if (own_y) {
         s_y = bf16_one(srow[y]);
         t_y = bf16_one(trow[y]);
@@ -301,7 +302,9 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   // one multiplication each instead of unpacking and exponentiating again, and leaves p_S and p_S (u - const) in the
   // same registers, so that the gradient sweep is one multiply-add per element.  Their references get 64 bits of head
   // room: an element's exponential is kept down to 2^-62 of the thread's first group's largest.
-  constexpr float kRefBias = SKEW ? 64.0f : 100.0f;
+  // Rows at any offset keep the 32 bits of head room (and the precise gradient form) they have in the streaming
+  // kernels: smaller arguments, hence smaller rounding errors, at the price of more careful re-runs on heavy tails.
+  const float kRefBias = a.ragged ? kRefSlack : (SKEW ? 64.0f : 100.0f);
   float cp[SKEW ? K : 1][8], cv[SKEW ? K : 1][8];
   if (ng > tid) {  // (threads without a group keep their empty partials)
     const float fs = pk_max_value(pk_max_group(sreg[0])), ft = pk_max_value(pk_max_group(treg[0]));
@@ -377,21 +380,20 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     }
   }
   const float r_s_thread = acc[0].r, r_t_thread = acc[1].r;  // what this thread's cached exponentials refer to
-  if (last) {
-    for (int e = nvec * 8 + tid; e < V; e += TH) {
-      const float xs = bf16_one(srow[e]);
-      const float xt = bf16_one(trow[e]);
-      if constexpr (REV) {
-        acc[1].add1(xt, c);
-        acc[0].add1_cross(xs, xs - xt, c);
-      } else {
-        acc[1].add1_cross(xt, xt - xs, c);
-        acc[0].add1(xs, c);
-      }
-      if constexpr (LSE1) {
-        if (lse1_t) acc[3].add1(xt, kLog2e);
-        acc[2].add1(xs, kLog2e);
-      }
+  if (last && tid < n_edge) {
+    const int e = sp.edge_elem(tid);
+    const float xs = bf16_one(srow[e]);
+    const float xt = bf16_one(trow[e]);
+    if constexpr (REV) {
+      acc[1].add1(xt, c);
+      acc[0].add1_cross(xs, xs - xt, c);
+    } else {
+      acc[1].add1_cross(xt, xt - xs, c);
+      acc[0].add1(xs, c);
+    }
+    if constexpr (LSE1) {
+      if (lse1_t) acc[3].add1(xt, kLog2e);
+      acc[2].add1(xs, kLog2e);
     }
   }
 
@@ -494,11 +496,11 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (last)
-      for (int e = nvec * 8 + tid; e < V; e += TH) {
-        float p, v;
-        skew_cache<DIVK>(bf16_one(srow[e]), bf16_one(trow[e]), ks, dsum, usum, p, v);
-      }
+    if (last && tid < n_edge) {
+      const int e = sp.edge_elem(tid);
+      float p, v;
+      skew_cache<DIVK>(bf16_one(srow[e]), bf16_one(trow[e]), ks, dsum, usum, p, v);
+    }
     // workgroup totals, second post / wait, row totals -- plain sums in a fixed order
     dsum = wave_sum_dpp(dsum);
     usum = wave_sum_dpp(usum);
@@ -534,6 +536,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       ks.Av = g;
     }
   }
+  kf.folded = kf.folded && !a.ragged;
   if constexpr (REV) {
     const float inv_z = 1.0f / acc[0].z;
     kf.ra = a.gscale * a.inv_tau * inv_z;
@@ -567,7 +570,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   }
 
   // ---- sweep 2: the gradient of the slice, from the registers, last group first
-  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow) + (size_t)g0 * 16;
+  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (size_t)g0 * 16;
   auto store = [&](int k, const uint4& o) {  // the group's base is uniform, the thread adds tid * 16
     const u32x4 w = {o.x, o.y, o.z, o.w};
     __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gslice + (size_t)k * GB) + tid);
@@ -577,8 +580,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
 #pragma unroll
     for (int k = 0; k < K; ++k)
       if (k < q || (k == q && tid < part)) store(k, qnan);
-    if (last)
-      for (int e = nvec * 8 + tid; e < V; e += TH) grow[e] = 0x7fc0;
+    if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0x7fc0;
     return;
   }
   // The label position of the composite loss (Eq. 1) gets its final value from fp32, rounded once: the group that
@@ -596,11 +598,11 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       gy = grad_dense_elem(s_y, t_y, kf.p);
     const uint32_t b16 = one_bf16(gy - a.cscale);
     y_tail = (uint16_t)b16;
-    if ((y >> 3) < nvec) {
-      const int yg = (y >> 3) - g0;  // group of the slice
+    if (sp.group_of(y) >= 0) {
+      const int yg = sp.group_of(y) - g0;  // group of the slice
       k_y = yg / TH;
       if (yg - k_y * TH == tid) {
-        const int j = y & 7;
+        const int j = (y - head) & 7;
         const uint32_t keep = (j & 1) ? 0x0000ffffu : 0xffff0000u, bits = (j & 1) ? b16 << 16 : b16;
         if ((j >> 1) == 0) { y_keep.x = keep; y_bits.x = bits; }
         if ((j >> 1) == 1) { y_keep.y = keep; y_bits.y = bits; }
@@ -615,17 +617,16 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     o.z = (o.z & y_keep.z) | y_bits.z;
     o.w = (o.w & y_keep.w) | y_bits.w;
   };
-  if (last) {
-    for (int e = nvec * 8 + tid; e < V; e += TH) {
-      const float xs = bf16_one(srow[e]), xt = bf16_one(trow[e]);
-      uint16_t o;
-      if constexpr (SKEW)
-        o = one_bf16(skew_grad<DIVK>(xs, xt, ks));
-      else
-        o = one_bf16(REV ? grad_reverse_elem(xs, xt, kf) : grad_dense_elem(xs, xt, kf.p));
-      if (ce && own_y && e == y) o = y_tail;
-      grow[e] = o;
-    }
+  if (last && tid < n_edge) {
+    const int e = sp.edge_elem(tid);
+    const float xs = bf16_one(srow[e]), xt = bf16_one(trow[e]);
+    uint16_t o;
+    if constexpr (SKEW)
+      o = one_bf16(skew_grad<DIVK>(xs, xt, ks));
+    else
+      o = one_bf16(REV ? grad_reverse_elem(xs, xt, kf) : grad_dense_elem(xs, xt, kf.p));
+    if (ce && own_y && e == y) o = y_tail;
+    grow[e] = o;
   }
   if constexpr (SKEW) {
 #pragma unroll

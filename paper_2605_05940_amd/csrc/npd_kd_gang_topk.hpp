@@ -31,13 +31,16 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   const int64_t row = blockIdx.x / (unsigned)G;
   const int slice = (int)(blockIdx.x - (unsigned)(row * G));
   const int tid = threadIdx.x;
-  const int V = a.V, nvec = a.nvec_s, k_top = a.k;
+  const int k_top = a.k;
+  const int V = a.V;
   uint16_t* grow = a.g + row * a.s_stride;
-  // This workgroup owns groups [g0, g1) -- the last slice also the sub-group tail of the row.  Boundaries inside the row
+  const RowSplit sp = row_split(grow, V, true);  // every dense row at the same offset from a 16-byte boundary
+  const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;
+  // This workgroup owns groups [g0, g1) -- the last slice also the edge elements of the row.  Boundaries inside the row
   // are moved down to the next 128-byte boundary of the gradient row's address (by `shift` groups), so that no cache
   // line is shared by two workgroups of a row; a slice is at most 7 groups longer than a.gang_groups for it.
   const bool last = slice == G - 1;
-  const int shift = (int)((reinterpret_cast<uintptr_t>(grow) >> 4) & 7u);
+  const int shift = (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
   const int b0 = slice * a.gang_groups - shift, b1 = b0 + a.gang_groups;
   const int g0 = slice == 0 ? 0 : (b0 < nvec ? b0 : nvec);
   const int g1 = last ? nvec : (b1 < nvec ? b1 : nvec);
@@ -49,9 +52,8 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
       if (a.nll) a.nll[row] = 0.0f;
       if (a.lse) a.lse[row] = 0.0f;
     }
-    gang_zero_slice<K>(grow, g0, ng, tid);
-    if (last)
-      for (int e = nvec * 8 + tid; e < V; e += TH) grow[e] = 0;
+    gang_zero_slice<K>(grow + head, g0, ng, tid);
+    if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
     return;
   }
 
@@ -59,21 +61,24 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   const float c = a.c;
   if (tid == 0) gave_up = y_in_support = 0;  // ordered before their use by the barrier below
 
-  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + (size_t)g0 * 8, ng);
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
   const int voff = tid * 16;
   const int q = ng / TH, part = ng - q * TH;  // uniform
   uint4 sreg[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) sreg[k] = ld_group<GB>(rs, voff, k, true, true);
 
-  // elements [e0, e1) are this workgroup's (the last slice also owns the sub-group tail)
-  const int e0 = g0 * 8, e1 = last ? V : g1 * 8;
+  // the elements of groups [g0, g1) are this workgroup's (the last slice also owns the edge elements)
+  auto owns = [&](int e) {
+    const int ge = sp.group_of(e);
+    return ge >= 0 ? ge >= g0 && ge < g1 : last;
+  };
   int y = -1;
   bool own_y = false;
   float s_y = 0.0f;
   if (a.labels) {
     y = a.labels[row];
-    own_y = y >= e0 && y < e1 && (unsigned)y < (unsigned)V;
+    own_y = (unsigned)y < (unsigned)V && owns(y);
     if (own_y) s_y = bf16_one(srow[y]);
   }
   const bool bad_label = a.labels && (unsigned)y >= (unsigned)V;  // uniform
@@ -90,7 +95,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
     tt.add1(vrow[j], c);
     if ((unsigned)id >= (unsigned)V) {
       bad_index = 1;
-    } else if (slice == 0 || (id >= e0 && id < e1)) {
+    } else if (slice == 0 || owns(id)) {
       sup_s[j] = srow[id];
     }
   }
@@ -100,7 +105,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   Lse acc[4];  // 0 student / tau, 2 student at tau = 1 (the indices accum8 uses; 1 and 3 stay empty)
 #pragma unroll
   for (int i = 0; i < 4; ++i) acc[i].init();
-  constexpr float kRefBias = 100.0f;
+  const float kRefBias = a.ragged ? kRefSlack : 100.0f;  // see npd_kd_gang.hpp
   if (ng > tid) {
     const float fs = pk_max_value(pk_max_group(sreg[0]));
     acc[0].r = __builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f);
@@ -139,12 +144,10 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
       }
     }
   }
-  if (last) {
-    for (int e = nvec * 8 + tid; e < V; e += TH) {
-      const float xs = bf16_one(srow[e]);
-      acc[0].add1(xs, c);
-      if constexpr (LSE1) acc[2].add1(xs, kLog2e);
-    }
+  if (last && tid < n_edge) {
+    const float xs = bf16_one(srow[sp.edge_elem(tid)]);
+    acc[0].add1(xs, c);
+    if constexpr (LSE1) acc[2].add1(xs, kLog2e);
   }
 
   // ---- wave totals, workgroup totals, post, wait, row totals (student); workgroup totals of the teacher's k values
@@ -223,6 +226,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   const float lse1_s = __fmul_rn(LSE1 ? st[1].log2_sum() : Ls, kLn2);
   const bool ce = a.cscale != 0.0f;  // uniform (tau = 1 here whenever it is set)
   Sweep2Coef kf = sweep2_coef(st[0], tt, c, a.gscale, a.cscale, true, false);
+  kf.folded = kf.folded && !a.ragged;
 
   // ---- kd_tok (slice 0) and the final values of the support positions of this slice
   float part_kd = 0.0f;
@@ -230,7 +234,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   if (!bad_index) {
     for (int j = tid; j < k_top; j += TH) {
       const int id = irow[j];
-      const bool mine = id >= e0 && id < e1;
+      const bool mine = owns(id);
       if (slice == 0 || mine) {
         const float b = vrow[j] * c;
         const float sj = bf16_one(sup_s[j]);
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   }
 
   // ---- sweep 2: dense part p_S * weights from the registers, then the support positions of this slice
-  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow) + (size_t)g0 * 16;
+  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (size_t)g0 * 16;
   auto store = [&](int k, const uint4& o) {
     const u32x4 w = {o.x, o.y, o.z, o.w};
     __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gslice + (size_t)k * GB) + tid);
@@ -289,8 +293,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
 #pragma unroll
     for (int k = 0; k < K; ++k)
       if (k < q || (k == q && tid < part)) store(k, qnan);
-    if (last)
-      for (int e = nvec * 8 + tid; e < V; e += TH) grow[e] = 0x7fc0;
+    if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0x7fc0;
     return;
   }
   // the label position of the composite loss, unless it is one of the support positions (patched with them)
@@ -301,11 +304,11 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   if (patch_y) {
     const uint32_t b16 = one_bf16(grad_student_elem(s_y, kf.p) - a.cscale);
     y_tail = (uint16_t)b16;
-    if ((y >> 3) < nvec) {
-      const int yg = (y >> 3) - g0;
+    if (sp.group_of(y) >= 0) {
+      const int yg = sp.group_of(y) - g0;
       k_y = yg / TH;
       if (yg - k_y * TH == tid) {
-        const int j = y & 7;
+        const int j = (y - head) & 7;
         const uint32_t keep = (j & 1) ? 0x0000ffffu : 0xffff0000u, bits = (j & 1) ? b16 << 16 : b16;
         if ((j >> 1) == 0) { y_keep.x = keep; y_bits.x = bits; }
         if ((j >> 1) == 1) { y_keep.y = keep; y_bits.y = bits; }
@@ -320,12 +323,11 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
     o.z = (o.z & y_keep.z) | y_bits.z;
     o.w = (o.w & y_keep.w) | y_bits.w;
   };
-  if (last) {
-    for (int e = nvec * 8 + tid; e < V; e += TH) {
-      uint16_t o = one_bf16(grad_student_elem(bf16_one(srow[e]), kf.p));
-      if (patch_y && e == y) o = y_tail;
-      grow[e] = o;
-    }
+  if (last && tid < n_edge) {
+    const int e = sp.edge_elem(tid);
+    uint16_t o = one_bf16(grad_student_elem(bf16_one(srow[e]), kf.p));
+    if (patch_y && e == y) o = y_tail;
+    grow[e] = o;
   }
   if (kf.folded) {  // uniform
 #pragma unroll
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   __syncthreads();
   for (int j = tid; j < k_top; j += TH) {
     const int id = irow[j];
-    if (id >= e0 && id < e1) grow[id] = sup_s[j];
+    if (owns(id)) grow[id] = sup_s[j];
   }
 }
 

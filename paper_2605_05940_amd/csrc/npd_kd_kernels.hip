@@ -18,10 +18,10 @@
 namespace npd {
 
 template <int BLOCK>
-__device__ __forceinline__ void zero_row(uint16_t* grow, int nvec, int V) {
+__device__ __forceinline__ void zero_row(uint16_t* grow, const RowSplit& sp, int V) {
   const uint4 z = make_uint4(0, 0, 0, 0);
-  for (int i = threadIdx.x; i < nvec; i += BLOCK) reinterpret_cast<uint4*>(grow)[i] = z;
-  for (int e = nvec * 8 + threadIdx.x; e < V; e += BLOCK) grow[e] = 0;
+  for (int i = threadIdx.x; i < sp.nvec; i += BLOCK) reinterpret_cast<uint4*>(grow + sp.head)[i] = z;
+  for (int j = threadIdx.x; j < V - sp.nvec * 8; j += BLOCK) grow[sp.edge_elem(j)] = 0;
 }
 
 template <int BLOCK, int TEACHER, bool GRAD>
@@ -31,8 +31,10 @@ __global__ __launch_bounds__(BLOCK) void kd_rows_kernel(const KdArgs a) {
   __shared__ int y_in_support;  // top-k teacher: the label is one of the k support positions of this row
   const int tid = threadIdx.x;
   const int64_t row = blockIdx.x;
-  const int V = a.V, nvec = a.nvec_s;
+  const int V = a.V;
   uint16_t* grow = GRAD ? a.g + row * a.s_stride : nullptr;
+  const RowSplit sp = row_split(a.s + row * a.s_stride, V, a.nvec_s != 0);
+  const int nvec = sp.nvec, n_edge = V - nvec * 8;
 
   if (!a.mask[row]) {  // not scored: scalars 0, gradient row zero-filled, logits never read
     if (tid == 0) {
@@ -41,12 +43,14 @@ __global__ __launch_bounds__(BLOCK) void kd_rows_kernel(const KdArgs a) {
       if (a.tnll) a.tnll[row] = 0.0f;
       if (a.lse) a.lse[row] = 0.0f;
     }
-    if constexpr (GRAD) zero_row<BLOCK>(grow, nvec, V);
+    if constexpr (GRAD) zero_row<BLOCK>(grow, sp, V);
     return;
   }
 
   const uint16_t* srow = a.s + row * a.s_stride;
   const uint16_t* trow = TEACHER == kDense ? a.t + row * a.t_stride : nullptr;
+  const uint4* svec = reinterpret_cast<const uint4*>(srow + sp.head);
+  const uint4* tvec = reinterpret_cast<const uint4*>(TEACHER == kDense ? trow + sp.head : nullptr);
   const float c = a.c;
   const bool lse1 = a.need_lse1 != 0;       // uniform
   const bool lse1_t = lse1 && a.tnll != nullptr;
@@ -69,17 +73,18 @@ __global__ __launch_bounds__(BLOCK) void kd_rows_kernel(const KdArgs a) {
   // ---- sweep 1
   for (int i = tid; i < nvec; i += BLOCK) {
     float xs[8];
-    unpack8(reinterpret_cast<const uint4*>(srow)[i], xs);
+    unpack8(svec[i], xs);
     if constexpr (TEACHER == kDense) {
       float xt[8];
-      unpack8(reinterpret_cast<const uint4*>(trow)[i], xt);
+      unpack8(tvec[i], xt);
       acc[1].add8_cross(xt, xs, c);
       if (lse1_t) acc[3].add8(xt, kLog2e);
     }
     acc[0].add8(xs, c);
     if (lse1) acc[2].add8(xs, kLog2e);
   }
-  for (int e = nvec * 8 + tid; e < V; e += BLOCK) {
+  for (int j = tid; j < n_edge; j += BLOCK) {
+    const int e = sp.edge_elem(j);
     const float xs = bf16_one(srow[e]);
     if constexpr (TEACHER == kDense) {
       const float xt = bf16_one(trow[e]);
@@ -168,16 +173,17 @@ __global__ __launch_bounds__(BLOCK) void kd_rows_kernel(const KdArgs a) {
       for (int e = tid; e < V; e += BLOCK) grow[e] = qnan;
       return;
     }
-    for (int e = nvec * 8 + tid; e < V; e += BLOCK) {
+    for (int j = tid; j < n_edge; j += BLOCK) {
+      const int e = sp.edge_elem(j);
       const float xs = bf16_one(srow[e]);
       grow[e] = one_bf16(TEACHER == kDense ? grad_dense_elem(xs, bf16_one(trow[e]), gk) : grad_student_elem(xs, gk));
     }
     for (int i = nvec - 1 - tid; i >= 0; i -= BLOCK) {
       float xs[8], gv[8];
-      unpack8(reinterpret_cast<const uint4*>(srow)[i], xs);
+      unpack8(svec[i], xs);
       if constexpr (TEACHER == kDense) {
         float xt[8];
-        unpack8(reinterpret_cast<const uint4*>(trow)[i], xt);
+        unpack8(tvec[i], xt);
 #pragma unroll
         for (int j = 0; j < 8; ++j) gv[j] = grad_dense_elem(xs[j], xt[j], gk);
       } else {
@@ -189,7 +195,7 @@ __global__ __launch_bounds__(BLOCK) void kd_rows_kernel(const KdArgs a) {
       o.y = pack_bf16(gv[2], gv[3]);
       o.z = pack_bf16(gv[4], gv[5]);
       o.w = pack_bf16(gv[6], gv[7]);
-      reinterpret_cast<uint4*>(grow)[i] = o;
+      reinterpret_cast<uint4*>(grow + sp.head)[i] = o;
     }
     if (TEACHER == kTopk || ce) {  // uniform
       // the k support positions and the label position are overwritten with their final values once the dense

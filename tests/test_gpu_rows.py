@@ -1,0 +1,126 @@
+"""GPU parity of rows that begin and end anywhere: unpadded vocabularies that are not a multiple of 8, tensors whose
+first element is not on a 16-byte boundary, and tensors that do not share their offsets."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_05940_amd import binding, synth
+
+from gpu_util import Guarded, check_row_canaries, compare_kd, dev
+
+pytestmark = pytest.mark.gpu
+DIVS = {"forward": 0, "reverse": 1, "skew": 2, "skew_reverse": 3}
+PAD = 64
+
+
+def _rows(T, V, pitch, off):
+    """A NaN-poisoned buffer and its bf16 view [T, V] with row pitch `pitch`, `off` elements past a 16-byte boundary."""
+    full = torch.full((T * pitch + 2 * PAD + off,), float("nan"), dtype=torch.bfloat16, device=dev())
+    return full, full[PAD + off:PAD + off + T * pitch].view(T, pitch)[:, :V]
+
+
+def _batch(V, k=0):
+    """Logits of a few packed samples and labels on the edges of the row."""
+    edges = [0, 1, 6, 7, 8, V // 2, V - 9, V - 8, V - 2, V - 1]
+    T = 2 * len(edges)
+    w = synth.scaled(synth.config(1), n_rows=1, row_len=T, vocab=V, length_lo=4, length_hi=9, topk=max(k, 1))
+    lay = synth.make_layout(w)
+    s = torch.empty((T, V), dtype=torch.bfloat16, device=dev())
+    t = torch.empty_like(s)
+    synth.fill_logits(w, s, t)
+    lab = np.array([max(0, min(V - 1, edges[i % len(edges)])) for i in range(T)], np.int32)
+    return w, lay, s, t, lab
+
+
+def _call(lay, s, t, lab, *, V, pitch, offs, pitch_t=None, div="forward", tau=1.0, gs=0.75, ce=0.0, grad=True,
+          inplace=False, topk=None, no_workspace=False):
+    """The call on copies of the logits at the offsets `offs` = (student, teacher, gradient); checks the guards."""
+    T = s.shape[0]
+    fs, vs = _rows(T, V, pitch, offs[0])
+    vs.copy_(s)
+    vt = None
+    if topk is None:
+        _, vt = _rows(T, V, pitch_t or pitch, offs[1])
+        vt.copy_(t)
+    fg, vg = (fs, vs) if inplace else _rows(T, V, pitch, offs[2])
+    out = {n: Guarded(T, torch.float32) for n in ("kd", "nll_s", "lse_s") + (("nll_t",) if topk is None else ())}
+    status = torch.zeros(1, dtype=torch.int32, device=dev())
+    binding.npd_kd_loss_fwd_bwd(
+        vs, torch.from_numpy(lay.loss_mask).to(dev()), teacher_dense=vt, teacher_idx=topk[0] if topk else None,
+        teacher_val=topk[1] if topk else None, labels=torch.from_numpy(lab).to(dev()), tau=tau, grad_scale=gs,
+        ce_grad_scale=ce, divergence=DIVS[div], skew_alpha=0.1, grad_out=vg if grad else None, kd_tok=out["kd"].t,
+        nll_tok=out["nll_s"].t, teacher_nll_tok=out["nll_t"].t if topk is None else None, lse_tok=out["lse_s"].t,
+        dev_status=status, no_workspace=no_workspace)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    got = {n: b.check().cpu().numpy().astype(np.float64) for n, b in out.items()}
+    if grad:
+        check_row_canaries(fg[offs[0 if inplace else 2]:], T, V, pitch)
+        got["grad"] = vg.float().cpu().numpy().astype(np.float64)
+    return got
+
+
+def _reference(oracle, lay, s, t, lab, div, tau, gs, ce):
+    sb, tb = synth.bf16_bits(s), synth.bf16_bits(t)
+    if div == "forward":
+        return oracle.kd_dense(sb, tb, lab, lay.loss_mask, tau=tau, grad_scale=gs, ce_grad_scale=ce)
+    ref = oracle.div_dense(sb, tb, div, 0.1, labels=lab, mask=lay.loss_mask, tau=tau, grad_scale=gs, ce_grad_scale=ce)
+    nl = oracle.kd_dense(sb, tb, lab, lay.loss_mask, want_grad=False)
+    ref.update(nll_s=nl["nll_s"], nll_t=nl["nll_t"], lse_s=nl["lse_s"])
+    return ref
+
+
+@pytest.mark.parametrize("V,pitch,offs,pitch_t", [
+    (30631, 30631, (0, 0, 0), None),      # two slices; rows at every offset in turn
+    (50003, 50003, (3, 3, 3), None),      # the tensors themselves begin inside a group
+    (151937, 151937, (0, 0, 0), None),    # eight slices, one element beyond a multiple of 8
+    (151936, 151944, (5, 5, 5), None),    # every row at the same odd offset
+    (50003, 50003, (1, 2, 1), None),      # teacher elsewhere: no common groups
+    (50003, 50003, (1, 1, 4), None),      # gradient elsewhere
+    (50003, 50003, (0, 0, 0), 50008),     # teacher padded, student not
+    (50003, 50003, (0, 0, 0), 50011),     # another pitch, the same offsets
+    (8199, 8199, (0, 0, 0), None),        # rows of one workgroup
+    (20481, 20483, (7, 7, 7), None),
+    (5003, 5003, (2, 2, 2), None),        # short rows
+    (1001, 1001, (0, 0, 0), None),
+    (17, 17, (0, 0, 0), None),            # one or two groups, most elements are edges
+    (9, 9, (5, 5, 5), None),              # rows without a whole group among them
+])
+@pytest.mark.parametrize("div,tau,ce", [("forward", 1.0, 0.25), ("forward", 2.0, 0.0), ("reverse", 1.0, 0.25),
+                                        ("skew", 1.0, 0.25), ("skew_reverse", 2.0, 0.0)])
+def test_dense_rows_at_any_offset(oracle, V, pitch, offs, pitch_t, div, tau, ce):
+    w, lay, s, t, lab = _batch(V)
+    ref = _reference(oracle, lay, s, t, lab, div, tau, 0.75, ce)
+    bars = dict(grad_scale=0.75 + ce, tau=tau, amp_from_ref=div != "forward", folded=div != "forward")
+    kw = dict(V=V, pitch=pitch, offs=offs, pitch_t=pitch_t, div=div, tau=tau, ce=ce)
+    for mode in (dict(), dict(inplace=True), dict(no_workspace=True)):
+        print(f"[rows] V={V} pitch={pitch} offs={offs} pitch_t={pitch_t} {div} tau={tau} {mode}", flush=True)
+        compare_kd(_call(lay, s, t, lab, **kw, **mode), ref, lay.loss_mask, lay.cu_seqlens, oracle, **bars)
+    fwd = _call(lay, s, t, lab, **kw | dict(ce=0.0), grad=False)
+    compare_kd(fwd, {n: ref[n] for n in ("kd", "nll_s", "nll_t", "lse_s")}, lay.loss_mask, lay.cu_seqlens, oracle)
+
+
+@pytest.mark.parametrize("V,pitch,offs", [
+    (30631, 30631, (0, 0, 0)), (151937, 151937, (3, 3, 3)), (50003, 50003, (1, 1, 4)), (8199, 8199, (0, 0, 0)),
+    (2003, 2003, (6, 6, 6)), (40, 43, (0, 0, 0)),
+])
+@pytest.mark.parametrize("tau,ce", [(1.0, 0.25), (2.0, 0.0)])
+def test_topk_rows_at_any_offset(oracle, V, pitch, offs, tau, ce):
+    k = 20
+    w, lay, s, t, lab = _batch(V, k)
+    idx, val = synth.make_topk_teacher(w, s)
+    idx_np = idx.cpu().numpy().copy()
+    for r in range(idx_np.shape[0]):  # support on both edges of the row; in even rows the label is in it
+        want = [0, 1, 7, V - 1, V - 2, V - 8] + ([int(lab[r])] if r % 2 == 0 else [])
+        want = list(dict.fromkeys(want))
+        idx_np[r] = want + [int(v) for v in idx_np[r] if int(v) not in want][:k - len(want)]
+    topk = (torch.from_numpy(idx_np).to(dev()), val)
+    ref = oracle.kd_topk(synth.bf16_bits(s), idx_np, val.cpu().numpy(), lab, lay.loss_mask, tau=tau, grad_scale=0.75,
+                         ce_grad_scale=ce)
+    kw = dict(V=V, pitch=pitch, offs=offs, tau=tau, ce=ce, topk=topk)
+    for mode in (dict(), dict(inplace=True), dict(no_workspace=True)):
+        print(f"[rows] top-k V={V} pitch={pitch} offs={offs} tau={tau} {mode}", flush=True)
+        compare_kd(_call(lay, s, None, lab, **kw, **mode), ref, lay.loss_mask, lay.cu_seqlens, oracle,
+                   grad_scale=0.75 + ce, tau=tau, folded=False)
+    fwd = _call(lay, s, None, lab, **kw | dict(ce=0.0), grad=False)
+    compare_kd(fwd, {n: ref[n] for n in ("kd", "nll_s", "lse_s")}, lay.loss_mask, lay.cu_seqlens, oracle)
