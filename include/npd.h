@@ -186,7 +186,8 @@ size_t npd_workspace_bytes(const npd_kd_desc* desc);
  *   teacher_nll_tok  fp32 [T] or NULL (dense teacher only)
  *   lse_tok          fp32 [T] or NULL
  *   dev_status       int32 [1] or NULL
- *   workspace        device, >= npd_workspace_bytes(desc) bytes, 256-byte aligned (NULL if 0); scratch of the call
+ *   workspace        device, >= npd_workspace_bytes(desc) bytes, 256-byte aligned (NULL if 0; may be NULL, too small or
+ *                    unaligned with ce_grad_scale != 0 at tau != 1: slower kernels run then); scratch of the call
  *                    (contents meaningless before and after); must not overlap any other argument, and two
  *                    calls that may run at the same time need a workspace each
  *

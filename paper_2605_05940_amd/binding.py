@@ -128,7 +128,8 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     The teacher kind follows from which teacher tensors are given; ``grad_out is None`` means forward
     only; ``grad_out`` sharing storage with ``student_logits`` means the in-place gradient.  ``workspace``:
     a uint8 tensor of at least ``npd_workspace_bytes`` bytes; if it is None one is taken from
-    ``workspace_for`` (a per-device tensor that this module keeps and grows).  ``no_workspace`` sets
+    ``workspace_for`` (a per-device tensor that this module keeps and grows), or, with a CE term at tau != 1, allocated
+    for the call.  ``no_workspace`` sets
     ``NPD_FLAG_NO_WORKSPACE``.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in
     scratch array; no workspace argument).
     """
@@ -161,7 +162,13 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
         flags |= NPD_FLAG_NO_WORKSPACE
     d.flags = flags
     if workspace is None and not no_workspace and not noalloc:
-        workspace = workspace_for(int(load().npd_workspace_bytes(ctypes.byref(d))), student_logits.device)
+        need = int(load().npd_workspace_bytes(ctypes.byref(d)))
+        if ce_grad_scale != 0.0 and tau != 1.0:
+            # these calls can do without and may run beside others on several streams: a block of this call's own,
+            # from torch's stream-ordered allocator (reused only behind this call on its stream)
+            workspace = torch.empty(need, dtype=torch.uint8, device=student_logits.device) if need else None
+        else:
+            workspace = workspace_for(need, student_logits.device)
     for name, t, n in (("loss_mask", loss_mask, T), ("labels", labels, T), ("kd_tok", kd_tok, T),
                        ("nll_tok", nll_tok, T), ("teacher_nll_tok", teacher_nll_tok, T), ("lse_tok", lse_tok, T)):
         if t is not None and (t.numel() != n or not t.is_contiguous()):

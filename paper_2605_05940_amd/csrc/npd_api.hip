@@ -112,12 +112,15 @@ void* noalloc_scratch_address(hipError_t* err) {
   return p;
 }
 
+// Calls that make do without the workspace npd_workspace_bytes() asks for: a CE term at tau != 1 once ran in kernels
+// that need none, and callers that bring none still get those.
+bool workspace_optional(const npd_kd_desc& d) { return d.ce_grad_scale != 0.0f && d.tau != 1.0f; }
+
 // workspace bytes of a call with a valid descriptor
 size_t workspace_bytes_of(const npd_kd_desc& d) {
   // only the row-gang kernels (gradient calls on long rows) exchange partial sums through device memory; every other
   // kernel keeps them in registers and LDS
   if (d.flags & (NPD_FLAG_FWD_ONLY | NPD_FLAG_NO_WORKSPACE)) return 0;
-  if (d.ce_grad_scale != 0.0f && d.tau != 1.0f) return 0;
   if (d.teacher_kind == NPD_TEACHER_TOPK)  // (forward KL only: checked with the descriptor)
     return npd::gang_workspace_bytes(d.n_tokens, d.vocab, npd::kTopk, npd::kForwardKl, false);
   if (d.teacher_kind != NPD_TEACHER_DENSE_BF16) return 0;
@@ -302,12 +305,17 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
                                       grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
   if (st != NPD_OK) return st;
   if (need > 0) {
-    if (!workspace || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u))
-      return NPD_ERR_WORKSPACE;
-    const KdBuffers b = kd_buffers(*desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
-                                   grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status);
-    if (b.overlaps_any(range_of(workspace, need))) return NPD_ERR_ALIAS;
-    a.ws = static_cast<uint32_t*>(workspace);
+    bool usable = workspace && workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
+    if (!usable && !workspace_optional(*desc)) return NPD_ERR_WORKSPACE;
+    if (usable) {
+      const KdBuffers b = kd_buffers(*desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
+                                     grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status);
+      if (b.overlaps_any(range_of(workspace, need))) {
+        if (!workspace_optional(*desc)) return NPD_ERR_ALIAS;
+        usable = false;
+      }
+    }
+    a.ws = usable ? static_cast<uint32_t*>(workspace) : nullptr;
   }
   const bool want_grad = !(desc->flags & NPD_FLAG_FWD_ONLY);
   const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, static_cast<hipStream_t>(stream));
@@ -324,6 +332,7 @@ npd_status npd_kd_loss_fwd_bwd_noalloc(const npd_kd_desc* desc, const void* stud
   const npd_status st = check_kd_call(desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
                                       grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
   if (st != NPD_OK) return st;
+  if (workspace_optional(*desc)) need = 0;  // such calls have never used the scratch array: they may overlap
   if (need > (size_t)NPD_NOALLOC_WORKSPACE_BYTES) return NPD_ERR_WORKSPACE;  // the built-in scratch is too small
   if (need > 0) {
     hipError_t e = hipSuccess;

@@ -97,6 +97,7 @@ struct Sweep2Coef {
   // reverse KL (and its CE term at tau = 1): grad = 2^(x_s c - r_S) ((x_s - x_t) ra + rb),
   //   ra = grad_scale / (tau^2 z_S),  rb = (ce_grad_scale - grad_scale / tau (lse_S - lse_T + D)) / z_S
   float ra, rb;
+  float wc_square;  // CE term at tau = 2: ce_grad_scale Softmax(s)(c) = e_S^2 wc_square
   DivCoef dv;  // skew forms
 };
 
@@ -106,12 +107,13 @@ __device__ __forceinline__ float grad_reverse_elem(float xs, float xt, const Swe
   return exp2_fast(__builtin_fmaf(xs, k.c, -k.p.rs)) * __builtin_fmaf(__builtin_fmaxf(xs - xt, -1.0e30f), k.ra, k.rb);
 }
 
-__device__ __forceinline__ Sweep2Coef sweep2_coef(const Lse& S, const Lse& Tt, float c, float gscale, float cscale,
-                                                  bool has_teacher_stream, bool dense) {
+// `S1`, `ce_own`: the student at tau = 1, for a CE term whose softmax is not the KD term's (tau != 1)
+__device__ __forceinline__ Sweep2Coef sweep2_coef(const Lse& S, const Lse& Tt, const Lse& S1, float c, float gscale,
+                                                  float cscale, bool has_teacher_stream, bool dense, bool ce_own) {
   Sweep2Coef k;
-  k.p = make_grad_coef(S, Tt, S, c, gscale, cscale, has_teacher_stream, false);
+  k.p = make_grad_coef(S, Tt, S1, c, gscale, cscale, has_teacher_stream, ce_own);
   k.c = c;
-  const float A = gscale + cscale, B = dense ? gscale : 0.0f;
+  const float A = ce_own ? gscale : gscale + cscale, B = dense ? gscale : 0.0f;
   // log2(0) = -inf: the term becomes 2^-inf = 0
   k.fs = S.r + (S.log2_z() - __log2f(fabsf(A)));
   k.ft = dense ? Tt.r + (Tt.log2_z() - __log2f(fabsf(B))) : 0.0f;
@@ -119,13 +121,24 @@ __device__ __forceinline__ Sweep2Coef sweep2_coef(const Lse& S, const Lse& Tt, f
   const bool same_sign = (A >= 0.0f && B >= 0.0f) || (A <= 0.0f && B <= 0.0f);
   const bool small_s = A == 0.0f || fabsf(k.fs) < 1024.0f;
   const bool small_t = !dense || B == 0.0f || fabsf(k.ft) < 1024.0f;
-  k.folded = same_sign && small_s && small_t;
+  k.folded = same_sign && small_s && small_t && !(ce_own && cscale != 0.0f);
   k.ra = k.rb = 0.0f;
+  k.wc_square = ce_own ? k.p.wc * exp2_fast(2.0f * S.r - S1.r) : 0.0f;
   return k;
 }
 
+// Form of the gradient write: folded (weights in the exponents), or precise without a CE term, with one that shares
+// the student's exponential (tau = 1), with one that needs an exponential of its own (tau != 1).  One walk over the
+// registers per form: a test inside the walk would stand at every element.
+// At tau = 2 that exponential is the square of the KD term's: exp(x) = exp(x / 2)^2.
+enum GradForm { kFolded = 0, kPrecise = 1, kPreciseCe = 2, kPreciseCeOwn = 3, kPreciseCeSquare = 4 };
+
+__device__ __forceinline__ float add_ce_own(float g, float xs, const GradCoef& k) {
+  return __builtin_fmaf(exp2_fast(__builtin_fmaf(xs, kLog2e, -k.r1)), k.wc, g);
+}
+
 // gradient of 8 elements
-template <int TEACHER, bool FOLDED, int DIVK = kForwardKl>
+template <int TEACHER, int FORM, int DIVK = kForwardKl>
 __device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const Sweep2Coef& k) {
   float xs[8], gv[8];
   unpack8(vs, xs);
@@ -133,7 +146,14 @@ __device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const S
     float xt[8];
     unpack8(vt, xt);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) gv[j] = grad_reverse_elem(xs[j], xt[j], k);
+    for (int j = 0; j < 8; ++j) {
+      gv[j] = grad_reverse_elem(xs[j], xt[j], k);
+      if constexpr (FORM == kPreciseCeOwn) gv[j] = add_ce_own(gv[j], xs[j], k.p);
+      if constexpr (FORM == kPreciseCeSquare) {
+        const float es = exp2_fast(__builtin_fmaf(xs[j], k.c, -k.p.rs));
+        gv[j] = __builtin_fmaf(es * es, k.wc_square, gv[j]);
+      }
+    }
   } else if constexpr (DIVK != kForwardKl) {
     float xt[8];
     unpack8(vt, xt);
@@ -142,21 +162,33 @@ __device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const S
   } else if constexpr (TEACHER == kDense) {
     float xt[8];
     unpack8(vt, xt);
-    if constexpr (FOLDED) {
+    if constexpr (FORM == kFolded) {
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         gv[j] = exp2_fast(__builtin_fmaf(xs[j], k.c, -k.fs)) - exp2_fast(__builtin_fmaf(xt[j], k.c, -k.ft));
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) gv[j] = grad_dense_elem(xs[j], xt[j], k.p);
+      for (int j = 0; j < 8; ++j) {  // grad_dense_elem without its tests
+        const float es = exp2_fast(__builtin_fmaf(xs[j], k.p.c, -k.p.rs));
+        gv[j] = __builtin_fmaf(-exp2_fast(__builtin_fmaf(xt[j], k.p.c, -k.p.rt)), k.p.ratio, es) * k.p.ws;
+        if constexpr (FORM == kPreciseCe) gv[j] = __builtin_fmaf(es, k.p.wc, gv[j]);
+        if constexpr (FORM == kPreciseCeOwn) gv[j] = add_ce_own(gv[j], xs[j], k.p);
+        if constexpr (FORM == kPreciseCeSquare) gv[j] = __builtin_fmaf(es * es, k.wc_square, gv[j]);
+      }
     }
   } else {
-    if constexpr (FOLDED) {
+    if constexpr (FORM == kFolded) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) gv[j] = exp2_fast(__builtin_fmaf(xs[j], k.c, -k.fs));
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) gv[j] = grad_student_elem(xs[j], k.p);
+      for (int j = 0; j < 8; ++j) {  // grad_student_elem without its tests
+        const float es = exp2_fast(__builtin_fmaf(xs[j], k.p.c, -k.p.rs));
+        gv[j] = es * k.p.ws;
+        if constexpr (FORM == kPreciseCe) gv[j] = __builtin_fmaf(es, k.p.wc, gv[j]);
+        if constexpr (FORM == kPreciseCeOwn) gv[j] = add_ce_own(gv[j], xs[j], k.p);
+        if constexpr (FORM == kPreciseCeSquare) gv[j] = __builtin_fmaf(es * es, k.wc_square, gv[j]);
+      }
     }
   }
   uint4 o;
@@ -164,7 +196,7 @@ __device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const S
   o.y = pack_bf16(gv[2], gv[3]);
   o.z = pack_bf16(gv[4], gv[5]);
   o.w = pack_bf16(gv[6], gv[7]);
-  if constexpr (FOLDED && DIVK == kForwardKl) {
+  if constexpr (FORM == kFolded && DIVK == kForwardKl) {
     o.x ^= k.sign;
     o.y ^= k.sign;
     o.z ^= k.sign;
@@ -394,7 +426,8 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
     }
     const bool ce = GRAD && a.cscale != 0.0f;                       // uniform (tau = 1 here whenever it is set)
     const bool bad_label = a.labels && (unsigned)y >= (unsigned)V;  // uniform
-    Sweep2Coef k = sweep2_coef(acc[0], acc[1], c, a.gscale, a.cscale, TEACHER != kNone, TEACHER == kDense);
+    Sweep2Coef k =
+        sweep2_coef(acc[0], acc[1], acc[0], c, a.gscale, a.cscale, TEACHER != kNone, TEACHER == kDense, false);
     k.folded = k.folded && !a.ragged;  // rows at any offset have always had the precise form
     if constexpr (REV) {
       const float inv_z = 1.0f / acc[0].z;
@@ -508,7 +541,7 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
           if (i < nvec) {
             const uint4 vs = ld16_last(svec, i);
             const uint4 vt = TEACHER == kDense ? ld16_last(tvec, i) : make_uint4(0, 0, 0, 0);
-            st16_stream(gvec, i, grad8<TEACHER, false, DIVK>(vs, vt, k));
+            st16_stream(gvec, i, ce ? grad8<TEACHER, kPreciseCe, DIVK>(vs, vt, k) : grad8<TEACHER, kPrecise, DIVK>(vs, vt, k));
           }
         }
         if (k.folded) {  // uniform
@@ -535,7 +568,7 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
               }
             }
             {
-              const uint4 gq = grad8<TEACHER, true, DIVK>(vs, vt, k);
+              const uint4 gq = grad8<TEACHER, kFolded, DIVK>(vs, vt, k);
               if ((!SHORT && it < CS - 1) || it * CB + tid < nvec) st16_stream(gvec, it * CB + tid, gq);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -546,7 +579,7 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
             if (i < nvec) {
               const uint4 vs = ld16(svec, i);
               const uint4 vt = TEACHER == kDense ? ld16(tvec, i) : make_uint4(0, 0, 0, 0);
-              st16_stream(gvec, i, grad8<TEACHER, false, DIVK>(vs, vt, k));
+              st16_stream(gvec, i, ce ? grad8<TEACHER, kPreciseCe, DIVK>(vs, vt, k) : grad8<TEACHER, kPrecise, DIVK>(vs, vt, k));
             }
           }
         }

@@ -37,14 +37,11 @@ static bool rows_on_lines(const KdArgs& a) {
   return a.g != nullptr && (reinterpret_cast<uintptr_t>(a.g) & 127u) == 0 && a.s_stride % 64 == 0;
 }
 
-// Gradient calls with a dense teacher (forward or reverse KL) or a top-k teacher (forward KL), 16-byte aligned rows
-// that span at least two slices.  (The CE
-// softmax of the composite loss has no temperature; this path covers it at tau = 1, where it shares the student's
-// exponentials.)
+// Gradient calls with a dense teacher (any divergence) or a top-k teacher (forward KL), rows that span at least two
+// slices, with or without the CE term of the composite loss at any temperature.
 bool gang_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
   if ((teacher_kind != kDense && teacher_kind != kTopk) || !want_grad) return false;
   if (a.divergence != kForwardKl && teacher_kind != kDense) return false;
-  if (a.cscale != 0.0f && a.need_lse1) return false;
   const int g = gang_size(a.nvec_s, gang_k(teacher_kind, a.divergence), rows_on_lines(a));
   if (g < 2 || g > kGangMax) return false;
   return a.T * (int64_t)g <= 0x7fffffffLL;  // one workgroup per slice, 1-D grid
@@ -67,10 +64,20 @@ static hipError_t launch_gang_kernel(const KdArgs& a, int words_per_slice, Kerne
   return launch_kernel(kernel, dim3((unsigned)(a.T * a.gang)), dim3(kGangThreads), 0, stream, a);
 }
 
-template <bool LSE1, int DIVK>
+// the sums at tau = 1 of a call
+static int l1_mode(const KdArgs& a) {
+  if (!a.need_lse1) return kL1None;
+  return 2.0f * a.c == kLog2e ? kL1Square : kL1Own;  // tau = 2 (halving a float is exact)
+}
+
+template <int DIVK>
 static hipError_t launch_gang(const KdArgs& a, hipStream_t stream) {
   constexpr int K = DIVK == kSkewKl || DIVK == kSkewReverseKl ? kGangSkewK : kGangK;
-  return launch_gang_kernel(a, gang_words(LSE1 ? 4 : 2), kd_gang_kernel<K, kDense, LSE1, DIVK>, stream);
+  switch (l1_mode(a)) {
+    case kL1None: return launch_gang_kernel(a, gang_words(2), kd_gang_kernel<K, kDense, kL1None, DIVK>, stream);
+    case kL1Square: return launch_gang_kernel(a, gang_words(4), kd_gang_kernel<K, kDense, kL1Square, DIVK>, stream);
+    default: return launch_gang_kernel(a, gang_words(4), kd_gang_kernel<K, kDense, kL1Own, DIVK>, stream);
+  }
 }
 
 hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, hipStream_t stream) {
@@ -85,16 +92,18 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, hipStream_t stream
   while (a.gang_pow2 < a.gang) a.gang_pow2 *= 2;
   a.spin_limit = g_spin_limit.load(std::memory_order_relaxed);
   if (teacher_kind == kTopk) {
-    if (a.need_lse1) return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, true>, stream);
-    return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, false>, stream);
+    switch (l1_mode(a)) {
+      case kL1None: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1None>, stream);
+      case kL1Square: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Square>, stream);
+      default: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Own>, stream);
+    }
   }
-  if (a.divergence == kReverseKl)
-    return a.need_lse1 ? launch_gang<true, kReverseKl>(a, stream) : launch_gang<false, kReverseKl>(a, stream);
-  if (a.divergence == kSkewKl)
-    return a.need_lse1 ? launch_gang<true, kSkewKl>(a, stream) : launch_gang<false, kSkewKl>(a, stream);
-  if (a.divergence == kSkewReverseKl)
-    return a.need_lse1 ? launch_gang<true, kSkewReverseKl>(a, stream) : launch_gang<false, kSkewReverseKl>(a, stream);
-  return a.need_lse1 ? launch_gang<true, kForwardKl>(a, stream) : launch_gang<false, kForwardKl>(a, stream);
+  switch (a.divergence) {
+    case kReverseKl: return launch_gang<kReverseKl>(a, stream);
+    case kSkewKl: return launch_gang<kSkewKl>(a, stream);
+    case kSkewReverseKl: return launch_gang<kSkewReverseKl>(a, stream);
+    default: return launch_gang<kForwardKl>(a, stream);
+  }
 }
 
 }  // namespace npd

@@ -23,6 +23,8 @@
 // NPD_DEV_GANG_TIMEOUT and raises a launch-wide flag that ends every other wait of the launch early, so a kernel can
 // never hang, nor spend one limit per row.
 #pragma once
+#include <type_traits>
+
 #include "npd_kd_cached.hpp"
 
 namespace npd {
@@ -125,6 +127,9 @@ __device__ __forceinline__ uint32_t gang_wait(const uint32_t* p, uint32_t* aband
   }
 }
 
+// which sums at tau = 1 a kernel keeps, see kd_gang_kernel
+enum { kL1None = 0, kL1Own = 1, kL1Square = 2 };
+
 // words of scratch per slice: 3 per partial log-sum-exp, rounded up to a power of two
 __host__ __device__ constexpr int gang_words(int ns) { return ns == 2 ? 8 : 16; }
 
@@ -156,6 +161,7 @@ struct SkewCoef {
                               // folded into one logarithm: at logits in the thousands that would cost 2e-4 of p)
   float alpha, beta;          // beta = 1 - alpha
   float Av, B;                // gradient = Av v + B p_S, see skew_terms
+  float C;                    // + C p_S^2: the CE term at tau = 2
 };
 constexpr float kSkewTiny = 1.0e-37f;
 
@@ -200,11 +206,16 @@ __device__ __forceinline__ float skew_grad(float xs, float xt, const SkewCoef& k
 }
 
 // K: groups per thread and tensor a workgroup holds (a slice has at most a.gang_groups + 7 <= K * 256 - 1 groups).
-template <int K, int TEACHER, bool LSE1, int DIVK = kForwardKl>
+// L1: what is summed at tau = 1 beside the sums at tau -- 0 nothing (tau = 1, or no such output wanted), kL1Own with
+// exponentials of their own, kL1Square (tau = 2) from squares of the exponentials at tau.  Measured (MI355X, 4,096 x
+// 151,936, dense teacher, composite loss at tau = 2): one workgroup per row, both sweeps from memory 738 us; shared
+// rows with own exponentials 495 us, bound by the seven v_exp_f32 per pair of logits; squares, four of them, 459 us.
+template <int K, int TEACHER, int L1, int DIVK = kForwardKl>
 __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a) {
   static_assert(TEACHER == kDense, "dense teacher");
   constexpr int TH = kGangThreads;
   constexpr int GB = TH * 16;
+  constexpr bool LSE1 = L1 != kL1None;
   constexpr int NS = LSE1 ? 4 : 2;  // 0 student / tau, 1 teacher / tau (+ cross), 2 student tau = 1, 3 teacher tau = 1
   constexpr int NW3 = NS * 3;
   constexpr int W = gang_words(NS);
@@ -254,12 +265,12 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   if (tid == 0) gave_up = 0;  // ordered before its use by the barriers of block_merge
 
   // The slice as a buffer: all of a thread's groups are requested at once, unconditionally (a predicate around a load
-  // makes the compiler wait for it on the spot); groups past the slice's end read as zero and are never used.  Groups
-  // k < q are whole for every thread, group q belongs to the first `part` threads.
+  // makes the compiler wait for it on the spot); groups past the slice's end read as zero and are never used.  The thread
+  // owns its first n_mine groups (one comparison per group; masks kept for both sweeps were spilled).
   const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
   const __amdgpu_buffer_rsrc_t rt = row_rsrc(trow + head + (size_t)g0 * 8, ng);
   const int voff = tid * 16;
-  const int q = ng / TH, part = ng - q * TH;  // uniform
+  const int n_mine = (ng - tid + TH - 1) / TH;  // groups of this thread
   uint4 sreg[K], treg[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -304,20 +315,26 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   // room: an element's exponential is kept down to 2^-62 of the thread's first group's largest.
   // Rows at any offset keep the 32 bits of head room (and the precise gradient form) they have in the streaming
   // kernels: smaller arguments, hence smaller rounding errors, at the price of more careful re-runs on heavy tails.
-  const float kRefBias = a.ragged ? kRefSlack : (SKEW ? 64.0f : 100.0f);
+  // Squares of exponentials get 44 bits, so that a square is kept down to 2^-38 of the first group's largest square and
+  // its sum is inside the range up to 94 bits above the first group's largest logit.
+  const float kRefBias = a.ragged ? kRefSlack : (L1 == kL1Square ? 44.0f : (SKEW ? 64.0f : 100.0f));
   float cp[SKEW ? K : 1][8], cv[SKEW ? K : 1][8];
   if (ng > tid) {  // (threads without a group keep their empty partials)
     const float fs = pk_max_value(pk_max_group(sreg[0])), ft = pk_max_value(pk_max_group(treg[0]));
     acc[0].r = __builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f);
     acc[1].r = __builtin_fmaxf(__builtin_fmaf(ft, c, kRefBias), -1.0e30f);
-    if constexpr (LSE1) {
+    if constexpr (L1 == kL1Own) {
       acc[2].r = __builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f);
       acc[3].r = __builtin_fmaxf(__builtin_fmaf(ft, kLog2e, kRefBias), -1.0e30f);
+    }
+    if constexpr (L1 == kL1Square) {
+      acc[2].r = 2.0f * acc[0].r;
+      acc[3].r = 2.0f * acc[1].r;
     }
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    if (k < q || (k == q && tid < part)) {
+    if (k < n_mine) {
       float xs[8], xt[8];
       unpack8(sreg[k], xs);
       unpack8(treg[k], xt);
@@ -335,7 +352,11 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
           cp[k][j] = es;
           cv[k][j] = et;
         }
-        if constexpr (LSE1) {
+        if constexpr (L1 == kL1Square) {
+          acc[2].z = __builtin_fmaf(es, es, acc[2].z);
+          acc[3].z = __builtin_fmaf(et, et, acc[3].z);
+        }
+        if constexpr (L1 == kL1Own) {
           acc[2].z += exp2_fast(__builtin_fmaf(xs[j], kLog2e, -acc[2].r));
           if (lse1_t) acc[3].z += exp2_fast(__builtin_fmaf(xt[j], kLog2e, -acc[3].r));
         }
@@ -360,7 +381,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       }
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        if (k < q || (k == q && tid < part)) accum8<kDense, LSE1, REV>(sreg[k], treg[k], c, lse1_t, acc);
+        if (k < n_mine) accum8<kDense, LSE1, REV>(sreg[k], treg[k], c, lse1_t, acc);
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (SKEW) {  // the exponentials again, against the references the careful form ended with
@@ -473,8 +494,11 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   const float lse_diff = ((acc[0].r - acc[1].r) + (acc[0].log2_z() - acc[1].log2_z())) * kLn2;  // lse_S - lse_T at tau
   float kd = REV ? (acc[0].a / acc[0].z) * a.inv_tau - lse_diff : (acc[1].a / acc[1].z) * a.inv_tau + lse_diff;
   kd = kd < 0.0f ? 0.0f : kd;  // (the skew forms replace it below)
-  const bool ce = a.cscale != 0.0f;  // uniform (tau = 1 here whenever it is set)
-  Sweep2Coef kf = sweep2_coef(acc[0], acc[1], c, a.gscale, a.cscale, true, true);
+  // uniform.  With a CE term at tau != 1 (LSE1) the gradient takes a third exponential per element, against the
+  // student's normaliser at tau = 1 that sweep 1 has summed anyway.
+  const bool ce = a.cscale != 0.0f;
+  const float cs_shared = LSE1 ? 0.0f : a.cscale;  // weight of a CE term that shares the KD term's softmax
+  Sweep2Coef kf = sweep2_coef(acc[0], acc[1], acc[LSE1 ? 2 : 0], c, a.gscale, a.cscale, true, true, LSE1);
   SkewCoef ks;
   if constexpr (SKEW) {
     // ---- sweep 2 of the skew forms over the registers: D and ubar need the row's normalisers in every term
@@ -490,7 +514,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     const float fs = exp2_fast(r_s_thread - ks.Rs) * ks.izs, ft = exp2_fast(r_t_thread - ks.Rt) * ks.izt;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      if (k < q || (k == q && tid < part)) {
+      if (k < n_mine) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) skew_terms<DIVK>(cp[k][j] * fs, cv[k][j] * ft, ks, dsum, usum, cp[k][j], cv[k][j]);
       }
@@ -526,13 +550,14 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     kd = dsum * kLn2;
     kd = kd < 0.0f ? 0.0f : kd;
     const float g = a.gscale;  // (grad_scale / tau)
+    ks.C = kf.wc_square * acc[0].z * acc[0].z;  // Softmax(s) = e_S^2 / (...), e_S = p_S z_S
     if constexpr (DIVK == kSkewKl) {
       const float ubar = (a.alpha - 1.0f) * usum;
       ks.Av = (a.alpha - 1.0f) * g;
-      ks.B = a.cscale - g * ubar;
+      ks.B = cs_shared - g * ubar;
     } else {
       const float ubar = usum + 1.0f;
-      ks.B = __builtin_fmaf(g, 1.0f - ubar, a.cscale);
+      ks.B = __builtin_fmaf(g, 1.0f - ubar, cs_shared);
       ks.Av = g;
     }
   }
@@ -540,7 +565,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   if constexpr (REV) {
     const float inv_z = 1.0f / acc[0].z;
     kf.ra = a.gscale * a.inv_tau * inv_z;
-    kf.rb = (a.cscale - a.gscale * (lse_diff + kd)) * inv_z;
+    kf.rb = (cs_shared - a.gscale * (lse_diff + kd)) * inv_z;
     kf.folded = true;
   }
 
@@ -579,7 +604,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     const uint4 qnan = make_uint4(0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u);
 #pragma unroll
     for (int k = 0; k < K; ++k)
-      if (k < q || (k == q && tid < part)) store(k, qnan);
+      if (k < n_mine) store(k, qnan);
     if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0x7fc0;
     return;
   }
@@ -596,6 +621,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       gy = skew_grad<DIVK>(s_y, t_y, ks);
     else
       gy = grad_dense_elem(s_y, t_y, kf.p);
+    if constexpr (LSE1 && (REV || SKEW)) gy = add_ce_own(gy, s_y, kf.p);
     const uint32_t b16 = one_bf16(gy - a.cscale);
     y_tail = (uint16_t)b16;
     if (sp.group_of(y) >= 0) {
@@ -620,45 +646,72 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   if (last && tid < n_edge) {
     const int e = sp.edge_elem(tid);
     const float xs = bf16_one(srow[e]), xt = bf16_one(trow[e]);
-    uint16_t o;
+    float ge;
     if constexpr (SKEW)
-      o = one_bf16(skew_grad<DIVK>(xs, xt, ks));
+      ge = skew_grad<DIVK>(xs, xt, ks);
     else
-      o = one_bf16(REV ? grad_reverse_elem(xs, xt, kf) : grad_dense_elem(xs, xt, kf.p));
+      ge = REV ? grad_reverse_elem(xs, xt, kf) : grad_dense_elem(xs, xt, kf.p);
+    if constexpr (LSE1 && (REV || SKEW))
+      if (ce) ge = add_ce_own(ge, xs, kf.p);
+    uint16_t o = one_bf16(ge);
     if (ce && own_y && e == y) o = y_tail;
     grow[e] = o;
   }
-  if constexpr (SKEW) {
-#pragma unroll
-    for (int k = K - 1; k >= 0; --k) {
-      float gv[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) gv[j] = __builtin_fmaf(cv[k][j], ks.Av, ks.B * cp[k][j]);
-      uint4 o = make_uint4(pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3]), pack_bf16(gv[4], gv[5]), pack_bf16(gv[6], gv[7]));
-      if (k == k_y) patch_label(o);  // uniform
-      if (k < q || (k == q && tid < part)) store(k, o);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else if (kf.folded) {  // uniform
-#pragma unroll
-    for (int k = K - 1; k >= 0; --k) {
-      opaque(sreg[k]);  // sweep 2 unpacks the registers again instead of keeping sweep 1's floats alive
-      opaque(treg[k]);
-      uint4 o = grad8<kDense, true, DIVK>(sreg[k], treg[k], kf);
-      if (k == k_y) patch_label(o);  // uniform
-      if (k < q || (k == q && tid < part)) store(k, o);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {  // rows whose reference exponents are in the thousands: precise form
+  // The walk over the slice, last group first.  Unpacked again from the packed registers (`opaque`) instead of keeping
+  // sweep 1's floats alive.
+  auto walk = [&](auto form) {
+    constexpr int FORM = decltype(form)::value;
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
       opaque(sreg[k]);
       opaque(treg[k]);
-      uint4 o = grad8<kDense, false, DIVK>(sreg[k], treg[k], kf);
+      uint4 o = grad8<kDense, FORM, DIVK>(sreg[k], treg[k], kf);
       if (k == k_y) patch_label(o);  // uniform
-      if (k < q || (k == q && tid < part)) store(k, o);
+      if (k < n_mine) store(k, o);
       __builtin_amdgcn_sched_barrier(0);
     }
+  };
+  if constexpr (SKEW) {
+    if (L1 == kL1Own && ce) {  // uniform: the packed student logits are gone, their slice is fetched again (this workgroup has
+                       // not overwritten it yet, and no other one does)
+#pragma unroll
+      for (int k = K - 1; k >= 0; --k) {
+        const uint4 vs = ld_group<GB>(rs, voff, k, true, true);
+        float xs[8], gv[8];
+        unpack8(vs, xs);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          gv[j] = add_ce_own(__builtin_fmaf(cv[k][j], ks.Av, ks.B * cp[k][j]), xs[j], kf.p);
+        uint4 o = make_uint4(pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3]), pack_bf16(gv[4], gv[5]), pack_bf16(gv[6], gv[7]));
+        if (k == k_y) patch_label(o);  // uniform
+        if (k < n_mine) store(k, o);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int k = K - 1; k >= 0; --k) {
+        float gv[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if constexpr (L1 == kL1Square)  // (ks.C = 0 without a CE term)
+            gv[j] = __builtin_fmaf(cv[k][j], ks.Av, __builtin_fmaf(ks.C, cp[k][j], ks.B) * cp[k][j]);
+          else
+            gv[j] = __builtin_fmaf(cv[k][j], ks.Av, ks.B * cp[k][j]);
+        }
+        uint4 o = make_uint4(pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3]), pack_bf16(gv[4], gv[5]), pack_bf16(gv[6], gv[7]));
+        if (k == k_y) patch_label(o);  // uniform
+        if (k < n_mine) store(k, o);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else if (LSE1 && ce) {  // uniform
+    walk(std::integral_constant<int, L1 == kL1Square ? kPreciseCeSquare : kPreciseCeOwn>{});
+  } else if (kf.folded) {  // uniform
+    walk(std::integral_constant<int, kFolded>{});
+  } else if (ce) {  // rows at any offset, or whose reference exponents are in the thousands: precise form
+    walk(std::integral_constant<int, kPreciseCe>{});
+  } else {
+    walk(std::integral_constant<int, kPrecise>{});
   }
 }
 

@@ -14,10 +14,11 @@
 
 namespace npd {
 
-template <int K, bool LSE1>
+template <int K, int L1>
 __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdArgs a) {
   constexpr int TH = kGangThreads;
   constexpr int GB = TH * 16;
+  constexpr bool LSE1 = L1 != kL1None;
   constexpr int NS = LSE1 ? 2 : 1;  // student / tau, student at tau = 1
   constexpr int NW3 = NS * 3;
   constexpr int W = 8;              // words of scratch per slice
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
 
   const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
   const int voff = tid * 16;
-  const int q = ng / TH, part = ng - q * TH;  // uniform
+  const int n_mine = (ng - tid + TH - 1) / TH;  // groups of this thread
   uint4 sreg[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) sreg[k] = ld_group<GB>(rs, voff, k, true, true);
@@ -105,22 +106,25 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   Lse acc[4];  // 0 student / tau, 2 student at tau = 1 (the indices accum8 uses; 1 and 3 stay empty)
 #pragma unroll
   for (int i = 0; i < 4; ++i) acc[i].init();
-  const float kRefBias = a.ragged ? kRefSlack : 100.0f;  // see npd_kd_gang.hpp
+  const float kRefBias = a.ragged ? kRefSlack : (L1 == kL1Square ? 44.0f : 100.0f);  // see npd_kd_gang.hpp
   if (ng > tid) {
     const float fs = pk_max_value(pk_max_group(sreg[0]));
     acc[0].r = __builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f);
-    if constexpr (LSE1) acc[2].r = __builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f);
+    if constexpr (L1 == kL1Own) acc[2].r = __builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f);
+    if constexpr (L1 == kL1Square) acc[2].r = 2.0f * acc[0].r;
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    if (k < q || (k == q && tid < part)) {
+    if (k < n_mine) {
       float xs[8];
       unpack8(sreg[k], xs);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        acc[0].z += exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
-        if constexpr (LSE1) acc[2].z += exp2_fast(__builtin_fmaf(xs[j], kLog2e, -acc[2].r));
+        const float es = exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
+        acc[0].z += es;
+        if constexpr (L1 == kL1Square) acc[2].z = __builtin_fmaf(es, es, acc[2].z);
+        if constexpr (L1 == kL1Own) acc[2].z += exp2_fast(__builtin_fmaf(xs[j], kLog2e, -acc[2].r));
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
       acc[2].init();
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        if (k < q || (k == q && tid < part)) {
+        if (k < n_mine) {
           float xs[8];
           unpack8(sreg[k], xs);
           acc[0].add8(xs, c);
@@ -224,8 +228,8 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   const float Ls = st[0].log2_sum();
   const float Lt = tt.log2_sum();
   const float lse1_s = __fmul_rn(LSE1 ? st[1].log2_sum() : Ls, kLn2);
-  const bool ce = a.cscale != 0.0f;  // uniform (tau = 1 here whenever it is set)
-  Sweep2Coef kf = sweep2_coef(st[0], tt, c, a.gscale, a.cscale, true, false);
+  const bool ce = a.cscale != 0.0f;  // uniform
+  Sweep2Coef kf = sweep2_coef(st[0], tt, st[NS - 1], c, a.gscale, a.cscale, true, false, LSE1);
   kf.folded = kf.folded && !a.ragged;
 
   // ---- kd_tok (slice 0) and the final values of the support positions of this slice
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
     const uint4 qnan = make_uint4(0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u);
 #pragma unroll
     for (int k = 0; k < K; ++k)
-      if (k < q || (k == q && tid < part)) store(k, qnan);
+      if (k < n_mine) store(k, qnan);
     if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0x7fc0;
     return;
   }
@@ -329,25 +333,25 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
     if (patch_y && e == y) o = y_tail;
     grow[e] = o;
   }
-  if (kf.folded) {  // uniform
+  auto walk = [&](auto form) {
+    constexpr int FORM = decltype(form)::value;
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
       opaque(sreg[k]);
-      uint4 o = grad8<kTopk, true>(sreg[k], sreg[k], kf);
+      uint4 o = grad8<kTopk, FORM>(sreg[k], sreg[k], kf);
       if (k == k_y) patch_label(o);  // uniform
-      if (k < q || (k == q && tid < part)) store(k, o);
+      if (k < n_mine) store(k, o);
       __builtin_amdgcn_sched_barrier(0);
     }
-  } else {
-#pragma unroll
-    for (int k = K - 1; k >= 0; --k) {
-      opaque(sreg[k]);
-      uint4 o = grad8<kTopk, false>(sreg[k], sreg[k], kf);
-      if (k == k_y) patch_label(o);  // uniform
-      if (k < q || (k == q && tid < part)) store(k, o);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
+  };
+  if (LSE1 && ce)  // uniform
+    walk(std::integral_constant<int, L1 == kL1Square ? kPreciseCeSquare : kPreciseCeOwn>{});
+  else if (kf.folded)
+    walk(std::integral_constant<int, kFolded>{});
+  else if (ce)
+    walk(std::integral_constant<int, kPreciseCe>{});
+  else
+    walk(std::integral_constant<int, kPrecise>{});
   // the support positions get their final values once the dense stores of the whole workgroup are ordered before them
   __syncthreads();
   for (int j = tid; j < k_top; j += TH) {

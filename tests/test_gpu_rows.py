@@ -74,6 +74,8 @@ def _reference(oracle, lay, s, t, lab, div, tau, gs, ce):
     (30631, 30631, (0, 0, 0), None),      # two slices; rows at every offset in turn
     (50003, 50003, (3, 3, 3), None),      # the tensors themselves begin inside a group
     (151937, 151937, (0, 0, 0), None),    # eight slices, one element beyond a multiple of 8
+    (30624, 30624, (0, 0, 0), None),      # 16-byte aligned rows: two slices; padded rows
+    (100005, 100008, (0, 0, 0), None),
     (151936, 151944, (5, 5, 5), None),    # every row at the same odd offset
     (50003, 50003, (1, 2, 1), None),      # teacher elsewhere: no common groups
     (50003, 50003, (1, 1, 4), None),      # gradient elsewhere
@@ -87,11 +89,14 @@ def _reference(oracle, lay, s, t, lab, div, tau, gs, ce):
     (9, 9, (5, 5, 5), None),              # rows without a whole group among them
 ])
 @pytest.mark.parametrize("div,tau,ce", [("forward", 1.0, 0.25), ("forward", 2.0, 0.0), ("reverse", 1.0, 0.25),
-                                        ("skew", 1.0, 0.25), ("skew_reverse", 2.0, 0.0)])
+                                        ("skew", 1.0, 0.25), ("skew_reverse", 2.0, 0.0),
+                                        ("forward", 2.0, 0.25), ("reverse", 0.5, 0.25), ("skew", 2.0, 0.25),
+                                        ("skew_reverse", 2.0, 0.25)])   # the CE term with a softmax of its own
 def test_dense_rows_at_any_offset(oracle, V, pitch, offs, pitch_t, div, tau, ce):
     w, lay, s, t, lab = _batch(V)
     ref = _reference(oracle, lay, s, t, lab, div, tau, 0.75, ce)
-    bars = dict(grad_scale=0.75 + ce, tau=tau, amp_from_ref=div != "forward", folded=div != "forward")
+    bars = dict(grad_scale=0.75 + ce * max(1.0, tau), tau=tau, amp_from_ref=div != "forward",
+                folded=div != "forward" or (tau == 1.0 or ce == 0.0) and pitch % 8 == 0 and offs == (0, 0, 0))
     kw = dict(V=V, pitch=pitch, offs=offs, pitch_t=pitch_t, div=div, tau=tau, ce=ce)
     for mode in (dict(), dict(inplace=True), dict(no_workspace=True)):
         print(f"[rows] V={V} pitch={pitch} offs={offs} pitch_t={pitch_t} {div} tau={tau} {mode}", flush=True)
@@ -101,10 +106,10 @@ def test_dense_rows_at_any_offset(oracle, V, pitch, offs, pitch_t, div, tau, ce)
 
 
 @pytest.mark.parametrize("V,pitch,offs", [
-    (30631, 30631, (0, 0, 0)), (151937, 151937, (3, 3, 3)), (50003, 50003, (1, 1, 4)), (8199, 8199, (0, 0, 0)),
+    (30631, 30631, (0, 0, 0)), (151936, 151936, (0, 0, 0)), (151937, 151937, (3, 3, 3)), (50003, 50003, (1, 1, 4)), (8199, 8199, (0, 0, 0)),
     (2003, 2003, (6, 6, 6)), (40, 43, (0, 0, 0)),
 ])
-@pytest.mark.parametrize("tau,ce", [(1.0, 0.25), (2.0, 0.0)])
+@pytest.mark.parametrize("tau,ce", [(1.0, 0.25), (2.0, 0.0), (2.0, 0.25)])
 def test_topk_rows_at_any_offset(oracle, V, pitch, offs, tau, ce):
     k = 20
     w, lay, s, t, lab = _batch(V, k)
@@ -121,6 +126,30 @@ def test_topk_rows_at_any_offset(oracle, V, pitch, offs, tau, ce):
     for mode in (dict(), dict(inplace=True), dict(no_workspace=True)):
         print(f"[rows] top-k V={V} pitch={pitch} offs={offs} tau={tau} {mode}", flush=True)
         compare_kd(_call(lay, s, None, lab, **kw, **mode), ref, lay.loss_mask, lay.cu_seqlens, oracle,
-                   grad_scale=0.75 + ce, tau=tau, folded=False)
+                   grad_scale=0.75 + ce * max(1.0, tau), tau=tau,
+                   folded=(tau == 1.0 or ce == 0.0) and pitch % 8 == 0 and offs == (0, 0, 0))
     fwd = _call(lay, s, None, lab, **kw | dict(ce=0.0), grad=False)
     compare_kd(fwd, {n: ref[n] for n in ("kd", "nll_s", "lse_s")}, lay.loss_mask, lay.cu_seqlens, oracle)
+
+
+def test_composite_at_a_temperature_without_its_workspace(oracle):
+    """The CE term at tau != 1 takes the shared-row kernels with a workspace and the ones that need none without, be it
+    absent, short, off its alignment or over an output: never an error, the same result to rounding."""
+    V, tau, ce = 50264, 2.0, 0.25
+    w, lay, s, t, lab = _batch(V)
+    T = s.shape[0]
+    ref = _reference(oracle, lay, s, t, lab, "forward", tau, 0.75, ce)
+    need = 16 * 4 * T * 3 + 256
+    buf = torch.empty(need + 512, dtype=torch.uint8, device=dev())
+    off = -buf.data_ptr() % 256
+    mask, labels = torch.from_numpy(lay.loss_mask).to(dev()), torch.from_numpy(lab).to(dev())
+    grad = torch.empty_like(s)
+    for ws in (buf[off:off + need], buf[off:off + 512], buf[off + 8:off + 8 + need],
+               grad.view(torch.uint8).view(-1)[-grad.data_ptr() % 256:]):
+        kd, nll = (torch.empty(T, device=dev()) for _ in range(2))
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, labels=labels, tau=tau, grad_scale=0.75,
+                                    ce_grad_scale=ce, grad_out=grad, kd_tok=kd, nll_tok=nll, workspace=ws)
+        torch.cuda.synchronize()
+        got = dict(kd=kd.cpu().numpy().astype(np.float64), nll_s=nll.cpu().numpy().astype(np.float64),
+                   grad=grad.float().cpu().numpy().astype(np.float64))
+        compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce * tau, tau=tau, folded=False)
