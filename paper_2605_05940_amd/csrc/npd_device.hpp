@@ -3,7 +3,8 @@
 // Numerics.  All soft-max work is done in the base-2 domain: with c = log2(e) / tau,
 // exp(x / tau) = 2^(x * c).  A partial log-sum-exp is a pair (r, z) meaning
 // sum = z * 2^r; a partial cross term `a` carries the same implicit 2^r.  r is a lane's
-// private reference exponent.  It only moves when an incoming value exceeds it by more
+// private reference exponent, a whole number: scaling by 2^(r - r') and moving an exponent from z to r are then exact.
+// It only moves when an incoming value exceeds it by more
 // than 2^32, so the common case costs one fused multiply-add and one v_exp_f32 per
 // element and no rescaling; terms stay below 2^32 relative to r, far from fp32 overflow.
 #pragma once
@@ -89,10 +90,11 @@ struct Lse {
     if (__builtin_amdgcn_ballot_w64(lag) != 0) {
       asm volatile("");  // not speculatable: keeps this rare path behind a real branch
       if (lag) {
-        const float f = exp2_fast(r - u);  // the initial reference gives 0
+        const float R = __builtin_rintf(u);
+        const float f = exp2_fast(r - R);  // the initial reference gives 0
         z *= f;
         a *= f;
-        r = u;
+        r = R;
       }
     }
   }

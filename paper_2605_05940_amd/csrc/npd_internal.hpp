@@ -74,6 +74,14 @@ size_t gang_workspace_bytes(int64_t T, int32_t V, int teacher_kind, int divergen
 hipError_t launch_kd_gang(const KdArgs& a, int teacher_kind, hipStream_t stream);
 int set_gang_spin_limit(int polls);  // returns the previous limit; <= 0 restores the default
 
+// the row-gang kernels with a row to a workgroup, for rows that fit one (npd_kd_solo*.hip); no workspace
+bool solo_path_applies(const KdArgs& a, int teacher_kind, bool want_grad);
+hipError_t launch_kd_solo(const KdArgs& a, int teacher_kind, bool want_grad, hipStream_t stream);
+hipError_t launch_solo_forward(const KdArgs& a, hipStream_t stream);
+hipError_t launch_solo_reverse(const KdArgs& a, hipStream_t stream);
+hipError_t launch_solo_skew(const KdArgs& a, hipStream_t stream);
+hipError_t launch_solo_forward_only(const KdArgs& a, hipStream_t stream);
+
 // compute units of the current device (cached per device)
 int compute_units();
 

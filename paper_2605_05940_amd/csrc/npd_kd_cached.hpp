@@ -26,6 +26,7 @@
 
 namespace npd {
 
+constexpr int kCachedMinVocab = 8192;  // shorter rows have always had the precise gradient form
 constexpr int kCB = 1024;  // threads per workgroup: one workgroup owns a CU's whole register file
 constexpr int kGroupBytes = kCB * 16;  // one 128-bit group per thread
 

@@ -54,20 +54,21 @@ size_t gang_workspace_bytes(int64_t T, int32_t V, int teacher_kind, int divergen
   return ((size_t)T * g * gang_words(lse1 ? 4 : 2) + kGangTailWords) * sizeof(uint32_t);
 }
 
+// Runs in front of every launch of a row-gang kernel: clears the scratch record (and the words behind it) to the
+// pattern no posted word takes.
+__global__ __launch_bounds__(256) void gang_clear_kernel(uint32_t* ws, size_t words) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) ws[i] = kGangEmpty;
+}
+
 template <class Kernel>
-static hipError_t launch_gang_kernel(const KdArgs& a, int words_per_slice, Kernel kernel, hipStream_t stream) {
+static hipError_t launch_gang_kernel(const KdArgs& a, int words_per_slice, Kernel kernel, hipStream_t stream,
+                                     size_t lds_bytes = 0) {
   const size_t words = (size_t)a.T * a.gang * words_per_slice + kGangTailWords;
   const int64_t want = (int64_t)((words + 1023) / 1024);  // four words per thread
   const int64_t clear_grid = want < 8 * (int64_t)compute_units() ? want : 8 * (int64_t)compute_units();
   const hipError_t e = launch_kernel(gang_clear_kernel, dim3((unsigned)clear_grid), dim3(256), 0, stream, a.ws, words);
   if (e != hipSuccess) return e;
-  return launch_kernel(kernel, dim3((unsigned)(a.T * a.gang)), dim3(kGangThreads), 0, stream, a);
-}
-
-// the sums at tau = 1 of a call
-static int l1_mode(const KdArgs& a) {
-  if (!a.need_lse1) return kL1None;
-  return 2.0f * a.c == kLog2e ? kL1Square : kL1Own;  // tau = 2 (halving a float is exact)
+  return launch_kernel(kernel, dim3((unsigned)(a.T * a.gang)), dim3(kGangThreads), lds_bytes, stream, a);
 }
 
 template <int DIVK>
@@ -92,10 +93,11 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, hipStream_t stream
   while (a.gang_pow2 < a.gang) a.gang_pow2 *= 2;
   a.spin_limit = g_spin_limit.load(std::memory_order_relaxed);
   if (teacher_kind == kTopk) {
+    const size_t lds = (size_t)topk_lds_words(kGangThreads, kGangTopkK, a.k, false) * sizeof(uint32_t);
     switch (l1_mode(a)) {
-      case kL1None: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1None>, stream);
-      case kL1Square: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Square>, stream);
-      default: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Own>, stream);
+      case kL1None: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1None>, stream, lds);
+      case kL1Square: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Square>, stream, lds);
+      default: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Own>, stream, lds);
     }
   }
   switch (a.divergence) {

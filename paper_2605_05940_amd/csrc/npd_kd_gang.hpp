@@ -130,25 +130,47 @@ __device__ __forceinline__ uint32_t gang_wait(const uint32_t* p, uint32_t* aband
 // which sums at tau = 1 a kernel keeps, see kd_gang_kernel
 enum { kL1None = 0, kL1Own = 1, kL1Square = 2 };
 
+// which of them a call runs
+inline int l1_mode(const KdArgs& a) {
+  if (!a.need_lse1) return kL1None;
+  return 2.0f * a.c == kLog2e ? kL1Square : kL1Own;  // tau = 2 (halving a float is exact)
+}
+
 // words of scratch per slice: 3 per partial log-sum-exp, rounded up to a power of two
 __host__ __device__ constexpr int gang_words(int ns) { return ns == 2 ? 8 : 16; }
-
-// Runs in front of every launch of a row-gang kernel: clears the scratch record (and the words behind it) to the
-// pattern no posted word takes.
-__global__ __launch_bounds__(256) void gang_clear_kernel(uint32_t* ws, size_t words) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) ws[i] = kGangEmpty;
-}
 
 // Zero-fills the groups [g0, g0 + ng) of a gradient row, ng <= K * 256: what the workgroup of a slice does when its
 // row is not scored.  With slices that begin on 128-byte boundaries these short-lived workgroups, started in address
 // order among those of the scored rows, fill as fast as a separate fill pass (and save that pass).
-template <int K>
+template <int K, int TH = kGangThreads>
 __device__ __forceinline__ void gang_zero_slice(uint16_t* grow, int g0, int ng, int tid) {
   const u32x4 z = {0, 0, 0, 0};
   u32x4* p = reinterpret_cast<u32x4*>(grow) + g0;
 #pragma unroll
   for (int k = 0; k < K; ++k)
-    if (k * kGangThreads + tid < ng) __builtin_nontemporal_store(z, p + k * kGangThreads + tid);
+    if (k * TH + tid < ng) __builtin_nontemporal_store(z, p + k * TH + tid);
+}
+
+// The same kernels with a row to a workgroup (SOLO: no exchange, no workspace) take rows that fit one: TH threads of K
+// groups.  One wave per row (TH = 64) needs no barrier either; four such rows share a workgroup, which costs a quarter
+// of the workgroups to start.
+__host__ __device__ constexpr int solo_rows(int th) { return th == kWave ? 4 : 1; }
+__host__ __device__ constexpr int gang_block(int th, bool solo) { return solo ? th * solo_rows(th) : th; }
+// row of this workgroup (of this wave, where several rows share a workgroup)
+template <int TH>
+__device__ __forceinline__ int64_t solo_row() {
+  if constexpr (solo_rows(TH) == 1) return blockIdx.x;
+  return (int64_t)blockIdx.x * solo_rows(TH) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+}
+// waves per SIMD a kernel is compiled for: what its registers of data leave room for
+__host__ __device__ constexpr int gang_waves(int data_registers) { return data_registers <= 32 ? 6 : 4; }
+// orders a wave's or workgroup's earlier LDS accesses before its later ones
+template <int TH>
+__device__ __forceinline__ void row_sync() {
+  if constexpr (TH == kWave)
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  else
+    __syncthreads();
 }
 
 // ---- the skew divergences (three sweeps): sums and gradient on normalised log2-probabilities.
@@ -210,10 +232,12 @@ __device__ __forceinline__ float skew_grad(float xs, float xt, const SkewCoef& k
 // exponentials of their own, kL1Square (tau = 2) from squares of the exponentials at tau.  Measured (MI355X, 4,096 x
 // 151,936, dense teacher, composite loss at tau = 2): one workgroup per row, both sweeps from memory 738 us; shared
 // rows with own exponentials 495 us, bound by the seven v_exp_f32 per pair of logits; squares, four of them, 459 us.
-template <int K, int TEACHER, int L1, int DIVK = kForwardKl>
-__global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a) {
+template <int K, int TEACHER, int L1, int DIVK = kForwardKl, int TH = kGangThreads, bool SOLO = false, bool GRAD = true>
+__global__ __launch_bounds__(gang_block(TH, SOLO),
+                             gang_waves(DIVK == kSkewKl || DIVK == kSkewReverseKl ? 16 * K : 8 * K)) void
+kd_gang_kernel(const KdArgs a) {
   static_assert(TEACHER == kDense, "dense teacher");
-  constexpr int TH = kGangThreads;
+  static_assert(SOLO || (TH == kGangThreads && GRAD), "shared rows: gradient calls, 256 threads");
   constexpr int GB = TH * 16;
   constexpr bool LSE1 = L1 != kL1None;
   constexpr int NS = LSE1 ? 4 : 2;  // 0 student / tau, 1 teacher / tau (+ cross), 2 student tau = 1, 3 teacher tau = 1
@@ -224,22 +248,24 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   constexpr bool SKEW = DIVK == kSkewKl || DIVK == kSkewReverseKl;
   static_assert(NW3 + 2 <= W, "the second exchange of the skew forms uses two spare words of a slice's record");
   __shared__ float red[4 * 3 * (TH / kWave)];
-  __shared__ uint32_t xch[kGangMax * W];
-  __shared__ uint32_t xch2[SKEW ? kGangMax * 2 : 1];
+  __shared__ uint32_t xch[SOLO ? 1 : kGangMax * W];
+  __shared__ uint32_t xch2[SKEW && !SOLO ? kGangMax * 2 : 1];
   __shared__ int gave_up;
 
-  const int G = a.gang;
-  const int64_t row = blockIdx.x / (unsigned)G;
-  const int slice = (int)(blockIdx.x - (unsigned)(row * G));
-  const int tid = threadIdx.x;
+  const int G = SOLO ? 1 : a.gang;
+  const int64_t row = SOLO ? solo_row<TH>() : (int64_t)(blockIdx.x / (unsigned)G);
+  const int slice = SOLO ? 0 : (int)(blockIdx.x - (unsigned)(row * G));
+  const int tid = threadIdx.x % (unsigned)TH;
+  if constexpr (solo_rows(TH) > 1)
+    if (row >= a.T) return;
   const int V = a.V;
-  uint16_t* grow = a.g + row * a.s_stride;
-  const RowSplit sp = row_split(grow, V, true);  // every dense row at the same offset from a 16-byte boundary
+  uint16_t* grow = GRAD ? a.g + row * a.s_stride : nullptr;
+  const RowSplit sp = row_split(a.s + row * a.s_stride, V, true);  // all dense rows at one offset from a 16-byte boundary
   const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;
   // This workgroup owns groups [g0, g1) -- the last slice also the edge elements of the row.  Boundaries inside the row
   // are moved down to the next 128-byte boundary of the gradient row's address (by `shift` groups), so that no cache
   // line is shared by two workgroups of a row; a slice is at most 7 groups longer than a.gang_groups for it.
-  const bool last = slice == G - 1;
+  const bool last = SOLO || slice == G - 1;
   const int shift = (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
   const int b0 = slice * a.gang_groups - shift, b1 = b0 + a.gang_groups;
   const int g0 = slice == 0 ? 0 : (b0 < nvec ? b0 : nvec);
@@ -253,8 +279,10 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       if (a.tnll) a.tnll[row] = 0.0f;
       if (a.lse) a.lse[row] = 0.0f;
     }
-    gang_zero_slice<K>(grow + head, g0, ng, tid);
-    if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
+    if constexpr (GRAD) {
+      gang_zero_slice<K, TH>(grow + head, g0, ng, tid);
+      if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
+    }
     return;
   }
 
@@ -262,7 +290,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   const uint16_t* trow = a.t + row * a.t_stride;
   const float c = a.c;
   const bool lse1_t = LSE1 && a.tnll != nullptr;
-  if (tid == 0) gave_up = 0;  // ordered before its use by the barriers of block_merge
+  if (!SOLO && tid == 0) gave_up = 0;  // ordered before its use by the barrier of the workgroup's merge
 
   // The slice as a buffer: all of a thread's groups are requested at once, unconditionally (a predicate around a load
   // makes the compiler wait for it on the spot); groups past the slice's end read as zero and are never used.  The thread
@@ -313,19 +341,31 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
   // one multiplication each instead of unpacking and exponentiating again, and leaves p_S and p_S (u - const) in the
   // same registers, so that the gradient sweep is one multiply-add per element.  Their references get 64 bits of head
   // room: an element's exponential is kept down to 2^-62 of the thread's first group's largest.
-  // Rows at any offset keep the 32 bits of head room (and the precise gradient form) they have in the streaming
-  // kernels: smaller arguments, hence smaller rounding errors, at the price of more careful re-runs on heavy tails.
+  // Rows of one workgroup and rows at any offset take the largest of all the thread's logits and no head room: arguments
+  // are then <= 0 and as small as can be where a term matters (rounding errors no larger than in the streaming kernels
+  // that such rows once ran in, also on heavy tails, and no careful re-runs there), for half an instruction per logit
+  // and a wait for all loads, which short rows hide behind one another.
   // Squares of exponentials get 44 bits, so that a square is kept down to 2^-38 of the first group's largest square and
   // its sum is inside the range up to 94 bits above the first group's largest logit.
-  const float kRefBias = a.ragged ? kRefSlack : (L1 == kL1Square ? 44.0f : (SKEW ? 64.0f : 100.0f));
+  const bool ref_of_all = SOLO || a.ragged;  // uniform
+  const float kRefBias = ref_of_all ? 0.0f : (L1 == kL1Square ? 44.0f : (SKEW ? 64.0f : 100.0f));
   float cp[SKEW ? K : 1][8], cv[SKEW ? K : 1][8];
   if (ng > tid) {  // (threads without a group keep their empty partials)
-    const float fs = pk_max_value(pk_max_group(sreg[0])), ft = pk_max_value(pk_max_group(treg[0]));
-    acc[0].r = __builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f);
-    acc[1].r = __builtin_fmaxf(__builtin_fmaf(ft, c, kRefBias), -1.0e30f);
+    uint32_t ms = pk_max_group(sreg[0]), mt = pk_max_group(treg[0]);
+    if (ref_of_all) {
+#pragma unroll
+      for (int k = 1; k < K; ++k)
+        if (k < n_mine) {
+          ms = pk_max_i16(ms, pk_max_group(sreg[k]));
+          mt = pk_max_i16(mt, pk_max_group(treg[k]));
+        }
+    }
+    const float fs = pk_max_value(ms), ft = pk_max_value(mt);
+    acc[0].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f));
+    acc[1].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(ft, c, kRefBias), -1.0e30f));
     if constexpr (L1 == kL1Own) {
-      acc[2].r = __builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f);
-      acc[3].r = __builtin_fmaxf(__builtin_fmaf(ft, kLog2e, kRefBias), -1.0e30f);
+      acc[2].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f));
+      acc[3].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(ft, kLog2e, kRefBias), -1.0e30f));
     }
     if constexpr (L1 == kL1Square) {
       acc[2].r = 2.0f * acc[0].r;
@@ -429,63 +469,70 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     else
       wave_merge_rescaled<false>(acc[i]);
   }
-  if (lane == 0) {
+  bool timeout = false;
+  uint32_t* rec = nullptr;
+  uint32_t* abandon = nullptr;
+  if constexpr (NWV > 1) {
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        red[(i * 3 + 0) * NWV + wid] = acc[i].r;
+        red[(i * 3 + 1) * NWV + wid] = acc[i].z;
+        red[(i * 3 + 2) * NWV + wid] = acc[i].a;
+      }
+    }
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      red[(i * 3 + 0) * NWV + wid] = acc[i].r;
-      red[(i * 3 + 1) * NWV + wid] = acc[i].z;
-      red[(i * 3 + 2) * NWV + wid] = acc[i].a;
+      acc[i].init();
+      if (lane < NWV) {
+        acc[i].r = red[(i * 3 + 0) * NWV + lane];
+        acc[i].z = red[(i * 3 + 1) * NWV + lane];
+        acc[i].a = red[(i * 3 + 2) * NWV + lane];
+      }
+      if (i == (REV ? 0 : 1) && !SKEW)  // the stream that carries the cross term
+        wave_merge_rescaled<true>(acc[i]);
+      else
+        wave_merge_rescaled<false>(acc[i]);
     }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    acc[i].init();
-    if (lane < NWV) {
-      acc[i].r = red[(i * 3 + 0) * NWV + lane];
-      acc[i].z = red[(i * 3 + 1) * NWV + lane];
-      acc[i].a = red[(i * 3 + 2) * NWV + lane];
-    }
-    if (i == (REV ? 0 : 1) && !SKEW)  // the stream that carries the cross term
-      wave_merge_rescaled<true>(acc[i]);
-    else
-      wave_merge_rescaled<false>(acc[i]);
-  }
 
-  uint32_t* rec = a.ws + (size_t)blockIdx.x * W;  // scratch[row][slice]
-  uint32_t* abandon = a.ws + (size_t)gridDim.x * W;  // behind the record
-  if (tid < NW3) {
-    float v = acc[0].r;
-#pragma unroll
-    for (int i = 0; i < NS; ++i) {
-      if (tid == i * 3 + 0) v = acc[i].r;
-      if (tid == i * 3 + 1) v = acc[i].z;
-      if (tid == i * 3 + 2) v = acc[i].a;
-    }
-    gang_post(rec + tid, v);
   }
-  {
-    const uint32_t* rrow = a.ws + (size_t)row * G * W;
-    const int nw = G * NW3;
-    for (int w = tid; w < nw; w += TH) {
-      const int s = w / NW3, f = w - s * NW3;
-      xch[s * W + f] = gang_wait(rrow + s * W + f, abandon, a.spin_limit, &gave_up);
-    }
-  }
-  __syncthreads();
-  bool timeout = gave_up != 0;  // uniform
+  if constexpr (!SOLO) {
+    rec = a.ws + (size_t)blockIdx.x * W;  // scratch[row][slice]
+    abandon = a.ws + (size_t)gridDim.x * W;  // behind the record
+    if (tid < NW3) {
+      float v = acc[0].r;
 #pragma unroll
-  for (int i = 0; i < NS; ++i) {  // lane s < G takes slice s: every wave of every workgroup of the row computes the
-    acc[i].init();                // same totals in the same order
-    if (lane < G) {
-      acc[i].r = __builtin_bit_cast(float, xch[lane * W + i * 3 + 0]);
-      acc[i].z = __builtin_bit_cast(float, xch[lane * W + i * 3 + 1]);
-      acc[i].a = __builtin_bit_cast(float, xch[lane * W + i * 3 + 2]);
+      for (int i = 0; i < NS; ++i) {
+        if (tid == i * 3 + 0) v = acc[i].r;
+        if (tid == i * 3 + 1) v = acc[i].z;
+        if (tid == i * 3 + 2) v = acc[i].a;
+      }
+      gang_post(rec + tid, v);
     }
-    if (i == (REV ? 0 : 1) && !SKEW)  // the stream that carries the cross term
-      wave_merge_rescaled<true>(acc[i]);
-    else
-      wave_merge_rescaled<false>(acc[i]);
+    {
+      const uint32_t* rrow = a.ws + (size_t)row * G * W;
+      const int nw = G * NW3;
+      for (int w = tid; w < nw; w += TH) {
+        const int s = w / NW3, f = w - s * NW3;
+        xch[s * W + f] = gang_wait(rrow + s * W + f, abandon, a.spin_limit, &gave_up);
+      }
+    }
+    __syncthreads();
+    timeout = gave_up != 0;  // uniform
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {  // lane s < G takes slice s: every wave of every workgroup of the row computes the
+      acc[i].init();                // same totals in the same order
+      if (lane < G) {
+        acc[i].r = __builtin_bit_cast(float, xch[lane * W + i * 3 + 0]);
+        acc[i].z = __builtin_bit_cast(float, xch[lane * W + i * 3 + 1]);
+        acc[i].a = __builtin_bit_cast(float, xch[lane * W + i * 3 + 2]);
+      }
+      if (i == (REV ? 0 : 1) && !SKEW)  // the stream that carries the cross term
+        wave_merge_rescaled<true>(acc[i]);
+      else
+        wave_merge_rescaled<false>(acc[i]);
+    }
   }
 
   const float Ls = acc[0].log2_sum();
@@ -528,25 +575,30 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     // workgroup totals, second post / wait, row totals -- plain sums in a fixed order
     dsum = wave_sum_dpp(dsum);
     usum = wave_sum_dpp(usum);
-    if (lane == 0) {
-      red[wid] = dsum;
-      red[NWV + wid] = usum;
-    }
-    __syncthreads();
-    dsum = wave_sum_dpp(lane < NWV ? red[lane] : 0.0f);
-    usum = wave_sum_dpp(lane < NWV ? red[NWV + lane] : 0.0f);
-    if (tid < 2) gang_post(rec + NW3 + tid, tid == 0 ? dsum : usum);
-    {
-      const uint32_t* rrow = a.ws + (size_t)row * G * W;
-      for (int w = tid; w < 2 * G; w += TH) {
-        const int s = w >> 1, f = w & 1;
-        xch2[w] = gang_wait(rrow + s * W + NW3 + f, abandon, a.spin_limit, &gave_up);
+    if constexpr (NWV > 1) {
+      if constexpr (SOLO) __syncthreads();  // the first merge's readers of `red` are done
+      if (lane == 0) {
+        red[wid] = dsum;
+        red[NWV + wid] = usum;
       }
+      __syncthreads();
+      dsum = wave_sum_dpp(lane < NWV ? red[lane] : 0.0f);
+      usum = wave_sum_dpp(lane < NWV ? red[NWV + lane] : 0.0f);
     }
-    __syncthreads();
-    timeout = gave_up != 0;
-    dsum = wave_sum_dpp(lane < G ? __builtin_bit_cast(float, xch2[2 * lane]) : 0.0f);
-    usum = wave_sum_dpp(lane < G ? __builtin_bit_cast(float, xch2[2 * lane + 1]) : 0.0f);
+    if constexpr (!SOLO) {
+      if (tid < 2) gang_post(rec + NW3 + tid, tid == 0 ? dsum : usum);
+      {
+        const uint32_t* rrow = a.ws + (size_t)row * G * W;
+        for (int w = tid; w < 2 * G; w += TH) {
+          const int s = w >> 1, f = w & 1;
+          xch2[w] = gang_wait(rrow + s * W + NW3 + f, abandon, a.spin_limit, &gave_up);
+        }
+      }
+      __syncthreads();
+      timeout = gave_up != 0;
+      dsum = wave_sum_dpp(lane < G ? __builtin_bit_cast(float, xch2[2 * lane]) : 0.0f);
+      usum = wave_sum_dpp(lane < G ? __builtin_bit_cast(float, xch2[2 * lane + 1]) : 0.0f);
+    }
     kd = dsum * kLn2;
     kd = kd < 0.0f ? 0.0f : kd;
     const float g = a.gscale;  // (grad_scale / tau)
@@ -561,7 +613,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
       ks.Av = g;
     }
   }
-  kf.folded = kf.folded && !a.ragged;
+  kf.folded = kf.folded && !a.ragged && !(SOLO && V < kCachedMinVocab);
   if constexpr (REV) {
     const float inv_z = 1.0f / acc[0].z;
     kf.ra = a.gscale * a.inv_tau * inv_z;
@@ -594,6 +646,7 @@ __global__ __launch_bounds__(kGangThreads, 4) void kd_gang_kernel(const KdArgs a
     if (flags && a.status) atomicOr(a.status, flags);
   }
 
+  if constexpr (!GRAD) return;
   // ---- sweep 2: the gradient of the slice, from the registers, last group first
   uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (size_t)g0 * 16;
   auto store = [&](int k, const uint4& o) {  // the group's base is uniform, the thread adds tid * 16

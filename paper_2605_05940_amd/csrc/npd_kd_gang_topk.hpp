@@ -14,33 +14,61 @@
 
 namespace npd {
 
-template <int K, int L1>
-__global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdArgs a) {
-  constexpr int TH = kGangThreads;
+// SOLO, TH, GRAD: as in npd_kd_gang.hpp; the forward-only SOLO form also takes calls without a teacher (k = 0).
+// Dynamic LDS: topk_lds_words per row of the workgroup.
+//
+// SOLO puts the final values of the support positions into the groups before they are stored: each group of the row has
+// a list of them in LDS that the threads build with exchanges (its order does not matter: the ids are distinct).
+// Stored behind the dense values they cost a wait for the whole workgroup's stores and k partial lines per row, which
+// dominates short rows (65,536 rows of 4,096, k = 64: 412 us, with lists 255 us).  On shared rows the k positions are
+// few per slice; they are stored behind the dense values there.
+constexpr int kMaxEdges = 16;
+__host__ __device__ constexpr int topk_lds_words(int th, int groups, int k, bool lists) {
+  return (lists ? th * groups + kMaxEdges + k : 0) + (k + 1) / 2;
+}
+
+template <int K, int L1, int TH = kGangThreads, bool SOLO = false, bool GRAD = true>
+__global__ __launch_bounds__(gang_block(TH, SOLO), SOLO && K <= 8 ? 8 : 6) void
+kd_gang_topk_kernel(const KdArgs a) {
+  static_assert(SOLO || (TH == kGangThreads && GRAD), "shared rows: gradient calls, 256 threads");
   constexpr int GB = TH * 16;
   constexpr bool LSE1 = L1 != kL1None;
+  constexpr bool LIST = SOLO && GRAD;
   constexpr int NS = LSE1 ? 2 : 1;  // student / tau, student at tau = 1
   constexpr int NW3 = NS * 3;
   constexpr int W = 8;              // words of scratch per slice
   constexpr int NWV = TH / kWave;
   __shared__ float red[2 * 3 * NWV + NWV];
-  __shared__ uint32_t xch[kGangMax * W];
-  __shared__ uint16_t sup_s[kTopkMax];  // student logits at the support positions (bf16 bits); later their patches
-  __shared__ int gave_up, y_in_support;
+  __shared__ uint32_t xch[SOLO ? 1 : kGangMax * W];
+  extern __shared__ uint32_t topk_rows[];
+  __shared__ int gave_up, y_hit_row;
 
-  const int G = a.gang;
-  const int64_t row = blockIdx.x / (unsigned)G;
-  const int slice = (int)(blockIdx.x - (unsigned)(row * G));
-  const int tid = threadIdx.x;
+  const int G = SOLO ? 1 : a.gang;
+  const int64_t row = SOLO ? solo_row<TH>() : (int64_t)(blockIdx.x / (unsigned)G);
+  const int slice = SOLO ? 0 : (int)(blockIdx.x - (unsigned)(row * G));
+  const int tid = threadIdx.x % (unsigned)TH;
+  if constexpr (solo_rows(TH) > 1)
+    if (row >= a.T) return;
   const int k_top = a.k;
+  // LDS of the row: per group (and per edge element) the first of its support positions (entry + 1, 0: none), per entry
+  // the next one of the same group (same encoding, low half) and its element of the group (high half); the student
+  // logits at the support positions (bf16 bits), later their final gradient values
+  uint32_t* first = topk_rows + (solo_rows(TH) > 1 ? (threadIdx.x / TH) * topk_lds_words(TH, K, k_top, LIST) : 0);
+  uint32_t* link = first + K * TH + kMaxEdges;
+  uint16_t* sup_s = reinterpret_cast<uint16_t*>(LIST ? link + k_top : first);
+  if constexpr (LIST) {  // ordered before their use by the barrier below
+#pragma unroll
+    for (int k = 0; k < K; ++k) first[k * TH + tid] = 0;
+    if (tid < kMaxEdges) first[K * TH + tid] = 0;
+  }
   const int V = a.V;
-  uint16_t* grow = a.g + row * a.s_stride;
-  const RowSplit sp = row_split(grow, V, true);  // every dense row at the same offset from a 16-byte boundary
+  uint16_t* grow = GRAD ? a.g + row * a.s_stride : nullptr;
+  const RowSplit sp = row_split(a.s + row * a.s_stride, V, true);  // all dense rows at one offset from a 16-byte boundary
   const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;
   // This workgroup owns groups [g0, g1) -- the last slice also the edge elements of the row.  Boundaries inside the row
   // are moved down to the next 128-byte boundary of the gradient row's address (by `shift` groups), so that no cache
   // line is shared by two workgroups of a row; a slice is at most 7 groups longer than a.gang_groups for it.
-  const bool last = slice == G - 1;
+  const bool last = SOLO || slice == G - 1;
   const int shift = (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
   const int b0 = slice * a.gang_groups - shift, b1 = b0 + a.gang_groups;
   const int g0 = slice == 0 ? 0 : (b0 < nvec ? b0 : nvec);
@@ -53,14 +81,16 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
       if (a.nll) a.nll[row] = 0.0f;
       if (a.lse) a.lse[row] = 0.0f;
     }
-    gang_zero_slice<K>(grow + head, g0, ng, tid);
-    if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
+    if constexpr (GRAD) {
+      gang_zero_slice<K, TH>(grow + head, g0, ng, tid);
+      if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
+    }
     return;
   }
 
   const uint16_t* srow = a.s + row * a.s_stride;
   const float c = a.c;
-  if (tid == 0) gave_up = y_in_support = 0;  // ordered before their use by the barrier below
+  if (TH > kWave && tid == 0) gave_up = y_hit_row = 0;  // ordered before their use by the barrier below
 
   const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
   const int voff = tid * 16;
@@ -91,26 +121,40 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   Lse tt;
   tt.init();
   int bad_index = 0;
-  for (int j = tid; j < k_top; j += TH) {
-    const int id = irow[j];
-    tt.add1(vrow[j], c);
+  // entries tid, tid + TH, ...; the first (for k <= TH the only one) is kept in registers
+  const bool has_entry = tid < k_top;
+  const int id_first = has_entry ? irow[tid] : 0;
+  const float v_first = has_entry ? vrow[tid] : 0.0f;
+  auto each_entry = [&](auto&& f) {
+    if (has_entry) f(tid, id_first, v_first);
+    for (int j = tid + TH; j < k_top; j += TH) f(j, irow[j], vrow[j]);
+  };
+  each_entry([&](int j, int id, float v) {
+    tt.add1(v, c);
     if ((unsigned)id >= (unsigned)V) {
       bad_index = 1;
     } else if (slice == 0 || owns(id)) {
       sup_s[j] = srow[id];
     }
-  }
+  });
 
   // ---- sweep 1 over the student slice (see npd_kd_gang.hpp: fixed reference from the first group, careful re-run
   // of a wave whose sums show an anomaly)
   Lse acc[4];  // 0 student / tau, 2 student at tau = 1 (the indices accum8 uses; 1 and 3 stay empty)
 #pragma unroll
   for (int i = 0; i < 4; ++i) acc[i].init();
-  const float kRefBias = a.ragged ? kRefSlack : (L1 == kL1Square ? 44.0f : 100.0f);  // see npd_kd_gang.hpp
+  const bool ref_of_all = SOLO || a.ragged;
+  const float kRefBias = ref_of_all ? 0.0f : (L1 == kL1Square ? 44.0f : 100.0f);  // see npd_kd_gang.hpp
   if (ng > tid) {
-    const float fs = pk_max_value(pk_max_group(sreg[0]));
-    acc[0].r = __builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f);
-    if constexpr (L1 == kL1Own) acc[2].r = __builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f);
+    uint32_t ms = pk_max_group(sreg[0]);
+    if (ref_of_all) {
+#pragma unroll
+      for (int k = 1; k < K; ++k)
+        if (k < n_mine) ms = pk_max_i16(ms, pk_max_group(sreg[k]));
+    }
+    const float fs = pk_max_value(ms);
+    acc[0].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f));
+    if constexpr (L1 == kL1Own) acc[2].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f));
     if constexpr (L1 == kL1Square) acc[2].r = 2.0f * acc[0].r;
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -165,64 +209,70 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   normalise(tt);
   wave_merge_rescaled<false>(tt);
   bad_index = __builtin_amdgcn_ballot_w64(bad_index != 0) != 0;
-  if (lane == 0) {
+  if constexpr (NWV == 1) row_sync<TH>();  // the gathered support logits before their readers
+  if constexpr (NWV > 1) {
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        red[(i * 2 + 0) * NWV + wid] = st[i].r;
+        red[(i * 2 + 1) * NWV + wid] = st[i].z;
+      }
+      red[4 * NWV + wid] = tt.r;
+      red[5 * NWV + wid] = tt.z;
+      red[6 * NWV + wid] = bad_index ? 1.0f : 0.0f;
+    }
+    __syncthreads();  // also orders the gathered support logits in sup_s before their readers
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      red[(i * 2 + 0) * NWV + wid] = st[i].r;
-      red[(i * 2 + 1) * NWV + wid] = st[i].z;
+      st[i].init();
+      if (lane < NWV) {
+        st[i].r = red[(i * 2 + 0) * NWV + lane];
+        st[i].z = red[(i * 2 + 1) * NWV + lane];
+      }
+      wave_merge_rescaled<false>(st[i]);
     }
-    red[4 * NWV + wid] = tt.r;
-    red[5 * NWV + wid] = tt.z;
-    red[6 * NWV + wid] = bad_index ? 1.0f : 0.0f;
-  }
-  __syncthreads();  // also orders the gathered support logits in sup_s before their readers
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    st[i].init();
+    tt.init();
     if (lane < NWV) {
-      st[i].r = red[(i * 2 + 0) * NWV + lane];
-      st[i].z = red[(i * 2 + 1) * NWV + lane];
+      tt.r = red[4 * NWV + lane];
+      tt.z = red[5 * NWV + lane];
     }
-    wave_merge_rescaled<false>(st[i]);
+    wave_merge_rescaled<false>(tt);
+    bad_index = __builtin_amdgcn_ballot_w64(lane < NWV && red[6 * NWV + (lane & (NWV - 1))] != 0.0f) != 0;  // uniform
   }
-  tt.init();
-  if (lane < NWV) {
-    tt.r = red[4 * NWV + lane];
-    tt.z = red[5 * NWV + lane];
-  }
-  wave_merge_rescaled<false>(tt);
-  bad_index = (red[6 * NWV + 0] + red[6 * NWV + 1] + red[6 * NWV + 2] + red[6 * NWV + 3]) != 0.0f;  // uniform
 
-  uint32_t* rec = a.ws + (size_t)blockIdx.x * W;
-  uint32_t* abandon = a.ws + (size_t)gridDim.x * W;  // behind the record
-  if (tid < NW3) {
-    float v = st[0].r;
+  bool timeout = false;
+  if constexpr (!SOLO) {
+    uint32_t* rec = a.ws + (size_t)blockIdx.x * W;
+    uint32_t* abandon = a.ws + (size_t)gridDim.x * W;  // behind the record
+    if (tid < NW3) {
+      float v = st[0].r;
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        if (tid == i * 3 + 0) v = st[i].r;
+        if (tid == i * 3 + 1) v = st[i].z;
+        if (tid == i * 3 + 2) v = 0.0f;
+      }
+      gang_post(rec + tid, v);
+    }
+    {
+      const uint32_t* rrow = a.ws + (size_t)row * G * W;
+      const int nw = G * NW3;
+      for (int w = tid; w < nw; w += TH) {
+        const int s = w / NW3, f = w - s * NW3;
+        xch[s * W + f] = gang_wait(rrow + s * W + f, abandon, a.spin_limit, &gave_up);
+      }
+    }
+    __syncthreads();
+    timeout = gave_up != 0;  // uniform
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      if (tid == i * 3 + 0) v = st[i].r;
-      if (tid == i * 3 + 1) v = st[i].z;
-      if (tid == i * 3 + 2) v = 0.0f;
+      st[i].init();
+      if (lane < G) {
+        st[i].r = __builtin_bit_cast(float, xch[lane * W + i * 3 + 0]);
+        st[i].z = __builtin_bit_cast(float, xch[lane * W + i * 3 + 1]);
+      }
+      wave_merge_rescaled<false>(st[i]);
     }
-    gang_post(rec + tid, v);
-  }
-  {
-    const uint32_t* rrow = a.ws + (size_t)row * G * W;
-    const int nw = G * NW3;
-    for (int w = tid; w < nw; w += TH) {
-      const int s = w / NW3, f = w - s * NW3;
-      xch[s * W + f] = gang_wait(rrow + s * W + f, abandon, a.spin_limit, &gave_up);
-    }
-  }
-  __syncthreads();
-  const bool timeout = gave_up != 0;  // uniform
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    st[i].init();
-    if (lane < G) {
-      st[i].r = __builtin_bit_cast(float, xch[lane * W + i * 3 + 0]);
-      st[i].z = __builtin_bit_cast(float, xch[lane * W + i * 3 + 1]);
-    }
-    wave_merge_rescaled<false>(st[i]);
   }
 
   const float Ls = st[0].log2_sum();
@@ -230,42 +280,54 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
   const float lse1_s = __fmul_rn(LSE1 ? st[1].log2_sum() : Ls, kLn2);
   const bool ce = a.cscale != 0.0f;  // uniform
   Sweep2Coef kf = sweep2_coef(st[0], tt, st[NS - 1], c, a.gscale, a.cscale, true, false, LSE1);
-  kf.folded = kf.folded && !a.ragged;
+  kf.folded = kf.folded && !a.ragged && !(SOLO && V < kCachedMinVocab);
 
   // ---- kd_tok (slice 0) and the final values of the support positions of this slice
   float part_kd = 0.0f;
   int y_hit = 0;
   if (!bad_index) {
-    for (int j = tid; j < k_top; j += TH) {
-      const int id = irow[j];
+    each_entry([&](int j, int id, float v) {
       const bool mine = owns(id);
       if (slice == 0 || mine) {
-        const float b = vrow[j] * c;
+        const float b = v * c;
         const float sj = bf16_one(sup_s[j]);
         if (slice == 0) {
           const float lpt = b - Lt;
           const float lps = __builtin_fmaf(sj, c, -Ls);
           part_kd = __builtin_fmaf(exp2_fast(lpt), __builtin_fmaxf(lpt - lps, -3.4028234663852886e38f) * kLn2, part_kd);
         }
-        if (mine) {
+        if (GRAD && mine) {
           float gj = grad_pair_elem(sj, b, kf.p);
           if (ce && id == y) {
             gj -= a.cscale;
             y_hit = 1;
           }
-          sup_s[j] = one_bf16(gj);  // this thread read sup_s[j] above: no other thread touches entry j
+          sup_s[j] = one_bf16(gj);  // this thread read sup_s[j] above: no other thread touches entry j before the barrier
+          if constexpr (LIST) {
+            const int ge = sp.group_of(id);
+            const int list = ge >= 0 ? ge : K * TH + (id < head ? id : id - nvec * 8);
+            link[j] = atomicExch(&first[list], (uint32_t)(j + 1)) | ((uint32_t)((id - head) & 7) << 16);
+          }
         }
       }
-    }
+    });
   }
+  if constexpr (LIST && NWV == 1) row_sync<TH>();  // the lists before their readers (else: the barrier below)
   float kd = wave_sum_dpp(part_kd);
-  y_hit = __builtin_amdgcn_ballot_w64(y_hit != 0) != 0;
-  if (lane == 0) {
-    red[wid] = kd;
-    if (y_hit) y_in_support = 1;
+  bool y_in_support = __builtin_amdgcn_ballot_w64(y_hit != 0) != 0;  // the label is one of the support positions
+  if constexpr (NWV > 1) {
+    if constexpr (SOLO) __syncthreads();  // the first merge's readers of `red` are done
+    if (lane == 0) {
+      red[wid] = kd;
+      if (y_in_support) y_hit_row = 1;
+    }
+    __syncthreads();
+    y_in_support = y_hit_row != 0;
+    if constexpr (NWV == 4)
+      kd = (red[0] + red[1]) + (red[2] + red[3]);
+    else
+      kd = wave_sum_dpp(lane < NWV ? red[lane] : 0.0f);
   }
-  __syncthreads();
-  kd = (red[0] + red[1]) + (red[2] + red[3]);
   kd = kd < 0.0f ? 0.0f : kd;
   if (bad_index) kd = __builtin_nanf("");
 
@@ -286,6 +348,7 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
     if (flags && a.status) atomicOr(a.status, flags);
   }
 
+  if constexpr (!GRAD) return;
   // ---- sweep 2: dense part p_S * weights from the registers, then the support positions of this slice
   uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (size_t)g0 * 16;
   auto store = [&](int k, const uint4& o) {
@@ -327,20 +390,29 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
     o.z = (o.z & y_keep.z) | y_bits.z;
     o.w = (o.w & y_keep.w) | y_bits.w;
   };
-  if (last && tid < n_edge) {
-    const int e = sp.edge_elem(tid);
-    uint16_t o = one_bf16(grad_student_elem(bf16_one(srow[e]), kf.p));
-    if (patch_y && e == y) o = y_tail;
-    grow[e] = o;
-  }
+  // the final values of the support positions on the list that begins with entry j1 - 1
+  auto patch_support = [&](uint4& o, uint32_t j1) {
+    while (j1 != 0) {
+      const uint32_t l = link[j1 - 1], b16 = sup_s[j1 - 1], e = l >> 16;
+      j1 = l & 0xffffu;
+      const uint32_t keep = (e & 1) ? 0x0000ffffu : 0xffff0000u, bits = (e & 1) ? b16 << 16 : b16;
+      o.x = (e >> 1) == 0 ? (o.x & keep) | bits : o.x;
+      o.y = (e >> 1) == 1 ? (o.y & keep) | bits : o.y;
+      o.z = (e >> 1) == 2 ? (o.z & keep) | bits : o.z;
+      o.w = (e >> 1) == 3 ? (o.w & keep) | bits : o.w;
+    }
+  };
   auto walk = [&](auto form) {
     constexpr int FORM = decltype(form)::value;
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
-      opaque(sreg[k]);
-      uint4 o = grad8<kTopk, FORM>(sreg[k], sreg[k], kf);
-      if (k == k_y) patch_label(o);  // uniform
-      if (k < n_mine) store(k, o);
+      if (k < n_mine) {
+        opaque(sreg[k]);
+        uint4 o = grad8<kTopk, FORM>(sreg[k], sreg[k], kf);
+        if (k == k_y) patch_label(o);  // uniform
+        if constexpr (LIST) patch_support(o, first[k * TH + tid]);
+        store(k, o);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -352,11 +424,23 @@ __global__ __launch_bounds__(kGangThreads, 6) void kd_gang_topk_kernel(const KdA
     walk(std::integral_constant<int, kPreciseCe>{});
   else
     walk(std::integral_constant<int, kPrecise>{});
-  // the support positions get their final values once the dense stores of the whole workgroup are ordered before them
-  __syncthreads();
-  for (int j = tid; j < k_top; j += TH) {
-    const int id = irow[j];
-    if (owns(id)) grow[id] = sup_s[j];
+  if (last && tid < n_edge) {
+    const int e = sp.edge_elem(tid);
+    uint16_t o = one_bf16(grad_student_elem(bf16_one(srow[e]), kf.p));
+    if (patch_y && e == y) o = y_tail;
+    if constexpr (LIST) {
+      const uint32_t j1 = first[K * TH + tid];
+      if (j1 != 0) o = sup_s[j1 - 1];
+    }
+    grow[e] = o;
+  }
+  if constexpr (!LIST) {
+    // the support positions get their final values once the stores of the whole workgroup are ordered before them
+    __syncthreads();
+    for (int j = tid; j < k_top; j += TH) {
+      const int id = irow[j];
+      if (owns(id)) grow[id] = sup_s[j];
+    }
   }
 }
 

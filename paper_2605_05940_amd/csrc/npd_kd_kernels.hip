@@ -230,6 +230,7 @@ static hipError_t launch_teacher(const KdArgs& a, bool want_grad, hipStream_t st
 // the kernel family launch_kd picks for these arguments
 const char* kd_kernel_name(const KdArgs& a, int teacher_kind, bool want_grad) {
   if (a.ws && gang_path_applies(a, teacher_kind, want_grad)) return "kd_gang_kernel";
+  if (solo_path_applies(a, teacher_kind, want_grad)) return "kd_solo_kernel";
   if (cached_path_applies(a, teacher_kind, want_grad)) return "kd_cached_kernel";
   if (a.divergence != kForwardKl) return "div_rows_kernel";
   return "kd_rows_kernel";
@@ -237,6 +238,7 @@ const char* kd_kernel_name(const KdArgs& a, int teacher_kind, bool want_grad) {
 
 hipError_t launch_kd(const KdArgs& a, int teacher_kind, bool want_grad, hipStream_t stream) {
   if (a.ws && gang_path_applies(a, teacher_kind, want_grad)) return launch_kd_gang(a, teacher_kind, stream);
+  if (solo_path_applies(a, teacher_kind, want_grad)) return launch_kd_solo(a, teacher_kind, want_grad, stream);
   if (cached_path_applies(a, teacher_kind, want_grad)) return launch_kd_cached(a, teacher_kind, want_grad, stream);
   if (a.divergence != kForwardKl) return launch_div(a, want_grad, stream);  // dense teacher (checked by the API)
   switch (teacher_kind) {

@@ -1,0 +1,37 @@
+// Rows that fit one workgroup: which calls, and the kernels without a dense teacher.
+#include "npd_kd_solo.hpp"
+
+namespace npd {
+
+// Every call with whole 128-bit groups whose row fits, forward-only calls with the forward KL or without a teacher --
+// except where the row-resident kernel with 256 threads (npd_kd_cached.hpp) is a little faster: 16-byte aligned rows
+// whose gradient needs no sum at tau = 1, of more than 2,048 groups (forward KL) or 1,536 groups (reverse KL).
+// Measured (MI355X, 1e9 logits, all scored, % of 8 TB/s, the kernel that ran such a row before / this one):
+//   dense, forward KL  V = 1,024 46 / 69, 2,048 51 / 77, 4,096 38 / 74, 8,192 58 / 78, 12,288 68 / 74, 18,432 74 / 75,
+//                      24,576 75 / 72;  at tau = 2 with CE 2,048 43 / 62, 8,192 45 / 70, 16,384 51 / 71, 24,576 50 / 64
+//   reverse KL         2,048 52 / 77, 8,192 59 / 77, 12,288 70 / 75, 16,384 74 / 70
+//   skew KL            2,048 35 / 73, 8,192 39 / 77, 12,288 44 / 73, 16,384 46 / 70
+//   top-k (64), tau 2  2,048 31 / 54, 4,096 33 / 53, 8,192 44 / 63, 16,384 58 / 61, 24,576 58 / 67
+//   NLL alone          2,048 68 / 78, 4,096 40 / 82, 8,192 57 / 84, 24,576 85 / 89
+// Short rows used to stream twice; a row that lives in registers is read once, and 5 .. 8 waves per SIMD hide its
+// reductions.
+constexpr int kSoloForwardGroups = 256 * 8, kSoloReverseGroups = 256 * 6;
+bool solo_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
+  if (a.nvec_s == 0) return false;
+  if (teacher_kind != kDense) return a.nvec_s <= kSoloGroups;
+  if (!want_grad) return a.divergence == kForwardKl && a.nvec_s <= kSoloGroups;
+  if (a.divergence != kForwardKl && a.divergence != kReverseKl) return a.nvec_s <= kSoloSkewGroups;
+  if (a.ragged || a.need_lse1) return a.nvec_s <= kSoloGroups;
+  return a.nvec_s <= (a.divergence == kForwardKl ? kSoloForwardGroups : kSoloReverseGroups);
+}
+
+hipError_t launch_kd_solo(const KdArgs& a, int teacher_kind, bool want_grad, hipStream_t stream) {
+  if (teacher_kind != kDense)
+    return want_grad && teacher_kind == kTopk ? launch_solo_student<true>(a, stream) : launch_solo_student<false>(a, stream);
+  if (!want_grad) return launch_solo_forward_only(a, stream);
+  if (a.divergence == kForwardKl) return launch_solo_forward(a, stream);
+  if (a.divergence == kReverseKl) return launch_solo_reverse(a, stream);
+  return launch_solo_skew(a, stream);
+}
+
+}  // namespace npd

@@ -87,6 +87,13 @@ def _reference(oracle, lay, s, t, lab, div, tau, gs, ce):
     (1001, 1001, (0, 0, 0), None),
     (17, 17, (0, 0, 0), None),            # one or two groups, most elements are edges
     (9, 9, (5, 5, 5), None),              # rows without a whole group among them
+    # rows of one workgroup, 16-byte aligned: the last row of a shape and the first of the next
+    (1024, 1024, (0, 0, 0), None), (1032, 1032, (0, 0, 0), None), (2048, 2048, (0, 0, 0), None),
+    (2056, 2056, (0, 0, 0), None), (4096, 4096, (0, 0, 0), None), (4104, 4104, (0, 0, 0), None),
+    (8192, 8192, (0, 0, 0), None), (8200, 8200, (0, 0, 0), None), (12288, 12288, (0, 0, 0), None),
+    (12296, 12296, (0, 0, 0), None), (16384, 16384, (0, 0, 0), None), (16392, 16392, (0, 0, 0), None),
+    (20480, 20480, (0, 0, 0), None), (20488, 20488, (0, 0, 0), None), (32768, 32768, (0, 0, 0), None),
+    (32776, 32776, (0, 0, 0), None),
 ])
 @pytest.mark.parametrize("div,tau,ce", [("forward", 1.0, 0.25), ("forward", 2.0, 0.0), ("reverse", 1.0, 0.25),
                                         ("skew", 1.0, 0.25), ("skew_reverse", 2.0, 0.0),
@@ -96,7 +103,7 @@ def test_dense_rows_at_any_offset(oracle, V, pitch, offs, pitch_t, div, tau, ce)
     w, lay, s, t, lab = _batch(V)
     ref = _reference(oracle, lay, s, t, lab, div, tau, 0.75, ce)
     bars = dict(grad_scale=0.75 + ce * max(1.0, tau), tau=tau, amp_from_ref=div != "forward",
-                folded=div != "forward" or (tau == 1.0 or ce == 0.0) and pitch % 8 == 0 and offs == (0, 0, 0))
+                folded=div != "forward" or (tau == 1.0 or ce == 0.0) and pitch % 8 == 0 and offs == (0, 0, 0) and V >= 8192)
     kw = dict(V=V, pitch=pitch, offs=offs, pitch_t=pitch_t, div=div, tau=tau, ce=ce)
     for mode in (dict(), dict(inplace=True), dict(no_workspace=True)):
         print(f"[rows] V={V} pitch={pitch} offs={offs} pitch_t={pitch_t} {div} tau={tau} {mode}", flush=True)
@@ -108,6 +115,9 @@ def test_dense_rows_at_any_offset(oracle, V, pitch, offs, pitch_t, div, tau, ce)
 @pytest.mark.parametrize("V,pitch,offs", [
     (30631, 30631, (0, 0, 0)), (151936, 151936, (0, 0, 0)), (151937, 151937, (3, 3, 3)), (50003, 50003, (1, 1, 4)), (8199, 8199, (0, 0, 0)),
     (2003, 2003, (6, 6, 6)), (40, 43, (0, 0, 0)),
+    (1024, 1024, (0, 0, 0)), (1032, 1032, (0, 0, 0)), (2056, 2056, (0, 0, 0)), (4096, 4096, (0, 0, 0)),
+    (4104, 4104, (0, 0, 0)), (8200, 8200, (0, 0, 0)), (16392, 16392, (0, 0, 0)), (20488, 20488, (0, 0, 0)),
+    (32768, 32768, (0, 0, 0)),
 ])
 @pytest.mark.parametrize("tau,ce", [(1.0, 0.25), (2.0, 0.0), (2.0, 0.25)])
 def test_topk_rows_at_any_offset(oracle, V, pitch, offs, tau, ce):
@@ -127,7 +137,7 @@ def test_topk_rows_at_any_offset(oracle, V, pitch, offs, tau, ce):
         print(f"[rows] top-k V={V} pitch={pitch} offs={offs} tau={tau} {mode}", flush=True)
         compare_kd(_call(lay, s, None, lab, **kw, **mode), ref, lay.loss_mask, lay.cu_seqlens, oracle,
                    grad_scale=0.75 + ce * max(1.0, tau), tau=tau,
-                   folded=(tau == 1.0 or ce == 0.0) and pitch % 8 == 0 and offs == (0, 0, 0))
+                   folded=(tau == 1.0 or ce == 0.0) and pitch % 8 == 0 and offs == (0, 0, 0) and V >= 8192)
     fwd = _call(lay, s, None, lab, **kw | dict(ce=0.0), grad=False)
     compare_kd(fwd, {n: ref[n] for n in ("kd", "nll_s", "lse_s")}, lay.loss_mask, lay.cu_seqlens, oracle)
 
@@ -153,3 +163,42 @@ def test_composite_at_a_temperature_without_its_workspace(oracle):
         got = dict(kd=kd.cpu().numpy().astype(np.float64), nll_s=nll.cpu().numpy().astype(np.float64),
                    grad=grad.float().cpu().numpy().astype(np.float64))
         compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce * tau, tau=tau, folded=False)
+
+
+@pytest.mark.parametrize("V,k", [(600, 600), (1000, 513), (3001, 1300), (9000, 4096)])
+def test_long_topk_records_on_short_rows(oracle, V, k):
+    """Records of hundreds of entries, up to the whole vocabulary: many support positions per group of eight."""
+    w, lay, s, _, lab = _batch(V, 1)
+    T = s.shape[0]
+    g = torch.Generator(device=dev()).manual_seed(V)
+    idx = torch.rand((T, V), generator=g, device=dev()).argsort(dim=1)[:, :k].to(torch.int32).contiguous()
+    val = torch.randn((T, k), generator=g, device=dev())
+    for tau, ce in ((1.0, 0.25), (3.0, 0.0)):
+        print(f"[rows] long record V={V} k={k} tau={tau}", flush=True)
+        ref = oracle.kd_topk(synth.bf16_bits(s), idx.cpu().numpy(), val.cpu().numpy(), lab, lay.loss_mask, tau=tau,
+                             grad_scale=0.75, ce_grad_scale=ce)
+        got = _call(lay, s, None, lab, V=V, pitch=V, offs=(0, 0, 0), tau=tau, ce=ce, topk=(idx, val))
+        compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce, tau=tau)
+
+
+@pytest.mark.parametrize("V", [1000, 6003, 16384])
+@pytest.mark.parametrize("low", [False, True])
+def test_extreme_logits_on_short_rows(oracle, V, low):
+    """Logits whose largest is far from a thread's first ones, rows of negative logits alone, and logits of a thousand:
+    sums whose references have to follow the data."""
+    w, lay, s, t, lab = _batch(V)
+    s, t = s.float(), t.float()
+    s[::3] = s[::3] * 40.0
+    t[1::3] = t[1::3] * 40.0
+    if low:
+        s -= 900.0
+        t -= 1200.0
+    s[:, V // 3] += 500.0
+    s, t = s.to(torch.bfloat16), t.to(torch.bfloat16)
+    for div, tau, ce in (("forward", 1.0, 0.25), ("forward", 2.0, 0.25), ("skew", 1.0, 0.0)):
+        print(f"[rows] extreme V={V} low={low} {div} tau={tau}", flush=True)
+        ref = _reference(oracle, lay, s, t, lab, div, tau, 0.75, ce)
+        got = _call(lay, s, t, lab, V=V, pitch=V, offs=(0, 0, 0), div=div, tau=tau, ce=ce)
+        # per-position scalars are differences of numbers in the thousands: 1e-4 relative of those
+        compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce * tau, tau=tau,
+                   amp_from_ref=div != "forward")
