@@ -105,6 +105,10 @@ struct TopkArgs {
   int32_t V, k, nvec, log_probs;
 };
 
+// rows that fit one workgroup's registers (npd_topk_rows.hip)
+bool topk_rows_applies(const TopkArgs& a);
+hipError_t launch_topk_rows(const TopkArgs& a, hipStream_t stream);
+
 hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, int log_probs, const uint16_t* t,
                                const uint8_t* mask, int32_t* idx, float* val, hipStream_t stream);
 

@@ -3,8 +3,8 @@
 // NPD_TOPK_CAND (candidate capacity per row), NPD_TOPK_WINDOW / NPD_TOPK_SAMPLE (register window of the one-read
 // kernel and the part of it that gives the bound) and NPD_TOPK_ANY_SHAPE (1: also the kernel for unaligned or short
 // rows).  See npd_topk_kernels.hip for the method.
-#include "npd_device.hpp"
 #include "npd_internal.hpp"
+#include "npd_topk_order.hpp"
 
 namespace npd {
 namespace NPD_TOPK_NS {
@@ -19,10 +19,6 @@ __device__ __forceinline__ uint32_t key_of(uint32_t b) {
   b &= 0xffffu;
   if (b == 0x8000u) b = 0;
   return (b & 0x8000u) ? (~b & 0xffffu) : (b | 0x8000u);
-}
-__device__ __forceinline__ float value_of_key(uint32_t key) {
-  const uint32_t b = (key & 0x8000u) ? (key & 0x7fffu) : (~key & 0xffffu);
-  return __builtin_bit_cast(float, b << 16);
 }
 __device__ __forceinline__ unsigned long long cand_word(uint32_t key, uint32_t id) {
   return ((unsigned long long)key << 32) | (unsigned long long)(0xffffffffu - id);  // larger = better
@@ -395,27 +391,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
 #endif  // NPD_TOPK_ANY_SHAPE
 
 // ------------------------------------------------------------------------------------------------ one read
-typedef short short2v __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ short2v as_s2(uint32_t x) { return __builtin_bit_cast(short2v, x); }
-__device__ __forceinline__ short2v pk_max(short2v a, short2v b) { return __builtin_elementwise_max(a, b); }
-__device__ __forceinline__ short2v pk_min(short2v a, short2v b) { return __builtin_elementwise_min(a, b); }
-// bf16 bit patterns (sign-magnitude) -> 16-bit two's complement integers in value order (an involution);
-// -0 becomes -1, directly below +0
-__device__ __forceinline__ uint32_t pk_ordered(uint32_t x) {
-  const uint32_t sign = __builtin_bit_cast(uint32_t, as_s2(x) >> (short)15);
-  return x ^ (sign & 0x7fff7fffu);
-}
-__device__ __forceinline__ int ordered_of(uint32_t b) {  // one pattern
-  const int x = (int)(short)(uint16_t)b;
-  return x < 0 ? (x ^ 0x7fff) : x;
-}
-// the 16-bit sort key of an ordered integer (the same keys as key_of: -0 is filed under +0)
-__device__ __forceinline__ uint32_t key_of_ordered(int o) {
-  const uint32_t key = ((uint32_t)o ^ 0x8000u) & 0xffffu;
-  return key == 0x7fffu ? 0x8000u : key;
-}
 
 constexpr uint32_t kFillPair = 0xff80ff80u;  // two bf16 -inf: below every element, and never a candidate (id >= V)
 

@@ -11,6 +11,8 @@
 // search of the k-th key by counting passes over the row, then the ties of lowest id are collected in id order with
 // block-wide scans.
 //
+// Rows that fit one workgroup's registers have a kernel of their own for k <= 256 (npd_topk_rows.hip).
+//
 // teacher_topk_stream_kernel (16-byte aligned rows of at least 8192 elements) reads each row from HBM once: the
 // 16-byte groups of a row are visited in a strided order, so that the first window of groups a thread loads (12 of
 // the 19 groups of a 151,936-entry row with 1024 threads) samples the whole vocabulary range; the bound comes from
@@ -54,6 +56,7 @@ hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, 
   const bool aligned = (reinterpret_cast<uintptr_t>(t) & 15u) == 0 && stride % 8 == 0;
   a.nvec = aligned ? V / 8 : 0;
   a.log_probs = log_probs;
+  if (topk_rows_applies(a)) return launch_topk_rows(a, stream);
   if (a.nvec >= 1024) return k <= kSmallK ? topk512::launch_stream(a, stream) : topk1024::launch_stream(a, stream);
   return topk1024::launch_any(a, stream);
 }

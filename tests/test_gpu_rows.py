@@ -202,3 +202,44 @@ def test_extreme_logits_on_short_rows(oracle, V, low):
         # per-position scalars are differences of numbers in the thousands: 1e-4 relative of those
         compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce * tau, tau=tau,
                    amp_from_ref=div != "forward")
+
+
+@pytest.mark.parametrize("V,pitch,off", [
+    (1024, 1024, 0), (1000, 1003, 5), (2048, 2048, 0), (2056, 2056, 0), (4096, 4096, 0), (4104, 4104, 0),
+    (8192, 8192, 0), (8199, 8199, 0), (16384, 16384, 0), (16392, 16392, 0), (32768, 32768, 0),
+    (32775, 32775, 3), (32777, 32777, 3), (50003, 50003, 0), (151937, 151937, 1), (300, 301, 2), (17, 17, 1), (9, 9, 5),
+])
+@pytest.mark.parametrize("k", [1, 10, 64, 65, 256, 300])
+def test_teacher_topk_rows_at_any_offset(oracle, V, pitch, off, k):
+    """The record of rows of every shape and offset, plain rows and rows of ties: distinct logits, a handful of values
+    (long runs of equal logits at the cut), one value, negative ones alone, zeros of both signs, the largest on the
+    edges."""
+    k = min(k, V)
+    T = 12
+    g = torch.Generator(device=dev()).manual_seed(V * 1000 + k)
+    x = 3.0 * torch.randn((T, V), generator=g, device=dev())
+    x[1] = torch.randint(0, 3, (V,), generator=g, device=dev()).float()
+    x[2] = 1.5
+    x[3] = -x[3].abs() - 0.01
+    x[4] = torch.where(torch.rand(V, generator=g, device=dev()) < 0.5, 0.0, -0.0)
+    x[5, 0] = x[5, V - 1] = x[5, V // 2] = 50.0
+    x[6] = -0.0
+    x[6, V // 3:] = 0.0
+    x[7] = torch.arange(V, device=dev()).float() - V
+    x[8] = -x[7]
+    _, t = _rows(T, V, pitch, off)
+    t.copy_(x)
+    mask = torch.ones(T, dtype=torch.uint8, device=dev())
+    mask[10] = 0
+    idx, val = Guarded(T * k, torch.int32), Guarded(T * k, torch.float32)
+    print(f"[rows] teacher top-k V={V} pitch={pitch} off={off} k={k}", flush=True)
+    for log_probs in (True, False):
+        binding.npd_teacher_topk(t, k, topk_idx=idx.t.view(T, k), topk_val=val.t.view(T, k), loss_mask=mask,
+                                 log_probs=log_probs)
+        torch.cuda.synchronize()
+        ref = oracle.teacher_topk(synth.bf16_bits(t.contiguous()), k, mask.cpu().numpy(), log_probs)
+        np.testing.assert_array_equal(idx.check().cpu().numpy().reshape(T, k), ref["idx"])
+        # the log-softmax subtracts one fp32 number near the row's largest logit (up to V in rows 7 and 8): its rounding
+        # is half a step, at most 2^-23 of it
+        bar = 2e-5 + 2.0 ** -23 * t.float().abs().amax(1, keepdim=True).cpu().numpy()
+        assert (np.abs(val.check().cpu().numpy().reshape(T, k) - ref["val"]) <= bar).all()
