@@ -2,7 +2,8 @@
 // defines NPD_TOPK_NS (namespace of this configuration), NPD_TOPK_TB (threads per workgroup, 512 or 1024),
 // NPD_TOPK_CAND (candidate capacity per row), NPD_TOPK_WINDOW / NPD_TOPK_SAMPLE (register window of the one-read
 // kernel and the part of it that gives the bound) and NPD_TOPK_ANY_SHAPE (1: also the kernel for unaligned or short
-// rows).  See npd_topk_kernels.hip for the method.
+// rows) and NPD_TOPK_GROUPS (not 0: the one-read kernel lists whole groups first, so many at most).  See
+// npd_topk_kernels.hip for the method.
 #include "npd_internal.hpp"
 #include "npd_topk_order.hpp"
 
@@ -11,6 +12,7 @@ namespace NPD_TOPK_NS {
 
 constexpr int kTB = NPD_TOPK_TB;          // threads per workgroup
 constexpr int kCandCap = NPD_TOPK_CAND;   // candidates staged per row (8 bytes each)
+constexpr int kGroupCap = NPD_TOPK_GROUPS > 0 ? NPD_TOPK_GROUPS : 1;  // groups with a candidate staged per row
 static_assert(kTB == 512 || kTB == 1024, "workgroups of 8 or 16 waves");
 static_assert((kCandCap & (kCandCap - 1)) == 0 && kCandCap >= 2 * kTB, "the bitonic fallback pads the list to a power of two");
 
@@ -86,12 +88,23 @@ __device__ __forceinline__ int block_excl_scan(int v, int* red, int& total) {
 }
 
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 struct TopkShared {
   unsigned long long cand[kCandCap];
-  unsigned long long shortlist[kTB];  // the candidates at or above the k-th key, when cand is long
-  unsigned long long sorted[kTB];     // rank-sorted short lists
-  int rank[kTB];
-  int hist[2][256];
+  union {  // the groups are dead once the candidates are listed
+    struct {
+      unsigned long long shortlist[kTB];  // the candidates at or above the k-th key, when cand is long
+      unsigned long long sorted[kTB];     // rank-sorted short lists
+      int rank[kTB];
+      int hist[2][256];
+    };
+    struct {
+      u32x4 group[kGroupCap];  // groups with a candidate
+      int group_id[kGroupCap];
+    };
+  };
+  int ngroups;
   int nshort;
 #if NPD_TOPK_ANY_SHAPE
   uint32_t mx[kTB];
@@ -114,9 +127,10 @@ __device__ __forceinline__ void write_unscored(const TopkArgs& a, int64_t row, i
 
 // Exact selection for any row, by counting passes over global memory.  Called by all threads; leaves the k
 // selected words in sh.cand[0..k) (unordered) behind a barrier.
-__device__ __forceinline__ void slow_select(const uint16_t* trow, int nvec, int V, int k, TopkShared& sh,
+__device__ __forceinline__ void slow_select(const uint16_t* trow, const RowSplit& sp, int V, int k, TopkShared& sh,
                                             int tid) {
-  const uint4* tvec = reinterpret_cast<const uint4*>(trow);
+  const int nvec = sp.nvec, head = sp.head, n_edge = V - nvec * 8;
+  const uint4* tvec = reinterpret_cast<const uint4*>(trow + head);
   unsigned long long* cand = sh.cand;
   // Tk = the largest key with count(key >= Tk) >= k, by bisection over 16 bits.
   uint32_t lo = 0, hi = 0x10000u;  // invariant: count(>= lo) >= k, count(>= hi) < k
@@ -129,7 +143,7 @@ __device__ __forceinline__ void slow_select(const uint16_t* trow, int nvec, int 
 #pragma unroll
       for (int j = 0; j < 8; ++j) c += kk[j] >= mid;
     }
-    for (int e = nvec * 8 + tid; e < V; e += kTB) c += key_of(trow[e]) >= mid;
+    for (int j = tid; j < n_edge; j += kTB) c += key_of(trow[sp.edge_elem(j)]) >= mid;
     c = block_sum_i(c, sh.red);
     if (c >= k)
       lo = mid;
@@ -149,10 +163,11 @@ __device__ __forceinline__ void slow_select(const uint16_t* trow, int nvec, int 
       if (kk[j] > Tk) {
         ++above;
         const int pos = atomicAdd(&sh.ncand, 1);  // fewer than k <= 4096 by the choice of Tk
-        if (pos < kCandCap) cand[pos] = cand_word(kk[j], (uint32_t)(i * 8 + j));
+        if (pos < kCandCap) cand[pos] = cand_word(kk[j], (uint32_t)(head + i * 8 + j));
       }
   }
-  for (int e = nvec * 8 + tid; e < V; e += kTB) {
+  for (int j = tid; j < n_edge; j += kTB) {
+    const int e = sp.edge_elem(j);
     const uint32_t kk = key_of(trow[e]);
     if (kk > Tk) {
       ++above;
@@ -164,6 +179,17 @@ __device__ __forceinline__ void slow_select(const uint16_t* trow, int nvec, int 
   const int need = k - above;  // ties at Tk to take, lowest ids first (>= 1)
   // ties in id order: chunk after chunk, each thread owning consecutive ids inside a chunk
   int taken = 0;  // uniform
+  auto take_elements = [&](int e_first, int e_end) {
+    for (int e0 = e_first; e0 < e_end && taken < need; e0 += kTB) {
+      const int e = e0 + tid;
+      const int mine = e < e_end && key_of(trow[e]) == Tk;
+      int total;
+      const int rank = taken + block_excl_scan(mine, sh.red, total);
+      if (mine && rank < need) cand[above + rank] = cand_word(Tk, (uint32_t)e);
+      taken += total;
+    }
+  };
+  take_elements(0, head);
   for (int c0 = 0; c0 < nvec && taken < need; c0 += kTB) {
     const int i = c0 + tid;
     uint32_t kk[8];
@@ -179,20 +205,13 @@ __device__ __forceinline__ void slow_select(const uint16_t* trow, int nvec, int 
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         if (kk[j] == Tk) {
-          if (rank < need) cand[above + rank] = cand_word(Tk, (uint32_t)(i * 8 + j));
+          if (rank < need) cand[above + rank] = cand_word(Tk, (uint32_t)(head + i * 8 + j));
           ++rank;
         }
     }
     taken += total;
   }
-  for (int e0 = nvec * 8; e0 < V && taken < need; e0 += kTB) {
-    const int e = e0 + tid;
-    const int mine = e < V && key_of(trow[e]) == Tk;
-    int total;
-    const int rank = taken + block_excl_scan(mine, sh.red, total);
-    if (mine && rank < need) cand[above + rank] = cand_word(Tk, (uint32_t)e);
-    taken += total;
-  }
+  take_elements(head + nvec * 8, V);
   __syncthreads();
 }
 
@@ -327,13 +346,15 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
   __shared__ TopkShared sh;
   const int tid = threadIdx.x;
   const int64_t row = blockIdx.x;
-  const int V = a.V, k = a.k, nvec = a.nvec;
+  const int V = a.V, k = a.k;
   if (a.mask && !a.mask[row]) {
     write_unscored(a, row, tid);
     return;
   }
   const uint16_t* trow = a.t + row * a.stride;
-  const uint4* tvec = reinterpret_cast<const uint4*>(trow);
+  const RowSplit sp{0, a.nvec};
+  const int nvec = sp.nvec, head = sp.head, n_edge = V - nvec * 8;
+  const uint4* tvec = reinterpret_cast<const uint4*>(trow + head);
 
   // ---- one maximum per thread
   uint32_t best = 0;  // below every key of a finite value
@@ -344,8 +365,8 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
 #pragma unroll
     for (int j = 0; j < 8; ++j) best = kk[j] > best ? kk[j] : best;
   }
-  for (int e = nvec * 8 + tid; e < V; e += kTB) {
-    const uint32_t kk = key_of(trow[e]);
+  for (int j = tid; j < n_edge; j += kTB) {
+    const uint32_t kk = key_of(trow[sp.edge_elem(j)]);
     best = kk > best ? kk : best;
   }
   sh.mx[tid] = best;
@@ -365,11 +386,12 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
       for (int j = 0; j < 8; ++j) {
         if (kk[j] >= L) {
           const int pos = atomicAdd(&sh.ncand, 1);
-          if (pos < kCandCap) sh.cand[pos] = cand_word(kk[j], (uint32_t)(i * 8 + j));
+          if (pos < kCandCap) sh.cand[pos] = cand_word(kk[j], (uint32_t)(head + i * 8 + j));
         }
       }
     }
-    for (int e = nvec * 8 + tid; e < V; e += kTB) {
+    for (int j = tid; j < n_edge; j += kTB) {
+      const int e = sp.edge_elem(j);
       const uint32_t kk = key_of(trow[e]);
       if (kk >= L) {
         const int pos = atomicAdd(&sh.ncand, 1);
@@ -382,7 +404,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
   int n = sh.ncand;
   __syncthreads();
   if (slow) {
-    slow_select(trow, nvec, V, k, sh, tid);
+    slow_select(trow, sp, V, k, sh, tid);
     n = k;
   }
   order_and_emit(sh, n, k, a.log_probs, a.idx + row * (int64_t)k, a.val + row * (int64_t)k, tid);
@@ -391,8 +413,6 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
 #endif  // NPD_TOPK_ANY_SHAPE
 
 // ------------------------------------------------------------------------------------------------ one read
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 constexpr uint32_t kFillPair = 0xff80ff80u;  // two bf16 -inf: below every element, and never a candidate (id >= V)
 
 // one 16-byte group of a row; 32-bit byte offsets keep the address in one VGPR next to the scalar row base
@@ -408,11 +428,38 @@ __device__ __forceinline__ void append(TopkShared& sh, int o, int id) {
   if (pos < kCandCap) sh.cand[pos] = cand_word(key_of_ordered(o), (uint32_t)id);
 }
 
+// A group with an element >= Lp goes to the LDS list whole (its patterns and its index): one exchange and two writes
+// instead of a test of its eight elements by one lane out of 64; they are tested later, a group to a thread (8,192 rows
+// of 151,936, all scored, 512 threads: k = 64 414 -> 385 us, k = 10 397 -> 390; 50,304 k = 128 199 -> 175).
+template <bool ORDERED>
+__device__ __forceinline__ void append_group(const u32x4& v, int i, int Lp, int nvec, int head, TopkShared& sh) {
+  uint32_t d[4] = {v.x, v.y, v.z, v.w};
+  if (ORDERED) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d[q] = pk_ordered(d[q]);
+  }
+  const short2v gm = pk_max(pk_max(as_s2(d[0]), as_s2(d[1])), pk_max(as_s2(d[2]), as_s2(d[3])));
+  if (max((int)gm.x, (int)gm.y) >= Lp && i < nvec) {
+    const int pos = atomicAdd(&sh.ngroups, 1);
+    if (pos < kGroupCap) {
+      sh.group[pos] = v;
+      sh.group_id[pos] = i;
+    } else {  // the list is full (rare): element by element
+#pragma unroll 1
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t pair = (j >> 1) == 0 ? v.x : (j >> 1) == 1 ? v.y : (j >> 1) == 2 ? v.z : v.w;
+        const int o = ordered_of((j & 1) ? pair >> 16 : pair & 0xffffu);
+        if (o >= Lp) append(sh, o, head + i * 8 + j);
+      }
+    }
+  }
+}
+
 // candidates of one register group: elements whose ordered value is >= Lp.  With ORDERED = false the patterns are
 // compared as they are, which is the same thing for Lp >= 1 (patterns of positive values are ordered integers,
 // those of negative values are negative integers).
 template <bool ORDERED>
-__device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, int nvec, TopkShared& sh) {
+__device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, int nvec, int head, TopkShared& sh) {
   uint32_t d[4] = {v.x, v.y, v.z, v.w};
   if (ORDERED) {
 #pragma unroll
@@ -424,32 +471,36 @@ __device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, int
     for (int j = 0; j < 8; ++j) {
       const short2v pr = as_s2(d[j >> 1]);
       const int o = (j & 1) ? (int)pr.y : (int)pr.x;
-      if (o >= Lp) append(sh, o, i * 8 + j);
+      if (o >= Lp) append(sh, o, head + i * 8 + j);
     }
   }
 }
 
 // W = register window (groups in flight per thread), S <= W = groups of the sample that gives the bound.
 // ngroups = ceil(nvec / 1024) >= 1 groups are visited in the order (g * step) mod ngroups, step coprime to ngroups.
-template <int W, int S>
+// RAGGED: rows begin anywhere inside a 16-byte group.
+template <int W, int S, bool RAGGED>
 __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkArgs a, int ngroups, int step) {
   __shared__ TopkShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int64_t row = blockIdx.x;
-  const int V = a.V, k = a.k, nvec = a.nvec;
+  const int V = a.V, k = a.k;
   if (a.mask && !a.mask[row]) {
     write_unscored(a, row, tid);
     return;
   }
   const uint16_t* trow = a.t + row * a.stride;
+  const RowSplit sp = RAGGED ? row_split(trow, V, true) : RowSplit{0, a.nvec};
+  const int nvec = sp.nvec, head = sp.head, n_edge = V - nvec * 8;
+  const uint16_t* tvec = trow + head;
   auto vec_index = [&](int g) { return ((g * step) % ngroups) * kTB + tid; };
 
   u32x4 w[W];
 #pragma unroll
-  for (int j = 0; j < W; ++j) w[j] = load_group(trow, vec_index(j), j < ngroups ? nvec : 0);
+  for (int j = 0; j < W; ++j) w[j] = load_group(tvec, vec_index(j), j < ngroups ? nvec : 0);
 
   // ---- one maximum per thread over the sample, in value order: the largest non-negative pattern if there is one,
-  // else the smallest negative pattern (sign-magnitude: the one closest to zero).  Group 0 is full (nvec >= 1024),
+  // else the smallest negative pattern (sign-magnitude: the one closest to zero).  Group 0 is full (nvec >= kTB),
   // so every thread's maximum is an element of the row.
   short2v mx2 = as_s2(0x80008000u), mn2 = as_s2(0x7fff7fffu);
 #pragma unroll
@@ -480,6 +531,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkA
     if (lane == 0) sh.wave_bound[wid] = blo;
   }
   if (tid == 0) sh.ncand = 0;
+  if (kGroupCap > 1 && tid == 0) sh.ngroups = 0;
   __syncthreads();
 
   if (!slow) {
@@ -493,16 +545,28 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkA
       for (int j = 0; j < W; ++j) {
         const int g = base + j;
         if (g < ngroups) {
-          if (Lp >= 1)
-            collect_group<false>(w[j], vec_index(g), Lp, nvec, sh);
-          else
-            collect_group<true>(w[j], vec_index(g), Lp, nvec, sh);
+          if constexpr (kGroupCap > 1) {
+            if (Lp >= 1)
+              append_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
+            else
+              append_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
+          } else {
+            if (Lp >= 1)
+              collect_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
+            else
+              collect_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
+          }
         }
-        if (g + W < ngroups) w[j] = load_group(trow, vec_index(g + W), nvec);
+        if (g + W < ngroups) w[j] = load_group(tvec, vec_index(g + W), nvec);
       }
     }
-    const int e = nvec * 8 + tid;  // the last V mod 8 elements
-    if (e < V) {
+    if constexpr (kGroupCap > 1) {
+      __syncthreads();
+      const int ng = min(sh.ngroups, kGroupCap);
+      for (int p = tid; p < ng; p += kTB) collect_group<true>(sh.group[p], sh.group_id[p], Lp, nvec, head, sh);
+    }
+    if (tid < n_edge) {  // elements in front of and behind the whole groups
+      const int e = sp.edge_elem(tid);
       const int o = ordered_of(trow[e]);
       if (o >= Lp) append(sh, o, e);
     }
@@ -512,7 +576,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkA
   int n = sh.ncand;
   __syncthreads();
   if (slow) {
-    slow_select(trow, nvec, V, k, sh, tid);
+    slow_select(trow, sp, V, k, sh, tid);
     n = k;
   }
   order_and_emit(sh, n, k, a.log_probs, a.idx + row * (int64_t)k, a.val + row * (int64_t)k, tid);
@@ -527,15 +591,24 @@ static int gcd_int(int x, int y) {
   return x;
 }
 
-// one-read kernel of this configuration; a.nvec >= kTB (16-byte aligned rows)
+// rows begin anywhere inside a 16-byte group
+static bool rows_ragged(const TopkArgs& a) {
+  return (reinterpret_cast<uintptr_t>(a.t) & 15u) != 0 || a.stride % 8 != 0;
+}
+
+// one-read kernel of this configuration; every row has kTB whole groups at least
 hipError_t launch_stream(const TopkArgs& a, hipStream_t stream) {
   constexpr int kWindow = NPD_TOPK_WINDOW, kSample = NPD_TOPK_SAMPLE;
   const int ngroups = (a.nvec + kTB - 1) / kTB;
   // visiting order: the first kSample groups spread over the row
   int step = ngroups > kSample ? (ngroups + kSample - 1) / kSample : 1;
   while (gcd_int(step, ngroups) != 1) ++step;
-  return launch_kernel(teacher_topk_stream_kernel<kWindow, kSample>, dim3((unsigned)a.T), dim3(kTB), 0, stream, a,
-                       ngroups, step % ngroups == 0 ? 1 : step % ngroups);
+  auto go = [&](auto kernel) {
+    return launch_kernel(kernel, dim3((unsigned)a.T), dim3(kTB), 0, stream, a, ngroups,
+                         step % ngroups == 0 ? 1 : step % ngroups);
+  };
+  return rows_ragged(a) ? go(teacher_topk_stream_kernel<kWindow, kSample, true>)
+                : go(teacher_topk_stream_kernel<kWindow, kSample, false>);
 }
 
 #if NPD_TOPK_ANY_SHAPE

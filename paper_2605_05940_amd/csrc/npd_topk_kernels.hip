@@ -13,7 +13,7 @@
 //
 // Rows that fit one workgroup's registers have a kernel of their own for k <= 256 (npd_topk_rows.hip).
 //
-// teacher_topk_stream_kernel (16-byte aligned rows of at least 8192 elements) reads each row from HBM once: the
+// teacher_topk_stream_kernel (rows of more than 8,192 elements, at any offset) reads each row from HBM once: the
 // 16-byte groups of a row are visited in a strided order, so that the first window of groups a thread loads (12 of
 // the 19 groups of a 151,936-entry row with 1024 threads) samples the whole vocabulary range; the bound comes from
 // that sample alone (the k-th largest of a subset never exceeds the k-th largest of the row), and the rest of the
@@ -28,6 +28,7 @@
 #define NPD_TOPK_WINDOW 12
 #define NPD_TOPK_SAMPLE 12
 #define NPD_TOPK_ANY_SHAPE 1
+#define NPD_TOPK_GROUPS 0
 #include "npd_topk_impl.hpp"
 
 namespace npd {
@@ -53,11 +54,18 @@ hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, 
   a.T = T;
   a.V = V;
   a.k = k;
-  const bool aligned = (reinterpret_cast<uintptr_t>(t) & 15u) == 0 && stride % 8 == 0;
-  a.nvec = aligned ? V / 8 : 0;
+  a.nvec = V / 8;  // (a row that begins inside a 16-byte group may have one group less)
   a.log_probs = log_probs;
   if (topk_rows_applies(a)) return launch_topk_rows(a, stream);
-  if (a.nvec >= 1024) return k <= kSmallK ? topk512::launch_stream(a, stream) : topk1024::launch_stream(a, stream);
+  // every thread of a workgroup of 1024 needs a whole group
+  const bool aligned = (reinterpret_cast<uintptr_t>(t) & 15u) == 0 && stride % 8 == 0;
+  if (a.nvec > 1024 || (aligned && a.nvec == 1024)) {
+    // about twice k / 8 candidates per chunk of 512 groups pass the bound of the 512-thread kernel, whose list holds 2,048
+    const int64_t chunks = (a.nvec + 511) / 512;
+    if (k <= kSmallK && k * chunks <= 8 * 700) return topk512::launch_stream(a, stream);
+    return topk1024::launch_stream(a, stream);
+  }
+  if (!aligned) a.nvec = 0;  // element by element: rows this short fit the caches, and few wait for bytes
   return topk1024::launch_any(a, stream);
 }
 

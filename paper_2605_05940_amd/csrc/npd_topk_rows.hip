@@ -7,10 +7,10 @@
 // wave for up to 4,096 logits, without a single barrier; four such rows share a workgroup), and the bound that picks the
 // candidates is taken from the maxima of the groups, not of the threads: the k-th largest of them (each wave's
 // ceil(k / waves)-th, the smallest report of all waves) lets barely more than k elements through, so the list that
-// has to be ordered is short -- rank sort, all pairs, 32-bit words.  Where there are fewer groups than that, and
+// has to be ordered is short -- rank sort, all pairs, 32-bit words.  Where k is most of the groups or more, and
 // where more elements pass than the list holds (massive ties), the k-th key itself is found by bisection over the
 // registers and the ties are taken in id order.
-#include "npd_kd_cached.hpp"
+#include "npd_kd_gang.hpp"
 #include "npd_topk_order.hpp"
 
 namespace npd {
@@ -25,7 +25,7 @@ __device__ __forceinline__ uint32_t row_word(int o, int id) { return (key_of_ord
 
 template <int TH>
 struct RowTopkShared {
-  uint32_t cand[kRowsCand];
+  __attribute__((aligned(16))) uint32_t cand[kRowsCand];
   uint32_t sorted[kRowsTopkMax];
   int ncand;
   int red[TH / kWave];
@@ -43,7 +43,7 @@ __device__ __forceinline__ void rows_sync() {
 // sum over the TH threads of a row
 template <int TH>
 __device__ __forceinline__ int rows_sum(int v, int* red) {
-  if constexpr (TH == kWave) return wave_sum_int(v);
+  if constexpr (TH == kWave) return (int)wave_sum_dpp((float)v);  // (whole numbers below 2^24)
   return block_sum_int<TH>(v, red);
 }
 
@@ -128,7 +128,8 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
   // ---- the bound: each wave's m-th largest group maximum; NW m >= k elements of the row are >= the smallest report.
   // Every wave owns at least (nvec / TH) * 64 whole groups.
   const int m = (k + NW - 1) / NW;
-  bool exact = m > nvec / TH * kWave;  // uniform
+  // Beyond three quarters of a wave's maxima the bound lets more than 1.7 k elements through.
+  bool exact = m > nvec / TH * kWave / 4 * 3;  // uniform
   if (!exact) {
     int lmax = gmax[0], lmin = gmax[0];
 #pragma unroll
@@ -293,11 +294,24 @@ static hipError_t launch_rows(const TopkArgs& a, hipStream_t stream) {
 // 1,597 / 98, 4,096 1,583 / 190, 8,192 598 / 276, 16,384 620 / 453, 24,576 463 / 683; k = 10 1,488 / 49, 1,487 / 102,
 // 466 / 177, 492 / 332, 360 / 544.  Longer rows are better off with the kernel that streams them: eight waves that wait
 // for one another at every step no longer hide behind other rows.
-bool topk_rows_applies(const TopkArgs& a) { return a.k <= kRowsTopkMax && a.V / 8 <= 256 * 8; }
+// Few rows do not hide a row's serial steps behind others: they stay with the kernels of 512 or 1024 threads per row
+// where the list to order is long or most of the row (T = 64, V = 2,500: k = 20 11.0 / 6.4 us, 64 11.6 / 10.5, 128
+// 12.9 / 16.2).
+constexpr int kManyRows = 1024;
+bool topk_rows_applies(const TopkArgs& a) {
+  if (a.k > kRowsTopkMax || a.V / 8 > 256 * 8) return false;
+  return a.T >= kManyRows || (a.k <= 64 && 16 * a.k <= a.V);
+}
 
 hipError_t launch_topk_rows(const TopkArgs& a, hipStream_t stream) {
   const int nvec = a.V / 8;
   if (nvec <= 64 * 2) return launch_rows<64, 2>(a, stream);
+  if (a.T < kManyRows) {  // more threads per row
+    if (nvec <= 128 * 2) return launch_rows<128, 2>(a, stream);
+    if (nvec <= 256 * 2) return launch_rows<256, 2>(a, stream);
+    if (nvec <= 256 * 4) return launch_rows<256, 4>(a, stream);
+    return launch_rows<256, 8>(a, stream);
+  }
   if (nvec <= 64 * 4) return launch_rows<64, 4>(a, stream);
   if (nvec <= 64 * 8) return launch_rows<64, 8>(a, stream);
   if (nvec <= 128 * 8) return launch_rows<128, 8>(a, stream);

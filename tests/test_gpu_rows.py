@@ -211,11 +211,21 @@ def test_extreme_logits_on_short_rows(oracle, V, low):
 ])
 @pytest.mark.parametrize("k", [1, 10, 64, 65, 256, 300])
 def test_teacher_topk_rows_at_any_offset(oracle, V, pitch, off, k):
+    _check_teacher_topk(oracle, V, pitch, off, k, 12)
+
+
+@pytest.mark.parametrize("V,pitch", [(2056, 2056), (4100, 4100), (8192, 8192)])
+@pytest.mark.parametrize("k", [10, 100, 256])
+def test_teacher_topk_of_many_rows(oracle, V, pitch, k):
+    """The same with so many rows that a row gets fewer threads."""
+    _check_teacher_topk(oracle, V, pitch, 0, k, 1100)
+
+
+def _check_teacher_topk(oracle, V, pitch, off, k, T):
     """The record of rows of every shape and offset, plain rows and rows of ties: distinct logits, a handful of values
     (long runs of equal logits at the cut), one value, negative ones alone, zeros of both signs, the largest on the
     edges."""
     k = min(k, V)
-    T = 12
     g = torch.Generator(device=dev()).manual_seed(V * 1000 + k)
     x = 3.0 * torch.randn((T, V), generator=g, device=dev())
     x[1] = torch.randint(0, 3, (V,), generator=g, device=dev()).float()
