@@ -67,7 +67,7 @@ static int forward_only_threads(const KdArgs& a) {
   return 1024;
 }
 
-// Row-resident path: 16-byte aligned rows that are long enough.  (The CE softmax of the composite loss has no
+// Row-resident path: rows of whole 128-bit groups that are long enough.  (The CE softmax of the composite loss has no
 // temperature; this path covers it at tau = 1, where it shares the student's exponentials.)
 bool cached_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
   const bool grad = want_grad && teacher_kind != kNone;

@@ -1,5 +1,5 @@
-// Row-resident variant of the fused KD loss + gradient kernel (gfx950), for rows of 8,192 entries and more, 16-byte
-// aligned: the kernel template and its launcher.  The instantiations are spread over several translation units
+// Row-resident variant of the fused KD loss + gradient kernel (gfx950), for rows of 8,192 entries and more that neither
+// fit one workgroup's registers (npd_kd_solo.hip) nor are shared (npd_kd_gang.hip): the kernel template and its launcher.  The instantiations are spread over several translation units
 // (npd_kd_cached_*.hip) so that they compile in parallel.
 //
 // One workgroup per token row.  A row of ~150k bf16 logits (student + teacher = 608 KB) does not fit one CU, but most
