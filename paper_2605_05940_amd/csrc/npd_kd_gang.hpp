@@ -97,6 +97,30 @@ __device__ __forceinline__ float pk_max_value(uint32_t m) {
   return bf16_one((uint16_t)(lo > hi ? lo : hi));
 }
 
+// Largest logit of a thread's n >= 1 groups, whatever their signs, with v_pk_max_f16: fp16 patterns are sign and
+// magnitude like bf16 ones, so their order is the same.  The patterns it takes for NaN are magnitudes of more than
+// 2^121: infinities and NaN, which it passes over while the other operand is a number.  Where there is nothing else the
+// result is far below every logit: sums against it are 0 if all logits are -inf and show an anomaly otherwise.  (Written
+// out because the compiler canonicalises both operands of the builtin.)
+__device__ __forceinline__ uint32_t pk_max_bf16(uint32_t a, uint32_t b) {
+  uint32_t d;
+  asm("v_pk_max_f16 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+template <int K>
+__device__ __forceinline__ float thread_max(const uint4 (&v)[K], int n) {
+  constexpr uint32_t kNothing = 0xff80ff80u;  // a pair of -inf, for the groups behind the thread's last
+  uint32_t m = kNothing;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint32_t g = pk_max_bf16(pk_max_bf16(v[k].x, v[k].y), pk_max_bf16(v[k].z, v[k].w));
+    m = k == 0 ? g : pk_max_bf16(m, k < n ? g : kNothing);
+  }
+  const float lo = bf16_lo(m), hi = bf16_hi(m);
+  const float x = lo > hi ? lo : hi;
+  return fabsf(x) < 2.6e36f ? x : -3.0e38f;
+}
+
 __device__ __forceinline__ void gang_post(uint32_t* p, float v) {
   uint32_t w = __builtin_bit_cast(uint32_t, v);
   if (w == kGangEmpty) w = 0x7fc00000u;  // another NaN
@@ -341,26 +365,25 @@ kd_gang_kernel(const KdArgs a) {
   // one multiplication each instead of unpacking and exponentiating again, and leaves p_S and p_S (u - const) in the
   // same registers, so that the gradient sweep is one multiply-add per element.  Their references get 64 bits of head
   // room: an element's exponential is kept down to 2^-62 of the thread's first group's largest.
-  // Rows of one workgroup and rows at any offset take the largest of all the thread's logits and no head room: arguments
-  // are then <= 0 and as small as can be where a term matters (rounding errors no larger than in the streaming kernels
-  // that such rows once ran in, also on heavy tails, and no careful re-runs there), for half an instruction per logit
-  // and a wait for all loads, which short rows hide behind one another.
+  // Rows of one workgroup and rows at any offset take the largest of all the thread's logits (thread_max) and no head
+  // room: arguments are then <= 0 to rounding and as small as can be where a term matters (rounding errors no larger than
+  // in the streaming kernels that such rows once ran in, also on heavy tails and on rows of log-probabilities, and no
+  // careful re-runs there), for half an instruction per logit and a wait for all loads, which short rows hide behind one
+  // another.
   // Squares of exponentials get 44 bits, so that a square is kept down to 2^-38 of the first group's largest square and
   // its sum is inside the range up to 94 bits above the first group's largest logit.
   const bool ref_of_all = SOLO || a.ragged;  // uniform
   const float kRefBias = ref_of_all ? 0.0f : (L1 == kL1Square ? 44.0f : (SKEW ? 64.0f : 100.0f));
   float cp[SKEW ? K : 1][8], cv[SKEW ? K : 1][8];
   if (ng > tid) {  // (threads without a group keep their empty partials)
-    uint32_t ms = pk_max_group(sreg[0]), mt = pk_max_group(treg[0]);
+    float fs, ft;
     if (ref_of_all) {
-#pragma unroll
-      for (int k = 1; k < K; ++k)
-        if (k < n_mine) {
-          ms = pk_max_i16(ms, pk_max_group(sreg[k]));
-          mt = pk_max_i16(mt, pk_max_group(treg[k]));
-        }
+      fs = thread_max(sreg, n_mine);
+      ft = thread_max(treg, n_mine);
+    } else {
+      fs = pk_max_value(pk_max_group(sreg[0]));
+      ft = pk_max_value(pk_max_group(treg[0]));
     }
-    const float fs = pk_max_value(ms), ft = pk_max_value(mt);
     acc[0].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f));
     acc[1].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(ft, c, kRefBias), -1.0e30f));
     if constexpr (L1 == kL1Own) {

@@ -146,13 +146,7 @@ kd_gang_topk_kernel(const KdArgs a) {
   const bool ref_of_all = SOLO || a.ragged;
   const float kRefBias = ref_of_all ? 0.0f : (L1 == kL1Square ? 44.0f : 100.0f);  // see npd_kd_gang.hpp
   if (ng > tid) {
-    uint32_t ms = pk_max_group(sreg[0]);
-    if (ref_of_all) {
-#pragma unroll
-      for (int k = 1; k < K; ++k)
-        if (k < n_mine) ms = pk_max_i16(ms, pk_max_group(sreg[k]));
-    }
-    const float fs = pk_max_value(ms);
+    const float fs = ref_of_all ? thread_max(sreg, n_mine) : pk_max_value(pk_max_group(sreg[0]));
     acc[0].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f));
     if constexpr (L1 == kL1Own) acc[2].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f));
     if constexpr (L1 == kL1Square) acc[2].r = 2.0f * acc[0].r;

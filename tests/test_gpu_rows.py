@@ -253,3 +253,38 @@ def _check_teacher_topk(oracle, V, pitch, off, k, T):
         # is half a step, at most 2^-23 of it
         bar = 2e-5 + 2.0 ** -23 * t.float().abs().amax(1, keepdim=True).cpu().numpy()
         assert (np.abs(val.check().cpu().numpy().reshape(T, k) - ref["val"]) <= bar).all()
+
+
+def _scalar_errors(oracle, s, t, pitch, tau=1.0, ce=0.0, topk=None):
+    """Root mean square over the rows of the errors of lse and kd, with a gradient and forward only."""
+    T, V = s.shape
+    mask, lab = np.ones(T, np.uint8), np.arange(T, dtype=np.int32)
+    lay = synth.Layout(T, np.array([0, T], np.int32), mask, lab, np.zeros(1, bool))
+    sb = synth.bf16_bits(s)
+    ref = (oracle.kd_dense(sb, synth.bf16_bits(t), lab, mask, tau=tau, want_grad=False) if topk is None else
+           oracle.kd_topk(sb, topk[0].cpu().numpy(), topk[1].cpu().numpy(), lab, mask, tau=tau, want_grad=False))
+    kw = dict(V=V, pitch=pitch, offs=(0, 0, 0), tau=tau, topk=topk)
+    errs = {}
+    for mode, got in (("grad", _call(lay, s, t, lab, ce=ce, **kw)), ("forward", _call(lay, s, t, lab, grad=False, **kw))):
+        for n in ("lse_s", "kd"):
+            errs[mode, n] = float(np.sqrt(np.mean((got[n] - ref[n]) ** 2)))
+    print(f"[rows] errors V={V} pitch={pitch} tau={tau} ce={ce} {errs}", flush=True)
+    return errs
+
+
+@pytest.mark.parametrize("V,pitch", [(2048, 2048), (8192, 8192), (5003, 5003), (24576, 24576), (50003, 50003)])
+def test_rows_of_log_probabilities(oracle, V, pitch):
+    """Rows of negative logits alone: exponents are taken against a thread's largest logit there too.
+
+    The terms that carry a thread's sum lie within 8 bits of its largest, so an argument's rounding is at most 2^-22 of
+    the term and the exponential's and the sum's own are of that size: 4e-7 for a log-sum-exp near 0.  kd weighs the same
+    errors with differences of logits of about 4.  (Arguments as long as the row's spread, 64 bits and more, carry 2^-18.)"""
+    g = torch.Generator(device=dev()).manual_seed(V)
+    x = 8.0 * torch.randn((64, V), generator=g, device=dev())
+    y = 0.8 * x + 4.0 * torch.randn((64, V), generator=g, device=dev())
+    s, t = (torch.log_softmax(v, dim=1).to(torch.bfloat16) for v in (x, y))
+    val, idx = torch.topk(t.float(), 50, dim=1)
+    for topk in (None, (idx.to(torch.int32).contiguous(), val.contiguous())):
+        errs = _scalar_errors(oracle, s, t, pitch, topk=topk)
+        assert max(errs["grad", "lse_s"], errs["forward", "lse_s"]) <= 4e-7
+        assert max(errs["grad", "kd"], errs["forward", "kd"]) <= 1.5e-6
