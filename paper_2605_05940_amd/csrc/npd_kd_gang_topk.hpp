@@ -143,7 +143,7 @@ kd_gang_topk_kernel(const KdArgs a) {
   Lse acc[4];  // 0 student / tau, 2 student at tau = 1 (the indices accum8 uses; 1 and 3 stay empty)
 #pragma unroll
   for (int i = 0; i < 4; ++i) acc[i].init();
-  const bool ref_of_all = SOLO || a.ragged;
+  const bool ref_of_all = SOLO || a.ragged || (LSE1 && a.cscale != 0.0f);  // see npd_kd_gang.hpp
   const float kRefBias = ref_of_all ? 0.0f : (L1 == kL1Square ? 44.0f : 100.0f);  // see npd_kd_gang.hpp
   if (ng > tid) {
     const float fs = ref_of_all ? thread_max(sreg, n_mine) : pk_max_value(pk_max_group(sreg[0]));

@@ -288,3 +288,20 @@ def test_rows_of_log_probabilities(oracle, V, pitch):
         errs = _scalar_errors(oracle, s, t, pitch, topk=topk)
         assert max(errs["grad", "lse_s"], errs["forward", "lse_s"]) <= 4e-7
         assert max(errs["grad", "kd"], errs["forward", "kd"]) <= 1.5e-6
+
+
+@pytest.mark.parametrize("V", [32768, 50304])
+@pytest.mark.parametrize("tau", [0.5, 2.0])
+def test_composite_at_a_temperature_keeps_its_precision(oracle, V, tau):
+    """Rows that a CE term at tau != 1 brings to the shared-row kernels: the errors of the streaming ones, whose exponents
+    are as short as they can be.  Terms within 8 bits of a thread's largest: 2^-22 of the term for the argument, as much
+    again for the exponential and the sums, times differences of logits of 2 / tau in kd."""
+    g = torch.Generator(device=dev()).manual_seed(V)
+    x = torch.randn((48, V), generator=g, device=dev())
+    y = 0.8 * x + 0.5 * torch.randn((48, V), generator=g, device=dev())
+    for scale, log_probs in ((3.0, False), (8.0, True)):
+        s, t = ((torch.log_softmax(scale * v, dim=1) if log_probs else scale * v).to(torch.bfloat16) for v in (x, y))
+        errs = _scalar_errors(oracle, s, t, V, tau=tau, ce=0.25)
+        assert errs["grad", "kd"] <= (1.5e-6 if log_probs else 1e-6)
+        if log_probs:  # near 0: the rounding of the result itself is out of the way
+            assert errs["grad", "lse_s"] <= 2e-7
