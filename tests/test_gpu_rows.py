@@ -305,3 +305,34 @@ def test_composite_at_a_temperature_keeps_its_precision(oracle, V, tau):
         assert errs["grad", "kd"] <= (1.5e-6 if log_probs else 1e-6)
         if log_probs:  # near 0: the rounding of the result itself is out of the way
             assert errs["grad", "lse_s"] <= 2e-7
+
+
+@pytest.mark.parametrize("V,k,T", [
+    (1000, 20, 1030), (1000, 600, 30),      # 64 threads to a row, four rows to a workgroup | 128 threads
+    (1032, 64, 1030), (2048, 255, 1030), (2048, 256, 1030), (2051, 300, 30),
+    (3000, 200, 1030), (4096, 128, 1030), (4096, 129, 1030), (4096, 1025, 30),
+    (5000, 100, 1030), (8192, 200, 1030), (8192, 513, 1030), (8195, 40, 30),
+    (8200, 64, 1030), (16384, 300, 1030), (16387, 20, 30),
+    (16392, 300, 30), (20480, 64, 1030), (20488, 300, 30), (20488, 65, 1030), (20488, 65, 1300), (32768, 100, 640),
+])
+def test_topk_teacher_by_rows_and_record(oracle, V, k, T):
+    """Every shape of the one-workgroup kernels for a top-k teacher: few rows and many, short records and long ones."""
+    g = torch.Generator(device=dev()).manual_seed(V + k)
+    s = (3.0 * torch.randn((T, V), generator=g, device=dev())).to(torch.bfloat16)
+    idx = torch.empty((T, k), dtype=torch.int32, device=dev())
+    for r in range(0, T, 128):
+        idx[r:r + 128] = torch.rand((min(128, T - r), V), generator=g, device=dev()).topk(k, dim=1)[1]
+    val = torch.randn((T, k), generator=g, device=dev())
+    mask = np.ones(T, np.uint8)
+    mask[::17] = 0
+    lay = synth.Layout(T, np.array([0, T], np.int32), mask, None, np.zeros(1, bool))
+    lab = idx[:, k // 2].cpu().numpy().copy()  # the label among the entries, elsewhere in every other row
+    lab[::2] = np.random.default_rng(V).integers(0, V, lab[::2].size)
+    for tau, ce in ((1.0, 0.25), (2.0, 0.0)):
+        print(f"[rows] by rows and record V={V} k={k} T={T} tau={tau}", flush=True)
+        ref = oracle.kd_topk(synth.bf16_bits(s), idx.cpu().numpy(), val.cpu().numpy(), lab, mask, tau=tau,
+                             grad_scale=0.75, ce_grad_scale=ce)
+        kw = dict(V=V, pitch=V, offs=(0, 0, 0), tau=tau, topk=(idx, val), no_workspace=True)
+        compare_kd(_call(lay, s, None, lab, ce=ce, **kw), ref, mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce, tau=tau)
+        compare_kd(_call(lay, s, None, lab, grad=False, **kw), {n: ref[n] for n in ("kd", "nll_s", "lse_s")}, mask,
+                   lay.cu_seqlens, oracle)
