@@ -12,13 +12,16 @@ namespace npd {
 //   reverse KL         2,048 52 / 77, 8,192 59 / 77, 12,288 70 / 75, 16,384 74 / 70
 //   skew KL            2,048 35 / 73, 8,192 39 / 77, 12,288 44 / 73, 16,384 46 / 70
 //   top-k (64), tau 2  2,048 31 / 54, 4,096 33 / 53, 8,192 44 / 63, 16,384 58 / 61, 24,576 58 / 67
-//   NLL alone          2,048 68 / 78, 4,096 40 / 82, 8,192 57 / 84, 24,576 85 / 89
+//   NLL alone          2,048 68 / 78, 4,096 40 / 82, 8,192 57 / 84
 // Short rows used to stream twice; a row that lives in registers is read once, and 5 .. 8 waves per SIMD hide its
 // reductions.
+// What stays with the kernels that ran it before, with both sides (us, that kernel / this one):
+//   no teacher, more than 2,048 groups      V = 20,480 1,500 rows 12.1 / 12.9, 20,000 122 / 132; 30,000 512 rows 6.8 / 7.5
 constexpr int kSoloForwardGroups = 256 * 8, kSoloReverseGroups = 256 * 6;
 bool solo_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
   if (a.nvec_s == 0) return false;
-  if (teacher_kind != kDense) return a.nvec_s <= kSoloGroups;
+  if (teacher_kind == kNone) return a.nvec_s <= kSoloForwardGroups;
+  if (teacher_kind == kTopk) return a.nvec_s <= kSoloGroups;
   if (!want_grad) return a.divergence == kForwardKl && a.nvec_s <= kSoloGroups;
   if (a.divergence != kForwardKl && a.divergence != kReverseKl) return a.nvec_s <= kSoloSkewGroups;
   if (a.ragged || a.need_lse1) return a.nvec_s <= kSoloGroups;

@@ -204,6 +204,18 @@ def test_workspace_rules(lib):
     assert call(d, student=None) == E_NULL
 
 
+@pytest.mark.parametrize("name,desc", [
+    # no teacher: rows of up to 2,048 groups live in one workgroup's registers, longer ones are faster streamed
+    ("kd_solo_kernel", dict(teacher_kind=2, vocab=16384, flags=1)),
+    ("kd_cached_kernel", dict(teacher_kind=2, vocab=16392, flags=1)),
+    ("kd_cached_kernel", dict(teacher_kind=2, vocab=32768, flags=1)),
+])
+def test_kernel_choice(lib, name, desc):
+    d = _desc(**desc)
+    d.student_stride = d.teacher_stride = d.vocab
+    assert lib.npd_kd_kernel_name(ctypes.byref(d)).decode() == name
+
+
 def test_segment_and_ifd_argument_validation(lib):
     assert lib.npd_segment_reduce(-1, 1, *([FAKE] * 8), None) == E_SHAPE
     assert lib.npd_segment_reduce(8, -1, *([FAKE] * 8), None) == E_SHAPE
