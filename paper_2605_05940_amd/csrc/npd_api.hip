@@ -279,6 +279,8 @@ const char* npd_kd_kernel_name(const npd_kd_desc* desc) {
   npd::KdArgs a{};
   a.T = d.n_tokens;
   a.V = d.vocab;
+  a.k = d.teacher_kind == NPD_TEACHER_TOPK ? d.topk : 0;
+  a.c = (float)(1.4426950408889634 / (double)d.tau);
   a.nvec_s = same_pitch_offset(d) ? d.vocab / 8 : 0;
   a.ragged = d.student_stride % 8 != 0;
   a.cscale = d.ce_grad_scale;

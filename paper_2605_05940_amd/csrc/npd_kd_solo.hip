@@ -17,6 +17,8 @@ namespace npd {
 // reductions.
 // What stays with the kernels that ran it before, with both sides (us, that kernel / this one):
 //   no teacher, more than 2,048 groups      V = 20,480 1,500 rows 12.1 / 12.9, 20,000 122 / 132; 30,000 512 rows 6.8 / 7.5
+//   a sum at tau = 1 without a CE term, 16-byte aligned rows that fill less than 0.72 (tau = 2; else 0.81) of 512 threads
+//                                           V = 20,488 tau = 2 4,096 rows 104 / 110, tau = 3 104 / 118; 24,576 tau = 3 121 / 129
 constexpr int kSoloForwardGroups = 256 * 8, kSoloReverseGroups = 256 * 6;
 bool solo_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
   if (a.nvec_s == 0) return false;
@@ -24,7 +26,9 @@ bool solo_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
   if (teacher_kind == kTopk) return a.nvec_s <= kSoloGroups;
   if (!want_grad) return a.divergence == kForwardKl && a.nvec_s <= kSoloGroups;
   if (a.divergence != kForwardKl && a.divergence != kReverseKl) return a.nvec_s <= kSoloSkewGroups;
-  if (a.ragged || a.need_lse1) return a.nvec_s <= kSoloGroups;
+  if (a.ragged || (a.need_lse1 && a.cscale != 0.0f)) return a.nvec_s <= kSoloGroups;
+  if (a.need_lse1)
+    return a.nvec_s <= kSoloGroups && (a.nvec_s <= 256 * 10 || a.nvec_s >= (l1_mode(a) == kL1Square ? 2944 : 3328));
   return a.nvec_s <= (a.divergence == kForwardKl ? kSoloForwardGroups : kSoloReverseGroups);
 }
 

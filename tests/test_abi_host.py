@@ -209,6 +209,12 @@ def test_workspace_rules(lib):
     ("kd_solo_kernel", dict(teacher_kind=2, vocab=16384, flags=1)),
     ("kd_cached_kernel", dict(teacher_kind=2, vocab=16392, flags=1)),
     ("kd_cached_kernel", dict(teacher_kind=2, vocab=32768, flags=1)),
+    # forward and reverse KL with a sum at tau = 1: not where 512 threads would be filled badly, unless the CE term
+    # leaves no other kernel for whole groups
+    ("kd_solo_kernel", dict(vocab=20480, tau=2.0)), ("kd_cached_kernel", dict(vocab=20488, tau=2.0)),
+    ("kd_cached_kernel", dict(vocab=23544, tau=2.0, divergence=1)), ("kd_solo_kernel", dict(vocab=23552, tau=2.0)),
+    ("kd_cached_kernel", dict(vocab=26616, tau=3.0)), ("kd_solo_kernel", dict(vocab=26624, tau=3.0, divergence=1)),
+    ("kd_solo_kernel", dict(vocab=20488, tau=2.0, ce_grad_scale=0.5)), ("kd_solo_kernel", dict(vocab=20489, tau=3.0)),
 ])
 def test_kernel_choice(lib, name, desc):
     d = _desc(**desc)
