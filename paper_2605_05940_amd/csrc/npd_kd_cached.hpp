@@ -608,7 +608,9 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
   }
 }
 
-template <int CS, int CSR, int CT, int D, int TEACHER, bool GRAD, int DIVK = kForwardKl, int CB = kCB, bool SHORT = false>
+// LSE1: the shape also runs calls that want a sum at tau = 1 beside the one at tau
+template <int CS, int CSR, int CT, int D, int TEACHER, bool GRAD, int DIVK = kForwardKl, int CB = kCB, bool SHORT = false,
+          bool LSE1 = true>
 static hipError_t launch_cached_lse1(const KdArgs& a, hipStream_t stream) {
   constexpr size_t lds_bytes = CT > 0 ? (size_t)(CT | 1) * CB * sizeof(uint4) : 0;
   auto launch = [&](auto kernel) -> hipError_t {
@@ -626,7 +628,10 @@ static hipError_t launch_cached_lse1(const KdArgs& a, hipStream_t stream) {
     }
     return launch_kernel(kernel, dim3((unsigned)a.T), dim3(CB), lds_bytes, stream, a);
   };
-  if (a.need_lse1) return launch(kd_cached_kernel<CS, CSR, CT, D, TEACHER, GRAD, true, DIVK, CB, SHORT>);
+  if (a.need_lse1) {
+    if constexpr (LSE1) return launch(kd_cached_kernel<CS, CSR, CT, D, TEACHER, GRAD, true, DIVK, CB, SHORT>);
+    return hipErrorInvalidValue;  // the dispatch sends no such call here
+  }
   return launch(kd_cached_kernel<CS, CSR, CT, D, TEACHER, GRAD, false, DIVK, CB, SHORT>);
 }
 

@@ -8,7 +8,7 @@ static hipError_t launch_divergence(const KdArgs& a, hipStream_t stream) {
   constexpr int CB = 256;
   constexpr int CSR = kResidentGroups < CS ? kResidentGroups : CS;
   if (a.divergence == kReverseKl)
-    return launch_cached_lse1<CS, CSR, 9, kAhead, kDense, true, kReverseKl, CB, true>(a, stream);
+    return launch_cached_lse1<CS, CSR, 9, kAhead, kDense, true, kReverseKl, CB, true, CS != 16>(a, stream);
   if (a.divergence == kSkewKl)
     return launch_cached_lse1<CS, CSR, 9, kAhead, kDense, true, kSkewKl, CB, true>(a, stream);
   return launch_cached_lse1<CS, CSR, 9, kAhead, kDense, true, kSkewReverseKl, CB, true>(a, stream);

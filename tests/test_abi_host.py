@@ -214,6 +214,16 @@ def test_workspace_rules(lib):
     ("kd_solo_kernel", dict(vocab=20480, tau=2.0)), ("kd_cached_kernel", dict(vocab=20488, tau=2.0)),
     ("kd_cached_kernel", dict(vocab=23544, tau=2.0, divergence=1)), ("kd_solo_kernel", dict(vocab=23552, tau=2.0)),
     ("kd_cached_kernel", dict(vocab=26616, tau=3.0)), ("kd_solo_kernel", dict(vocab=26624, tau=3.0, divergence=1)),
+    # top-k teacher: short records on long rows, and the forward pass over many rows of a short vocabulary
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=64, vocab=20480)),
+    ("kd_cached_kernel", dict(teacher_kind=1, topk=64, vocab=20488)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=65, vocab=20488)),
+    ("kd_cached_kernel", dict(teacher_kind=1, topk=20, vocab=26624)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=20, vocab=26632)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=64, vocab=20488, tau=2.0)),
+    ("kd_rows_kernel", dict(teacher_kind=1, topk=64, vocab=2048, n_tokens=11719, flags=1)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=64, vocab=2048, n_tokens=11718, flags=1)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=200, vocab=2048, n_tokens=65536, flags=1)),
     ("kd_solo_kernel", dict(vocab=20488, tau=2.0, ce_grad_scale=0.5)), ("kd_solo_kernel", dict(vocab=20489, tau=3.0)),
 ])
 def test_kernel_choice(lib, name, desc):
