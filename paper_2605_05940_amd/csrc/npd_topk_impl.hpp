@@ -12,7 +12,7 @@ namespace NPD_TOPK_NS {
 
 constexpr int kTB = NPD_TOPK_TB;          // threads per workgroup
 constexpr int kCandCap = NPD_TOPK_CAND;   // candidates staged per row (8 bytes each)
-constexpr int kGroupCap = NPD_TOPK_GROUPS > 0 ? NPD_TOPK_GROUPS : 1;  // groups with a candidate staged per row
+constexpr int kGroupCap = NPD_TOPK_GROUPS;  // groups with a candidate staged per row (0: none are)
 static_assert(kTB == 512 || kTB == 1024, "workgroups of 8 or 16 waves");
 static_assert((kCandCap & (kCandCap - 1)) == 0 && kCandCap >= 2 * kTB, "the bitonic fallback pads the list to a power of two");
 
@@ -90,14 +90,19 @@ __device__ __forceinline__ int block_excl_scan(int v, int* red, int& total) {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// (Without the groups the arrays stand as they always have: with the union and its 16-byte alignment around them the
+// 1024-thread kernel takes 0.85 us more per row's ordering phase, k = 256, 32 rows of 8,200: 17.3 / 18.1 us.)
 struct TopkShared {
   unsigned long long cand[kCandCap];
+#if NPD_TOPK_GROUPS
   union {  // the groups are dead once the candidates are listed
     struct {
+#endif
       unsigned long long shortlist[kTB];  // the candidates at or above the k-th key, when cand is long
       unsigned long long sorted[kTB];     // rank-sorted short lists
       int rank[kTB];
       int hist[2][256];
+#if NPD_TOPK_GROUPS
     };
     struct {
       u32x4 group[kGroupCap];  // groups with a candidate
@@ -105,6 +110,7 @@ struct TopkShared {
     };
   };
   int ngroups;
+#endif
   int nshort;
 #if NPD_TOPK_ANY_SHAPE
   uint32_t mx[kTB];
@@ -352,9 +358,8 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
     return;
   }
   const uint16_t* trow = a.t + row * a.stride;
-  const RowSplit sp{0, a.nvec};
-  const int nvec = sp.nvec, head = sp.head, n_edge = V - nvec * 8;
-  const uint4* tvec = reinterpret_cast<const uint4*>(trow + head);
+  const int nvec = a.nvec;
+  const uint4* tvec = reinterpret_cast<const uint4*>(trow);
 
   // ---- one maximum per thread
   uint32_t best = 0;  // below every key of a finite value
@@ -365,8 +370,8 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
 #pragma unroll
     for (int j = 0; j < 8; ++j) best = kk[j] > best ? kk[j] : best;
   }
-  for (int j = tid; j < n_edge; j += kTB) {
-    const uint32_t kk = key_of(trow[sp.edge_elem(j)]);
+  for (int e = nvec * 8 + tid; e < V; e += kTB) {
+    const uint32_t kk = key_of(trow[e]);
     best = kk > best ? kk : best;
   }
   sh.mx[tid] = best;
@@ -386,12 +391,11 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
       for (int j = 0; j < 8; ++j) {
         if (kk[j] >= L) {
           const int pos = atomicAdd(&sh.ncand, 1);
-          if (pos < kCandCap) sh.cand[pos] = cand_word(kk[j], (uint32_t)(head + i * 8 + j));
+          if (pos < kCandCap) sh.cand[pos] = cand_word(kk[j], (uint32_t)(i * 8 + j));
         }
       }
     }
-    for (int j = tid; j < n_edge; j += kTB) {
-      const int e = sp.edge_elem(j);
+    for (int e = nvec * 8 + tid; e < V; e += kTB) {
       const uint32_t kk = key_of(trow[e]);
       if (kk >= L) {
         const int pos = atomicAdd(&sh.ncand, 1);
@@ -404,7 +408,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
   int n = sh.ncand;
   __syncthreads();
   if (slow) {
-    slow_select(trow, sp, V, k, sh, tid);
+    slow_select(trow, RowSplit{0, nvec}, V, k, sh, tid);
     n = k;
   }
   order_and_emit(sh, n, k, a.log_probs, a.idx + row * (int64_t)k, a.val + row * (int64_t)k, tid);
@@ -428,6 +432,7 @@ __device__ __forceinline__ void append(TopkShared& sh, int o, int id) {
   if (pos < kCandCap) sh.cand[pos] = cand_word(key_of_ordered(o), (uint32_t)id);
 }
 
+#if NPD_TOPK_GROUPS
 // A group with an element >= Lp goes to the LDS list whole (its patterns and its index): one exchange and two writes
 // instead of a test of its eight elements by one lane out of 64; they are tested later, a group to a thread (8,192 rows
 // of 151,936, all scored, 512 threads: k = 64 414 -> 385 us, k = 10 397 -> 390; 50,304 k = 128 199 -> 175).
@@ -454,6 +459,7 @@ __device__ __forceinline__ void append_group(const u32x4& v, int i, int Lp, int 
     }
   }
 }
+#endif
 
 // candidates of one register group: elements whose ordered value is >= Lp.  With ORDERED = false the patterns are
 // compared as they are, which is the same thing for Lp >= 1 (patterns of positive values are ordered integers,
@@ -477,7 +483,7 @@ __device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, int
 }
 
 // W = register window (groups in flight per thread), S <= W = groups of the sample that gives the bound.
-// ngroups = ceil(nvec / 1024) >= 1 groups are visited in the order (g * step) mod ngroups, step coprime to ngroups.
+// ngroups = ceil(nvec / kTB) >= 1 groups are visited in the order (g * step) mod ngroups, step coprime to ngroups.
 // RAGGED: rows begin anywhere inside a 16-byte group.
 template <int W, int S, bool RAGGED>
 __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkArgs a, int ngroups, int step) {
@@ -531,7 +537,9 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkA
     if (lane == 0) sh.wave_bound[wid] = blo;
   }
   if (tid == 0) sh.ncand = 0;
-  if (kGroupCap > 1 && tid == 0) sh.ngroups = 0;
+#if NPD_TOPK_GROUPS
+  if (tid == 0) sh.ngroups = 0;
+#endif
   __syncthreads();
 
   if (!slow) {
@@ -545,26 +553,26 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkA
       for (int j = 0; j < W; ++j) {
         const int g = base + j;
         if (g < ngroups) {
-          if constexpr (kGroupCap > 1) {
-            if (Lp >= 1)
-              append_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
-            else
-              append_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
-          } else {
-            if (Lp >= 1)
-              collect_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
-            else
-              collect_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
-          }
+#if NPD_TOPK_GROUPS
+          if (Lp >= 1)
+            append_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
+          else
+            append_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
+#else
+          if (Lp >= 1)
+            collect_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
+          else
+            collect_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
+#endif
         }
         if (g + W < ngroups) w[j] = load_group(tvec, vec_index(g + W), nvec);
       }
     }
-    if constexpr (kGroupCap > 1) {
-      __syncthreads();
-      const int ng = min(sh.ngroups, kGroupCap);
-      for (int p = tid; p < ng; p += kTB) collect_group<true>(sh.group[p], sh.group_id[p], Lp, nvec, head, sh);
-    }
+#if NPD_TOPK_GROUPS
+    __syncthreads();
+    const int ng = min(sh.ngroups, kGroupCap);
+    for (int p = tid; p < ng; p += kTB) collect_group<true>(sh.group[p], sh.group_id[p], Lp, nvec, head, sh);
+#endif
     if (tid < n_edge) {  // elements in front of and behind the whole groups
       const int e = sp.edge_elem(tid);
       const int o = ordered_of(trow[e]);
