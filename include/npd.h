@@ -218,9 +218,14 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
  *     of a 151,936-entry vocabulary; with a dense teacher at tau != 1 half of that; the skew divergences count
  *     ceil(vocab / 12224)).  Pass NPD_FLAG_NO_WORKSPACE, or use
  *     npd_kd_loss_fwd_bwd with a workspace, for larger batches.
- *   - Every call on a GPU uses that GPU's one array (cleared by the call itself before use): calls that overlap in
- *     time on one GPU -- two streams, two host threads -- race on it and give wrong results.  Order them on one
- *     stream.
+ *   - Every other call that needs a workspace uses its GPU's one array (cleared by the call itself before use): such
+ *     calls that overlap in time on one GPU -- two streams, two host threads -- race on it and give wrong results.
+ *     Order them on one stream.
+ *   - Calls with ce_grad_scale != 0 at tau != 1 and calls on rows that are not 16-byte aligned (a tensor that begins
+ *     elsewhere, or a row stride that is not a multiple of 8) never use the array and may overlap.  They run in the
+ *     kernels that exchange nothing, as under NPD_FLAG_NO_WORKSPACE: slower on long rows than npd_kd_loss_fwd_bwd with a
+ *     workspace, with the same results to rounding.  With ce_grad_scale != 0 at tau != 1 the size limit above does not
+ *     apply either.
  *   - The first call on a device asks the runtime for the array's address (no allocation); make it outside stream
  *     capture.
  */

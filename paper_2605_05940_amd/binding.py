@@ -149,9 +149,8 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     The teacher kind follows from which teacher tensors are given; ``grad_out is None`` means forward
     only; ``grad_out`` sharing storage with ``student_logits`` means the in-place gradient.  ``workspace``:
     a uint8 tensor of at least ``npd_workspace_bytes`` bytes; if it is None one is taken from
-    ``workspace_for`` (a per-device tensor that this module keeps and grows), or, with a CE term at tau != 1, allocated
-    for the call.  ``no_workspace`` sets
-    ``NPD_FLAG_NO_WORKSPACE``.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in
+    ``workspace_for`` (a per-device tensor that this module keeps and grows) or, with a CE term at tau != 1 and for rows
+    that are not 16-byte aligned, allocated for the call.  ``no_workspace`` sets ``NPD_FLAG_NO_WORKSPACE``.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in
     scratch array; no workspace argument).
     """
     T, V = shape = student_logits.shape
@@ -183,10 +182,11 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     # (forward-only calls need no workspace)
     if workspace is None and grad_out is not None and not no_workspace and not noalloc:
         need = L.npd_workspace_bytes(desc)
-        if ce_grad_scale != 0.0 and tau != 1.0:
-            # these calls can do without and may run beside others on several streams: a block of this call's own,
-            # from torch's stream-ordered allocator (reused only behind this call on its stream)
-            workspace = torch.empty(need, dtype=torch.uint8, device=student_logits.device) if need else None
+        if need and (ce_grad_scale != 0.0 and tau != 1.0 or (student_logits.data_ptr() | 2 * student_stride) & 15):
+            # a CE term at tau != 1 and rows that are not 16-byte aligned: these calls can run without any scratch and
+            # may run beside others on several streams: a block of this call's own, from torch's stream-ordered
+            # allocator (reused only behind this call on its stream)
+            workspace = torch.empty(need, dtype=torch.uint8, device=student_logits.device)
         else:
             workspace = workspace_for(need, student_logits.device)
     args = (desc, _ptr(student_logits, torch.bfloat16), _ptr(teacher_dense, torch.bfloat16),

@@ -334,8 +334,10 @@ npd_status npd_kd_loss_fwd_bwd_noalloc(const npd_kd_desc* desc, const void* stud
   const npd_status st = check_kd_call(desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
                                       grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
   if (st != NPD_OK) return st;
-  if (workspace_optional(*desc)) need = 0;  // such calls have never used the scratch array: they may overlap
+  // calls that have never used the scratch array may overlap: they keep to the kernels that need none
+  if (workspace_optional(*desc)) need = 0;
   if (need > (size_t)NPD_NOALLOC_WORKSPACE_BYTES) return NPD_ERR_WORKSPACE;  // the built-in scratch is too small
+  if (a.ragged) need = 0;  // nor have these
   if (need > 0) {
     hipError_t e = hipSuccess;
     void* scratch = noalloc_scratch_address(&e);

@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_05940_amd import binding, synth
 
@@ -290,6 +291,41 @@ def test_binding_refuses_host_tensors():
 
 
 # --------------------------------------------------------------------------- synthetic layouts
+
+@pytest.mark.parametrize("pitch,off,tau,ce,own", [
+    (50048, 0, 1.0, 0.5, False), (50048, 0, 2.0, 0.0, False),   # aligned rows: the buffer the module keeps
+    (50048, 0, 2.0, 0.5, True),                                 # a CE term at tau != 1
+    (50003, 0, 1.0, 0.0, True), (50048, 3, 1.0, 0.0, True),     # rows that are not 16-byte aligned
+])
+def test_calls_that_may_overlap_get_scratch_of_their_own(lib, monkeypatch, pitch, off, tau, ce, own):
+    """Two calls on two streams share no scratch where such calls once needed none."""
+    seen = []
+
+    class Library:
+        npd_workspace_bytes = staticmethod(lib.npd_workspace_bytes)
+
+        @staticmethod
+        def npd_kd_loss_fwd_bwd(*args):
+            seen.append(args[13])
+            return 0
+
+    monkeypatch.setattr(binding, "load", lambda: Library)
+    monkeypatch.setattr(binding, "_stream", lambda: None)
+    monkeypatch.setattr(binding, "_ptr", lambda t, dtype=None: None if t is None else t.data_ptr())
+    monkeypatch.setattr(binding, "_array", lambda name, t, n, dtype: None if t is None else t.data_ptr())
+    monkeypatch.setattr(binding, "_workspaces", {})
+    kept = []
+    empty = torch.empty
+    monkeypatch.setattr(binding.torch, "empty", lambda *a, **kw: kept.append(empty(*a, **kw)) or kept[-1])
+    T, V = 4, 50000
+    s, t, g = (empty(T * pitch + 64, dtype=torch.bfloat16) for _ in range(3))
+    s, t, g = (x[-(x.data_ptr() // 2) % 8 + off:][:T * pitch].view(T, pitch)[:, :V] for x in (s, t, g))
+    mask, labels = torch.ones(T, dtype=torch.uint8), torch.zeros(T, dtype=torch.int32)
+    for _ in range(2):
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, labels=labels, tau=tau, ce_grad_scale=ce, grad_out=g)
+    assert (seen[0] != seen[1]) == own
+    assert bool(binding._workspaces) != own
+
 
 def test_layouts_are_deterministic_and_well_formed():
     for i in range(5):

@@ -36,3 +36,38 @@ def test_noalloc_entry_point_matches_the_workspace_entry_point_bitwise():
         for a, b in zip(got, want):
             np.testing.assert_array_equal(a, b)
         assert np.isfinite(got[1].view(np.float32)).all()
+
+
+@pytest.mark.parametrize("noalloc", [True, False])
+def test_calls_on_rows_at_any_offset_may_overlap(noalloc):
+    """Rows that are not 16-byte aligned share no scratch between calls: two streams, the same results as one."""
+    T, V = 600, 50003
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(7)
+    mask = torch.ones(T, dtype=torch.uint8, device=dev)
+    calls = []
+    for _ in range(2):
+        s = (3.0 * torch.randn((T, V), device=dev, generator=g)).to(torch.bfloat16)
+        t = (0.8 * s.float() + 1.5 * torch.randn((T, V), device=dev, generator=g)).to(torch.bfloat16)
+        calls.append((s, t, torch.empty_like(s), torch.empty(T, device=dev)))
+
+    def run(s, t, grad, kd):
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, grad_out=grad, kd_tok=kd, noalloc=noalloc)
+
+    want = []
+    for c in calls:
+        run(*c)
+        torch.cuda.synchronize()
+        want.append([synth.bf16_bits(c[2]), c[3].cpu().numpy()])
+        c[2].zero_()
+        c[3].zero_()
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in calls]
+    for _ in range(4):
+        for c, stream in zip(calls, streams):
+            with torch.cuda.stream(stream):
+                run(*c)
+    torch.cuda.synchronize()
+    for c, (grad, kd) in zip(calls, want):
+        np.testing.assert_array_equal(synth.bf16_bits(c[2]), grad)
+        np.testing.assert_array_equal(c[3].cpu().numpy(), kd)
