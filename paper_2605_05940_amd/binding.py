@@ -185,8 +185,8 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
         if need and (ce_grad_scale != 0.0 and tau != 1.0 or (student_logits.data_ptr() | 2 * student_stride) & 15):
             # a CE term at tau != 1 and rows that are not 16-byte aligned: these calls can run without any scratch and
             # may run beside others on several streams: a block of this call's own, from torch's stream-ordered
-            # allocator (reused only behind this call on its stream)
-            workspace = torch.empty(need, dtype=torch.uint8, device=student_logits.device)
+            # allocator (reused only behind this call on its stream: the current device's, where the kernels run)
+            workspace = torch.empty(need, dtype=torch.uint8, device="cuda")
         else:
             workspace = workspace_for(need, student_logits.device)
     args = (desc, _ptr(student_logits, torch.bfloat16), _ptr(teacher_dense, torch.bfloat16),

@@ -314,9 +314,15 @@ def test_calls_that_may_overlap_get_scratch_of_their_own(lib, monkeypatch, pitch
     monkeypatch.setattr(binding, "_ptr", lambda t, dtype=None: None if t is None else t.data_ptr())
     monkeypatch.setattr(binding, "_array", lambda name, t, n, dtype: None if t is None else t.data_ptr())
     monkeypatch.setattr(binding, "_workspaces", {})
-    kept = []
+    kept, devices = [], []
     empty = torch.empty
-    monkeypatch.setattr(binding.torch, "empty", lambda *a, **kw: kept.append(empty(*a, **kw)) or kept[-1])
+
+    def record(*a, device, **kw):
+        devices.append(device)
+        kept.append(empty(*a, **kw))
+        return kept[-1]
+
+    monkeypatch.setattr(binding.torch, "empty", record)
     T, V = 4, 50000
     s, t, g = (empty(T * pitch + 64, dtype=torch.bfloat16) for _ in range(3))
     s, t, g = (x[-(x.data_ptr() // 2) % 8 + off:][:T * pitch].view(T, pitch)[:, :V] for x in (s, t, g))
@@ -325,6 +331,8 @@ def test_calls_that_may_overlap_get_scratch_of_their_own(lib, monkeypatch, pitch
         binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, labels=labels, tau=tau, ce_grad_scale=ce, grad_out=g)
     assert (seen[0] != seen[1]) == own
     assert bool(binding._workspaces) != own
+    if own:  # on the device and the stream that run the kernels, whatever device the logits are on
+        assert devices == ["cuda", "cuda"]
 
 
 def test_layouts_are_deterministic_and_well_formed():
