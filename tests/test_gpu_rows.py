@@ -98,7 +98,9 @@ def _reference(oracle, lay, s, t, lab, div, tau, gs, ce):
 @pytest.mark.parametrize("div,tau,ce", [("forward", 1.0, 0.25), ("forward", 2.0, 0.0), ("reverse", 1.0, 0.25),
                                         ("skew", 1.0, 0.25), ("skew_reverse", 2.0, 0.0),
                                         ("forward", 2.0, 0.25), ("reverse", 0.5, 0.25), ("skew", 2.0, 0.25),
-                                        ("skew_reverse", 2.0, 0.25)])   # the CE term with a softmax of its own
+                                        ("skew_reverse", 2.0, 0.25),   # the CE term with a softmax of its own: squares
+                                        ("forward", 0.5, 0.25), ("reverse", 2.0, 0.25), ("skew", 3.0, 0.25),
+                                        ("skew_reverse", 0.5, 0.25)])  # and exponentials of its own
 def test_dense_rows_at_any_offset(oracle, V, pitch, offs, pitch_t, div, tau, ce):
     w, lay, s, t, lab = _batch(V)
     ref = _reference(oracle, lay, s, t, lab, div, tau, 0.75, ce)
@@ -214,7 +216,8 @@ def test_teacher_topk_rows_at_any_offset(oracle, V, pitch, off, k):
     _check_teacher_topk(oracle, V, pitch, off, k, 12)
 
 
-@pytest.mark.parametrize("V,pitch", [(2056, 2056), (4100, 4100), (8192, 8192)])
+@pytest.mark.parametrize("V,pitch", [(1024, 1024), (1032, 1032), (2048, 2048), (2051, 2051), (2056, 2056), (4100, 4100),
+                                     (8192, 8192), (12291, 12291), (16384, 16384)])
 @pytest.mark.parametrize("k", [10, 100, 256])
 def test_teacher_topk_of_many_rows(oracle, V, pitch, k):
     """The same with so many rows that a row gets fewer threads."""
