@@ -15,35 +15,39 @@ namespace npd {
 //   NLL alone          2,048 68 / 78, 4,096 40 / 82, 8,192 57 / 84
 // Short rows used to stream twice; a row that lives in registers is read once, and 5 .. 8 waves per SIMD hide its
 // reductions.
-// What stays with the kernels that ran it before, with both sides (us, that kernel / this one):
+// What stays with the kernels that ran it before, with both sides (us, that kernel / this one), unless rows are so few
+// that each has a compute unit, or a good part of one, to itself (32 rows of 24,576: no teacher 5.5 / 4.9, tau = 3
+// 13.4 / 11.2, k = 20 8.6 / 7.1):
 //   no teacher, more than 2,048 groups      V = 20,480 1,500 rows 12.1 / 12.9, 20,000 122 / 132; 30,000 512 rows 6.8 / 7.5
 //   a sum at tau = 1 without a CE term, 16-byte aligned rows that fill less than 0.72 (tau = 2; else 0.81) of 512 threads
-//                                           V = 20,488 tau = 2 4,096 rows 104 / 110, tau = 3 104 / 118; 24,576 tau = 3 121 / 129
-//   top-k teacher with up to 64 entries, no sum at tau = 1, aligned rows of 2,561 .. 3,328 groups
+//                                           V = 20,488 4,096 rows tau = 2 104 / 110, tau = 3 104 / 118; 24,576 tau = 3 121 / 129
+//                                           (from 2,048 rows and 1,024 rows on; 22,000 640 rows tau = 2 25.4 / 23.5)
+//   top-k teacher with up to 32 entries, no sum at tau = 1, aligned rows of 2,561 .. 3,328 groups
 //                                           V = 24,576 k = 20 1,024 rows 17.4 / 18.2, 1,500 26.4 / 29.7
 //   top-k teacher, forward only, 33 .. 192 entries, aligned rows of 225 .. 512 groups, 48 MB of them and more (a row's
 //   record is gathered before its logits have arrived)
 //                                           V = 2,048 k = 64 32,768 rows 36.8 / 41.1; 3,072 k = 160 8,192 rows 19.8 / 20.7
 constexpr int kSoloForwardGroups = 256 * 8, kSoloReverseGroups = 256 * 6;
-constexpr int kShortRecord = 64;
+constexpr int kFewRows = 256;
 static bool solo_dense_applies(const KdArgs& a, bool want_grad) {
   const int n = a.nvec_s;
   if (!want_grad) return a.divergence == kForwardKl && n <= kSoloGroups;
   if (a.divergence != kForwardKl && a.divergence != kReverseKl) return n <= kSoloSkewGroups;
   if (a.ragged || (a.need_lse1 && a.cscale != 0.0f)) return n <= kSoloGroups;
-  if (a.need_lse1) return n <= kSoloGroups && (n <= 256 * 10 || n >= (l1_mode(a) == kL1Square ? 2944 : 3328));
+  if (a.need_lse1)
+    return n <= kSoloGroups && (n <= 256 * 10 || n >= (l1_mode(a) == kL1Square ? 2944 : 3328) || a.T < (l1_mode(a) == kL1Square ? 8 : 4) * kFewRows);
   return n <= (a.divergence == kForwardKl ? kSoloForwardGroups : kSoloReverseGroups);
 }
 static bool solo_topk_applies(const KdArgs& a, bool want_grad) {
   const int n = a.nvec_s;
   if (n > kSoloGroups) return false;
   if (a.ragged) return true;
-  if (want_grad) return n <= 256 * 10 || n > 256 * 13 || a.need_lse1 || a.k > kShortRecord;
+  if (want_grad) return n <= 256 * 10 || n > 256 * 13 || a.need_lse1 || a.k > 32 || a.T <= kFewRows;
   return !(n > 224 && n <= 512 && a.k > 32 && a.k <= 192 && a.T * (int64_t)a.V >= 24000000);
 }
 bool solo_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
   if (a.nvec_s == 0) return false;
-  if (teacher_kind == kNone) return a.nvec_s <= kSoloForwardGroups;
+  if (teacher_kind == kNone) return a.nvec_s <= (a.T <= kFewRows ? kSoloGroups : kSoloForwardGroups);
   return teacher_kind == kTopk ? solo_topk_applies(a, want_grad) : solo_dense_applies(a, want_grad);
 }
 

@@ -101,7 +101,7 @@ static hipError_t launch_solo_student(const KdArgs& a, hipStream_t stream) {
     if (few && a.k > 256) return launch_solo_student_shape<1024, 4, GRAD>(a, stream);
     return launch_solo_student_shape<256, 10, GRAD>(a, stream);
   }
-  if (a.T < 640 || (GRAD && !a.need_lse1 && a.T >= 1280)) return launch_solo_student_shape<1024, 4, GRAD>(a, stream);
+  if ((a.T < 640 && a.k > 0) || (GRAD && !a.need_lse1 && a.T >= 1280)) return launch_solo_student_shape<1024, 4, GRAD>(a, stream);
   return launch_solo_student_shape<512, 8, GRAD>(a, stream);
 }
 

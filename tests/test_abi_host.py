@@ -209,26 +209,33 @@ def test_workspace_rules(lib):
     # no teacher: rows of up to 2,048 groups live in one workgroup's registers, longer ones are faster streamed
     ("kd_solo_kernel", dict(teacher_kind=2, vocab=16384, flags=1)),
     ("kd_cached_kernel", dict(teacher_kind=2, vocab=16392, flags=1)),
-    ("kd_cached_kernel", dict(teacher_kind=2, vocab=32768, flags=1)),
+    ("kd_cached_kernel", dict(teacher_kind=2, vocab=32768, flags=1, n_tokens=257)),
+    ("kd_solo_kernel", dict(teacher_kind=2, vocab=32768, flags=1, n_tokens=256)),
     # forward and reverse KL with a sum at tau = 1: not where 512 threads would be filled badly, unless the CE term
     # leaves no other kernel for whole groups
-    ("kd_solo_kernel", dict(vocab=20480, tau=2.0)), ("kd_cached_kernel", dict(vocab=20488, tau=2.0)),
-    ("kd_cached_kernel", dict(vocab=23544, tau=2.0, divergence=1)), ("kd_solo_kernel", dict(vocab=23552, tau=2.0)),
+    ("kd_solo_kernel", dict(vocab=20480, tau=2.0, n_tokens=2048)),
+    ("kd_cached_kernel", dict(vocab=20488, tau=2.0, n_tokens=2048)),
+    ("kd_solo_kernel", dict(vocab=20488, tau=2.0, n_tokens=2047)),
+    ("kd_cached_kernel", dict(vocab=23544, tau=2.0, divergence=1, n_tokens=2048)),
+    ("kd_solo_kernel", dict(vocab=23552, tau=2.0, n_tokens=2048)),
     ("kd_cached_kernel", dict(vocab=26616, tau=3.0)), ("kd_solo_kernel", dict(vocab=26624, tau=3.0, divergence=1)),
+    ("kd_solo_kernel", dict(vocab=20488, tau=3.0, n_tokens=1023)),
+    ("kd_solo_kernel", dict(vocab=20488, tau=2.0, ce_grad_scale=0.5, n_tokens=2048)),
+    ("kd_solo_kernel", dict(vocab=20489, tau=3.0)),
     # top-k teacher: short records on long rows, and the forward pass over many rows of a short vocabulary
-    ("kd_solo_kernel", dict(teacher_kind=1, topk=64, vocab=20480)),
-    ("kd_cached_kernel", dict(teacher_kind=1, topk=64, vocab=20488)),
-    ("kd_solo_kernel", dict(teacher_kind=1, topk=65, vocab=20488)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=32, vocab=20480)),
+    ("kd_cached_kernel", dict(teacher_kind=1, topk=32, vocab=20488)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=33, vocab=20488)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=32, vocab=20488, tau=2.0)),
     ("kd_cached_kernel", dict(teacher_kind=1, topk=20, vocab=26624)),
+    ("kd_solo_kernel", dict(teacher_kind=1, topk=20, vocab=26624, n_tokens=256)),
     ("kd_solo_kernel", dict(teacher_kind=1, topk=20, vocab=26632)),
-    ("kd_solo_kernel", dict(teacher_kind=1, topk=64, vocab=20488, tau=2.0)),
     ("kd_rows_kernel", dict(teacher_kind=1, topk=64, vocab=2048, n_tokens=11719, flags=1)),
     ("kd_solo_kernel", dict(teacher_kind=1, topk=64, vocab=2048, n_tokens=11718, flags=1)),
     ("kd_solo_kernel", dict(teacher_kind=1, topk=200, vocab=2048, n_tokens=65536, flags=1)),
-    ("kd_solo_kernel", dict(vocab=20488, tau=2.0, ce_grad_scale=0.5)), ("kd_solo_kernel", dict(vocab=20489, tau=3.0)),
 ])
 def test_kernel_choice(lib, name, desc):
-    d = _desc(**desc)
+    d = _desc(**dict(dict(n_tokens=1024), **desc))
     d.student_stride = d.teacher_stride = d.vocab
     assert lib.npd_kd_kernel_name(ctypes.byref(d)).decode() == name
 
