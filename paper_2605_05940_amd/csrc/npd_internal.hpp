@@ -40,7 +40,6 @@ struct KdArgs {
   uint32_t* ws;          // scratch record, gang_workspace_bytes() bytes
   int32_t gang;          // slices (workgroups) per row
   int32_t gang_groups;   // 128-bit groups per slice
-  int32_t gang_pow2;     // gang rounded up to a power of two
   int32_t spin_limit;    // polls before a waiting workgroup gives up
 };
 

@@ -575,7 +575,8 @@ __global__ __launch_bounds__(CB, 4) void kd_cached_kernel(const KdArgs a) {
             __builtin_amdgcn_sched_barrier(0);
           }
         } else {
-          // rows whose reference exponents are in the thousands: precise form, plain loop over the row
+          // rows at any offset, and rows whose reference exponents are in the thousands: precise form, plain loop over
+          // the row, every group read again
           for (int i = (nit < CS ? nit : CS) * CB - CB + tid; i >= 0; i -= CB) {
             if (i < nvec) {
               const uint4 vs = ld16(svec, i);

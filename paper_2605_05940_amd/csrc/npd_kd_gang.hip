@@ -89,8 +89,6 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, hipStream_t stream
   // bytes begins anywhere): no cache line is then shared by two workgroups of a row -- measured +2.4 points of the HBM
   // peak on config 1, +2.5 on config 4, +3.6 on config 2; a row pitch of 16 bytes more than config 1's: +4.
   a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;
-  a.gang_pow2 = 1;
-  while (a.gang_pow2 < a.gang) a.gang_pow2 *= 2;
   a.spin_limit = g_spin_limit.load(std::memory_order_relaxed);
   if (teacher_kind == kTopk) {
     const size_t lds = (size_t)topk_lds_words(kGangThreads, kGangTopkK, a.k, false) * sizeof(uint32_t);
