@@ -125,8 +125,10 @@ const char* npd_status_string(npd_status st);
 
 /*
  * Name of the kernel family npd_kd_loss_fwd_bwd launches for `desc` when every tensor is 16-byte aligned and the
- * workspace npd_workspace_bytes() asks for is given ("kd_gang_kernel", "kd_cached_kernel", "kd_rows_kernel",
- * "div_rows_kernel"; "" for an invalid desc): lets a benchmark or profile say what it measured.  Static string.
+ * workspace npd_workspace_bytes() asks for is given ("kd_gang_kernel": rows shared by several workgroups;
+ * "kd_solo_kernel": the same kernels with a whole row to a workgroup, in a profile kd_gang_kernel and
+ * kd_gang_topk_kernel too; "kd_cached_kernel", "kd_rows_kernel", "div_rows_kernel"; "" for an invalid desc): lets a
+ * benchmark or profile say what it measured.  Static string.
  */
 const char* npd_kd_kernel_name(const npd_kd_desc* desc);
 
@@ -138,8 +140,9 @@ const char* npd_kd_kernel_name(const npd_kd_desc* desc);
 int npd_debug_gang_spin_limit(int polls);
 
 /*
- * Bytes of device workspace npd_kd_loss_fwd_bwd needs for `desc` (host call; 0 is a
- * legal answer and then `workspace` may be NULL).  Returns 0 for an invalid desc.
+ * Bytes of device workspace npd_kd_loss_fwd_bwd takes for `desc` (host call; 0 is a
+ * legal answer and then `workspace` may be NULL).  Required, except with ce_grad_scale != 0
+ * at tau != 1, where it makes the call faster.  Returns 0 for an invalid desc.
  */
 size_t npd_workspace_bytes(const npd_kd_desc* desc);
 
@@ -194,8 +197,8 @@ size_t npd_workspace_bytes(const npd_kd_desc* desc);
  * Each gradient element is rounded to bf16 once (round to nearest even) from an fp32
  * value; all sums are accumulated in fp32.  A call's results are bitwise reproducible from
  * run to run (no floating-point atomics).  Two different calls on the same data (forward only
- * vs with gradient, other strides or alignment) may sum a row in another order: their scalar
- * outputs then agree to fp32 rounding, not bit for bit.  The fast kernels take rows that begin at the
+ * vs with gradient, other strides or alignment, another number of rows) may sum a row in
+ * another order: their scalar outputs then agree to fp32 rounding, not bit for bit.  The fast kernels take rows that begin at the
  * same offset from a 16-byte boundary in student, teacher and gradient (tensors that are themselves
  * 16-byte aligned and share their row pitch modulo 8 elements, whatever the pitch); anything else is
  * handled element-wise, with the same results to rounding.
@@ -214,7 +217,7 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
  * the process ends).  The call allocates and frees nothing.
  *
  *   - A call whose npd_workspace_bytes(desc) exceeds NPD_NOALLOC_WORKSPACE_BYTES returns NPD_ERR_WORKSPACE and
- *     enqueues nothing (at tau = 1 the array covers n_tokens * ceil(vocab / 20416) <= 524,288, e.g. 65,536 positions
+ *     enqueues nothing, except with ce_grad_scale != 0 at tau != 1 (at tau = 1 the array covers n_tokens * ceil(vocab / 20416) <= 524,288, e.g. 65,536 positions
  *     of a 151,936-entry vocabulary; with a dense teacher at tau != 1 half of that; the skew divergences count
  *     ceil(vocab / 12224)).  Pass NPD_FLAG_NO_WORKSPACE, or use
  *     npd_kd_loss_fwd_bwd with a workspace, for larger batches.
@@ -224,8 +227,7 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
  *   - Calls with ce_grad_scale != 0 at tau != 1 and calls on rows that are not 16-byte aligned (a tensor that begins
  *     elsewhere, or a row stride that is not a multiple of 8) never use the array and may overlap.  They run in the
  *     kernels that exchange nothing, as under NPD_FLAG_NO_WORKSPACE: slower on long rows than npd_kd_loss_fwd_bwd with a
- *     workspace, with the same results to rounding.  With ce_grad_scale != 0 at tau != 1 the size limit above does not
- *     apply either.
+ *     workspace, with the same results to rounding.
  *   - The first call on a device asks the runtime for the array's address (no allocation); make it outside stream
  *     capture.
  */

@@ -255,7 +255,7 @@ __device__ __forceinline__ float skew_grad(float xs, float xt, const SkewCoef& k
 // L1: what is summed at tau = 1 beside the sums at tau -- 0 nothing (tau = 1, or no such output wanted), kL1Own with
 // exponentials of their own, kL1Square (tau = 2) from squares of the exponentials at tau.  Measured (MI355X, 4,096 x
 // 151,936, dense teacher, composite loss at tau = 2): one workgroup per row, both sweeps from memory 738 us; shared
-// rows with own exponentials 495 us, bound by the seven v_exp_f32 per pair of logits; squares, four of them, 459 us.
+// rows with own exponentials 495 us, bound by the seven v_exp_f32 per pair of logits; squares, four of them, 462 us.
 template <int K, int TEACHER, int L1, int DIVK = kForwardKl, int TH = kGangThreads, bool SOLO = false, bool GRAD = true>
 __global__ __launch_bounds__(gang_block(TH, SOLO),
                              gang_waves(DIVK == kSkewKl || DIVK == kSkewReverseKl ? 16 * K : 8 * K)) void

@@ -6,13 +6,14 @@ namespace npd {
 // Every call with whole 128-bit groups whose row fits, forward-only calls with the forward KL or without a teacher --
 // except where the row-resident kernel with 256 threads (npd_kd_cached.hpp) is a little faster: 16-byte aligned rows
 // whose gradient needs no sum at tau = 1, of more than 2,048 groups (forward KL) or 1,536 groups (reverse KL).
-// Measured (MI355X, 1e9 logits, all scored, % of 8 TB/s, the kernel that ran such a row before / this one):
-//   dense, forward KL  V = 1,024 46 / 69, 2,048 51 / 77, 4,096 38 / 74, 8,192 58 / 78, 12,288 68 / 74, 18,432 74 / 75,
-//                      24,576 75 / 72;  at tau = 2 with CE 2,048 43 / 62, 8,192 45 / 70, 16,384 51 / 71, 24,576 50 / 64
-//   reverse KL         2,048 52 / 77, 8,192 59 / 77, 12,288 70 / 75, 16,384 74 / 70
-//   skew KL            2,048 35 / 73, 8,192 39 / 77, 12,288 44 / 73, 16,384 46 / 70
-//   top-k (64), tau 2  2,048 31 / 54, 4,096 33 / 53, 8,192 44 / 63, 16,384 58 / 61, 24,576 58 / 67
-//   NLL alone          2,048 68 / 78, 4,096 40 / 82, 8,192 57 / 84
+// Measured (MI355X, 65,536 rows or what 1e9 logits give, all scored, % of 8 TB/s, the kernel that ran such a row before /
+// this one; in parentheses what was left to the other kernel for it):
+//   dense, forward KL  V = 1,024 41 / 61, 2,048 51 / 72, 4,096 41 / 77, 8,192 59 / 78, 12,288 69 / 73 (18,432 74 / 75,
+//                      24,576 75 / 72);  at tau = 2 with CE 2,048 46 / 70, 8,192 44 / 68, 16,384 49 / 71, 24,576 51 / 61
+//   reverse KL         2,048 53 / 79, 8,192 60 / 79, 12,288 69 / 75 (16,384 74 / 70)
+//   skew KL            2,048 36 / 79, 8,192 39 / 74, 12,288 43 / 75, 16,384 45 / 67
+//   top-k (64), tau 2  2,048 34 / 54, 4,096 35 / 53, 8,192 43 / 62, 16,384 56 / 62, 24,576 59 / 67
+//   NLL alone          2,048 72 / 82, 4,096 39 / 84, 8,192 59 / 87, 16,384 88 / 89
 // Short rows used to stream twice; a row that lives in registers is read once, and 5 .. 8 waves per SIMD hide its
 // reductions.
 // What stays with the kernels that ran it before, with both sides (us, that kernel / this one), unless rows are so few

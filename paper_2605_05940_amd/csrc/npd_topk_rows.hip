@@ -3,7 +3,7 @@
 //
 // Such rows were bound by the serial phases of a workgroup of 512 or 1024 threads per row (a sort of the thread maxima,
 // block-wide counting, 20 barriers) with one read or two of the row in front: 65,536 rows of 1,024 .. 8,192 logits took
-// 1.5 .. 2 ms, 1 .. 9 % of the HBM peak.  Here a row belongs to TH threads that hold K groups of eight logits each (one
+// 0.6 .. 1.6 ms for k = 64, 1 .. 23 % of the HBM peak.  Here a row belongs to TH threads that hold K groups of eight logits each (one
 // wave for up to 4,096 logits, without a single barrier; four such rows share a workgroup), and the bound that picks the
 // candidates is taken from the maxima of the groups, not of the threads: the k-th largest of them (each wave's
 // ceil(k / waves)-th, the smallest report of all waves) lets barely more than k elements through, so the list that
@@ -290,9 +290,9 @@ static hipError_t launch_rows(const TopkArgs& a, hipStream_t stream) {
                        stream, a);
 }
 
-// Measured (MI355X, 1e9 logits, all scored, us; the kernels of npd_topk_kernels.hip / this one): k = 64 V = 1,024
-// 1,597 / 98, 4,096 1,583 / 190, 8,192 598 / 276, 16,384 620 / 453, 24,576 463 / 683; k = 10 1,488 / 49, 1,487 / 102,
-// 466 / 177, 492 / 332, 360 / 544.  Longer rows are better off with the kernel that streams them: eight waves that wait
+// Measured (MI355X, 65,536 rows -- 61,035 of 16,384 logits, 40,690 of 24,576 --, all scored, us; the kernels of
+// npd_topk_kernels.hip / this one): k = 64 V = 1,024 1,594 / 91, 4,096 1,579 / 179, 8,192 586 / 274, 16,384 616 / 449,
+// 24,576 463 / 683; k = 10 1,486 / 48, 1,480 / 99, 467 / 180, 490 / 329, 360 / 544.  Longer rows are better off with the kernel that streams them: eight waves that wait
 // for one another at every step no longer hide behind other rows.
 // Few rows do not hide a row's serial steps behind others: they stay with the kernels of 512 or 1024 threads per row
 // where the list to order is long or most of the row (T = 64, V = 2,500: k = 20 11.0 / 6.4 us, 64 11.6 / 10.5, 128
