@@ -104,6 +104,9 @@ struct TopkArgs {
   int32_t V, k, nvec, log_probs;
 };
 
+// teacher top-k: so few rows that each has a compute unit to itself
+constexpr int64_t kTopkFewRows = 256;
+
 // rows that fit one workgroup's registers (npd_topk_rows.hip)
 bool topk_rows_applies(const TopkArgs& a);
 hipError_t launch_topk_rows(const TopkArgs& a, hipStream_t stream);

@@ -283,9 +283,25 @@ constexpr int kDirectRankMax = 192;  // lists up to this length are rank-sorted 
 
 // Orders the n >= k candidate words in sh.cand (all distinct: the ids differ) and writes the first k as the row's
 // record.  Called by all threads after a barrier that made the candidates visible; ends with a barrier.
-__device__ __forceinline__ void order_and_emit(TopkShared& sh, int n, int k, int log_probs, int32_t* irow,
+// Up to 1,024 candidates (k <= 512) whose keys span little enough that a candidate fits 32 bits beside its id (18 bits at
+// V = 262,144: a factor of 2^128 between equal signs) are cut and sorted by the first wave in its registers; the others
+// by all threads through LDS.
+__device__ __forceinline__ void order_and_emit(TopkShared& sh, int n, int k, int V, int log_probs, int32_t* irow,
                                                float* vrow, int tid) {
   const unsigned long long* out = nullptr;
+  if (n <= 2 * kWaveSortMax && k <= kWaveSortMax) {
+    if (tid < kWave) {
+      const CandWord c = list_word(sh.cand, n, V, tid);
+      const bool fits = c.id_bits >= 0;
+      if (fits) {
+        auto word = [&](int i) { return c.make((uint32_t)(sh.cand[i] >> 32), 0xffffffffu - (uint32_t)sh.cand[i]); };
+        wave_order_and_emit_any(word, n, k, c, reinterpret_cast<uint32_t*>(sh.shortlist), log_probs, irow, vrow, tid);
+      }
+      if (tid == 0) sh.nshort = fits;
+    }
+    __syncthreads();
+    if (sh.nshort) return;  // uniform
+  }
   if (n <= kDirectRankMax) {
     rank_sort(sh, sh.cand, n, k, tid);
     out = sh.sorted;
@@ -411,7 +427,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
     slow_select(trow, RowSplit{0, nvec}, V, k, sh, tid);
     n = k;
   }
-  order_and_emit(sh, n, k, a.log_probs, a.idx + row * (int64_t)k, a.val + row * (int64_t)k, tid);
+  order_and_emit(sh, n, k, V, a.log_probs, a.idx + row * (int64_t)k, a.val + row * (int64_t)k, tid);
 }
 
 #endif  // NPD_TOPK_ANY_SHAPE
@@ -485,8 +501,8 @@ __device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, int
 // W = register window (groups in flight per thread), S <= W = groups of the sample that gives the bound.
 // ngroups = ceil(nvec / kTB) >= 1 groups are visited in the order (g * step) mod ngroups, step coprime to ngroups.
 // RAGGED: rows begin anywhere inside a 16-byte group.
-template <int W, int S, bool RAGGED>
-__global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkArgs a, int ngroups, int step) {
+template <int W, int S, bool RAGGED, int WAVES = 8>
+__global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const TopkArgs a, int ngroups, int step) {
   __shared__ TopkShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int64_t row = blockIdx.x;
@@ -523,17 +539,16 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkA
 
   bool slow = k > kTB;  // uniform
   if (!slow) {
-    // each wave reports its m-th largest thread maximum (bisection on ballots); 16 m >= k elements of the row
-    // are >= the smallest report
+    // each wave reports its m-th largest thread maximum; NW m >= k elements of the row are >= the smallest report
     const int m = (k + kTB / kWave - 1) / (kTB / kWave);
-    int blo = -32768, bhi = 32768;  // count(best >= blo) >= m, count(best >= bhi) < m
-    while (bhi - blo > 1) {
-      const int mid = (blo + bhi) >> 1;
-      if (__popcll(__ballot(best >= mid)) >= m)
-        blo = mid;
-      else
-        bhi = mid;
+    int bhi = best, blo = best;
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+      bhi = max(bhi, __shfl_xor(bhi, off, kWave));
+      blo = min(blo, __shfl_xor(blo, off, kWave));
     }
+    const int x[1] = {best};
+    blo = wave_bound(x, m, 0, __builtin_amdgcn_readfirstlane(blo), __builtin_amdgcn_readfirstlane(bhi) + 1);
     if (lane == 0) sh.wave_bound[wid] = blo;
   }
   if (tid == 0) sh.ncand = 0;
@@ -587,7 +602,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_stream_kernel(const TopkA
     slow_select(trow, sp, V, k, sh, tid);
     n = k;
   }
-  order_and_emit(sh, n, k, a.log_probs, a.idx + row * (int64_t)k, a.val + row * (int64_t)k, tid);
+  order_and_emit(sh, n, k, V, a.log_probs, a.idx + row * (int64_t)k, a.val + row * (int64_t)k, tid);
 }
 
 static int gcd_int(int x, int y) {
@@ -604,20 +619,33 @@ static bool rows_ragged(const TopkArgs& a) {
   return (reinterpret_cast<uintptr_t>(a.t) & 15u) != 0 || a.stride % 8 != 0;
 }
 
-// one-read kernel of this configuration; every row has kTB whole groups at least
-hipError_t launch_stream(const TopkArgs& a, hipStream_t stream) {
-  constexpr int kWindow = NPD_TOPK_WINDOW, kSample = NPD_TOPK_SAMPLE;
+template <int W, int S, int WAVES>
+static hipError_t launch_window(const TopkArgs& a, hipStream_t stream) {
   const int ngroups = (a.nvec + kTB - 1) / kTB;
-  // visiting order: the first kSample groups spread over the row
-  int step = ngroups > kSample ? (ngroups + kSample - 1) / kSample : 1;
+  // visiting order: the first S groups spread over the row
+  int step = ngroups > S ? (ngroups + S - 1) / S : 1;
   while (gcd_int(step, ngroups) != 1) ++step;
   auto go = [&](auto kernel) {
     return launch_kernel(kernel, dim3((unsigned)a.T), dim3(kTB), 0, stream, a, ngroups,
                          step % ngroups == 0 ? 1 : step % ngroups);
   };
-  return rows_ragged(a) ? go(teacher_topk_stream_kernel<kWindow, kSample, true>)
-                : go(teacher_topk_stream_kernel<kWindow, kSample, false>);
+  return rows_ragged(a) ? go(teacher_topk_stream_kernel<W, S, true, WAVES>)
+                : go(teacher_topk_stream_kernel<W, S, false, WAVES>);
 }
+// one-read kernel of this configuration; every row has kTB whole groups at least
+hipError_t launch_stream(const TopkArgs& a, hipStream_t stream) {
+  return launch_window<NPD_TOPK_WINDOW, NPD_TOPK_SAMPLE, 8>(a, stream);
+}
+#if NPD_TOPK_ANY_SHAPE
+// few rows
+hipError_t launch_few(const TopkArgs& a, hipStream_t stream) {
+  const int ngroups = (a.nvec + kTB - 1) / kTB;
+  if (ngroups <= 8) return launch_window<8, 8, 4>(a, stream);
+  if (ngroups <= 12) return launch_window<12, 12, 4>(a, stream);
+  if (ngroups <= 16) return launch_window<16, 16, 4>(a, stream);
+  return launch_window<20, 20, 4>(a, stream);
+}
+#endif
 
 #if NPD_TOPK_ANY_SHAPE
 hipError_t launch_any(const TopkArgs& a, hipStream_t stream) {

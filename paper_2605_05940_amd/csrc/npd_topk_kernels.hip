@@ -4,9 +4,10 @@
 //
 // One workgroup per token row, several per CU so that one row's ordering phase overlaps the others' streaming
 // (1024 threads, two per CU; for small k 512 threads, four per CU: npd_topk_kernels_512.hip).  Both kernels derive
-// a lower bound L of the k-th largest logit from per-thread maxima, append every element >= L as a 64-bit
-// (key, ~id) word to an LDS list, cut the list down to the k-th key with a two-level radix count when it is long,
-// and order what is left by rank sort (bitonic sort for long tie lists).  Rows where more elements pass the bound
+// a lower bound L of the k-th largest logit from per-thread maxima and append every element >= L as a 64-bit
+// (key, ~id) word to an LDS list.  Up to 1,024 candidates are cut and ordered by one wave in its registers
+// (npd_topk_order.hpp); longer lists are cut at the k-th key with a two-level radix count and ordered by rank sort
+// (bitonic sort for long tie lists).  Rows where more elements pass the bound
 // than the list holds (massive ties, constant rows) and k beyond the workgroup size take an exact slow path: binary
 // search of the k-th key by counting passes over the row, then the ties of lowest id are collected in id order with
 // block-wide scans.
@@ -37,11 +38,17 @@ namespace topk512 {
 hipError_t launch_stream(const TopkArgs& a, hipStream_t stream);  // npd_topk_kernels_512.hip
 }
 
-// Small k (the paper's 5 .. 20, the benchmark's 64) runs with four 512-thread workgroups per CU: three rows stream
-// while a fourth is in its ordering phase.  Measured on config 1's teacher logits (k = 10 / 64 / 256): 1024 threads
-// 1.11 / 1.23 / 1.65 ms, 512 threads with an 8-group window 1.07 / 1.16 / 1.94 ms (with more candidates per row the
-// smaller list capacity and the narrower sample cost more than the overlap brings).
-constexpr int kSmallK = 128;
+// Which kernel streams a long row.  Many rows: four 512-thread workgroups per CU (three rows stream while a fourth is in
+// its ordering phase) as long as their bound, from a sample of eight groups per thread, lets few enough candidates pass;
+// else two of 1024 threads.  Up to 512 rows, which is what two per CU hold: 1024 threads.  Up to a row per CU: 1024 threads
+// with the whole CU's registers, up to 20 groups in flight per thread and the bound from all of them.
+// Measured (MI355X, all scored, us, 512 threads / two of 1024 / one of 1024 per CU; 151,936 logits):
+//   128 rows    k = 10 29.8 / 19.8 / 18.6, 64 33.7 / 23.0 / 20.7, 256 371 / 32.0 / 27.1
+//   512 rows    k = 10 39.4 / 33.6 / 41.6, 64 43.4 / 37.8 / 44.5
+//   2,048 rows  k = 10 105 / 111 / 149, 64 109 / 119 / 162, 128 139 / 130
+// Line between the first two (k times chunks of 512 groups): 2,048 rows of 262,144 k = 64 202 / 196, 4,096 362 / 370;
+// 8,192 rows of 50,304 k = 256 203 / 271, 65,536 278 / 291; 2,048 rows of 65,536 k = 256 93 / 81.
+constexpr int kSmallK = 256;
 
 hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, int log_probs, const uint16_t* t,
                                const uint8_t* mask, int32_t* idx, float* val, hipStream_t stream) {
@@ -60,9 +67,11 @@ hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, 
   // every thread of a workgroup of 1024 needs a whole group
   const bool aligned = (reinterpret_cast<uintptr_t>(t) & 15u) == 0 && stride % 8 == 0;
   if (a.nvec > 1024 || (aligned && a.nvec == 1024)) {
+    if (T <= kTopkFewRows) return topk1024::launch_few(a, stream);
+    if (T <= 512 && a.nvec > 6144) return topk1024::launch_stream(a, stream);
     // about twice k / 8 candidates per chunk of 512 groups pass the bound of the 512-thread kernel, whose list holds 2,048
     const int64_t chunks = (a.nvec + 511) / 512;
-    if (k <= kSmallK && k * chunks <= 8 * 700) return topk512::launch_stream(a, stream);
+    if (k <= kSmallK && k * chunks <= 8 * (T < 3072 ? 425 : 700)) return topk512::launch_stream(a, stream);
     return topk1024::launch_stream(a, stream);
   }
   if (!aligned) a.nvec = 0;  // element by element: rows this short fit the caches, and few wait for bytes

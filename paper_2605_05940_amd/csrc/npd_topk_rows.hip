@@ -1,15 +1,16 @@
-// Teacher-side top-k record of rows that fit one workgroup's registers (up to 16,384 logits, k <= 256), at any offset
+// Teacher-side top-k record of rows that fit one workgroup's registers (up to 65,536 logits, k <= 256), at any offset
 // from a 16-byte boundary.  Same exact selection and the same record as npd_topk_kernels.hip.
 //
-// Such rows were bound by the serial phases of a workgroup of 512 or 1024 threads per row (a sort of the thread maxima,
-// block-wide counting, 20 barriers) with one read or two of the row in front: 65,536 rows of 1,024 .. 8,192 logits took
-// 0.6 .. 1.6 ms for k = 64, 1 .. 23 % of the HBM peak.  Here a row belongs to TH threads that hold K groups of eight logits each (one
-// wave for up to 4,096 logits, without a single barrier; four such rows share a workgroup), and the bound that picks the
-// candidates is taken from the maxima of the groups, not of the threads: the k-th largest of them (each wave's
-// ceil(k / waves)-th, the smallest report of all waves) lets barely more than k elements through, so the list that
-// has to be ordered is short -- rank sort, all pairs, 32-bit words.  Where k is most of the groups or more, and
-// where more elements pass than the list holds (massive ties), the k-th key itself is found by bisection over the
-// registers and the ties are taken in id order.
+// A row belongs to TH threads that hold K groups of eight logits each (one wave for up to 4,096 logits, without a single
+// barrier; four such rows share a workgroup).  The bound that picks the candidates is taken from maxima of the row's
+// parts, as fine as k asks for, so that barely more than k elements pass; the groups that hold one are staged and looked
+// at 64 at a time, one to a lane; one wave then orders the list in its registers.  What bounds such rows is the vector
+// instructions of these serial steps, not the bytes.  Measured (MI355X, all scored, us; candidates appended one by one through
+// an atomic counter and ranked by comparing all pairs / this; k = 10, 64, 256):
+//   32,768 rows of 1,024   25.3 / 22.9, 47.2 / 36.2, 177 / 85      8,192 rows of 8,192  27.4 / 22.9, 42.3 / 30.2, 106 / 52
+//   32,768 rows of 16,384  175 / 163 (6.6 TB/s), 246 / 164, 524 / 283
+// Where k is most of the row's pairs, and where more elements pass than the list holds (massive ties), the k-th key
+// itself is found by bisection over the registers and the ties are taken in id order.
 #include "npd_kd_gang.hpp"
 #include "npd_topk_order.hpp"
 
@@ -18,18 +19,22 @@ namespace npd {
 namespace {
 
 constexpr int kRowsTopkMax = 256;   // largest k
-constexpr int kRowsCand = 512;      // candidates a row's list holds
+// candidates a row's list holds: with more waves each wave's bound is a smaller sample's (300 rows of 50,304 normal
+// logits, k = 256, 16 waves: 481 candidates on average, 717 at most; 4 waves, 16,384 logits: 328 and 433)
+constexpr int rows_cand(int th) { return th >= 256 ? 2 * kWaveSortMax : kWaveSortMax; }
 
-// candidate word: larger = better (16-bit key, then the smaller id); ids are below 65,536 here
-__device__ __forceinline__ uint32_t row_word(int o, int id) { return (key_of_ordered(o) << 16) | (0xffffu - (uint32_t)id); }
+constexpr int kRowsStage = 2 * kWave;  // groups with a candidate that a wave stages before it looks at their elements
+constexpr int kRowsMaxVocab = 1 << 16;
+constexpr CandWord kRowsWord{0u, 16};  // ids below 65,536: a candidate is one 32-bit word whatever the keys
+__device__ __forceinline__ uint32_t rows_word(int o, int id) { return kRowsWord.make(key_of_ordered(o), (uint32_t)id); }
 
 template <int TH>
 struct RowTopkShared {
-  __attribute__((aligned(16))) uint32_t cand[kRowsCand];
-  uint32_t sorted[kRowsTopkMax];
+  uint4 group[TH / kWave][kRowsStage];
+  uint32_t cand[rows_cand(TH)];
+  int group_id[TH / kWave][kRowsStage];
   int ncand;
   int red[TH / kWave];
-  float fred[TH / kWave];
 };
 
 template <int TH>
@@ -76,9 +81,9 @@ __device__ __forceinline__ int rows_scan(int v, int* red, int tid, int& total) {
 }  // namespace
 
 template <int TH, int K>
-__global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void teacher_topk_row_kernel(const TopkArgs a) {
+__global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, TH == 1024 ? 4 : K <= 4 && TH < 512 ? 8 : 5) void teacher_topk_row_kernel(const TopkArgs a) {
   constexpr int ROWS = TH == kWave ? 4 : 1;
-  constexpr int NW = TH / kWave;
+  constexpr int NW = TH / kWave, kRowsCand = rows_cand(TH);
   __shared__ RowTopkShared<TH> shs[ROWS];
   const int tid = threadIdx.x % (unsigned)TH, lane = tid & (kWave - 1), wid = tid / kWave;
   const int sub = ROWS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TH);
@@ -108,12 +113,17 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
   for (int i = 0; i < K; ++i) g[i] = ld_group<TH * 16>(rt, tid * 16, i, true, true);
   int edge = -32768;  // this thread's edge element
   if (tid < n_edge) edge = ordered_of(trow[sp.edge_elem(tid)]);
-  int gmax[K];
+  auto group_max = [&](int i) -> int {
+    const short2v m = pk_max(pk_max(as_s2(g[i].x), as_s2(g[i].y)), pk_max(as_s2(g[i].z), as_s2(g[i].w)));
+    return i < n_mine ? max((int)m.x, (int)m.y) : -32768;  // below every element
+  };
+  int lmax = -32768, lmin = 32767;  // largest and smallest maximum of this thread's groups
 #pragma unroll
   for (int i = 0; i < K; ++i) {
     g[i] = make_uint4(pk_ordered(g[i].x), pk_ordered(g[i].y), pk_ordered(g[i].z), pk_ordered(g[i].w));
-    const short2v m = pk_max(pk_max(as_s2(g[i].x), as_s2(g[i].y)), pk_max(as_s2(g[i].z), as_s2(g[i].w)));
-    gmax[i] = i < n_mine ? max((int)m.x, (int)m.y) : -32768;  // below every element
+    const int x = group_max(i);
+    lmax = max(lmax, x);
+    if (i < n_mine) lmin = min(lmin, x);
   }
   auto element = [&](int i, int j) -> int {  // i, j compile-time after unrolling
     const uint32_t d = (j >> 1) == 0 ? g[i].x : (j >> 1) == 1 ? g[i].y : (j >> 1) == 2 ? g[i].z : g[i].w;
@@ -122,22 +132,20 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
   auto id_of = [&](int i, int j) { return head + (i * TH + tid) * 8 + j; };
   auto append = [&](int o, int id) {
     const int pos = atomicAdd(&sh.ncand, 1);
-    if (pos < kRowsCand) sh.cand[pos] = row_word(o, id);
+    if (pos < kRowsCand) sh.cand[pos] = rows_word(o, id);
   };
 
-  // ---- the bound: each wave's m-th largest group maximum; NW m >= k elements of the row are >= the smallest report.
-  // Every wave owns at least (nvec / TH) * 64 whole groups.
+  // ---- the bound: each wave's m-th largest of some maxima of its elements; NW m >= k elements of the row are >= the
+  // smallest report.  Maxima of finer parts give a bound that fewer elements pass and take longer to bisect: one per thread
+  // where m is at most a quarter of them (1.15 k elements pass), one per group up to half (1.4 k), one per pair of elements
+  // up to three quarters (1.2 .. 1.4 k); every wave owns at least `units` whole groups.
   const int m = (k + NW - 1) / NW;
-  // Beyond three quarters of a wave's maxima the bound lets more than 1.7 k elements through.
-  bool exact = m > nvec / TH * kWave / 4 * 3;  // uniform
+  const int units = NW == 1 ? nvec : nvec / TH * kWave;
+  const bool per_thread = 4 * m <= kWave && units >= kWave, per_group = 2 * m <= units;  // uniform
+  constexpr bool kFine = K <= 8;  // (registers)
+  bool exact = kFine ? m > 3 * units : !per_thread;  // uniform
   if (!exact) {
-    int lmax = gmax[0], lmin = gmax[0];
-#pragma unroll
-    for (int i = 1; i < K; ++i) {
-      lmax = max(lmax, gmax[i]);
-      lmin = min(lmin, gmax[i]);
-    }
-    int bhi = lmax, blo = m <= kWave ? lmax : lmin;  // count(maxima >= blo) >= m: a maximum per lane, or all of them
+    int bhi = lmax, blo = per_thread ? lmax : lmin;
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) {
       bhi = max(bhi, __shfl_xor(bhi, off, kWave));
@@ -145,19 +153,27 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
     }
     bhi = __builtin_amdgcn_readfirstlane(bhi) + 1;  // count(maxima >= bhi) = 0
     blo = __builtin_amdgcn_readfirstlane(blo);
-    while (bhi - blo > 1) {
-      const int mid = (blo + bhi) >> 1;
-      int n = 0;
+    int bound;
+    if (per_thread || !kFine) {
+      const int x[1] = {lmax};
+      bound = wave_bound(x, m, m / 8, blo, bhi);
+    } else if (per_group) {
+      int gmax[K];
 #pragma unroll
-      for (int i = 0; i < K; ++i) n += __popcll(__ballot(gmax[i] >= mid));
-      if (n >= m)
-        blo = mid;
-      else
-        bhi = mid;
+      for (int i = 0; i < K; ++i) gmax[i] = group_max(i);
+      bound = wave_bound(gmax, m, m / 8, blo, bhi);
+    } else {
+      int pmax[4 * K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) pmax[4 * i + j] = i < n_mine ? max(element(i, 2 * j), element(i, 2 * j + 1)) : -32768;
+      }
+      bound = wave_bound(pmax, m, m / 8, -32768, bhi);
     }
-    int L = blo;
+    int L = bound;
     if constexpr (NW > 1) {
-      if (lane == 0) sh.red[wid] = blo;
+      if (lane == 0) sh.red[wid] = bound;
       __syncthreads();  // also orders ncand = 0 before the first append
 #pragma unroll
       for (int w = 0; w < NW; ++w) L = min(L, sh.red[w]);
@@ -165,15 +181,61 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
       rows_sync<TH>();
     }
     const int Lp = L == 0 ? -1 : L;  // +0 and -0 are one value
+    // ---- the groups with an element >= Lp are staged whole, up to 64 of them are then looked at together, one to a lane
+    uint4* sgroup = sh.group[wid];
+    int* sid = sh.group_id[wid];
+    int staged = 0, listed = 0;  // uniform; `listed`: candidates of this wave (one wave per row: of the row)
+    auto look = [&](int count) {  // at the last `count` <= 64 staged groups
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+      const int at = staged - count + lane;
+      uint4 v = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
+      int id0 = 0;
+      if (lane < count) {
+        v = sgroup[at];
+        id0 = head + sid[at] * 8;
+      }
+      auto elem = [&](int j) -> int {
+        const uint32_t d = (j >> 1) == 0 ? v.x : (j >> 1) == 1 ? v.y : (j >> 1) == 2 ? v.z : v.w;
+        return (j & 1) ? (int)d >> 16 : (int)(short)(uint16_t)d;
+      };
+      int mine = 0;
 #pragma unroll
-    for (int i = 0; i < K; ++i) {
-      if (gmax[i] >= Lp && i < n_mine) {
+      for (int j = 0; j < 8; ++j) mine += lane < count && elem(j) >= Lp;
+      const int incl = wave_scan(mine);
+      const int total = __builtin_amdgcn_readlane(incl, 63);
+      int base = listed;
+      if constexpr (NW > 1) {
+        if (lane == 0) base = atomicAdd(&sh.ncand, total);
+        base = __builtin_amdgcn_readfirstlane(base);
+      }
+      listed += total;
+      int pos = base + incl - mine;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int o = element(i, j);
-          if (o >= Lp) append(o, id_of(i, j));
+      for (int j = 0; j < 8; ++j) {
+        if (lane < count && elem(j) >= Lp) {
+          if (pos < kRowsCand) sh.cand[pos] = rows_word(elem(j), id0 + j);
+          ++pos;
         }
       }
+      staged -= count;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    };
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const bool pass = group_max(i) >= Lp && i < n_mine;
+      const unsigned long long who = __ballot(pass);
+      if (pass) {
+        const int at = staged + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+        sgroup[at] = g[i];
+        sid[at] = i * TH + tid;
+      }
+      staged += __popcll(who);  // (fewer than 64 before)
+      if (staged >= kWave) look(kWave);
+    }
+    if (staged > 0) look(staged);
+    if constexpr (NW == 1) {
+      if (lane == 0) sh.ncand = listed;
+      rows_sync<TH>();
     }
     if (tid < n_edge && edge >= Lp) append(edge, sp.edge_elem(tid));
     rows_sync<TH>();
@@ -233,7 +295,7 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
       taken += total;
     };
     const bool edge_tie = tid < n_edge && canonical(edge) == Tk;
-    auto put_edge = [&](int rank) { sh.cand[above + rank] = row_word(edge, sp.edge_elem(tid)); };
+    auto put_edge = [&](int rank) { sh.cand[above + rank] = rows_word(edge, sp.edge_elem(tid)); };
     take(edge_tie && tid < head, put_edge);
 #pragma unroll
     for (int i = 0; i < K; ++i) {
@@ -244,7 +306,7 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
 #pragma unroll
         for (int j = 0; j < 8; ++j)
           if (canonical(element(i, j)) == Tk) {
-            if (rank < need) sh.cand[above + rank] = row_word(Tk, id_of(i, j));
+            if (rank < need) sh.cand[above + rank] = rows_word(Tk, id_of(i, j));
             ++rank;
           }
       });
@@ -254,32 +316,10 @@ __global__ __launch_bounds__(TH == kWave ? 4 * TH : TH, K <= 4 ? 8 : 5) void tea
     n = k;
   }
 
-  // ---- rank sort: the rank of a word is the number of larger words (all distinct)
-  const int n4 = (n + 3) / 4;
-  if (tid < n4 * 4 - n) sh.cand[n + tid] = 0;  // below every candidate (n <= kRowsCand, a multiple of 4)
-  rows_sync<TH>();
-  for (int i = tid; i < n; i += TH) {
-    const uint32_t w = sh.cand[i];
-    int r = 0;
-    for (int j = 0; j < n4; ++j) {
-      const uint4 x = reinterpret_cast<const uint4*>(sh.cand)[j];
-      r += (x.x > w) + (x.y > w) + (x.z > w) + (x.w > w);
-    }
-    if (r < k) sh.sorted[r] = w;
-  }
-  rows_sync<TH>();
-  float lse = 0.0f;
-  if (a.log_probs) {  // log-softmax over the k selected logits; the first one is the largest
-    const float v0 = value_of_key(sh.sorted[0] >> 16);
-    float part = 0.0f;
-    for (int j = tid; j < k; j += TH) part += __expf(value_of_key(sh.sorted[j] >> 16) - v0);
-    part = TH == kWave ? wave_sum(part) : block_sum<TH>(part, sh.fred);
-    lse = v0 + __logf(part);
-  }
-  for (int j = tid; j < k; j += TH) {
-    const uint32_t w = sh.sorted[j];
-    irow[j] = (int32_t)(0xffffu - (w & 0xffffu));
-    vrow[j] = value_of_key(w >> 16) - lse;
+  // ---- one wave orders the list in its registers
+  if (wid == 0) {
+    uint32_t* cand = sh.cand;
+    wave_order_and_emit_any([&](int i) { return cand[i]; }, n, k, kRowsWord, cand, a.log_probs, irow, vrow, lane);
   }
 }
 
@@ -290,22 +330,25 @@ static hipError_t launch_rows(const TopkArgs& a, hipStream_t stream) {
                        stream, a);
 }
 
-// Measured (MI355X, 65,536 rows -- 61,035 of 16,384 logits, 40,690 of 24,576 --, all scored, us; the kernels of
-// npd_topk_kernels.hip / this one): k = 64 V = 1,024 1,594 / 91, 4,096 1,579 / 179, 8,192 586 / 274, 16,384 616 / 449,
-// 24,576 463 / 683; k = 10 1,486 / 48, 1,480 / 99, 467 / 180, 490 / 329, 360 / 544.  Longer rows are better off with the kernel that streams them: eight waves that wait
-// for one another at every step no longer hide behind other rows.
-// Few rows do not hide a row's serial steps behind others: they stay with the kernels of 512 or 1024 threads per row
-// where the list to order is long or most of the row (T = 64, V = 2,500: k = 20 11.0 / 6.4 us, 64 11.6 / 10.5, 128
-// 12.9 / 16.2).
+// Which rows.  Longer rows are better off with the kernels that stream them unless there are so few that each has a compute
+// unit (1,024 threads) or half of one (512 threads) to itself and waits for its own latency.  Measured (MI355X, all
+// scored, us, streamed / this): 256 rows of 50,304 k = 10 13.4 / 9.1, 64 16.9 / 10.2, 256 21.4 / 14.0; 65,536 k = 64 19.0 /
+// 10.6; 1,024 rows of 32,000 k = 10 16.3 / 15.4, k = 128 20.2 / 19.1; 2,048 26.8 / 27.9, 32.2 / 34.3; 512 rows of 65,536
+// k = 10 19.2 / 18.9.
 constexpr int kManyRows = 1024;
 bool topk_rows_applies(const TopkArgs& a) {
-  if (a.k > kRowsTopkMax || a.V / 8 > 256 * 8) return false;
-  return a.T >= kManyRows || (a.k <= 64 && 16 * a.k <= a.V);
+  const int nvec = a.V / 8;
+  if (a.k > kRowsTopkMax || a.V > kRowsMaxVocab) return false;
+  if (nvec <= 256 * 8) return true;
+  if (nvec <= 512 * 8) return a.T <= kManyRows;
+  return a.T <= kTopkFewRows;
 }
 
 hipError_t launch_topk_rows(const TopkArgs& a, hipStream_t stream) {
   const int nvec = a.V / 8;
   if (nvec <= 64 * 2) return launch_rows<64, 2>(a, stream);
+  if (nvec > 512 * 8) return launch_rows<1024, 8>(a, stream);
+  if (nvec > 256 * 8 || (nvec > 256 * 4 && a.k > 64 && a.T <= kManyRows / 2)) return launch_rows<512, 8>(a, stream);
   if (a.T < kManyRows) {  // more threads per row
     if (nvec <= 128 * 2) return launch_rows<128, 2>(a, stream);
     if (nvec <= 256 * 2) return launch_rows<256, 2>(a, stream);

@@ -339,3 +339,30 @@ def test_topk_teacher_by_rows_and_record(oracle, V, k, T):
         compare_kd(_call(lay, s, None, lab, ce=ce, **kw), ref, mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce, tau=tau)
         compare_kd(_call(lay, s, None, lab, grad=False, **kw), {n: ref[n] for n in ("kd", "nll_s", "lse_s")}, mask,
                    lay.cu_seqlens, oracle)
+
+
+# one row to a compute unit, half of one, two streams per compute unit, four; bounds from threads, groups and pairs of
+# elements; lists that one wave sorts as they are (64, 128, 256, 512 words), cuts first, or leaves to the workgroup
+@pytest.mark.parametrize("V,T,k", [
+    (1000, 40, 256), (1100, 40, 128), (1100, 2000, 64), (520, 40, 256), (16391, 40, 256), (16400, 1024, 100),
+    (16400, 1025, 100), (32775, 40, 200), (32776, 257, 64), (65536, 256, 256), (65543, 12, 20), (65544, 256, 200),
+    (65544, 300, 200), (65544, 513, 48), (65544, 513, 49), (50304, 600, 256), (131080, 280, 500), (131080, 12, 513),
+    (163840, 12, 190), (163848, 12, 192), (262144, 12, 256),
+])
+def test_teacher_topk_by_rows_and_length(oracle, V, T, k):
+    _check_teacher_topk(oracle, V, V, 0, k, T)
+
+
+@pytest.mark.parametrize("T", [8, 300, 520])
+def test_teacher_topk_keys_of_both_signs(oracle, T):
+    """Candidates that span so many keys that one does not fit 32 bits beside its id: fewer positive logits than k."""
+    V, k = 140000, 64
+    g = torch.Generator(device=dev()).manual_seed(T)
+    x = -1.0 - torch.rand((T, V), generator=g, device=dev())
+    x[:, ::4000] = 300.0 + torch.randn((T, 35), generator=g, device=dev())
+    t = x.to(torch.bfloat16)
+    idx, val = torch.empty((T, k), dtype=torch.int32, device=dev()), torch.empty((T, k), device=dev())
+    binding.npd_teacher_topk(t, k, topk_idx=idx, topk_val=val, log_probs=False)
+    ref = oracle.teacher_topk(synth.bf16_bits(t), k, None, False)
+    np.testing.assert_array_equal(idx.cpu().numpy(), ref["idx"])
+    np.testing.assert_array_equal(val.cpu().numpy().astype(np.float64), ref["val"])
