@@ -210,6 +210,21 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
                                size_t workspace_bytes, void* stream);
 
 /*
+ * Forward-only calls (desc->flags with NPD_FLAG_FWD_ONLY) with scratch memory: arguments, results and errors are those of
+ * npd_kd_loss_fwd_bwd without grad_out; rows that are too few to fill the GPU are split over several workgroups.
+ * npd_forward_scratch_bytes() says how many bytes that takes: 0 where splitting gains nothing, or for an invalid desc.
+ *
+ *   scratch   device, >= npd_forward_scratch_bytes(desc) bytes, 16-byte aligned, contents meaningless before and after; two
+ *             calls that may run at the same time need one each.  Optional: where it is NULL, too small, unaligned or
+ *             overlaps another argument the call runs as npd_kd_loss_fwd_bwd does, with the same results to rounding
+ */
+size_t npd_forward_scratch_bytes(const npd_kd_desc* desc);
+npd_status npd_kd_loss_forward(const npd_kd_desc* desc, const void* student_logits, const void* teacher_dense,
+                               const int32_t* teacher_idx, const float* teacher_val, const int32_t* labels,
+                               const uint8_t* loss_mask, float* kd_tok, float* nll_tok, float* teacher_nll_tok,
+                               float* lse_tok, int32_t* dev_status, void* scratch, size_t scratch_bytes, void* stream);
+
+/*
  * The same call for callers that cannot allocate or hold a workspace: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Arguments, results and errors are those of npd_kd_loss_fwd_bwd without
  * `workspace` / `workspace_bytes`; the scratch record comes from a fixed array of NPD_NOALLOC_WORKSPACE_BYTES bytes

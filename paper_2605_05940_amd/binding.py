@@ -25,7 +25,8 @@ NOALLOC_WORKSPACE_BYTES = 16 << 20   # NPD_NOALLOC_WORKSPACE_BYTES
 
 EXPORTS = ("npd_version", "npd_status_string", "npd_workspace_bytes", "npd_kd_loss_fwd_bwd",
            "npd_segment_reduce", "npd_delta_ifd_score", "npd_teacher_topk", "npd_debug_gang_spin_limit",
-           "npd_kd_loss_fwd_bwd_noalloc", "npd_policy_lag", "npd_segment_ppl", "npd_kd_kernel_name")
+           "npd_kd_loss_fwd_bwd_noalloc", "npd_policy_lag", "npd_segment_ppl", "npd_kd_kernel_name",
+           "npd_forward_scratch_bytes", "npd_kd_loss_forward")
 
 
 class NpdError(RuntimeError):
@@ -68,6 +69,10 @@ def load() -> ctypes.CDLL:
         L.npd_kd_loss_fwd_bwd.argtypes = [ctypes.POINTER(KdDesc)] + [_vp] * 13 + [ctypes.c_size_t, _vp]
         L.npd_kd_loss_fwd_bwd_noalloc.restype = ctypes.c_int
         L.npd_kd_loss_fwd_bwd_noalloc.argtypes = [ctypes.POINTER(KdDesc)] + [_vp] * 13
+        L.npd_forward_scratch_bytes.restype = ctypes.c_size_t
+        L.npd_forward_scratch_bytes.argtypes = [ctypes.POINTER(KdDesc)]
+        L.npd_kd_loss_forward.restype = ctypes.c_int
+        L.npd_kd_loss_forward.argtypes = [ctypes.POINTER(KdDesc)] + [_vp] * 12 + [ctypes.c_size_t, _vp]
         L.npd_segment_reduce.restype = ctypes.c_int
         L.npd_segment_reduce.argtypes = [ctypes.c_int64, ctypes.c_int32] + [_vp] * 9
         L.npd_delta_ifd_score.restype = ctypes.c_int
@@ -179,8 +184,12 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     desc = ctypes.byref(KdDesc(T, V, kind, student_stride, teacher_stride, topk, flags, tau, grad_scale, ce_grad_scale,
                                divergence, skew_alpha))
     L = load()
-    # (forward-only calls need no workspace)
-    if workspace is None and grad_out is not None and not no_workspace and not noalloc:
+    scratch = None
+    if workspace is None and not no_workspace and not noalloc and grad_out is None:
+        need = L.npd_forward_scratch_bytes(desc)
+        if need:  # rows to be split over several workgroups: a block of this call's own, as below
+            scratch = torch.empty(need, dtype=torch.uint8, device="cuda")
+    elif workspace is None and not no_workspace and not noalloc:
         need = L.npd_workspace_bytes(desc)
         if need and (ce_grad_scale != 0.0 and tau != 1.0 or (student_logits.data_ptr() | 2 * student_stride) & 15):
             # a CE term at tau != 1 and rows that are not 16-byte aligned: these calls can run without any scratch and
@@ -199,6 +208,9 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
         if workspace is not None:
             raise ValueError("the no-allocation entry point takes no workspace")
         _check(L.npd_kd_loss_fwd_bwd_noalloc(*args, _stream()))
+        return
+    if scratch is not None:
+        _check(L.npd_kd_loss_forward(*args[:7], *args[8:], scratch.data_ptr(), scratch.numel(), _stream()))
         return
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(L.npd_kd_loss_fwd_bwd(*args, _ptr(workspace), ws_bytes, _stream()))

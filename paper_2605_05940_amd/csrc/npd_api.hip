@@ -127,6 +127,12 @@ size_t workspace_bytes_of(const npd_kd_desc& d) {
   return npd::gang_workspace_bytes(d.n_tokens, d.vocab, npd::kDense, d.divergence, d.tau != 1.0f);
 }
 
+// bytes with which a forward-only call with a valid descriptor splits its rows
+size_t forward_scratch_bytes_of(const npd_kd_desc& d) {
+  if (!(d.flags & NPD_FLAG_FWD_ONLY) || (d.flags & NPD_FLAG_NO_WORKSPACE) || !same_pitch_offset(d)) return 0;
+  return npd::split_scratch_bytes(d.n_tokens, d.vocab, d.teacher_kind, d.divergence, d.tau != 1.0f);
+}
+
 // Every input and output buffer of a KD call as a byte range (empty for arguments that are absent).
 struct KdBuffers {
   Range in[6];   // student logits, dense teacher, top-k ids, top-k values, labels, loss mask
@@ -321,6 +327,31 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
   }
   const bool want_grad = !(desc->flags & NPD_FLAG_FWD_ONLY);
   const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
+}
+
+size_t npd_forward_scratch_bytes(const npd_kd_desc* desc) {
+  if (check_desc(desc) != NPD_OK) return 0;
+  return forward_scratch_bytes_of(*desc);
+}
+
+npd_status npd_kd_loss_forward(const npd_kd_desc* desc, const void* student_logits, const void* teacher_dense,
+                               const int32_t* teacher_idx, const float* teacher_val, const int32_t* labels,
+                               const uint8_t* loss_mask, float* kd_tok, float* nll_tok, float* teacher_nll_tok,
+                               float* lse_tok, int32_t* dev_status, void* scratch, size_t scratch_bytes, void* stream) {
+  npd::KdArgs a{};
+  size_t need = 0;
+  const npd_status st = check_kd_call(desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
+                                      nullptr, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
+  if (st != NPD_OK) return st;  // (also a descriptor that is not forward only: its gradient is missing)
+  need = a.nvec_s > 0 ? forward_scratch_bytes_of(*desc) : 0;
+  bool split = need > 0 && scratch && scratch_bytes >= need && !misaligned(scratch, 16);
+  if (split)
+    split = !kd_buffers(*desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask, nullptr, kd_tok,
+                        nll_tok, teacher_nll_tok, lse_tok, dev_status).overlaps_any(range_of(scratch, need));
+  if (split) a.ws = static_cast<uint32_t*>(scratch);
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const hipError_t e = split ? npd::launch_kd_split(a, desc->teacher_kind, s) : npd::launch_kd(a, desc->teacher_kind, false, s);
   return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
 }
 

@@ -36,8 +36,8 @@ struct KdArgs {
   int32_t need_lse1;   // tau != 1 and a tau = 1 quantity (nll, teacher nll, lse) is wanted
   int32_t divergence;  // Divergence
   float alpha;         // skew coefficient
-  // row-gang kernels (npd_kd_gang.hpp)
-  uint32_t* ws;          // scratch record, gang_workspace_bytes() bytes
+  // row-gang kernels (npd_kd_gang.hpp), split rows (npd_kd_split.hip)
+  uint32_t* ws;          // scratch record, gang_workspace_bytes() or split_scratch_bytes() bytes
   int32_t gang;          // slices (workgroups) per row
   int32_t gang_groups;   // 128-bit groups per slice
   int32_t spin_limit;    // polls before a waiting workgroup gives up
@@ -80,6 +80,10 @@ hipError_t launch_solo_forward(const KdArgs& a, hipStream_t stream);
 hipError_t launch_solo_reverse(const KdArgs& a, hipStream_t stream);
 hipError_t launch_solo_skew(const KdArgs& a, hipStream_t stream);
 hipError_t launch_solo_forward_only(const KdArgs& a, hipStream_t stream);
+
+// forward-only calls whose rows are split over several workgroups (npd_kd_split.hip); 0 bytes: not split
+size_t split_scratch_bytes(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1);
+hipError_t launch_kd_split(const KdArgs& a, int teacher_kind, hipStream_t stream);
 
 // compute units of the current device (cached per device)
 int compute_units();

@@ -1,0 +1,277 @@
+// Forward-only calls whose rows are split over several workgroups: a workgroup of 256 threads sums one slice of a row and
+// leaves its partial log-sum-exps in a scratch record; a second kernel, a wave to a row, merges a row's partials and writes
+// its scalars.
+//
+// Why: with a workgroup per row a row takes as long as one compute unit needs for it, which is its vector instructions
+// (17 us for the 151,936 pairs of logits of a dense teacher) behind the latency of its first loads; rows that are
+// fewer than the compute units leave the others idle, and the last rows of many leave most of them idle.  A slice is read,
+// summed once and gone; nothing waits for another workgroup.  The second launch costs about 2.5 us.
+#include "npd_kd_gang.hpp"
+
+namespace npd {
+
+namespace {
+
+constexpr int kSplitThreads = 256;
+constexpr int kSplitMax = kWave;  // slices per row at most: a lane each in the second kernel
+
+// partial log-sum-exps: 0 student / tau, 1 teacher / tau with the cross term, 2 student and 3 teacher at tau = 1 (LSE1); no
+// teacher: the student's at tau = 1 alone
+constexpr int split_sums(bool dense, bool lse1) { return dense ? (lse1 ? 4 : 2) : 1; }
+constexpr int split_words(bool dense, bool lse1) { return split_sums(dense, lse1) * 3; }
+
+}  // namespace
+
+// K: groups per thread and tensor; a slice is a.gang_groups <= K * 256 groups long.
+template <int K, bool DENSE, bool LSE1>
+__global__ __launch_bounds__(kSplitThreads, 4) void kd_split_kernel(const KdArgs a) {
+  constexpr int TH = kSplitThreads, GB = TH * 16, NS = split_sums(DENSE, LSE1), W = split_words(DENSE, LSE1);
+  constexpr int NWV = TH / kWave;
+  __shared__ float red[NS * 3 * NWV];
+  const int G = a.gang;
+  const int64_t row = blockIdx.x / (unsigned)G;
+  const int slice = (int)(blockIdx.x - (unsigned)(row * G));
+  if (!a.mask[row]) return;  // (the second kernel writes its zeros)
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+  const int V = a.V;
+  const uint16_t* srow = a.s + row * a.s_stride;
+  const uint16_t* trow = DENSE ? a.t + row * a.t_stride : nullptr;
+  const RowSplit sp = row_split(srow, V, true);
+  const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;
+  const int b0 = slice * a.gang_groups, b1 = b0 + a.gang_groups;
+  const int g0 = b0 < nvec ? b0 : nvec, g1 = slice == G - 1 ? nvec : (b1 < nvec ? b1 : nvec);
+  const int ng = g1 - g0;
+  const float c = DENSE ? a.c : kLog2e;
+  const bool lse1_t = LSE1 && a.tnll != nullptr;
+
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
+  const __amdgpu_buffer_rsrc_t rt = row_rsrc((DENSE ? trow : srow) + head + (size_t)g0 * 8, ng);
+  const int voff = tid * 16;
+  const int n_mine = (ng - tid + TH - 1) / TH;  // groups of this thread
+  uint4 sreg[K], treg[DENSE ? K : 1];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    sreg[k] = ld_group<GB>(rs, voff, k, true, true);
+    if constexpr (DENSE) treg[k] = ld_group<GB>(rt, voff, k, true, true);
+  }
+  Lse acc[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) acc[i].init();
+  __builtin_amdgcn_sched_barrier(0);
+
+  // As in kd_gang_kernel: every thread's references are the largest of its logits, no element is inspected again, and a wave
+  // whose sums show something else (a logit of -inf in the cross term) sums its registers once more in the careful form.
+  if (ng > tid) {
+    const float fs = thread_max(sreg, n_mine);
+    acc[0].r = __builtin_rintf(__builtin_fmaxf(fs * c, -1.0e30f));
+    if constexpr (LSE1) acc[2].r = __builtin_rintf(__builtin_fmaxf(fs * kLog2e, -1.0e30f));
+    if constexpr (DENSE) {
+      const float ft = thread_max(treg, n_mine);
+      acc[1].r = __builtin_rintf(__builtin_fmaxf(ft * c, -1.0e30f));
+      if constexpr (LSE1) acc[3].r = __builtin_rintf(__builtin_fmaxf(ft * kLog2e, -1.0e30f));
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (k < n_mine) {
+      float xs[8], xt[8];
+      unpack8(sreg[k], xs);
+      if constexpr (DENSE) unpack8(treg[k], xt);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        acc[0].z += exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
+        if constexpr (DENSE) {
+          const float et = exp2_fast(__builtin_fmaf(xt[j], c, -acc[1].r));
+          acc[1].z += et;
+          acc[1].a = __builtin_fmaf(et, xt[j] - xs[j], acc[1].a);
+        }
+        if constexpr (LSE1) {
+          acc[2].z += exp2_fast(__builtin_fmaf(xs[j], kLog2e, -acc[2].r));
+          if (lse1_t) acc[3].z += exp2_fast(__builtin_fmaf(xt[j], kLog2e, -acc[3].r));
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  {
+    constexpr float kBig = 1.2676506e30f;  // 2^100
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) odd = odd || !(acc[i].z < kBig) || !(fabsf(acc[i].a) < kBig);
+    if (__builtin_amdgcn_ballot_w64(odd) != 0) {  // wave-uniform
+#pragma unroll
+      for (int i = 0; i < NS; ++i) acc[i].init();
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        if (k < n_mine) {
+          if constexpr (DENSE) {
+            accum8<kDense, LSE1, false>(sreg[k], treg[k], c, lse1_t, acc);
+          } else {
+            float xs[8];
+            unpack8(sreg[k], xs);
+            acc[0].add8(xs, c);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  if (slice == G - 1 && tid < n_edge) {
+    const int e = sp.edge_elem(tid);
+    const float xs = bf16_one(srow[e]);
+    acc[0].add1(xs, c);
+    if constexpr (LSE1) acc[2].add1(xs, kLog2e);
+    if constexpr (DENSE) {
+      const float xt = bf16_one(trow[e]);
+      acc[1].add1_cross(xt, xt - xs, c);
+      if constexpr (LSE1)
+        if (lse1_t) acc[3].add1(xt, kLog2e);
+    }
+  }
+
+  // ---- wave totals, workgroup totals, left in the record
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    normalise(acc[i]);
+    wave_merge_rescaled<true>(acc[i]);
+    if (lane == 0) {
+      red[(i * 3 + 0) * NWV + wid] = acc[i].r;
+      red[(i * 3 + 1) * NWV + wid] = acc[i].z;
+      red[(i * 3 + 2) * NWV + wid] = acc[i].a;
+    }
+  }
+  __syncthreads();
+  if (wid > 0) return;
+  float* rec = reinterpret_cast<float*>(a.ws) + (size_t)blockIdx.x * W;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    acc[i].init();
+    if (lane < NWV) {
+      acc[i].r = red[(i * 3 + 0) * NWV + lane];
+      acc[i].z = red[(i * 3 + 1) * NWV + lane];
+      acc[i].a = red[(i * 3 + 2) * NWV + lane];
+    }
+    wave_merge_rescaled<true>(acc[i]);
+    if (lane == 0) {
+      rec[i * 3 + 0] = acc[i].r;
+      rec[i * 3 + 1] = acc[i].z;
+      rec[i * 3 + 2] = acc[i].a;
+    }
+  }
+}
+
+// Four rows to a workgroup, a wave each.
+template <bool DENSE, bool LSE1>
+__global__ __launch_bounds__(kSplitThreads) void kd_split_merge_kernel(const KdArgs a) {
+  constexpr int NS = split_sums(DENSE, LSE1), W = split_words(DENSE, LSE1);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t row = (int64_t)blockIdx.x * (kSplitThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (row >= a.T) return;
+  if (!a.mask[row]) {
+    if (lane == 0) {
+      if (a.kd) a.kd[row] = 0.0f;
+      if (a.nll) a.nll[row] = 0.0f;
+      if (a.tnll) a.tnll[row] = 0.0f;
+      if (a.lse) a.lse[row] = 0.0f;
+    }
+    return;
+  }
+  int y = -1;
+  float s_y = 0.0f, t_y = 0.0f;
+  if (a.labels) {
+    y = a.labels[row];
+    if ((unsigned)y < (unsigned)a.V) {
+      s_y = bf16_one(a.s[row * a.s_stride + y]);
+      if constexpr (DENSE) t_y = bf16_one(a.t[row * a.t_stride + y]);
+    }
+  }
+  const float* rec = reinterpret_cast<const float*>(a.ws) + ((size_t)row * a.gang + lane) * W;
+  Lse acc[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    acc[i].init();
+    if (lane < a.gang) {
+      acc[i].r = rec[i * 3 + 0];
+      acc[i].z = rec[i * 3 + 1];
+      acc[i].a = rec[i * 3 + 2];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NS; ++i) wave_merge_rescaled<true>(acc[i]);
+  if (lane != 0) return;
+  const float Ls = acc[0].log2_sum();
+  const float lse1_s = __fmul_rn(LSE1 ? acc[NS == 4 ? 2 : 0].log2_sum() : Ls, kLn2);
+  float lse1_t = 0.0f;
+  if constexpr (DENSE) {
+    lse1_t = __fmul_rn(LSE1 ? acc[NS == 4 ? 3 : 1].log2_sum() : acc[1].log2_sum(), kLn2);
+    const float lse_diff = ((acc[0].r - acc[1].r) + (acc[0].log2_z() - acc[1].log2_z())) * kLn2;  // lse_S - lse_T at tau
+    const float kd = (acc[1].a / acc[1].z) * a.inv_tau + lse_diff;
+    if (a.kd) a.kd[row] = kd < 0.0f ? 0.0f : kd;
+  }
+  if (a.lse) a.lse[row] = lse1_s;
+  const bool bad_label = a.labels && (unsigned)y >= (unsigned)a.V;
+  const float nanv = __builtin_nanf("");
+  if (a.nll) a.nll[row] = bad_label ? nanv : __fsub_rn(lse1_s, s_y);
+  if (a.tnll) a.tnll[row] = bad_label ? nanv : __fsub_rn(lse1_t, t_y);
+  if (bad_label && (a.nll || a.tnll) && a.status) atomicOr(a.status, 1);  // NPD_DEV_BAD_LABEL
+}
+
+namespace {
+
+// Groups per thread, 0: not split.  Measured (MI355X, all scored, us, a workgroup per row / split):
+//   dense teacher, tau = 1   1 row of 151,936 19.0 / 5.9;  64 rows of 50,304 10.4 / 7.9, 151,936 21.3 / 11.6;  181 rows of
+//                            151,936 23.2 / 21.3;  256 rows of 50,304 12.1 / 13.1, 131,072 and more the same;  800 rows of
+//                            50,304 34.0 / 29.1;  6,000 rows of 50,304 188 / 185, 151,936 565 / 548
+//                            (32,000: 128 rows 8.4 / 8.2, 4,096 80.7 / 84.2)
+//   dense teacher, tau = 2, NLL wanted   128 rows of 151,936 33.4 / 23.2;  6,000 rows of 50,304 255 / 236, 151,936 792 / 662
+//   no teacher               64 rows of 65,536 6.9 / 6.2, 128 rows of 151,936 12.3 / 11.0, 4,096 of 262,144 339 / 323
+//                            (181 rows of 151,936 11.7 / 13.4, 1,024 of 200,000 63.9 / 66.1)
+// Four groups of a dense teacher per thread for few rows, eight for many (2,048 rows of 151,936 at tau = 2: 246 / 225).
+int split_groups(int64_t T, int nvec, bool dense) {
+  constexpr int kFew = 256;  // rows: one to a compute unit
+  if (dense) {
+    if (nvec <= 5120 || (T > kFew / 2 && T <= kFew && nvec < 16384)) return 0;
+    return T <= kFew ? 4 : 8;
+  }
+  return nvec >= 30000 || (T <= kFew / 2 && nvec >= 12288) || (T <= kFew / 4 && nvec >= 8192) ? 8 : 0;
+}
+
+// slices of a row of nvec groups, 0: not split
+int split_slices(int64_t T, int nvec, bool dense) {
+  const int cap = split_groups(T, nvec, dense) * kSplitThreads;
+  if (cap == 0) return 0;
+  const int g = (nvec + cap - 1) / cap;
+  return g >= 2 && g <= kSplitMax && T * (int64_t)g <= 0x7fffffffLL ? g : 0;
+}
+
+template <int K, bool DENSE, bool LSE1>
+hipError_t launch_split(const KdArgs& a, hipStream_t stream) {
+  const hipError_t e =
+      launch_kernel(kd_split_kernel<K, DENSE, LSE1>, dim3((unsigned)(a.T * a.gang)), dim3(kSplitThreads), 0, stream, a);
+  if (e != hipSuccess) return e;
+  constexpr int rows = kSplitThreads / kWave;
+  return launch_kernel(kd_split_merge_kernel<DENSE, LSE1>, dim3((unsigned)((a.T + rows - 1) / rows)), dim3(kSplitThreads), 0,
+                       stream, a);
+}
+
+}  // namespace
+
+size_t split_scratch_bytes(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1) {
+  if ((teacher_kind != kDense && teacher_kind != kNone) || divergence != kForwardKl) return 0;
+  const bool dense = teacher_kind == kDense;
+  const int g = split_slices(T, V / 8, dense);
+  return (size_t)T * g * split_words(dense, dense && lse1) * sizeof(float);
+}
+
+hipError_t launch_kd_split(const KdArgs& a0, int teacher_kind, hipStream_t stream) {
+  KdArgs a = a0;
+  const bool dense = teacher_kind == kDense;
+  a.gang = split_slices(a.T, a.nvec_s, dense);
+  a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;
+  if (!dense) return launch_split<8, false, false>(a, stream);
+  if (split_groups(a.T, a.nvec_s, true) == 4)
+    return a.need_lse1 ? launch_split<4, true, true>(a, stream) : launch_split<4, true, false>(a, stream);
+  return a.need_lse1 ? launch_split<8, true, true>(a, stream) : launch_split<8, true, false>(a, stream);
+}
+
+}  // namespace npd

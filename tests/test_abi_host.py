@@ -401,3 +401,27 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=300)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_forward_scratch(lib):
+    """Scratch of the forward-only entry point: which calls ask for it, and the argument checks it shares."""
+    F = binding.NPD_FLAG_FWD_ONLY
+    big = dict(vocab=151936, n_tokens=64, student_stride=151936, teacher_stride=151936, flags=F)
+    ask = lambda **kw: lib.npd_forward_scratch_bytes(ctypes.byref(_desc(**{**big, **kw})))
+    assert ask() == 64 * 19 * 6 * 4 and ask(tau=2.0) == 64 * 19 * 12 * 4          # slices of 1,024 groups of 8 logits
+    assert ask(n_tokens=1000) == 1000 * 10 * 6 * 4                                # of 2,048
+    assert ask(teacher_kind=binding.NPD_TEACHER_NONE) == 64 * 10 * 3 * 4
+    assert ask(flags=0) == ask(flags=F | binding.NPD_FLAG_NO_WORKSPACE) == 0
+    assert ask(teacher_stride=151937) == 0                                        # rows that drift apart: element by element
+    assert ask(divergence=1) == ask(vocab=32768) == ask(tau=-1.0) == 0
+    assert ask(teacher_kind=binding.NPD_TEACHER_TOPK, topk=8) == 0
+
+    def forward(d, grad_flags=F, kd=FAKE + 0x10000000, student=FAKE, scratch=None, n=0):
+        return lib.npd_kd_loss_forward(ctypes.byref(d), student, FAKE + 0x4000000, None, None, None, FAKE + 0x8000000, kd,
+                                       None, None, None, None, scratch, n, None)
+
+    assert forward(_desc(**{**big, "flags": 0})) == E_NULL                        # a gradient call has no gradient here
+    assert forward(_desc(**{**big, "tau": 0.0})) == E_VALUE
+    assert forward(_desc(**big), student=None) == E_NULL
+    assert forward(_desc(**big), kd=FAKE + 2) == E_VALUE
+    assert forward(_desc(**big), kd=FAKE + 16) == E_ALIAS

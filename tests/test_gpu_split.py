@@ -1,0 +1,91 @@
+"""Forward-only calls whose rows are split over several workgroups, against the oracle and against the same call with a
+workgroup per row."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import compare_kd, dev, guarded_rows, run_gpu_kd
+from paper_2605_05940_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _scratch(T, V, teacher, tau):
+    d = binding.KdDesc(T, V, teacher, V, V, 0, binding.NPD_FLAG_FWD_ONLY, tau, 1.0, 0.0, 0, 0.0)
+    import ctypes
+    return binding.load().npd_forward_scratch_bytes(ctypes.byref(d))
+
+
+# slices of 1,024 groups of eight logits a tensor (up to 256 rows) or 2,048 (more, or no teacher): one more and one less than
+# a whole number of them, rows at any offset, last slices that hold edge elements alone
+@pytest.mark.parametrize("V,pitch,T", [
+    (40968, 40968, 24), (49152, 49152, 24), (49160, 49160, 24), (50003, 50003, 24), (65537, 65600, 20), (98305, 98305, 20),
+    (151936, 151936, 16), (262144, 262144, 8), (40976, 40976, 300), (49159, 49159, 280), (65544, 65544, 270),
+])
+@pytest.mark.parametrize("dense", [True, False])
+def test_split_rows(oracle, V, pitch, T, dense):
+    w = synth.scaled(synth.config(1), n_rows=1, row_len=T, vocab=V, length_lo=4, length_hi=16)
+    lay = synth.make_layout(w)
+    g = torch.Generator(device=dev()).manual_seed(V + T)
+    s, t = (guarded_rows(T, V, pitch)[1] for _ in range(2))
+    s.copy_(3.0 * torch.randn((T, V), generator=g, device=dev()))
+    t.copy_(0.8 * s.float() + 1.5 * torch.randn((T, V), generator=g, device=dev()))
+    m = lay.loss_mask.copy()
+    m[1:8] = 1
+    s[2] = torch.log_softmax(s[2].float(), 0) - 40.0            # negative logits alone
+    s[3, V // 2:] = float("-inf")                               # masked vocabulary entries, in both and in one
+    t[3, V // 2:] = float("-inf")
+    t[4, ::3] = float("-inf")
+    s[5, V - 1] = 700.0                                         # far above the other slices
+    t[6, 0] = 900.0
+    mask, lab = torch.from_numpy(m).to(dev()), torch.from_numpy(lay.labels).to(dev())
+    lab[7] = V - 1
+    lab[3:5] = 1                                                # (not a masked entry)
+    labels = lab.cpu().numpy()
+    assert _scratch(T, V, binding.NPD_TEACHER_NONE if not dense else 0, 2.0) > 0 or not dense
+    for tau in (1.0, 2.0) if dense else (1.0,):
+        print(f"[split] V={V} pitch={pitch} T={T} dense={dense} tau={tau}", flush=True)
+        got, one = (run_gpu_kd(s, mask, t=t if dense else None, labels=lab, tau=tau, want_grad=False, no_workspace=n)
+                    for n in (False, True))
+        if dense:
+            ref = oracle.kd_dense(synth.bf16_bits(s.contiguous()), synth.bf16_bits(t.contiguous()), labels, m, tau=tau,
+                                  want_grad=False)
+        else:
+            alone = oracle.nll(synth.bf16_bits(s.contiguous()), labels, m)
+            ref = dict(nll_s=alone["nll"], lse_s=alone["lse"])
+        compare_kd(got, ref, m)
+        assert got["status"] == one["status"] == 0
+        for key in ("kd", "nll_s", "nll_t", "lse_s"):
+            if got[key] is not None:
+                np.testing.assert_allclose(got[key], one[key], rtol=2e-5, atol=2e-5)
+
+
+def test_split_rows_bad_label_and_replays():
+    """A label outside the vocabulary marks its own row; a call that was captured gives the same on every replay."""
+    T, V = 12, 65536
+    g = torch.Generator(device=dev()).manual_seed(3)
+    s, t = (torch.randn((T, V), generator=g, device=dev()).mul_(3).to(torch.bfloat16) for _ in range(2))
+    mask, lab = torch.ones(T, dtype=torch.uint8, device=dev()), torch.arange(T, dtype=torch.int32, device=dev())
+    kd, nll, tnll = (torch.empty(T, device=dev()) for _ in range(3))
+    status = torch.zeros(1, dtype=torch.int32, device=dev())
+
+    def call():
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, labels=lab, kd_tok=kd, nll_tok=nll, teacher_nll_tok=tnll,
+                                    dev_status=status)
+
+    call()
+    want = [x.clone() for x in (kd, nll, tnll)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(3):
+        for x in (kd, nll, tnll):
+            x.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip((kd, nll, tnll), want)) and status.item() == 0
+    lab[5] = V
+    call()
+    assert status.item() == binding.NPD_DEV_BAD_LABEL and torch.isnan(nll[5]) and torch.isnan(tnll[5])
+    assert torch.equal(kd, want[0]) and torch.equal(nll[:5], want[1][:5]) and torch.equal(nll[6:], want[1][6:])
