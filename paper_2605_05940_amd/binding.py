@@ -5,6 +5,7 @@ the current HIP stream to the library, and raises ``NpdError`` on a non-zero sta
 fallback: without the built library these calls fail.
 """
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -13,6 +14,7 @@ import torch
 HERE = os.path.dirname(os.path.abspath(__file__))
 # NPD_LIB_PATH overrides the in-tree library (e.g. to try a differently tuned build)
 LIB_PATH = os.environ.get("NPD_LIB_PATH") or os.path.join(HERE, "libnpd.so")
+HOST_PATH = os.path.join(HERE, "npd_host.so")
 
 NPD_TEACHER_DENSE_BF16, NPD_TEACHER_TOPK, NPD_TEACHER_NONE = 0, 1, 2
 NPD_FLAG_FWD_ONLY, NPD_FLAG_INPLACE_GRAD, NPD_FLAG_NO_WORKSPACE = 1, 2, 4
@@ -45,12 +47,15 @@ class KdDesc(ctypes.Structure):
 
 
 _lib = None
+# native marshalling of the ordinary call (csrc/npd_host.cpp), there once the library is loaded; None without torch's raw
+# stream handles.  Its functions return libnpd's status, or -1 for a call that is left to the Python code below.
+_host = None
 _vp = ctypes.c_void_p
 
 
 def load() -> ctypes.CDLL:
     """Load ``libnpd.so`` (built beforehand by ``paper_2605_05940_amd/build.py``); raises if it is missing."""
-    global _lib
+    global _lib, _host
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is not built: run `python -m paper_2605_05940_amd.build` "
@@ -85,8 +90,24 @@ def load() -> ctypes.CDLL:
         L.npd_teacher_topk.restype = ctypes.c_int
         L.npd_teacher_topk.argtypes = ([ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32,
                                         ctypes.c_uint32] + [_vp] * 5)
+        _host = _load_host(L)
         _lib = L
     return _lib
+
+
+def _load_host(L):
+    if _raw_stream is None:
+        return None
+    if not os.path.exists(HOST_PATH):
+        raise RuntimeError(f"{HOST_PATH} is not built: run `python -m paper_2605_05940_amd.build` "
+                           "(or __graft_entry__.build()) first")
+    spec = importlib.util.spec_from_file_location("npd_host", HOST_PATH)
+    host = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(host)
+    entries = (L.npd_workspace_bytes, L.npd_forward_scratch_bytes, L.npd_kd_loss_fwd_bwd, L.npd_kd_loss_forward,
+               L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag)
+    host.bind(_raw_stream, _workspaces, tuple(ctypes.cast(f, _vp).value for f in entries))
+    return host
 
 
 def _check(status: int) -> None:
@@ -117,9 +138,6 @@ def _array(name: str, t: Optional[torch.Tensor], n: int, dtype):
     return t.data_ptr()
 
 
-# The small calls of a step are bound by this module (config: 512 x 1,024, loss and two reductions, 28 us a pass of which
-# the GPU works 11): the raw stream handle instead of a Stream object, one pass over each argument and a descriptor
-# filled by one call bring it to 20 us (64 x 151,936: 31 to 24 us).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
@@ -158,6 +176,12 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     that are not 16-byte aligned, allocated for the call.  ``no_workspace`` sets ``NPD_FLAG_NO_WORKSPACE``.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in
     scratch array; no workspace argument).
     """
+    if _host is not None and not noalloc:
+        st = _host.kd(student_logits, loss_mask, teacher_dense, teacher_idx, teacher_val, labels, tau, grad_scale,
+                      ce_grad_scale, divergence, skew_alpha, grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status,
+                      workspace, no_workspace)
+        if st >= 0:
+            return _check(st)
     T, V = shape = student_logits.shape
     student_stride, teacher_stride, topk = _row_stride(student_logits), 0, 0
     if teacher_dense is not None:
@@ -247,6 +271,10 @@ def npd_segment_reduce(values: Optional[torch.Tensor], loss_mask: torch.Tensor, 
                        seg_mean: Optional[torch.Tensor] = None, token_to_sample: Optional[torch.Tensor] = None,
                        dev_status: Optional[torch.Tensor] = None) -> None:
     """Enqueue the per-sample reduction on the current stream (see ``npd_segment_reduce`` in npd.h)."""
+    if _host is not None:
+        st = _host.segment_reduce(values, loss_mask, cu_seqlens, seg_sum, seg_count, seg_mean, token_to_sample, dev_status)
+        if st >= 0:
+            return _check(st)
     T = loss_mask.numel()
     S = cu_seqlens.numel() - 1
     _check(load().npd_segment_reduce(
@@ -262,6 +290,11 @@ def npd_delta_ifd_score(mean_nll_student: torch.Tensor, mean_nll_teacher: torch.
                         delta: Optional[torch.Tensor] = None, zone: Optional[torch.Tensor] = None,
                         keep: Optional[torch.Tensor] = None, keep_count: Optional[torch.Tensor] = None) -> None:
     """Enqueue the Delta-IFD score on the current stream (see ``npd_delta_ifd_score`` in npd.h)."""
+    if _host is not None:
+        st = _host.delta_ifd(mean_nll_student, mean_nll_teacher, seg_count, pair_cond, pair_uncond, lo, hi, flags, ifd_student,
+                             ifd_teacher, delta, zone, keep, keep_count)
+        if st >= 0:
+            return _check(st)
     S = mean_nll_student.numel()
     P = pair_cond.numel()
     if mean_nll_teacher.numel() != S or seg_count.numel() != S or pair_uncond.numel() != P:
@@ -281,6 +314,10 @@ def npd_delta_ifd_score(mean_nll_student: torch.Tensor, mean_nll_teacher: torch.
 def npd_teacher_topk(teacher_logits: torch.Tensor, k: int, *, topk_idx: torch.Tensor, topk_val: torch.Tensor,
                      loss_mask: Optional[torch.Tensor] = None, log_probs: bool = True) -> None:
     """Enqueue the teacher-side top-k extraction on the current stream (see ``npd_teacher_topk`` in npd.h)."""
+    if _host is not None:
+        st = _host.teacher_topk(teacher_logits, k, topk_idx, topk_val, loss_mask, log_probs)
+        if st >= 0:
+            return _check(st)
     T, V = teacher_logits.shape
     for name, t in (("topk_idx", topk_idx), ("topk_val", topk_val)):
         if t.shape != (T, k) or not t.is_contiguous():
@@ -297,6 +334,11 @@ def npd_policy_lag(kl_tok: torch.Tensor, loss_mask: torch.Tensor, cu_seqlens: to
                    batch_kl_mean: Optional[torch.Tensor] = None, batch_count: Optional[torch.Tensor] = None,
                    lag_exceeded: Optional[torch.Tensor] = None, dev_status: Optional[torch.Tensor] = None) -> None:
     """Enqueue the policy-latency monitor on the current stream (see ``npd_policy_lag`` in npd.h)."""
+    if _host is not None:
+        st = _host.policy_lag(kl_tok, loss_mask, cu_seqlens, epsilon, seg_kl_mean, seg_count, batch_kl_mean, batch_count,
+                              lag_exceeded, dev_status)
+        if st >= 0:
+            return _check(st)
     T = loss_mask.numel()
     S = cu_seqlens.numel() - 1
     for name, t, n in (("kl_tok", kl_tok, T), ("seg_kl_mean", seg_kl_mean, S), ("seg_count", seg_count, S),

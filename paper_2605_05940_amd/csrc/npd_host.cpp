@@ -1,0 +1,326 @@
+// The argument marshalling of binding.py in native code: the same checks on the same tensors, the same scratch memory and
+// the same calls into libnpd (whose entry points arrive as addresses, see `bind`).
+//
+// Every function returns libnpd's status, or -1 if anything about its arguments is out of the ordinary -- a tensor that is
+// not a plain one on the GPU, a type, shape or stride that the call does not take, a number that is not one: nothing has
+// been enqueued then, and the caller's Python code, which is the reference for what is accepted, handles the call or raises.
+//
+// Why: a call of a few hundred positions keeps the GPU busy for 5 us, and reading fifteen tensors' attributes and filling
+// the foreign-function call's arguments from Python took as long (MI355X, loss and two reductions, us a pass, marshalled
+// from Python / here: 512 x 1,024 20.3 / 12.3, 64 x 151,936 24.8 / 21.1; the GPU alone needs 8.6 and 19.9).
+#include <Python.h>
+#include <ATen/core/Tensor.h>
+#include <ATen/ops/empty.h>
+#include <c10/core/impl/VirtualGuardImpl.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "../../include/npd.h"
+
+namespace {
+
+struct Entry {
+  decltype(&npd_workspace_bytes) workspace_bytes;
+  decltype(&npd_forward_scratch_bytes) forward_scratch_bytes;
+  decltype(&npd_kd_loss_fwd_bwd) kd;
+  decltype(&npd_kd_loss_forward) kd_forward;
+  decltype(&npd_segment_reduce) segment_reduce;
+  decltype(&npd_delta_ifd_score) delta_ifd;
+  decltype(&npd_teacher_topk) teacher_topk;
+  decltype(&npd_policy_lag) policy_lag;
+};
+Entry lib;                            // written by bind() under the interpreter lock, before any call
+PyObject* raw_stream = nullptr;       // torch's current raw stream of a device index
+PyObject* workspaces = nullptr;       // the buffers it keeps, by device index
+
+struct NotPlain {};                   // thrown by the helpers below: the caller's Python code takes the call
+
+// the tensor behind an argument, nullptr for None
+const at::Tensor* tensor(PyObject* o) {
+  if (o == Py_None) return nullptr;
+  if (!THPVariable_CheckExact(o)) throw NotPlain();
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.is_cuda() || !t.has_storage() || t.layout() != at::kStrided) throw NotPlain();
+  return &t;
+}
+const at::Tensor& required(PyObject* o) {
+  const at::Tensor* t = tensor(o);
+  if (!t) throw NotPlain();
+  return *t;
+}
+void* pointer(const at::Tensor* t, at::ScalarType type) {
+  if (!t) return nullptr;
+  if (t->scalar_type() != type) throw NotPlain();
+  return t->data_ptr();
+}
+// contiguous array of n elements, nullptr if it is absent
+void* array(PyObject* o, int64_t n, at::ScalarType type) {
+  const at::Tensor* t = tensor(o);
+  if (t && (t->numel() != n || !t->is_contiguous())) throw NotPlain();
+  return pointer(t, type);
+}
+template <class T>
+T* array_of(PyObject* o, int64_t n, at::ScalarType type) {
+  return static_cast<T*>(array(o, n, type));
+}
+int64_t row_stride(const at::Tensor& t) {
+  if (t.dim() != 2 || t.stride(1) != 1) throw NotPlain();
+  return t.stride(0);
+}
+double number(PyObject* o) {
+  const double x = PyFloat_AsDouble(o);
+  if (x == -1.0 && PyErr_Occurred()) throw NotPlain();
+  return x;
+}
+long whole(PyObject* o) {
+  if (!PyLong_Check(o)) throw NotPlain();
+  int over = 0;
+  const long x = PyLong_AsLongAndOverflow(o, &over);
+  if (over || x != (long)(int32_t)x) throw NotPlain();
+  return x;
+}
+bool flag(PyObject* o) {
+  const int x = PyObject_IsTrue(o);
+  if (x < 0) throw NotPlain();
+  return x != 0;
+}
+
+c10::Device current_device() { return c10::impl::VirtualGuardImpl(c10::DeviceType::CUDA).getDevice(); }
+
+void* current_stream() {
+  PyObject* index = PyLong_FromLong(current_device().index());
+  if (!index) throw NotPlain();
+  PyObject* r = PyObject_CallOneArg(raw_stream, index);
+  Py_DECREF(index);
+  if (!r) throw NotPlain();
+  void* s = PyLong_AsVoidPtr(r);
+  Py_DECREF(r);
+  if (!s && PyErr_Occurred()) throw NotPlain();
+  return s;
+}
+
+// scratch of one call: from torch's stream-ordered allocator, reused only behind the call on its stream
+at::Tensor scratch(size_t bytes) {
+  return at::empty({(int64_t)bytes}, at::TensorOptions().dtype(at::kByte).device(current_device()));
+}
+
+// A call into libnpd, without the interpreter lock: a launch may wait for room in its queue.
+template <class F, class... A>
+int call(F f, A... a) {
+  PyThreadState* state = PyEval_SaveThread();
+  const npd_status st = f(a...);
+  PyEval_RestoreThread(state);
+  return (int)st;
+}
+
+template <class Call>
+PyObject* guarded(Call body) {
+  try {
+    return PyLong_FromLong((long)body());
+  } catch (const NotPlain&) {
+  } catch (const std::exception&) {  // torch's own: a tensor without memory of its own
+  }
+  PyErr_Clear();
+  return PyLong_FromLong(-1);
+}
+
+// (student_logits, loss_mask, teacher_dense, teacher_idx, teacher_val, labels, tau, grad_scale, ce_grad_scale, divergence,
+//  skew_alpha, grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, workspace, no_workspace)
+PyObject* kd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 19) return PyLong_FromLong(-1);
+  return guarded([&]() -> int {
+    const at::Tensor& s = required(a[0]);
+    npd_kd_desc d{};
+    d.student_stride = row_stride(s);
+    const int64_t T = s.size(0), V = s.size(1);
+    if (V > NPD_MAX_VOCAB) throw NotPlain();
+    d.n_tokens = T;
+    d.vocab = (int32_t)V;
+    const at::Tensor *t = tensor(a[2]), *idx = nullptr, *val = nullptr;
+    if (t) {
+      d.teacher_kind = NPD_TEACHER_DENSE_BF16;
+      d.teacher_stride = row_stride(*t);
+      if (t->size(0) != T || t->size(1) != V) throw NotPlain();
+      if (a[3] != Py_None || a[4] != Py_None) throw NotPlain();
+    } else {
+      idx = tensor(a[3]);
+      val = tensor(a[4]);
+      d.teacher_kind = idx ? NPD_TEACHER_TOPK : NPD_TEACHER_NONE;
+      if (!idx != !val) throw NotPlain();
+      if (idx) {
+        if (idx->dim() != 2 || idx->size(0) != T || idx->size(1) > V || !idx->is_contiguous() || !val->is_contiguous() ||
+            val->sizes() != idx->sizes())
+          throw NotPlain();
+        d.topk = (int32_t)idx->size(1);
+      }
+    }
+    d.tau = (float)number(a[6]);
+    d.grad_scale = (float)number(a[7]);
+    d.ce_grad_scale = (float)number(a[8]);
+    const double tau = number(a[6]), ce = number(a[8]);
+    d.divergence = (int32_t)whole(a[9]);
+    d.skew_alpha = (float)number(a[10]);
+    const at::Tensor* g = tensor(a[11]);
+    if (!g) {
+      d.flags |= NPD_FLAG_FWD_ONLY;
+    } else {
+      if (row_stride(*g) != d.student_stride || g->size(0) != T || g->size(1) != V) throw NotPlain();
+      if (g->data_ptr() == s.data_ptr()) d.flags |= NPD_FLAG_INPLACE_GRAD;
+    }
+    const bool no_workspace = flag(a[18]);
+    if (no_workspace) d.flags |= NPD_FLAG_NO_WORKSPACE;
+    const at::Tensor* ws = tensor(a[17]);
+    void* const sp = pointer(&s, at::kBFloat16);
+    void* const tp = pointer(t, at::kBFloat16);
+    int32_t* const ip = static_cast<int32_t*>(pointer(idx, at::kInt));
+    float* const vp = static_cast<float*>(pointer(val, at::kFloat));
+    int32_t* const labels = array_of<int32_t>(a[5], T, at::kInt);
+    uint8_t* const mask = static_cast<uint8_t*>(array(a[1], T, at::kByte));
+    void* const gp = pointer(g, at::kBFloat16);
+    float* const kd_tok = array_of<float>(a[12], T, at::kFloat);
+    float* const nll = array_of<float>(a[13], T, at::kFloat);
+    float* const tnll = array_of<float>(a[14], T, at::kFloat);
+    float* const lse = array_of<float>(a[15], T, at::kFloat);
+    int32_t* const status = static_cast<int32_t*>(pointer(tensor(a[16]), at::kInt));
+    void* const stream = current_stream();
+    if (!ws && !no_workspace && !g) {
+      const size_t need = lib.forward_scratch_bytes(&d);
+      if (need) {
+        const at::Tensor own = scratch(need);
+        return call(lib.kd_forward, &d, sp, tp, ip, vp, labels, mask, kd_tok, nll, tnll, lse, status, own.data_ptr(), need, stream);
+      }
+    }
+    if (!ws && !no_workspace && g) {
+      const size_t need = lib.workspace_bytes(&d);
+      if (need && ((ce != 0.0 && tau != 1.0) || (((uintptr_t)sp | (uintptr_t)(2 * d.student_stride)) & 15) != 0)) {
+        const at::Tensor own = scratch(need);
+        return call(lib.kd, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, own.data_ptr(), need, stream);
+      }
+      if (need) {  // the buffer that binding.workspace_for keeps
+        PyObject* key = PyLong_FromLong(s.get_device());
+        PyObject* kept = key ? PyDict_GetItemWithError(workspaces, key) : nullptr;  // borrowed
+        Py_XDECREF(key);
+        if (!kept || !THPVariable_CheckExact(kept)) throw NotPlain();  // (Python makes it)
+        const at::Tensor w = THPVariable_Unpack(kept);  // (held through the call)
+        if (!w.is_cuda() || (size_t)w.numel() < need) throw NotPlain();
+        return call(lib.kd, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, w.data_ptr(), (size_t)w.nbytes(),
+                      stream);
+      }
+    }
+    return call(lib.kd, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, ws ? ws->data_ptr() : nullptr,
+                  ws ? (size_t)ws->numel() * ws->element_size() : 0, stream);
+  });
+}
+
+// (values, loss_mask, cu_seqlens, seg_sum, seg_count, seg_mean, token_to_sample, dev_status)
+PyObject* segment_reduce(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 8) return PyLong_FromLong(-1);
+  return guarded([&]() -> int {
+    const at::Tensor &mask = required(a[1]), &cu = required(a[2]);
+    const int64_t T = mask.numel(), S = cu.numel() - 1;
+    if (S < 0 || S > 0x7fffffffLL) throw NotPlain();
+    return call(lib.segment_reduce, T, (int32_t)S, array_of<float>(a[0], T, at::kFloat),
+                              static_cast<uint8_t*>(pointer(&mask, at::kByte)), static_cast<int32_t*>(pointer(&cu, at::kInt)),
+                              array_of<float>(a[3], S, at::kFloat), array_of<int32_t>(a[4], S, at::kInt),
+                              array_of<float>(a[5], S, at::kFloat), array_of<int32_t>(a[6], T, at::kInt),
+                              static_cast<int32_t*>(pointer(tensor(a[7]), at::kInt)), current_stream());
+  });
+}
+
+// (mean_nll_student, mean_nll_teacher, seg_count, pair_cond, pair_uncond, lo, hi, flags, ifd_student, ifd_teacher, delta,
+//  zone, keep, keep_count)
+PyObject* delta_ifd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 14) return PyLong_FromLong(-1);
+  return guarded([&]() -> int {
+    const at::Tensor &ms = required(a[0]), &mt = required(a[1]), &cnt = required(a[2]), &pc = required(a[3]),
+                     &pu = required(a[4]);
+    const int64_t S = ms.numel(), P = pc.numel();
+    if (mt.numel() != S || cnt.numel() != S || pu.numel() != P || S > 0x7fffffffLL || P > 0x7fffffffLL) throw NotPlain();
+    const long flags = whole(a[7]);
+    if (flags < 0) throw NotPlain();
+    return call(lib.delta_ifd, (int32_t)P, (int32_t)S, static_cast<float*>(pointer(&ms, at::kFloat)),
+                         static_cast<float*>(pointer(&mt, at::kFloat)), static_cast<int32_t*>(pointer(&cnt, at::kInt)),
+                         static_cast<int32_t*>(pointer(&pc, at::kInt)), static_cast<int32_t*>(pointer(&pu, at::kInt)),
+                         (float)number(a[5]), (float)number(a[6]), (uint32_t)flags, array_of<float>(a[8], P, at::kFloat),
+                         array_of<float>(a[9], P, at::kFloat), array_of<float>(a[10], P, at::kFloat),
+                         array_of<uint8_t>(a[11], P, at::kByte), array_of<uint8_t>(a[12], P, at::kByte),
+                         static_cast<int32_t*>(pointer(tensor(a[13]), at::kInt)), current_stream());
+  });
+}
+
+// (teacher_logits, k, topk_idx, topk_val, loss_mask, log_probs)
+PyObject* teacher_topk(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 6) return PyLong_FromLong(-1);
+  return guarded([&]() -> int {
+    const at::Tensor &t = required(a[0]), &idx = required(a[2]), &val = required(a[3]);
+    const int64_t stride = row_stride(t), T = t.size(0), V = t.size(1);
+    const long k = whole(a[1]);
+    if (V > 0x7fffffffLL) throw NotPlain();
+    for (const at::Tensor* o : {&idx, &val})
+      if (o->dim() != 2 || o->size(0) != T || o->size(1) != k || !o->is_contiguous()) throw NotPlain();
+    return call(lib.teacher_topk, T, (int32_t)V, stride, (int32_t)k, flag(a[5]) ? NPD_TOPK_LOG_PROBS : 0u,
+                            pointer(&t, at::kBFloat16), array_of<uint8_t>(a[4], T, at::kByte),
+                            static_cast<int32_t*>(pointer(&idx, at::kInt)), static_cast<float*>(pointer(&val, at::kFloat)),
+                            current_stream());
+  });
+}
+
+// (kl_tok, loss_mask, cu_seqlens, epsilon, seg_kl_mean, seg_count, batch_kl_mean, batch_count, lag_exceeded, dev_status)
+PyObject* policy_lag(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 10) return PyLong_FromLong(-1);
+  return guarded([&]() -> int {
+    const at::Tensor &mask = required(a[1]), &cu = required(a[2]);
+    const int64_t T = mask.numel(), S = cu.numel() - 1;
+    if (S < 0 || S > 0x7fffffffLL) throw NotPlain();
+    return call(lib.policy_lag, T, (int32_t)S, array_of<float>(a[0], T, at::kFloat),
+                          static_cast<uint8_t*>(pointer(&mask, at::kByte)), static_cast<int32_t*>(pointer(&cu, at::kInt)),
+                          (float)number(a[3]), array_of<float>(a[4], S, at::kFloat), array_of<int32_t>(a[5], S, at::kInt),
+                          array_of<float>(a[6], 1, at::kFloat), array_of<int32_t>(a[7], 1, at::kInt),
+                          array_of<int32_t>(a[8], 1, at::kInt), static_cast<int32_t*>(pointer(tensor(a[9]), at::kInt)),
+                          current_stream());
+  });
+}
+
+// bind(raw_stream, workspaces, addresses): `addresses` of libnpd's entry points in the order of Entry
+PyObject* bind(PyObject*, PyObject* args) {
+  PyObject *stream, *kept, *addresses;
+  if (!PyArg_ParseTuple(args, "OO!O!", &stream, &PyDict_Type, &kept, &PyTuple_Type, &addresses)) return nullptr;
+  void* p[8];
+  if (PyTuple_GET_SIZE(addresses) != 8) {
+    PyErr_SetString(PyExc_ValueError, "8 addresses");
+    return nullptr;
+  }
+  for (int i = 0; i < 8; ++i) {
+    p[i] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(addresses, i));
+    if (!p[i]) {
+      if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "a null address");
+      return nullptr;
+    }
+  }
+  Py_INCREF(stream);
+  Py_INCREF(kept);
+  Py_XSETREF(raw_stream, stream);
+  Py_XSETREF(workspaces, kept);
+  lib.workspace_bytes = reinterpret_cast<decltype(lib.workspace_bytes)>(p[0]);
+  lib.forward_scratch_bytes = reinterpret_cast<decltype(lib.forward_scratch_bytes)>(p[1]);
+  lib.kd = reinterpret_cast<decltype(lib.kd)>(p[2]);
+  lib.kd_forward = reinterpret_cast<decltype(lib.kd_forward)>(p[3]);
+  lib.segment_reduce = reinterpret_cast<decltype(lib.segment_reduce)>(p[4]);
+  lib.delta_ifd = reinterpret_cast<decltype(lib.delta_ifd)>(p[5]);
+  lib.teacher_topk = reinterpret_cast<decltype(lib.teacher_topk)>(p[6]);
+  lib.policy_lag = reinterpret_cast<decltype(lib.policy_lag)>(p[7]);
+  Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {
+    {"bind", bind, METH_VARARGS, nullptr},
+    {"kd", reinterpret_cast<PyCFunction>(kd), METH_FASTCALL, nullptr},
+    {"segment_reduce", reinterpret_cast<PyCFunction>(segment_reduce), METH_FASTCALL, nullptr},
+    {"delta_ifd", reinterpret_cast<PyCFunction>(delta_ifd), METH_FASTCALL, nullptr},
+    {"teacher_topk", reinterpret_cast<PyCFunction>(teacher_topk), METH_FASTCALL, nullptr},
+    {"policy_lag", reinterpret_cast<PyCFunction>(policy_lag), METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "npd_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit_npd_host() { return PyModule_Create(&module); }
