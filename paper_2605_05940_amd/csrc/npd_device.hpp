@@ -63,6 +63,34 @@ __device__ __forceinline__ void unpack8(const uint4& v, float x[8]) {
   x[6] = bf16_lo(v.w); x[7] = bf16_hi(v.w);
 }
 
+// The same by the matrix cores: a 4 x 4 identity times the four bf16 values that each lane holds in two registers gives the
+// lane its own four values as floats, exactly (one product and zeros).  One instruction of two passes for four values, where
+// shifts and masks take four.  With C given it adds, with the identity negated it subtracts: y - x of four pairs, rounded
+// once like the subtraction.  Only for finite values: an infinity or NaN makes the other three of its four NaN (0 times it).
+// Every lane of the wave has to be active.  Measured (MI355X, 4 waves per SIMD, cycles of a SIMD per pair of logits): sums
+// of the forward KL 50.3 / 43.2 (exponentials 16 of them), gradient 40.3 / 36.8.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s16x4 lane_identity(short one) {
+  const int l = threadIdx.x & 3;
+  return s16x4{l == 0 ? one : (short)0, l == 1 ? one : (short)0, l == 2 ? one : (short)0, l == 3 ? one : (short)0};
+}
+constexpr short kBf16One = 0x3f80, kBf16MinusOne = (short)0xbf80;
+__device__ __forceinline__ void mfma8(const uint4& v, const s16x4& m, const float c[8], float x[8]) {
+  const uint2 lo = make_uint2(v.x, v.y), hi = make_uint2(v.z, v.w);
+  const f32x4 a = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(m, __builtin_bit_cast(s16x4, lo), f32x4{c[0], c[1], c[2], c[3]}, 0, 0, 0);
+  const f32x4 b = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(m, __builtin_bit_cast(s16x4, hi), f32x4{c[4], c[5], c[6], c[7]}, 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    x[j] = a[j];
+    x[4 + j] = b[j];
+  }
+}
+__device__ __forceinline__ void unpack8_mfma(const uint4& v, const s16x4& identity, float x[8]) {
+  const float zero[8] = {};
+  mfma8(v, identity, zero, x);
+}
+
 // v_max3_f32 without the input canonicalisation the compiler adds around fmaxf (the values come straight
 // from bf16 bit patterns; a NaN among them simply propagates into the sums)
 __device__ __forceinline__ float max3(float a, float b, float c) {

@@ -108,11 +108,10 @@ __device__ __forceinline__ float grad_reverse_elem(float xs, float xt, const Swe
   return exp2_fast(__builtin_fmaf(xs, k.c, -k.p.rs)) * __builtin_fmaf(__builtin_fmaxf(xs - xt, -1.0e30f), k.ra, k.rb);
 }
 
-// `S1`, `ce_own`: the student at tau = 1, for a CE term whose softmax is not the KD term's (tau != 1)
-__device__ __forceinline__ Sweep2Coef sweep2_coef(const Lse& S, const Lse& Tt, const Lse& S1, float c, float gscale,
-                                                  float cscale, bool has_teacher_stream, bool dense, bool ce_own) {
+// The folded form's share; `p` and wc_square are not set.
+__device__ __forceinline__ Sweep2Coef folded_coef(const Lse& S, const Lse& Tt, float c, float gscale, float cscale,
+                                                  bool dense, bool ce_own) {
   Sweep2Coef k;
-  k.p = make_grad_coef(S, Tt, S1, c, gscale, cscale, has_teacher_stream, ce_own);
   k.c = c;
   const float A = ce_own ? gscale : gscale + cscale, B = dense ? gscale : 0.0f;
   // log2(0) = -inf: the term becomes 2^-inf = 0
@@ -124,23 +123,44 @@ __device__ __forceinline__ Sweep2Coef sweep2_coef(const Lse& S, const Lse& Tt, c
   const bool small_t = !dense || B == 0.0f || fabsf(k.ft) < 1024.0f;
   k.folded = same_sign && small_s && small_t && !(ce_own && cscale != 0.0f);
   k.ra = k.rb = 0.0f;
+  k.wc_square = 0.0f;
+  return k;
+}
+
+// ... and the rest.  `S1`, `ce_own`: the student at tau = 1, for a CE term whose softmax is not the KD term's (tau != 1)
+__device__ __forceinline__ void set_precise_coef(Sweep2Coef& k, const Lse& S, const Lse& Tt, const Lse& S1, float c,
+                                                 float gscale, float cscale, bool has_teacher_stream, bool ce_own) {
+  k.p = make_grad_coef(S, Tt, S1, c, gscale, cscale, has_teacher_stream, ce_own);
   k.wc_square = ce_own ? k.p.wc * exp2_fast(2.0f * S.r - S1.r) : 0.0f;
+}
+__device__ __forceinline__ Sweep2Coef sweep2_coef(const Lse& S, const Lse& Tt, const Lse& S1, float c, float gscale,
+                                                  float cscale, bool has_teacher_stream, bool dense, bool ce_own) {
+  Sweep2Coef k = folded_coef(S, Tt, c, gscale, cscale, dense, ce_own);
+  set_precise_coef(k, S, Tt, S1, c, gscale, cscale, has_teacher_stream, ce_own);
   return k;
 }
 
 // Form of the gradient write: folded (weights in the exponents), or precise without a CE term, with one that shares
 // the student's exponential (tau = 1), with one that needs an exponential of its own (tau != 1).  One walk over the
 // registers per form: a test inside the walk would stand at every element.
-// At tau = 2 that exponential is the square of the KD term's: exp(x) = exp(x / 2)^2.
-enum GradForm { kFolded = 0, kPrecise = 1, kPreciseCe = 2, kPreciseCeOwn = 3, kPreciseCeSquare = 4 };
+// At tau = 2 that exponential is the square of the KD term's: exp(x) = exp(x / 2)^2.  kFoldedPlus: kFolded with weights that
+// are not negative, without the instruction per pair that sets the sign.
+enum GradForm { kFoldedPlus = 5, kFolded = 0, kPrecise = 1, kPreciseCe = 2, kPreciseCeOwn = 3, kPreciseCeSquare = 4 };
 
 __device__ __forceinline__ float add_ce_own(float g, float xs, const GradCoef& k) {
   return __builtin_fmaf(exp2_fast(__builtin_fmaf(xs, kLog2e, -k.r1)), k.wc, g);
 }
 
-// gradient of 8 elements
-template <int TEACHER, int FORM, int DIVK = kForwardKl>
-__device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const Sweep2Coef& k) {
+// gradient of 8 elements; MFMA: logits that are known to be finite, unpacked by the matrix cores (all lanes active)
+template <int TEACHER, int FORM, int DIVK = kForwardKl, bool MFMA = false>
+__device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const Sweep2Coef& k,
+                                       const s16x4& identity = s16x4{}) {
+  auto unpack8 = [&](const uint4& v, float x[8]) {
+    if constexpr (MFMA)
+      unpack8_mfma(v, identity, x);
+    else
+      npd::unpack8(v, x);
+  };
   float xs[8], gv[8];
   unpack8(vs, xs);
   if constexpr (DIVK == kReverseKl) {
@@ -163,7 +183,7 @@ __device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const S
   } else if constexpr (TEACHER == kDense) {
     float xt[8];
     unpack8(vt, xt);
-    if constexpr (FORM == kFolded) {
+    if constexpr (FORM == kFolded || FORM == kFoldedPlus) {
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         gv[j] = exp2_fast(__builtin_fmaf(xs[j], k.c, -k.fs)) - exp2_fast(__builtin_fmaf(xt[j], k.c, -k.ft));
@@ -178,7 +198,7 @@ __device__ __forceinline__ uint4 grad8(const uint4& vs, const uint4& vt, const S
       }
     }
   } else {
-    if constexpr (FORM == kFolded) {
+    if constexpr (FORM == kFolded || FORM == kFoldedPlus) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) gv[j] = exp2_fast(__builtin_fmaf(xs[j], k.c, -k.fs));
     } else {

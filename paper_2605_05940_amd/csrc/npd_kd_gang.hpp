@@ -40,36 +40,61 @@ constexpr int kGangSpinLimitDefault = 1 << 20;    // polls before a workgroup gi
 __device__ __forceinline__ float lane63(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
+__device__ __forceinline__ float lane0(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
 // Sum / maximum over the 64 lanes, every lane gets the result: pairs, quads, half rows, rows of 16, then lane 15 of
 // rows 0 / 2 into rows 1 / 3 and lane 31 into rows 2 and 3, so that lane 63 holds everything.  Each step is one
 // instruction whose first operand is read through DPP (lanes that a row mask leaves out keep their value); written out
 // because the compiler spends four instructions per step on the maximum.  A DPP operand must not be read within two
 // wait states of the instruction that wrote it: hence the s_nop in front of every step.
-#define NPD_DPP_REDUCE(op)                                                  \
-  "s_nop 4\n" op " %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n" \
-  "s_nop 1\n" op " %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n" \
-  "s_nop 1\n" op " %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n"     \
-  "s_nop 1\n" op " %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n"          \
-  "s_nop 1\n" op " %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n"        \
-  "s_nop 1\n" op " %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n"        \
+// LANES < 64: only the first LANES lanes hold something and lane 0 gives the result -- the same steps as far as they change
+// it.
+#define NPD_DPP_STEP(op, how) "s_nop 1\n" op " %0, %0, %0 " how "\n"
+#define NPD_DPP_REDUCE4(op)                                                          \
+  "s_nop 4\n" op " %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"      \
+  NPD_DPP_STEP(op, "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
+#define NPD_DPP_REDUCE16(op)                                                         \
+  NPD_DPP_REDUCE4(op)                                                                \
+  NPD_DPP_STEP(op, "row_half_mirror row_mask:0xf bank_mask:0xf")                     \
+  NPD_DPP_STEP(op, "row_mirror row_mask:0xf bank_mask:0xf")
+#define NPD_DPP_REDUCE(op)                                                           \
+  NPD_DPP_REDUCE16(op)                                                               \
+  NPD_DPP_STEP(op, "row_bcast:15 row_mask:0xa bank_mask:0xf")                        \
+  NPD_DPP_STEP(op, "row_bcast:31 row_mask:0xc bank_mask:0xf")                        \
   "s_nop 1\n"
+template <int LANES = kWave>
 __device__ __forceinline__ float wave_sum_dpp(float x) {
-  asm volatile(NPD_DPP_REDUCE("v_add_f32_dpp") : "+v"(x));
-  return lane63(x);
+  static_assert(LANES == 4 || LANES == 16 || LANES == kWave, "");
+  if constexpr (LANES == 4)
+    asm volatile(NPD_DPP_REDUCE4("v_add_f32_dpp") "s_nop 1\n" : "+v"(x));
+  else if constexpr (LANES == 16)
+    asm volatile(NPD_DPP_REDUCE16("v_add_f32_dpp") "s_nop 1\n" : "+v"(x));
+  else
+    asm volatile(NPD_DPP_REDUCE("v_add_f32_dpp") : "+v"(x));
+  return LANES == kWave ? lane63(x) : lane0(x);
 }
+template <int LANES = kWave>
 __device__ __forceinline__ float wave_max_dpp(float x) {
-  asm volatile(NPD_DPP_REDUCE("v_max_f32_dpp") : "+v"(x));
-  return lane63(x);
+  if constexpr (LANES == 4)
+    asm volatile(NPD_DPP_REDUCE4("v_max_f32_dpp") "s_nop 1\n" : "+v"(x));
+  else if constexpr (LANES == 16)
+    asm volatile(NPD_DPP_REDUCE16("v_max_f32_dpp") "s_nop 1\n" : "+v"(x));
+  else
+    asm volatile(NPD_DPP_REDUCE("v_max_f32_dpp") : "+v"(x));
+  return LANES == kWave ? lane63(x) : lane0(x);
 }
 // merges the 64 lanes' partials (sum = z 2^r, cross term a 2^r); every lane returns with the total
-template <bool CROSS>
+template <bool CROSS, int LANES = kWave>
 __device__ __forceinline__ void wave_merge_rescaled(Lse& v) {
-  const float R = wave_max_dpp(v.r);
+  const float R = wave_max_dpp<LANES>(v.r);
   const float f = exp2_fast(v.r - R);  // exactly 1 where r == R; 0 for empty partials far below
-  v.z = wave_sum_dpp(__fmul_rn(v.z, f));
-  if constexpr (CROSS) v.a = wave_sum_dpp(__fmul_rn(v.a, f));
+  v.z = wave_sum_dpp<LANES>(__fmul_rn(v.z, f));
+  if constexpr (CROSS) v.a = wave_sum_dpp<LANES>(__fmul_rn(v.a, f));
   v.r = R;
 }
+// the lanes that a merge of n partials goes through
+constexpr int merge_lanes(int n) { return n <= 4 ? 4 : n <= 16 ? 16 : kWave; }
 // a lane's partial with its sum brought into [1, 2): r takes up the exponent of z, so that later rescaling to a
 // larger reference can only shrink values (z may be anywhere below 2^100 when the reference was a guess)
 __device__ __forceinline__ void normalise(Lse& v) {
@@ -396,44 +421,68 @@ kd_gang_kernel(const KdArgs a) {
       acc[3].r = 2.0f * acc[1].r;
     }
   }
+  // The forward and the reverse KL unpack with the matrix cores (a logit that is not finite shows in the sums as above) where
+  // a thread has more than four groups; shorter rows wait for latencies, not for the vector ALUs.  Measured (MI355X, us,
+  // shifts and masks / this, same bits; with the shorter merges and the folded form without its sign): 8,192 rows of 50,003
+  // 376 / 364, 24,576 at tau = 2 232 / 210 and with a CE term 251 / 221, 50,304 at tau = 2 424 / 400, 4,096 x 151,936 at
+  // tau = 2 with a CE term 458 / 453; 64 rows of 4,096 (four groups per thread) 4.9 / 5.2.
+  constexpr bool MFMA = !SKEW && K > 4;
+  const s16x4 identity = lane_identity(kBf16One);
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
+  auto add_group = [&](const float (&xs)[8], const float (&xt)[8], const float (&d)[8], int k) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float es = exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
+      const float et = exp2_fast(__builtin_fmaf(xt[j], c, -acc[1].r));
+      acc[0].z += es;
+      acc[1].z += et;
+      if constexpr (REV)
+        acc[0].a = __builtin_fmaf(es, MFMA ? d[j] : xs[j] - xt[j], acc[0].a);
+      else if constexpr (!SKEW)
+        acc[1].a = __builtin_fmaf(et, MFMA ? d[j] : xt[j] - xs[j], acc[1].a);
+      if constexpr (SKEW) {
+        cp[k][j] = es;
+        cv[k][j] = et;
+      }
+      if constexpr (L1 == kL1Square) {
+        acc[2].z = __builtin_fmaf(es, es, acc[2].z);
+        acc[3].z = __builtin_fmaf(et, et, acc[3].z);
+      }
+      if constexpr (L1 == kL1Own) {
+        acc[2].z += exp2_fast(__builtin_fmaf(xs[j], kLog2e, -acc[2].r));
+        if (lse1_t) acc[3].z += exp2_fast(__builtin_fmaf(xt[j], kLog2e, -acc[3].r));
+      }
+    }
+  };
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    if (k < n_mine) {
-      float xs[8], xt[8];
+    float xs[8], xt[8], d[8] = {};
+    if constexpr (MFMA) {
+      if (k * TH + wave0 < ng) {  // uniform: a group for the wave's first lane at least
+        unpack8_mfma(sreg[k], identity, xs);
+        unpack8_mfma(treg[k], identity, xt);
+        const s16x4 minus = identity ^ (short)0x8000;
+        if constexpr (REV)
+          mfma8(treg[k], minus, xs, d);
+        else
+          mfma8(sreg[k], minus, xt, d);
+        if (k < n_mine) add_group(xs, xt, d, k);
+      }
+    } else if (k < n_mine) {
       unpack8(sreg[k], xs);
       unpack8(treg[k], xt);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float es = exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
-        const float et = exp2_fast(__builtin_fmaf(xt[j], c, -acc[1].r));
-        acc[0].z += es;
-        acc[1].z += et;
-        if constexpr (REV)
-          acc[0].a = __builtin_fmaf(es, xs[j] - xt[j], acc[0].a);
-        else if constexpr (!SKEW)
-          acc[1].a = __builtin_fmaf(et, xt[j] - xs[j], acc[1].a);
-        if constexpr (SKEW) {
-          cp[k][j] = es;
-          cv[k][j] = et;
-        }
-        if constexpr (L1 == kL1Square) {
-          acc[2].z = __builtin_fmaf(es, es, acc[2].z);
-          acc[3].z = __builtin_fmaf(et, et, acc[3].z);
-        }
-        if constexpr (L1 == kL1Own) {
-          acc[2].z += exp2_fast(__builtin_fmaf(xs[j], kLog2e, -acc[2].r));
-          if (lse1_t) acc[3].z += exp2_fast(__builtin_fmaf(xt[j], kLog2e, -acc[3].r));
-        }
-      }
+      add_group(xs, xt, d, k);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
+  bool all_finite = true;  // wave-uniform: no infinity or NaN among the wave's logits
   {
     constexpr float kBig = 1.2676506e30f;  // 2^100
     bool odd = false;
 #pragma unroll
     for (int i = 0; i < NS; ++i) odd = odd || !(acc[i].z < kBig) || !(fabsf(acc[i].a) < kBig);
     if (__builtin_amdgcn_ballot_w64(odd) != 0) {  // wave-uniform
+      all_finite = false;
 #pragma unroll
       for (int i = 0; i < NS; ++i) acc[i].init();
       if constexpr (SKEW) {  // the packed logits are gone: fetched again (rare; they are still in a cache)
@@ -515,9 +564,9 @@ kd_gang_kernel(const KdArgs a) {
         acc[i].a = red[(i * 3 + 2) * NWV + lane];
       }
       if (i == (REV ? 0 : 1) && !SKEW)  // the stream that carries the cross term
-        wave_merge_rescaled<true>(acc[i]);
+        wave_merge_rescaled<true, merge_lanes(NWV)>(acc[i]);
       else
-        wave_merge_rescaled<false>(acc[i]);
+        wave_merge_rescaled<false, merge_lanes(NWV)>(acc[i]);
     }
 
   }
@@ -552,10 +601,18 @@ kd_gang_kernel(const KdArgs a) {
         acc[i].z = __builtin_bit_cast(float, xch[lane * W + i * 3 + 1]);
         acc[i].a = __builtin_bit_cast(float, xch[lane * W + i * 3 + 2]);
       }
-      if (i == (REV ? 0 : 1) && !SKEW)  // the stream that carries the cross term
-        wave_merge_rescaled<true>(acc[i]);
-      else
-        wave_merge_rescaled<false>(acc[i]);
+      constexpr bool kCross = !SKEW;
+      if (G <= 16) {  // uniform
+        if (kCross && i == (REV ? 0 : 1))  // the stream that carries the cross term
+          wave_merge_rescaled<true, 16>(acc[i]);
+        else
+          wave_merge_rescaled<false, 16>(acc[i]);
+      } else {
+        if (kCross && i == (REV ? 0 : 1))
+          wave_merge_rescaled<true>(acc[i]);
+        else
+          wave_merge_rescaled<false>(acc[i]);
+      }
     }
   }
 
@@ -569,7 +626,10 @@ kd_gang_kernel(const KdArgs a) {
   // student's normaliser at tau = 1 that sweep 1 has summed anyway.
   const bool ce = a.cscale != 0.0f;
   const float cs_shared = LSE1 ? 0.0f : a.cscale;  // weight of a CE term that shares the KD term's softmax
-  Sweep2Coef kf = sweep2_coef(acc[0], acc[1], acc[LSE1 ? 2 : 0], c, a.gscale, a.cscale, true, true, LSE1);
+  Sweep2Coef kf = folded_coef(acc[0], acc[1], c, a.gscale, a.cscale, true, LSE1);
+  kf.folded = kf.folded && !a.ragged && !(SOLO && V < kCachedMinVocab);
+  if (!MFMA || REV || !kf.folded || last || (ce && own_y))  // uniform: the folded form alone needs none of these quotients
+    set_precise_coef(kf, acc[0], acc[1], acc[LSE1 ? 2 : 0], c, a.gscale, a.cscale, true, LSE1);
   SkewCoef ks;
   if constexpr (SKEW) {
     // ---- sweep 2 of the skew forms over the registers: D and ubar need the row's normalisers in every term
@@ -637,7 +697,6 @@ kd_gang_kernel(const KdArgs a) {
       ks.Av = g;
     }
   }
-  kf.folded = kf.folded && !a.ragged && !(SOLO && V < kCachedMinVocab);
   if constexpr (REV) {
     const float inv_z = 1.0f / acc[0].z;
     kf.ra = a.gscale * a.inv_tau * inv_z;
@@ -736,17 +795,29 @@ kd_gang_kernel(const KdArgs a) {
   }
   // The walk over the slice, last group first.  Unpacked again from the packed registers (`opaque`) instead of keeping
   // sweep 1's floats alive.
-  auto walk = [&](auto form) {
+  auto walk_unpacked = [&](auto form, auto mfma) __attribute__((always_inline)) {
     constexpr int FORM = decltype(form)::value;
+    constexpr bool M = decltype(mfma)::value;
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
+      if constexpr (MFMA)
+        if (k * TH + wave0 >= ng) continue;  // uniform
       opaque(sreg[k]);
       opaque(treg[k]);
-      uint4 o = grad8<kDense, FORM, DIVK>(sreg[k], treg[k], kf);
+      uint4 o = grad8<kDense, FORM, DIVK, M>(sreg[k], treg[k], kf, identity);
       if (k == k_y) patch_label(o);  // uniform
       if (k < n_mine) store(k, o);
       __builtin_amdgcn_sched_barrier(0);
     }
+  };
+  auto walk = [&](auto form) __attribute__((always_inline)) {
+    if constexpr (MFMA) {
+      if (all_finite) {  // wave-uniform
+        walk_unpacked(form, std::true_type{});
+        return;
+      }
+    }
+    walk_unpacked(form, std::false_type{});
   };
   if constexpr (SKEW) {
     if (L1 == kL1Own && ce) {  // uniform: the packed student logits are gone, their slice is fetched again (this workgroup has
@@ -783,7 +854,9 @@ kd_gang_kernel(const KdArgs a) {
     }
   } else if (LSE1 && ce) {  // uniform
     walk(std::integral_constant<int, L1 == kL1Square ? kPreciseCeSquare : kPreciseCeOwn>{});
-  } else if (kf.folded) {  // uniform
+  } else if (MFMA && kf.folded && (REV || kf.sign == 0)) {  // uniform
+    walk(std::integral_constant<int, kFoldedPlus>{});
+  } else if (kf.folded) {
     walk(std::integral_constant<int, kFolded>{});
   } else if (ce) {  // rows at any offset, or whose reference exponents are in the thousands: precise form
     walk(std::integral_constant<int, kPreciseCe>{});

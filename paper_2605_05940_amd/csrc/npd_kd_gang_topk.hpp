@@ -223,14 +223,14 @@ kd_gang_topk_kernel(const KdArgs a) {
         st[i].r = red[(i * 2 + 0) * NWV + lane];
         st[i].z = red[(i * 2 + 1) * NWV + lane];
       }
-      wave_merge_rescaled<false>(st[i]);
+      wave_merge_rescaled<false, merge_lanes(NWV)>(st[i]);
     }
     tt.init();
     if (lane < NWV) {
       tt.r = red[4 * NWV + lane];
       tt.z = red[5 * NWV + lane];
     }
-    wave_merge_rescaled<false>(tt);
+    wave_merge_rescaled<false, merge_lanes(NWV)>(tt);
     bad_index = __builtin_amdgcn_ballot_w64(lane < NWV && red[6 * NWV + (lane & (NWV - 1))] != 0.0f) != 0;  // uniform
   }
 
@@ -265,7 +265,10 @@ kd_gang_topk_kernel(const KdArgs a) {
         st[i].r = __builtin_bit_cast(float, xch[lane * W + i * 3 + 0]);
         st[i].z = __builtin_bit_cast(float, xch[lane * W + i * 3 + 1]);
       }
-      wave_merge_rescaled<false>(st[i]);
+      if (G <= 16)  // uniform
+        wave_merge_rescaled<false, 16>(st[i]);
+      else
+        wave_merge_rescaled<false>(st[i]);
     }
   }
 

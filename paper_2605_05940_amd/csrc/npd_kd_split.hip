@@ -71,19 +71,28 @@ __global__ __launch_bounds__(kSplitThreads, 4) void kd_split_kernel(const KdArgs
       if constexpr (LSE1) acc[3].r = __builtin_rintf(__builtin_fmaxf(ft * kLog2e, -1.0e30f));
     }
   }
+  // A dense teacher's logits are unpacked, and subtracted, by the matrix cores (a logit that is not finite shows in the sums):
+  // 6,000 rows of 151,936 549 / 533 us, at tau = 2 with NLLs 652 / 633; of 50,304 177 / 180, 225 / 218.
+  const s16x4 identity = lane_identity(kBf16One);
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
 #pragma unroll
   for (int k = 0; k < K; ++k) {
+    float xs[8], xt[8], d[8];
+    if constexpr (DENSE) {
+      if (k * TH + wave0 >= ng) break;  // uniform: no group for this wave from here on
+      unpack8_mfma(sreg[k], identity, xs);
+      unpack8_mfma(treg[k], identity, xt);
+      mfma8(sreg[k], identity ^ (short)0x8000, xt, d);
+    }
     if (k < n_mine) {
-      float xs[8], xt[8];
-      unpack8(sreg[k], xs);
-      if constexpr (DENSE) unpack8(treg[k], xt);
+      if constexpr (!DENSE) unpack8(sreg[k], xs);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         acc[0].z += exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
         if constexpr (DENSE) {
           const float et = exp2_fast(__builtin_fmaf(xt[j], c, -acc[1].r));
           acc[1].z += et;
-          acc[1].a = __builtin_fmaf(et, xt[j] - xs[j], acc[1].a);
+          acc[1].a = __builtin_fmaf(et, d[j], acc[1].a);
         }
         if constexpr (LSE1) {
           acc[2].z += exp2_fast(__builtin_fmaf(xs[j], kLog2e, -acc[2].r));
@@ -151,7 +160,7 @@ __global__ __launch_bounds__(kSplitThreads, 4) void kd_split_kernel(const KdArgs
       acc[i].z = red[(i * 3 + 1) * NWV + lane];
       acc[i].a = red[(i * 3 + 2) * NWV + lane];
     }
-    wave_merge_rescaled<true>(acc[i]);
+    wave_merge_rescaled<true, merge_lanes(NWV)>(acc[i]);
     if (lane == 0) {
       rec[i * 3 + 0] = acc[i].r;
       rec[i * 3 + 1] = acc[i].z;
@@ -221,9 +230,9 @@ namespace {
 // Groups per thread, 0: not split.  Measured (MI355X, all scored, us, a workgroup per row / split):
 //   dense teacher, tau = 1   1 row of 151,936 19.0 / 5.9;  64 rows of 50,304 10.4 / 7.9, 151,936 21.3 / 11.6;  181 rows of
 //                            151,936 23.2 / 21.3;  256 rows of 50,304 12.1 / 13.1, 131,072 and more the same;  800 rows of
-//                            50,304 34.0 / 29.1;  6,000 rows of 50,304 188 / 185, 151,936 565 / 548
+//                            50,304 34.0 / 29.1;  6,000 rows of 50,304 188 / 180, 151,936 565 / 533
 //                            (32,000: 128 rows 8.4 / 8.2, 4,096 80.7 / 84.2)
-//   dense teacher, tau = 2, NLL wanted   128 rows of 151,936 33.4 / 23.2;  6,000 rows of 50,304 255 / 236, 151,936 792 / 662
+//   dense teacher, tau = 2, NLL wanted   128 rows of 151,936 33.4 / 23.2;  6,000 rows of 50,304 255 / 218, 151,936 792 / 633
 //   no teacher               64 rows of 65,536 6.9 / 6.2, 128 rows of 151,936 12.3 / 11.0, 4,096 of 262,144 339 / 323
 //                            (181 rows of 151,936 11.7 / 13.4, 1,024 of 200,000 63.9 / 66.1)
 // Four groups of a dense teacher per thread for few rows, eight for many (2,048 rows of 151,936 at tau = 2: 246 / 225).

@@ -366,3 +366,28 @@ def test_teacher_topk_keys_of_both_signs(oracle, T):
     ref = oracle.teacher_topk(synth.bf16_bits(t), k, None, False)
     np.testing.assert_array_equal(idx.cpu().numpy(), ref["idx"])
     np.testing.assert_array_equal(val.cpu().numpy().astype(np.float64), ref["val"])
+
+
+# threads of eight and ten groups unpack with the matrix cores, four values of a lane at a time, unless one of the wave's
+# logits is not finite
+@pytest.mark.parametrize("V", [12288, 16384, 20480, 24576, 50304, 50003])
+@pytest.mark.parametrize("div,tau,ce", [("forward", 1.0, 0.0), ("forward", 1.0, 0.25), ("forward", 2.0, 0.25),
+                                        ("forward", 3.0, 0.0), ("reverse", 1.0, 0.0), ("reverse", 2.0, 0.25)])
+def test_masked_entries_among_finite_ones(oracle, V, div, tau, ce):
+    w, lay, s, t, lab = _batch(V)
+    s, t = s.clone(), t.clone()
+    n = s.shape[0]
+    for r in range(n):                                  # rows 0, 4, ...: none; one; every 67th; both tensors or one
+        at = [] if r % 4 == 0 else [5 * r + 3] if r % 4 == 1 else list(range(r, V, 67))
+        s[r, at] = float("-inf")
+        if r % 4 != 2 or div == "reverse":              # (a teacher entry that the student masks: kd is infinite)
+            t[r, at] = float("-inf")
+        if r % 4 == 2 and div == "forward":
+            s[r, at], t[r, at] = 1.0, float("-inf")
+    y = lab.copy()
+    y[:] = 1                                            # (not a masked entry)
+    print(f"[rows] masked entries V={V} {div} tau={tau} ce={ce}", flush=True)
+    ref = _reference(oracle, lay, s, t, y, div, tau, 0.75, ce)
+    got = _call(lay, s, t, y, V=V, pitch=V, offs=(0, 0, 0), div=div, tau=tau, ce=ce)
+    compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce * tau, tau=tau,
+               amp_from_ref=div != "forward")
