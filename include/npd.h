@@ -142,7 +142,9 @@ int npd_debug_gang_spin_limit(int polls);
 /*
  * Bytes of device workspace npd_kd_loss_fwd_bwd takes for `desc` (host call; 0 is a
  * legal answer and then `workspace` may be NULL).  Required, except with ce_grad_scale != 0
- * at tau != 1, where it makes the call faster.  Returns 0 for an invalid desc.
+ * at tau != 1, where it makes the call faster.  Calls that are given twice as many bytes share a row between more
+ * workgroups where that is faster (few rows, and rows of some lengths), with the same results to rounding.
+ * Returns 0 for an invalid desc.
  */
 size_t npd_workspace_bytes(const npd_kd_desc* desc);
 

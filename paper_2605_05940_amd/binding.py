@@ -171,7 +171,7 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
 
     The teacher kind follows from which teacher tensors are given; ``grad_out is None`` means forward
     only; ``grad_out`` sharing storage with ``student_logits`` means the in-place gradient.  ``workspace``:
-    a uint8 tensor of at least ``npd_workspace_bytes`` bytes; if it is None one is taken from
+    a uint8 tensor of at least ``npd_workspace_bytes`` bytes, better twice as many; if it is None one is taken from
     ``workspace_for`` (a per-device tensor that this module keeps and grows) or, with a CE term at tau != 1 and for rows
     that are not 16-byte aligned, allocated for the call.  ``no_workspace`` sets ``NPD_FLAG_NO_WORKSPACE``.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in
     scratch array; no workspace argument).
@@ -214,7 +214,7 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
         if need:  # rows to be split over several workgroups: a block of this call's own, as below
             scratch = torch.empty(need, dtype=torch.uint8, device="cuda")
     elif workspace is None and not no_workspace and not noalloc:
-        need = L.npd_workspace_bytes(desc)
+        need = 2 * L.npd_workspace_bytes(desc)  # (twice the least: shorter slices where they are faster)
         if need and (ce_grad_scale != 0.0 and tau != 1.0 or (student_logits.data_ptr() | 2 * student_stride) & 15):
             # a CE term at tau != 1 and rows that are not 16-byte aligned: these calls can run without any scratch and
             # may run beside others on several streams: a block of this call's own, from torch's stream-ordered

@@ -308,7 +308,7 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
                                float* teacher_nll_tok, float* lse_tok, int32_t* dev_status, void* workspace,
                                size_t workspace_bytes, void* stream) {
   npd::KdArgs a{};
-  size_t need = 0;
+  size_t need = 0, have = 0;
   const npd_status st = check_kd_call(desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
                                       grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
   if (st != NPD_OK) return st;
@@ -322,11 +322,13 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
         if (!workspace_optional(*desc)) return NPD_ERR_ALIAS;
         usable = false;
       }
+      // bytes beyond those are used only where they are nobody else's
+      have = workspace_bytes >= 2 * need && !b.overlaps_any(range_of(workspace, 2 * need)) ? 2 * need : need;
     }
     a.ws = usable ? static_cast<uint32_t*>(workspace) : nullptr;
   }
   const bool want_grad = !(desc->flags & NPD_FLAG_FWD_ONLY);
-  const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, static_cast<hipStream_t>(stream));
+  const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, have, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
 }
 
@@ -351,7 +353,7 @@ npd_status npd_kd_loss_forward(const npd_kd_desc* desc, const void* student_logi
                         nll_tok, teacher_nll_tok, lse_tok, dev_status).overlaps_any(range_of(scratch, need));
   if (split) a.ws = static_cast<uint32_t*>(scratch);
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t e = split ? npd::launch_kd_split(a, desc->teacher_kind, s) : npd::launch_kd(a, desc->teacher_kind, false, s);
+  const hipError_t e = split ? npd::launch_kd_split(a, desc->teacher_kind, s) : npd::launch_kd(a, desc->teacher_kind, false, 0, s);
   return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
 }
 
@@ -376,7 +378,8 @@ npd_status npd_kd_loss_fwd_bwd_noalloc(const npd_kd_desc* desc, const void* stud
     a.ws = static_cast<uint32_t*>(scratch);
   }
   const bool want_grad = !(desc->flags & NPD_FLAG_FWD_ONLY);
-  const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, static_cast<hipStream_t>(stream));
+  const hipError_t e =
+      npd::launch_kd(a, desc->teacher_kind, want_grad, NPD_NOALLOC_WORKSPACE_BYTES, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
 }
 

@@ -1,8 +1,7 @@
 // Row-gang KD kernels (npd_kd_gang.hpp): which calls they take, the scratch record they need, and the launch.
 #include <atomic>
 
-#include "npd_kd_gang.hpp"
-#include "npd_kd_gang_topk.hpp"
+#include "npd_kd_gang_launch.hpp"
 
 namespace npd {
 
@@ -23,15 +22,18 @@ static int gang_k(int teacher_kind, int divergence) {
 
 // Slices per row.  A workgroup holds up to k * 256 groups; slices are sized to 8 groups less, because a slice is moved
 // by up to 7 groups so that it begins on a 128-byte boundary of memory (see launch_kd_gang).
+// `on_lines`: every row of the launch begins on a 128-byte boundary, no boundary is ever moved and a slice may be as
+// long as a workgroup holds (V = 102,400: 5 full slices instead of 6).
+static int gang_slices(int nvec, int k, bool on_lines) {
+  const int cap = k * kGangThreads - 8;
+  return on_lines ? (nvec + cap + 7) / (cap + 8) : (nvec + cap - 1) / cap;
+}
 // Rows of less than one and a half slices stay with one workgroup per row (1 is returned): two half-filled slices
 // cost more in exchanges than the access order gains (dense teacher, % of the HBM peak, row gangs / one workgroup per
 // row: V = 20,480 50 / 72, 24,576 67 / 74, 32,000 73 / 69, 50,304 77 / 69, 100,352 81 / 67).
-// `on_lines`: every row of the launch begins on a 128-byte boundary, no boundary is ever moved and a slice may be as
-// long as a workgroup holds (V = 102,400: 5 full slices instead of 6).
 static int gang_size(int nvec, int k, bool on_lines) {
   const int cap = k * kGangThreads - 8;
-  if (2 * nvec < 3 * cap) return 1;
-  return on_lines ? (nvec + cap + 7) / (cap + 8) : (nvec + cap - 1) / cap;
+  return 2 * nvec < 3 * cap ? 1 : gang_slices(nvec, k, on_lines);
 }
 static bool rows_on_lines(const KdArgs& a) {
   return a.g != nullptr && (reinterpret_cast<uintptr_t>(a.g) & 127u) == 0 && a.s_stride % 64 == 0;
@@ -60,44 +62,60 @@ __global__ __launch_bounds__(256) void gang_clear_kernel(uint32_t* ws, size_t wo
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) ws[i] = kGangEmpty;
 }
 
-template <class Kernel>
-static hipError_t launch_gang_kernel(const KdArgs& a, int words_per_slice, Kernel kernel, hipStream_t stream,
-                                     size_t lds_bytes = 0) {
-  const size_t words = (size_t)a.T * a.gang * words_per_slice + kGangTailWords;
+hipError_t clear_gang_record(uint32_t* ws, size_t words, hipStream_t stream) {
   const int64_t want = (int64_t)((words + 1023) / 1024);  // four words per thread
-  const int64_t clear_grid = want < 8 * (int64_t)compute_units() ? want : 8 * (int64_t)compute_units();
-  const hipError_t e = launch_kernel(gang_clear_kernel, dim3((unsigned)clear_grid), dim3(256), 0, stream, a.ws, words);
-  if (e != hipSuccess) return e;
-  return launch_kernel(kernel, dim3((unsigned)(a.T * a.gang)), dim3(kGangThreads), lds_bytes, stream, a);
+  const int64_t grid = want < 8 * (int64_t)compute_units() ? want : 8 * (int64_t)compute_units();
+  return launch_kernel(gang_clear_kernel, dim3((unsigned)grid), dim3(256), 0, stream, ws, words);
+}
+
+// Shorter slices, for calls whose workspace has room for their record (at most twice the bytes a call asks for, so that
+// what a call runs does not depend on how much more it was given): groups per thread, 0: none.
+//   5  calls of so few rows that all their slices run at once, and wait for the latency of each step of a slice.
+//      Measured (MI355X, all scored, us with the clearing launch, 10 groups / 5): dense, tau = 1 32 rows of 32,000 10.0 /
+//      8.5, 128 11.4 / 10.4, 64 rows of 50,304 11.8 / 10.9, 256 19.3 / 18.2, 32 of 100,352 12.3 / 10.9, 128 19.9 / 17.7, 64 of
+//      151,936 15.4 / 14.9, 128 24.6 / 27.3; tau = 2 64 of 50,304 13.1 / 12.0; top-k 64 of 40,960 10.4 / 8.9
+//   7  tau = 1, rows that two slices of 10 groups fill to four fifths and more, or three to two thirds: one more workgroup
+//      per compute unit (94 registers), and no register left empty.  10,000 rows of 36,000 379 / 342, top-k (40 entries)
+//      281 / 248; of 40,960 395 / 386, 289 / 275 (32,000 308 / 306, 50,304 475 / 474; with sums at tau = 1 the registers
+//      do not allow that workgroup: 36,000 tau = 2 with a CE term 382 / 401)
+static int fine_groups(int64_t T, int nvec, int teacher_kind, int divergence, bool lse1) {
+  if (divergence != kForwardKl && divergence != kReverseKl) return 0;
+  const int g = gang_slices(nvec, 5, false);
+  if (g <= kGangMax && T * g <= 1400) return 5;
+  return !lse1 && nvec > 4080 && nvec <= 5352 ? 7 : 0;
 }
 
 template <int DIVK>
 static hipError_t launch_gang(const KdArgs& a, hipStream_t stream) {
-  constexpr int K = DIVK == kSkewKl || DIVK == kSkewReverseKl ? kGangSkewK : kGangK;
-  switch (l1_mode(a)) {
-    case kL1None: return launch_gang_kernel(a, gang_words(2), kd_gang_kernel<K, kDense, kL1None, DIVK>, stream);
-    case kL1Square: return launch_gang_kernel(a, gang_words(4), kd_gang_kernel<K, kDense, kL1Square, DIVK>, stream);
-    default: return launch_gang_kernel(a, gang_words(4), kd_gang_kernel<K, kDense, kL1Own, DIVK>, stream);
-  }
+  return launch_gang_dense<DIVK, DIVK == kSkewKl || DIVK == kSkewReverseKl ? kGangSkewK : kGangK>(a, stream);
 }
 
-hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, hipStream_t stream) {
+hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_bytes, hipStream_t stream) {
   KdArgs a = a0;
-  a.gang = gang_size(a.nvec_s, gang_k(teacher_kind, a.divergence), rows_on_lines(a));
+  const bool on_lines = rows_on_lines(a);
+  const int base = gang_size(a.nvec_s, gang_k(teacher_kind, a.divergence), on_lines);
+  a.gang = base;
+  int k = fine_groups(a.T, a.nvec_s, teacher_kind, a.divergence, a.need_lse1 != 0);
+  if (k > 0) {
+    const int g = gang_slices(a.nvec_s, k, on_lines);
+    const int words = gang_words(teacher_kind == kTopk || !a.need_lse1 ? 2 : 4);
+    const size_t bytes = ((size_t)a.T * g * words + kGangTailWords) * sizeof(uint32_t);
+    const size_t asked =
+        gang_workspace_bytes(a.T, a.V, teacher_kind, a.divergence, teacher_kind == kDense && a.c != kLog2e);
+    if (g >= 2 && bytes <= workspace_bytes && bytes <= 2 * asked)
+      a.gang = g;
+    else
+      k = 0;
+  }
   // Slices are multiples of 8 groups = 128 bytes long, and the kernels move every boundary inside a row down to the
   // next 128-byte boundary of the gradient row's address (by 0 .. 7 groups: a row whose pitch is not a multiple of 128
   // bytes begins anywhere): no cache line is then shared by two workgroups of a row -- measured +2.4 points of the HBM
-  // peak on config 1, +2.5 on config 4, +3.6 on config 2; a row pitch of 16 bytes more than config 1's: +4.
+  // peak on 32,768 x 151,936, +2.5 on 262,144 logits in place, +3.6 with a top-k teacher; a row pitch of 16 bytes more than
+  // 151,936 logits: +4.
   a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;
   a.spin_limit = g_spin_limit.load(std::memory_order_relaxed);
-  if (teacher_kind == kTopk) {
-    const size_t lds = (size_t)topk_lds_words(kGangThreads, kGangTopkK, a.k, false) * sizeof(uint32_t);
-    switch (l1_mode(a)) {
-      case kL1None: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1None>, stream, lds);
-      case kL1Square: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Square>, stream, lds);
-      default: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<kGangTopkK, kL1Own>, stream, lds);
-    }
-  }
+  if (k > 0) return launch_gang_fine(a, k, teacher_kind, stream);
+  if (teacher_kind == kTopk) return launch_gang_topk<kGangTopkK>(a, stream);
   switch (a.divergence) {
     case kReverseKl: return launch_gang<kReverseKl>(a, stream);
     case kSkewKl: return launch_gang<kSkewKl>(a, stream);

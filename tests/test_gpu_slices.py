@@ -1,0 +1,86 @@
+"""Rows shared by workgroups with slices of 10, 7 or 5 groups per thread: which of them a call runs follows from its rows and
+from whether its workspace has room for the record of the shorter ones."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import compare_kd, dev
+from paper_2605_05940_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+DIVS = {"forward": 0, "reverse": 1}
+
+
+def _edges(V):
+    """First and last elements of slices of all three lengths, next to a boundary that a row's address moves, and the tail."""
+    nvec, e = V // 8, {0, V // 2, 8 * (V // 8) - 1, V - 1}
+    for cap in (2552, 1784, 1272):
+        g = -(-nvec // cap)
+        per = -(-(-(-nvec // g)) // 8) * 8
+        e |= {8 * per - 1, 8 * per, 8 * (per - 3), 8 * (g - 1) * per}
+    return sorted(x for x in e if 0 <= x < V)
+
+
+@pytest.mark.parametrize("V,pitch,T", [
+    (30624, 30624, 24), (36000, 36008, 24), (40816, 40816, 24), (50003, 50003, 24), (65536, 65536, 24), (101760, 101760, 14),
+    (151936, 151936, 12), (262144, 262144, 8), (36000, 36000, 360), (40817, 40832, 300), (42816, 42816, 290),
+])
+@pytest.mark.parametrize("what", ["forward", "forward_tau2", "reverse", "topk"])
+def test_slices_of_every_length(oracle, V, pitch, T, what):
+    w = synth.scaled(synth.config(1), n_rows=1, row_len=T, vocab=V, length_lo=4, length_hi=9)
+    lay = synth.make_layout(w)
+    g = torch.Generator(device=dev()).manual_seed(V + T)
+    s, t, grad = (torch.empty((T, pitch), dtype=torch.bfloat16, device=dev())[:, :V] for _ in range(3))
+    s.copy_(3.0 * torch.randn((T, V), generator=g, device=dev()))
+    t.copy_(0.8 * s.float() + 1.5 * torch.randn((T, V), generator=g, device=dev()))
+    mask = torch.from_numpy(lay.loss_mask).to(dev())
+    edges = _edges(V)
+    lab = np.array([edges[i % len(edges)] for i in range(T)], np.int32)
+    sb, tb = synth.bf16_bits(s.contiguous()), synth.bf16_bits(t.contiguous())
+    tau, ce = (2.0, 0.25) if what == "forward_tau2" else (1.0, 0.0 if T > 100 else 0.25)
+    kw, kind = dict(tau=tau, grad_scale=0.75, ce_grad_scale=ce), binding.NPD_TEACHER_DENSE_BF16
+    if what == "topk":
+        k, kind = 24, binding.NPD_TEACHER_TOPK
+        idx = torch.topk(t.float(), k, dim=1)[1].to(torch.int32)
+        for r in range(T):                              # support positions on the edges; the label is one of them or not
+            have = [e for e in edges if r % 2 == 0 or e != lab[r]][:k]
+            rest = [int(i) for i in idx[r].tolist() if int(i) not in have and int(i) != lab[r]][:k - len(have)]
+            idx[r] = torch.tensor(have + rest, dtype=torch.int32)
+        val = t.float().gather(1, idx.long()).contiguous()
+        ref = oracle.kd_topk(sb, idx.cpu().numpy(), val.cpu().numpy(), lab, lay.loss_mask, **kw)
+        teacher = dict(teacher_idx=idx, teacher_val=val)
+    else:
+        div = what.split("_")[0]
+        if div == "forward":
+            ref = oracle.kd_dense(sb, tb, lab, lay.loss_mask, **kw)
+        else:
+            ref = oracle.div_dense(sb, tb, div, 0.1, labels=lab, mask=lay.loss_mask, **kw)
+            nl = oracle.kd_dense(sb, tb, lab, lay.loss_mask, want_grad=False)
+            ref.update(nll_s=nl["nll_s"], nll_t=nl["nll_t"], lse_s=nl["lse_s"])
+        teacher = dict(teacher_dense=t, divergence=DIVS[div])
+    d = binding.KdDesc(T, V, kind, pitch, pitch, 24 if what == "topk" else 0, 0, tau, 0.75, ce, teacher.get("divergence", 0),
+                       0.0)
+    need = int(binding.load().npd_workspace_bytes(ctypes.byref(d)))
+    assert need > 0
+    bits = {}
+    for name, size in (("least", need), ("twice", 2 * need), ("more", 5 * need), ("binding", None)):
+        print(f"[slices] V={V} pitch={pitch} T={T} {what} workspace {name}", flush=True)
+        grad.fill_(float("nan"))
+        out = {n: torch.full((T,), -1.0, device=dev()) for n in ("kd", "nll_s", "lse_s")}
+        status = torch.zeros(1, dtype=torch.int32, device=dev())
+        ws = None if size is None else torch.full((size + 64,), 7, dtype=torch.uint8, device=dev())
+        binding.npd_kd_loss_fwd_bwd(s, mask, labels=torch.from_numpy(lab).to(dev()), grad_out=grad, kd_tok=out["kd"],
+                                    nll_tok=out["nll_s"], lse_tok=out["lse_s"], dev_status=status,
+                                    workspace=None if ws is None else ws[:size], **kw, **teacher)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0 and (ws is None or (ws[size:] == 7).all())
+        got = {n: x.cpu().numpy().astype(np.float64) for n, x in out.items()}
+        got["grad"] = grad.float().cpu().numpy().astype(np.float64)
+        compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce * tau, tau=tau,
+                   amp_from_ref=what == "reverse")
+        bits[name] = [grad.contiguous().view(torch.int16)] + [x.view(torch.int32) for x in out.values()]
+    # what runs does not depend on how much more than twice the least a call is given
+    for name in ("more", "binding"):
+        assert all(torch.equal(a, b) for a, b in zip(bits[name], bits["twice"])), name
