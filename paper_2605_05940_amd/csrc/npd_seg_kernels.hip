@@ -2,8 +2,7 @@
 // monitor of the appendix and the perplexity of a sample.
 // Both are tiny next to the loss kernel; what matters here is exact bookkeeping and a fixed
 // summation order (no floating-point atomics), so results are bitwise reproducible.
-#include "npd_device.hpp"
-#include "npd_internal.hpp"
+#include "npd_kd_gang.hpp"
 
 namespace npd {
 
@@ -13,11 +12,12 @@ __global__ __launch_bounds__(kSegBlock) void fill_i32_kernel(int32_t* p, int64_t
   for (int64_t i = blockIdx.x * (int64_t)kSegBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSegBlock) p[i] = v;
 }
 
-// Sum and number of the scored positions of [b, e): thread t of TH adds positions b + t, b + t + TH, ... in order; `own` is
-// called with every position.  What such a sum waits for is a chain of loads per position, so up to kAhead positions'
-// masks and values are requested together (values of positions that are not scored are read and left out).  Measured
-// (MI355X, in a graph): 4 samples of 8,192 positions 10.1 us one position at a time, 4.8 us so; 10 samples of 819 3.4 / 3.0.
-constexpr int kAhead = 8;
+// Sum (of a thread) and number (of its wave) of the scored positions of [b, e): thread t of TH adds positions b + t,
+// b + t + TH, ... in order; `own` is called with every position.  What such a sum waits for is a chain of loads per position,
+// so up to kSumAhead positions' masks and values are requested together (values of positions that are not scored are read
+// and left out).  Measured (MI355X, in a graph): 4 samples of 8,192 positions 10.1 us one position at a time, 4.8 us so; 10
+// samples of 819 3.4 / 3.0.
+constexpr int kSumAhead = 8;
 template <int TH, int N, class Own>
 __device__ __forceinline__ void masked_sum_step(const float* __restrict__ x, const uint8_t* __restrict__ mask, int64_t p0,
                                                 int64_t e, int tid, float& acc, int& n, Own own) {
@@ -33,20 +33,17 @@ __device__ __forceinline__ void masked_sum_step(const float* __restrict__ x, con
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int64_t p = p0 + i * TH + tid;
-    if (p < e) {
-      own(p);
-      if (m[i]) {
-        acc += v[i];
-        n += 1;
-      }
-    }
+    const bool scored = p < e && m[i];
+    if (p < e) own(p);
+    if (scored) acc += v[i];
+    n += (int)__popcll(__ballot(scored));  // of the wave
   }
 }
 template <int TH, class Own>
 __device__ __forceinline__ void masked_sum(const float* __restrict__ x, const uint8_t* __restrict__ mask, int64_t b, int64_t e,
                                            int tid, float& acc, int& n, Own own) {
   int64_t p = b;
-  for (; e - p > TH; p += kAhead * TH) masked_sum_step<TH, kAhead>(x, mask, p, e, tid, acc, n, own);
+  for (; e - p > TH; p += kSumAhead * TH) masked_sum_step<TH, kSumAhead>(x, mask, p, e, tid, acc, n, own);
   if (p < e) masked_sum_step<TH, 1>(x, mask, p, e, tid, acc, n, own);
 }
 
@@ -70,9 +67,8 @@ __device__ __forceinline__ void reduce_segment(int64_t T, int seg, int tid, cons
   masked_sum<kSegBlock>(x, mask, b, e, tid, acc, n, [&](int64_t p) {
     if (token_to_sample) token_to_sample[p] = seg;
   });
-  // the 256 partials are folded by the fixed shuffle tree, the four wave totals in wave order
-  acc = wave_sum(acc);
-  n = wave_sum_int(n);
+  // the 256 partials are folded by a fixed tree, the four wave totals in wave order
+  acc = wave_sum_dpp(acc);
   if ((tid & (kWave - 1)) == 0) {
     fred[tid / kWave] = acc;
     ired[tid / kWave] = n;
@@ -204,7 +200,7 @@ constexpr int kLagBlock = 1024;
 // Thread t adds positions begin + t, begin + t + 1024, ... in order, then one fixed tree: reproducible.
 // Workgroups 1 ..: the means of four samples each, if they are wanted.  Both in one launch: the sums do not depend on one
 // another, and each by itself is a few microseconds of waiting (MI355X, in a graph, two launches and one position at a
-// time / this: 64 positions 5.5 / 3.5 us, 8,192 8.1 / 4.0, 32,768 20.5 / 6.1).
+// time / this: 64 positions 5.5 / 2.7 us, 8,192 8.1 / 3.5, 32,768 20.5 / 6.1).
 __global__ __launch_bounds__(kLagBlock) void policy_lag_kernel(int64_t T, int32_t S, const float* __restrict__ kl,
                                                                const uint8_t* __restrict__ mask,
                                                                const int32_t* __restrict__ cu, float epsilon,
@@ -228,8 +224,18 @@ __global__ __launch_bounds__(kLagBlock) void policy_lag_kernel(int64_t T, int32_
   float acc = 0.0f;
   int n = 0;
   if (!bad && S > 0) masked_sum<kLagBlock>(kl, mask, cu[0], cu[S], threadIdx.x, acc, n, [](int64_t) {});
-  acc = block_sum<kLagBlock>(acc, fred);
-  n = block_sum_int<kLagBlock>(n, ired);
+  constexpr int NW = kLagBlock / kWave;
+  const int lane = threadIdx.x % kWave;
+  acc = wave_sum_dpp(acc);
+  if (lane == 0) {
+    fred[threadIdx.x / kWave] = acc;
+    ired[threadIdx.x / kWave] = n;
+  }
+  __syncthreads();
+  acc = wave_sum_dpp<merge_lanes(NW)>(lane < NW ? fred[lane] : 0.0f);
+  n = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) n += ired[w];
   if (threadIdx.x == 0) {
     const float mean = bad ? __builtin_nanf("") : (n > 0 ? acc / (float)n : 0.0f);
     if (batch_mean) *batch_mean = mean;
