@@ -433,14 +433,15 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
 #endif  // NPD_TOPK_ANY_SHAPE
 
 // ------------------------------------------------------------------------------------------------ one read
-constexpr uint32_t kFillPair = 0xff80ff80u;  // two bf16 -inf: below every element, and never a candidate (id >= V)
-
-// one 16-byte group of a row; 32-bit byte offsets keep the address in one VGPR next to the scalar row base
+// One 16-byte group of a row; 32-bit byte offsets keep the address in one VGPR next to the scalar row base.  `i` past the
+// row's groups: group 0 instead, to be left out by the caller.  No branch around a load, here or in the loop over full
+// windows below: the compiler cannot tell then how many loads are under way, and waits for all of them at every group
+// (MI355X, all scored, with / without the branches: 151,936 logits, k = 64, 1,024 rows 58.2 / 54.0 us, 4,096 205 / 195;
+// k = 256, 4,096 rows 268 / 234; 8 rows of 262,144 k = 10 21.9 / 17.0; where the memory is the limit, 8,192 rows of 262,144
+// k = 10, 649 / 668).
 __device__ __forceinline__ u32x4 load_group(const uint16_t* trow, int i, int nvec) {
-  u32x4 v = u32x4{kFillPair, kFillPair, kFillPair, kFillPair};
-  const uint32_t off = (uint32_t)i * 16u;
-  if (i < nvec) v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(trow) + off));
-  return v;
+  const uint32_t off = i < nvec ? (uint32_t)i * 16u : 0u;
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(trow) + off));
 }
 
 __device__ __forceinline__ void append(TopkShared& sh, int o, int id) {
@@ -452,10 +453,9 @@ __device__ __forceinline__ void append(TopkShared& sh, int o, int id) {
 // A group with an element >= Lp goes to the LDS list whole (its patterns and its index): one exchange and two writes
 // instead of a test of its eight elements by one lane out of 64; they are tested later, a group to a thread (8,192 rows
 // of 151,936, all scored, 512 threads: k = 64 414 -> 385 us, k = 10 397 -> 390; 50,304 k = 128 199 -> 175).
-template <bool ORDERED>
-__device__ __forceinline__ void append_group(const u32x4& v, int i, int Lp, int nvec, int head, TopkShared& sh) {
+__device__ __forceinline__ void append_group(const u32x4& v, int i, int Lp, bool ordered, int nvec, int head, TopkShared& sh) {
   uint32_t d[4] = {v.x, v.y, v.z, v.w};
-  if (ORDERED) {
+  if (ordered) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) d[q] = pk_ordered(d[q]);
   }
@@ -477,13 +477,12 @@ __device__ __forceinline__ void append_group(const u32x4& v, int i, int Lp, int 
 }
 #endif
 
-// candidates of one register group: elements whose ordered value is >= Lp.  With ORDERED = false the patterns are
-// compared as they are, which is the same thing for Lp >= 1 (patterns of positive values are ordered integers,
+// candidates of one register group: elements whose ordered value is >= Lp.  With `ordered` false (uniform) the patterns
+// are compared as they are, which is the same thing for Lp >= 1 (patterns of positive values are ordered integers,
 // those of negative values are negative integers).
-template <bool ORDERED>
-__device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, int nvec, int head, TopkShared& sh) {
+__device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, bool ordered, int nvec, int head, TopkShared& sh) {
   uint32_t d[4] = {v.x, v.y, v.z, v.w};
-  if (ORDERED) {
+  if (ordered) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) d[q] = pk_ordered(d[q]);
   }
@@ -499,7 +498,7 @@ __device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, int
 }
 
 // W = register window (groups in flight per thread), S <= W = groups of the sample that gives the bound.
-// ngroups = ceil(nvec / kTB) >= 1 groups are visited in the order (g * step) mod ngroups, step coprime to ngroups.
+// ngroups = ceil(nvec / kTB) >= 1 groups are visited in the order (g * step) mod ngroups, step < ngroups coprime to it.
 // RAGGED: rows begin anywhere inside a 16-byte group.
 template <int W, int S, bool RAGGED, int WAVES = 8>
 __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const TopkArgs a, int ngroups, int step) {
@@ -515,23 +514,36 @@ __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const T
   const RowSplit sp = RAGGED ? row_split(trow, V, true) : RowSplit{0, a.nvec};
   const int nvec = sp.nvec, head = sp.head, n_edge = V - nvec * 8;
   const uint16_t* tvec = trow + head;
-  auto vec_index = [&](int g) { return ((g * step) % ngroups) * kTB + tid; };
+  int at_load = 0, at_test = 0;  // uniform
+  auto visit = [&](int& at) {
+    const int i = at * kTB + tid;
+    at += step;
+    at -= at >= ngroups ? ngroups : 0;
+    return i;
+  };
 
   u32x4 w[W];
 #pragma unroll
-  for (int j = 0; j < W; ++j) w[j] = load_group(tvec, vec_index(j), j < ngroups ? nvec : 0);
+  for (int j = 0; j < W; ++j) {
+    const int i = visit(at_load);
+    w[j] = u32x4{0u, 0u, 0u, 0u};
+    if (j < ngroups) w[j] = load_group(tvec, i, nvec);
+  }
 
   // ---- one maximum per thread over the sample, in value order: the largest non-negative pattern if there is one,
   // else the smallest negative pattern (sign-magnitude: the one closest to zero).  Group 0 is full (nvec >= kTB),
   // so every thread's maximum is an element of the row.
   short2v mx2 = as_s2(0x80008000u), mn2 = as_s2(0x7fff7fffu);
+  {
+    int at = 0;
 #pragma unroll
-  for (int j = 0; j < S; ++j) {
-    const uint32_t d[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      mx2 = pk_max(mx2, as_s2(d[q]));
-      mn2 = pk_min(mn2, as_s2(d[q]));
+    for (int j = 0; j < S; ++j) {
+      const bool mine = visit(at) < nvec && j < ngroups;
+      const uint32_t d[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
+      const short2v mx = pk_max(pk_max(as_s2(d[0]), as_s2(d[1])), pk_max(as_s2(d[2]), as_s2(d[3])));
+      const short2v mn = pk_min(pk_min(as_s2(d[0]), as_s2(d[1])), pk_min(as_s2(d[2]), as_s2(d[3])));
+      mx2 = pk_max(mx2, mine ? mx : as_s2(0x80008000u));
+      mn2 = pk_min(mn2, mine ? mn : as_s2(0x7fff7fffu));
     }
   }
   const int hi = max((int)mx2.x, (int)mx2.y), lo = min((int)mn2.x, (int)mn2.y);
@@ -563,30 +575,39 @@ __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const T
     for (int q = 1; q < kTB / kWave; ++q) L = min(L, sh.wave_bound[q]);
     const int Lp = L == 0 ? -1 : L;  // +0 and -0 are one value
     // ---- the row streams through the window; every group is tested as it arrives and replaced by a later one
-    for (int base = 0; base < ngroups; base += W) {
+    const bool ordered = Lp < 1;  // uniform; patterns of positive values are ordered as they are
+    auto test = [&](const u32x4& v) __attribute__((always_inline)) {
+      const int i = visit(at_test);
+#if NPD_TOPK_GROUPS
+      append_group(v, i, Lp, ordered, nvec, head, sh);
+#else
+      collect_group(v, i, Lp, ordered, nvec, head, sh);
+#endif
+    };
+    int left = ngroups;  // groups not tested yet; the first W of them are in the window
+    for (; left >= 2 * W; left -= W) {
 #pragma unroll
       for (int j = 0; j < W; ++j) {
-        const int g = base + j;
-        if (g < ngroups) {
-#if NPD_TOPK_GROUPS
-          if (Lp >= 1)
-            append_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
-          else
-            append_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
-#else
-          if (Lp >= 1)
-            collect_group<false>(w[j], vec_index(g), Lp, nvec, head, sh);
-          else
-            collect_group<true>(w[j], vec_index(g), Lp, nvec, head, sh);
-#endif
-        }
-        if (g + W < ngroups) w[j] = load_group(tvec, vec_index(g + W), nvec);
+        test(w[j]);
+        w[j] = load_group(tvec, visit(at_load), nvec);
       }
     }
+    const int more = left - W;  // groups behind the window, fewer than W (a load for nothing costs more here than the wait)
+    if (more > 0) {
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        test(w[j]);
+        if (j < more) w[j] = load_group(tvec, visit(at_load), nvec);
+      }
+      left = more;
+    }
+#pragma unroll
+    for (int j = 0; j < W; ++j)
+      if (j < left) test(w[j]);
 #if NPD_TOPK_GROUPS
     __syncthreads();
     const int ng = min(sh.ngroups, kGroupCap);
-    for (int p = tid; p < ng; p += kTB) collect_group<true>(sh.group[p], sh.group_id[p], Lp, nvec, head, sh);
+    for (int p = tid; p < ng; p += kTB) collect_group(sh.group[p], sh.group_id[p], Lp, true, nvec, head, sh);
 #endif
     if (tid < n_edge) {  // elements in front of and behind the whole groups
       const int e = sp.edge_elem(tid);

@@ -38,16 +38,18 @@ namespace topk512 {
 hipError_t launch_stream(const TopkArgs& a, hipStream_t stream);  // npd_topk_kernels_512.hip
 }
 
-// Which kernel streams a long row.  Many rows: four 512-thread workgroups per CU (three rows stream while a fourth is in
-// its ordering phase) as long as their bound, from a sample of eight groups per thread, lets few enough candidates pass;
-// else two of 1024 threads.  Up to 512 rows, which is what two per CU hold: 1024 threads.  Up to a row per CU: 1024 threads
-// with the whole CU's registers, up to 20 groups in flight per thread and the bound from all of them.
-// Measured (MI355X, all scored, us, 512 threads / two of 1024 / one of 1024 per CU; 151,936 logits):
-//   128 rows    k = 10 29.8 / 19.8 / 18.6, 64 33.7 / 23.0 / 20.7, 256 371 / 32.0 / 27.1
-//   512 rows    k = 10 39.4 / 33.6 / 41.6, 64 43.4 / 37.8 / 44.5
-//   2,048 rows  k = 10 105 / 111 / 149, 64 109 / 119 / 162, 128 139 / 130
-// Line between the first two (k times chunks of 512 groups): 2,048 rows of 262,144 k = 64 202 / 196, 4,096 362 / 370;
-// 8,192 rows of 50,304 k = 256 203 / 271, 65,536 278 / 291; 2,048 rows of 65,536 k = 256 93 / 81.
+// Which kernel streams a long row.  Four 512-thread workgroups per CU (three rows stream while a fourth is in its ordering
+// phase) as long as their bound, from a sample of eight groups per thread, lets few enough groups pass, about k / 4 per chunk
+// of 512; else two of 1024 threads.  Up to a row per CU the second choice is one workgroup of 1024 threads with the whole
+// CU's registers, up to 20 groups in flight per thread and the bound from all of them.  Where memory alone is the limit
+// (k <= 64, many long rows) two workgroups of 1024 threads read a little faster.
+// Measured (MI355X, all scored, us, 512 threads / two of 1024 / one of 1024 per CU), k chunks in brackets:
+//   8 rows       65,600 k = 128 [2176] 11.7 / 13.3 / 13.3; 128,256 k = 64 [2048] 15.6 / - / 13.5; 262,144 k = 10 [640] 19.4 / 17.5 / 18.1
+//   256 rows     100,352 k = 10 [250] 14.4 / 15.1 / 15.6; 151,936 k = 10 [380] 18.1 / 18.5 / 20.8; 65,600 k = 256 [4352] 29.6 / 18.7 / 18.8
+//   512 rows     65,600 k = 64 [1088] 15.4 / 19.1; 151,936 k = 64 [2432] 30.1 / 32.2; 50,304 k = 256 [3328] 27.9 / 23.9
+//   1,000 rows   50,304 k = 256 [3328] 34.9 / 40.9; 262,144 k = 64 [4096] 122 / 93
+//   4,000 rows   65,600 k = 256 [4352] 116 / 145; 151,936 k = 128 [4864] 210 / 197
+//   8,192 rows   100,352 k = 10 249 / 241, 64 254 / 249, 128 261 / 276; 65,600 k = 10 161 / 170
 constexpr int kSmallK = 256;
 
 hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, int log_probs, const uint16_t* t,
@@ -67,12 +69,13 @@ hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, 
   // every thread of a workgroup of 1024 needs a whole group
   const bool aligned = (reinterpret_cast<uintptr_t>(t) & 15u) == 0 && stride % 8 == 0;
   if (a.nvec > 1024 || (aligned && a.nvec == 1024)) {
-    if (T <= kTopkFewRows) return topk1024::launch_few(a, stream);
-    if (T <= 512 && a.nvec > 6144) return topk1024::launch_stream(a, stream);
-    // about twice k / 8 candidates per chunk of 512 groups pass the bound of the 512-thread kernel, whose list holds 2,048
-    const int64_t chunks = (a.nvec + 511) / 512;
-    if (k <= kSmallK && k * chunks <= 8 * (T < 3072 ? 425 : 700)) return topk512::launch_stream(a, stream);
-    return topk1024::launch_stream(a, stream);
+    const int64_t passing = (int64_t)k * ((a.nvec + 511) / 512);
+    const bool few = T <= kTopkFewRows, very_few = T <= kTopkFewRows / 2;
+    const int64_t most = very_few && a.nvec > 12288 ? 1300 : few ? 2200 : T <= 512 ? 3250 : T < 3072 ? 3400 : 4400;
+    const bool memory_bound = k <= 64 && a.nvec > 12288 && T * a.nvec > 100000000;
+    const bool threads512 = k <= kSmallK && passing <= most && !memory_bound && !(very_few && a.nvec > 20480);
+    if (threads512) return topk512::launch_stream(a, stream);
+    return few ? topk1024::launch_few(a, stream) : topk1024::launch_stream(a, stream);
   }
   if (!aligned) a.nvec = 0;  // element by element: rows this short fit the caches, and few wait for bytes
   return topk1024::launch_any(a, stream);

@@ -332,15 +332,15 @@ static hipError_t launch_rows(const TopkArgs& a, hipStream_t stream) {
 
 // Which rows.  Longer rows are better off with the kernels that stream them unless there are so few that each has a compute
 // unit (1,024 threads) or half of one (512 threads) to itself and waits for its own latency.  Measured (MI355X, all
-// scored, us, streamed / this): 256 rows of 50,304 k = 10 13.4 / 9.1, 64 16.9 / 10.2, 256 21.4 / 14.0; 65,536 k = 64 19.0 /
-// 10.6; 1,024 rows of 32,000 k = 10 16.3 / 15.4, k = 128 20.2 / 19.1; 2,048 26.8 / 27.9, 32.2 / 34.3; 512 rows of 65,536
-// k = 10 19.2 / 18.9.
+// scored, us, streamed / this): 256 rows of 50,304 k = 10 10.0 / 9.7, 64 11.1 / 10.4, 256 17.4 / 14.1; 400 rows of 32,000
+// k = 10 10.2 / 9.5, 256 15.6 / 13.9; 600 of 32,000 11.7 / 12.9, 19.3 / 22.8; 600 of 18,000 9.7 / 12.0, 15.7 / 21.5; 400 of
+// 18,000 8.7 / 8.6, 13.8 / 14.0.
 constexpr int kManyRows = 1024;
 bool topk_rows_applies(const TopkArgs& a) {
   const int nvec = a.V / 8;
   if (a.k > kRowsTopkMax || a.V > kRowsMaxVocab) return false;
   if (nvec <= 256 * 8) return true;
-  if (nvec <= 512 * 8) return a.T <= kManyRows;
+  if (nvec <= 512 * 8) return a.T <= 2 * kTopkFewRows;
   return a.T <= kTopkFewRows;
 }
 

@@ -353,6 +353,21 @@ def test_teacher_topk_by_rows_and_length(oracle, V, T, k):
     _check_teacher_topk(oracle, V, V, 0, k, T)
 
 
+# the register window of a streamed row: one window exactly, one and a part, two less a group, two, two and a part, three,
+# with a whole and with a partial last group, at windows of 8 groups of 512 threads and of 12 and 20 of 1,024; and the
+# numbers of rows, groups and k between which the kernel changes
+@pytest.mark.parametrize("V,T,k", [
+    (16400, 513, 10), (32776, 260, 10), (32768, 513, 10), (36864, 260, 20), (61440, 260, 20), (65536, 260, 7),
+    (65544, 12, 10), (69632, 260, 64), (98304, 260, 33), (98312, 129, 52), (98312, 128, 51), (98312, 128, 53),
+    (98304, 12, 190), (106496, 12, 190), (188416, 12, 140), (196608, 12, 140), (200008, 12, 140), (163840, 12, 140),
+    (163848, 129, 55), (327680, 12, 200), (335872, 12, 10), (98304, 257, 256), (106496, 257, 256), (188416, 257, 256),
+    (196616, 257, 256), (65600, 513, 201), (50304, 512, 250), (50304, 512, 251),
+])
+@pytest.mark.parametrize("off", [0, 3])
+def test_teacher_topk_windows(oracle, V, T, k, off):
+    _check_teacher_topk(oracle, V, V, off, k, T)
+
+
 @pytest.mark.parametrize("T", [8, 300, 520])
 def test_teacher_topk_keys_of_both_signs(oracle, T):
     """Candidates that span so many keys that one does not fit 32 bits beside its id: fewer positive logits than k."""
