@@ -261,7 +261,7 @@ npd_status check_kd_call(const npd_kd_desc* desc, const void* student_logits, co
 
 extern "C" {
 
-int npd_version(void) { return 118; }
+int npd_version(void) { return 119; }
 
 const char* npd_status_string(npd_status st) {
   switch (st) {
