@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
 // windows below: the compiler cannot tell then how many loads are under way, and waits for all of them at every group
 // (MI355X, all scored, with / without the branches: 151,936 logits, k = 64, 1,024 rows 58.2 / 54.0 us, 4,096 205 / 195;
 // k = 256, 4,096 rows 268 / 234; 8 rows of 262,144 k = 10 21.9 / 17.0; where the memory is the limit, 8,192 rows of 262,144
-// k = 10, 649 / 668).
+// k = 10, 649 / 668 with 512 threads; such calls take 1,024 threads, 646).
 __device__ __forceinline__ u32x4 load_group(const uint16_t* trow, int i, int nvec) {
   const uint32_t off = i < nvec ? (uint32_t)i * 16u : 0u;
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(trow) + off));

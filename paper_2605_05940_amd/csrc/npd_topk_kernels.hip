@@ -50,6 +50,8 @@ hipError_t launch_stream(const TopkArgs& a, hipStream_t stream);  // npd_topk_ke
 //   1,000 rows   50,304 k = 256 [3328] 34.9 / 40.9; 262,144 k = 64 [4096] 122 / 93
 //   4,000 rows   65,600 k = 256 [4352] 116 / 145; 151,936 k = 128 [4864] 210 / 197
 //   8,192 rows   100,352 k = 10 249 / 241, 64 254 / 249, 128 261 / 276; 65,600 k = 10 161 / 170
+//                100,352 k = 10 243 / 237, 128,256 309 / 305, 200,064 490 / 476, 262,144 670 / 648;  5,700 rows of 151,936
+//                k = 10 258 / 259, 200,064 342 / 337, 262,144 470 / 461
 constexpr int kSmallK = 256;
 
 hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, int log_probs, const uint16_t* t,
