@@ -173,8 +173,11 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     only; ``grad_out`` sharing storage with ``student_logits`` means the in-place gradient.  ``workspace``:
     a uint8 tensor of at least ``npd_workspace_bytes`` bytes, better twice as many; if it is None one is taken from
     ``workspace_for`` (a per-device tensor that this module keeps and grows) or, with a CE term at tau != 1 and for rows
-    that are not 16-byte aligned, allocated for the call.  ``no_workspace`` sets ``NPD_FLAG_NO_WORKSPACE``.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in
-    scratch array; no workspace argument).
+    that are not 16-byte aligned, allocated for the call.  Forward-only calls allocate a block of their own where splitting
+    rows pays, and run without it where there is no memory for it; both blocks are torch's and go back to its allocator when
+    the call returns, so a capture that is not ``torch.cuda.graph``'s should set ``no_workspace``.  ``no_workspace`` sets
+    ``NPD_FLAG_NO_WORKSPACE``: no scratch memory at all.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the
+    library's built-in scratch array; no workspace argument).
     """
     if _host is not None and not noalloc:
         st = _host.kd(student_logits, loss_mask, teacher_dense, teacher_idx, teacher_val, labels, tau, grad_scale,
@@ -211,8 +214,8 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     scratch = None
     if workspace is None and not no_workspace and not noalloc and grad_out is None:
         need = L.npd_forward_scratch_bytes(desc)
-        if need:  # rows to be split over several workgroups: a block of this call's own, as below
-            scratch = torch.empty(need, dtype=torch.uint8, device="cuda")
+        if need:  # rows to be split over several workgroups; without the block they are not
+            scratch = _own_block(need)
     elif workspace is None and not no_workspace and not noalloc:
         need = 2 * L.npd_workspace_bytes(desc)  # (twice the least: shorter slices where they are faster)
         if need and (ce_grad_scale != 0.0 and tau != 1.0 or (student_logits.data_ptr() | 2 * student_stride) & 15):
@@ -238,6 +241,15 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
         return
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(L.npd_kd_loss_fwd_bwd(*args, _ptr(workspace), ws_bytes, _stream()))
+
+
+def _own_block(n_bytes: int) -> Optional[torch.Tensor]:
+    """Scratch of one call, from torch's stream-ordered allocator (reused only behind this call on its stream: the current
+    device's, where the kernels run); None where there is no memory for it."""
+    try:
+        return torch.empty(n_bytes, dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        return None
 
 
 _workspaces = {}

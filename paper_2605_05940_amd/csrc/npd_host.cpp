@@ -98,7 +98,8 @@ void* current_stream() {
   return s;
 }
 
-// scratch of one call: from torch's stream-ordered allocator, reused only behind the call on its stream
+// scratch of one call: from torch's stream-ordered allocator, reused only behind the call on its stream (no memory: its
+// exception leaves the call to the Python code, which knows what runs without)
 at::Tensor scratch(size_t bytes) {
   return at::empty({(int64_t)bytes}, at::TensorOptions().dtype(at::kByte).device(current_device()));
 }

@@ -342,6 +342,32 @@ def test_calls_that_may_overlap_get_scratch_of_their_own(lib, monkeypatch, pitch
         assert devices == ["cuda", "cuda"]
 
 
+def test_forward_only_calls_run_without_memory_for_their_scratch(monkeypatch):
+    """The scratch of a forward-only call is optional: where it cannot be allocated, the call is made without."""
+    calls = []
+
+    class Library:
+        npd_forward_scratch_bytes = staticmethod(lambda desc: 4096)
+        npd_kd_loss_forward = staticmethod(lambda *args: calls.append(("split", args[12], args[13])) or 0)
+        npd_kd_loss_fwd_bwd = staticmethod(lambda *args: calls.append(("whole", args[13], args[14])) or 0)
+
+    def none_left(n, device, **kw):
+        raise torch.cuda.OutOfMemoryError("no memory")
+
+    monkeypatch.setattr(binding, "load", lambda: Library)
+    monkeypatch.setattr(binding, "_stream", lambda: None)
+    monkeypatch.setattr(binding, "_ptr", lambda t, dtype=None: None if t is None else t.data_ptr())
+    monkeypatch.setattr(binding, "_array", lambda name, t, n, dtype: None if t is None else t.data_ptr())
+    s, mask, kd = torch.zeros((4, 64), dtype=torch.bfloat16), torch.ones(4, dtype=torch.uint8), torch.zeros(4)
+    empty = torch.empty
+    monkeypatch.setattr(binding.torch, "empty", none_left)
+    binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=s, kd_tok=kd)
+    assert calls == [("whole", None, 0)]
+    monkeypatch.setattr(binding.torch, "empty", lambda n, dtype, device: empty(n, dtype=dtype))
+    binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=s, kd_tok=kd)
+    assert calls[1][0] == "split" and calls[1][1] and calls[1][2] == 4096
+
+
 def test_layouts_are_deterministic_and_well_formed():
     for i in range(5):
         w = synth.config(i)

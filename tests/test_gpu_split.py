@@ -89,3 +89,36 @@ def test_split_rows_bad_label_and_replays():
     call()
     assert status.item() == binding.NPD_DEV_BAD_LABEL and torch.isnan(nll[5]) and torch.isnan(tnll[5])
     assert torch.equal(kd, want[0]) and torch.equal(nll[:5], want[1][:5]) and torch.equal(nll[6:], want[1][6:])
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_forward_only_call_with_no_memory_left_for_its_scratch(native, monkeypatch):
+    """Torch may allocate no more and its pools are used up: the call runs unsplit, as with no_workspace."""
+    T, V = 24, 65536
+    assert _scratch(T, V, 0, 1.0) > 0 and (not native or binding._host is not None)
+    if not native:
+        monkeypatch.setattr(binding, "_host", None)
+    g = torch.Generator(device=dev()).manual_seed(9)
+    s, t = (torch.randn((T, V), generator=g, device=dev()).mul_(3).to(torch.bfloat16) for _ in range(2))
+    mask, kd, want = torch.ones(T, dtype=torch.uint8, device=dev()), torch.empty(T, device=dev()), torch.empty(T, device=dev())
+    binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, kd_tok=want, no_workspace=True)
+    binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, kd_tok=kd)
+    torch.cuda.synchronize()
+    assert not torch.equal(kd, want)                       # (summed in another order)
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    used = []
+    try:
+        torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+        for n in (1 << 20, 1 << 16, 1 << 12, 512):         # what the allocator still holds
+            try:
+                while True:
+                    used.append(torch.empty(n, dtype=torch.uint8, device=dev()))
+            except torch.cuda.OutOfMemoryError:
+                pass
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, kd_tok=kd)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+        used.clear()
+    torch.cuda.synchronize()
+    assert torch.equal(kd, want)
