@@ -142,11 +142,12 @@ int npd_debug_gang_spin_limit(int polls);
 /*
  * Bytes of device workspace npd_kd_loss_fwd_bwd takes for `desc` (host call; 0 is a
  * legal answer and then `workspace` may be NULL).  Required, except with ce_grad_scale != 0
- * at tau != 1, where it makes the call faster.  Calls that are given twice as many bytes share a row between more
- * workgroups where that is faster (few rows, and rows of some lengths), with the same results to rounding.
- * Returns 0 for an invalid desc.
+ * at tau != 1, where it makes the call faster.  npd_workspace_bytes_preferred() says how many bytes the call can make use
+ * of: the same number, or up to twice as many where a row is better shared between more workgroups (few rows, and rows of
+ * some lengths; the same results to rounding).  Both return 0 for an invalid desc.
  */
 size_t npd_workspace_bytes(const npd_kd_desc* desc);
+size_t npd_workspace_bytes_preferred(const npd_kd_desc* desc);
 
 /*
  * The fused KD loss of one packed batch: for every scored position p (Alg. 1,

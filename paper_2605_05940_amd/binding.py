@@ -28,7 +28,7 @@ NOALLOC_WORKSPACE_BYTES = 16 << 20   # NPD_NOALLOC_WORKSPACE_BYTES
 EXPORTS = ("npd_version", "npd_status_string", "npd_workspace_bytes", "npd_kd_loss_fwd_bwd",
            "npd_segment_reduce", "npd_delta_ifd_score", "npd_teacher_topk", "npd_debug_gang_spin_limit",
            "npd_kd_loss_fwd_bwd_noalloc", "npd_policy_lag", "npd_segment_ppl", "npd_kd_kernel_name",
-           "npd_forward_scratch_bytes", "npd_kd_loss_forward")
+           "npd_forward_scratch_bytes", "npd_kd_loss_forward", "npd_workspace_bytes_preferred")
 
 
 class NpdError(RuntimeError):
@@ -70,6 +70,8 @@ def load() -> ctypes.CDLL:
         L.npd_kd_kernel_name.argtypes = [ctypes.POINTER(KdDesc)]
         L.npd_workspace_bytes.restype = ctypes.c_size_t
         L.npd_workspace_bytes.argtypes = [ctypes.POINTER(KdDesc)]
+        L.npd_workspace_bytes_preferred.restype = ctypes.c_size_t
+        L.npd_workspace_bytes_preferred.argtypes = [ctypes.POINTER(KdDesc)]
         L.npd_kd_loss_fwd_bwd.restype = ctypes.c_int
         L.npd_kd_loss_fwd_bwd.argtypes = [ctypes.POINTER(KdDesc)] + [_vp] * 13 + [ctypes.c_size_t, _vp]
         L.npd_kd_loss_fwd_bwd_noalloc.restype = ctypes.c_int
@@ -104,8 +106,8 @@ def _load_host(L):
     spec = importlib.util.spec_from_file_location("npd_host", HOST_PATH)
     host = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(host)
-    entries = (L.npd_workspace_bytes, L.npd_forward_scratch_bytes, L.npd_kd_loss_fwd_bwd, L.npd_kd_loss_forward,
-               L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag)
+    entries = (L.npd_workspace_bytes, L.npd_workspace_bytes_preferred, L.npd_forward_scratch_bytes, L.npd_kd_loss_fwd_bwd,
+               L.npd_kd_loss_forward, L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag)
     host.bind(_raw_stream, _workspaces, tuple(ctypes.cast(f, _vp).value for f in entries))
     return host
 
@@ -171,13 +173,13 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
 
     The teacher kind follows from which teacher tensors are given; ``grad_out is None`` means forward
     only; ``grad_out`` sharing storage with ``student_logits`` means the in-place gradient.  ``workspace``:
-    a uint8 tensor of at least ``npd_workspace_bytes`` bytes, better twice as many; if it is None one is taken from
-    ``workspace_for`` (a per-device tensor that this module keeps and grows) or, with a CE term at tau != 1 and for rows
-    that are not 16-byte aligned, allocated for the call.  Forward-only calls allocate a block of their own where splitting
-    rows pays, and run without it where there is no memory for it; both blocks are torch's and go back to its allocator when
-    the call returns, so a capture that is not ``torch.cuda.graph``'s should set ``no_workspace``.  ``no_workspace`` sets
-    ``NPD_FLAG_NO_WORKSPACE``: no scratch memory at all.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the
-    library's built-in scratch array; no workspace argument).
+    a uint8 tensor of at least ``npd_workspace_bytes`` bytes, better of ``npd_workspace_bytes_preferred``; if it is None one
+    is taken from ``workspace_for`` (a per-device tensor that this module keeps and grows) or, with a CE term at tau != 1, for
+    rows that are not 16-byte aligned and for calls that prefer more than is kept, allocated for the call.  Forward-only calls
+    allocate a block of their own where splitting rows pays, and run without it where there is no memory for it.  Blocks of a
+    call go back to torch's allocator when it returns, so a capture that is not ``torch.cuda.graph``'s should set
+    ``no_workspace`` (``NPD_FLAG_NO_WORKSPACE``: no scratch memory at all) or bring a workspace.  ``noalloc`` calls
+    ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in scratch array; no workspace argument).
     """
     if _host is not None and not noalloc:
         st = _host.kd(student_logits, loss_mask, teacher_dense, teacher_idx, teacher_val, labels, tau, grad_scale,
@@ -217,14 +219,10 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
         if need:  # rows to be split over several workgroups; without the block they are not
             scratch = _own_block(need)
     elif workspace is None and not no_workspace and not noalloc:
-        need = 2 * L.npd_workspace_bytes(desc)  # (twice the least: shorter slices where they are faster)
-        if need and (ce_grad_scale != 0.0 and tau != 1.0 or (student_logits.data_ptr() | 2 * student_stride) & 15):
-            # a CE term at tau != 1 and rows that are not 16-byte aligned: these calls can run without any scratch and
-            # may run beside others on several streams: a block of this call's own, from torch's stream-ordered
-            # allocator (reused only behind this call on its stream: the current device's, where the kernels run)
-            workspace = torch.empty(need, dtype=torch.uint8, device="cuda")
-        else:
-            workspace = workspace_for(need, student_logits.device)
+        # a CE term at tau != 1 and rows that are not 16-byte aligned: these calls can run without any scratch and may run
+        # beside others on several streams, so they share none
+        own = ce_grad_scale != 0.0 and tau != 1.0 or (student_logits.data_ptr() | 2 * student_stride) & 15
+        workspace = _workspace(L, desc, own, student_logits.device)
     args = (desc, _ptr(student_logits, torch.bfloat16), _ptr(teacher_dense, torch.bfloat16),
             _ptr(teacher_idx, torch.int32), _ptr(teacher_val, torch.float32),
             _array("labels", labels, T, torch.int32), _array("loss_mask", loss_mask, T, torch.uint8),
@@ -255,6 +253,28 @@ def _own_block(n_bytes: int) -> Optional[torch.Tensor]:
 _workspaces = {}
 
 
+def _workspace(L, desc, own: bool, device) -> Optional[torch.Tensor]:
+    """The scratch of a gradient call that brings none: as much as it prefers, so that what it runs does not depend on earlier
+    calls.  The kept buffer is replaced only by a call that cannot run with it; one that prefers more gets a block."""
+    need = L.npd_workspace_bytes(desc)
+    if not need:
+        return None
+    want = getattr(L, "npd_workspace_bytes_preferred", L.npd_workspace_bytes)(desc)
+    kept = None if own else _workspaces.get(torch.device(device).index or 0)
+    if not own and (kept is None or kept.numel() < need):
+        return workspace_for(want, device)
+    if kept is not None and kept.numel() >= want:
+        return kept
+    block = _own_block(want)
+    if block is None:
+        block = kept if kept is not None else torch.empty(need, dtype=torch.uint8, device="cuda")
+    return block
+
+
+# what a kept buffer holds at least: more than any call of few rows prefers (1,400 slices of 64 bytes and the words behind them)
+_KEPT_BYTES = 1 << 17
+
+
 def workspace_for(n_bytes: int, device) -> Optional[torch.Tensor]:
     """A device buffer of at least ``n_bytes`` bytes (None for 0), kept per device and grown on demand, for callers
     that do not manage the workspace of ``npd_kd_loss_fwd_bwd`` themselves.  Calls that share it must be ordered on
@@ -264,7 +284,7 @@ def workspace_for(n_bytes: int, device) -> Optional[torch.Tensor]:
     key = torch.device(device).index or 0
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < n_bytes:
-        ws = torch.empty(n_bytes, dtype=torch.uint8, device=device)
+        ws = torch.empty(max(n_bytes, _KEPT_BYTES), dtype=torch.uint8, device=device)
         _workspaces[key] = ws
     return ws
 

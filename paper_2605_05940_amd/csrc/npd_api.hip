@@ -116,15 +116,16 @@ void* noalloc_scratch_address(hipError_t* err) {
 // that need none, and callers that bring none still get those.
 bool workspace_optional(const npd_kd_desc& d) { return d.ce_grad_scale != 0.0f && d.tau != 1.0f; }
 
-// workspace bytes of a call with a valid descriptor
-size_t workspace_bytes_of(const npd_kd_desc& d) {
+// workspace bytes of a call with a valid descriptor: the least it takes, or as many as it can make use of
+size_t workspace_bytes_of(const npd_kd_desc& d, bool preferred = false) {
+  const auto bytes = preferred ? npd::gang_workspace_preferred : npd::gang_workspace_bytes;
   // only the row-gang kernels (gradient calls on long rows) exchange partial sums through device memory; every other
   // kernel keeps them in registers and LDS
   if (d.flags & (NPD_FLAG_FWD_ONLY | NPD_FLAG_NO_WORKSPACE)) return 0;
   if (d.teacher_kind == NPD_TEACHER_TOPK)  // (forward KL only: checked with the descriptor)
-    return npd::gang_workspace_bytes(d.n_tokens, d.vocab, npd::kTopk, npd::kForwardKl, false);
+    return bytes(d.n_tokens, d.vocab, npd::kTopk, npd::kForwardKl, false);
   if (d.teacher_kind != NPD_TEACHER_DENSE_BF16) return 0;
-  return npd::gang_workspace_bytes(d.n_tokens, d.vocab, npd::kDense, d.divergence, d.tau != 1.0f);
+  return bytes(d.n_tokens, d.vocab, npd::kDense, d.divergence, d.tau != 1.0f);
 }
 
 // bytes with which a forward-only call with a valid descriptor splits its rows
@@ -261,7 +262,7 @@ npd_status check_kd_call(const npd_kd_desc* desc, const void* student_logits, co
 
 extern "C" {
 
-int npd_version(void) { return 119; }
+int npd_version(void) { return 120; }
 
 const char* npd_status_string(npd_status st) {
   switch (st) {
@@ -302,6 +303,11 @@ size_t npd_workspace_bytes(const npd_kd_desc* desc) {
   return workspace_bytes_of(*desc);
 }
 
+size_t npd_workspace_bytes_preferred(const npd_kd_desc* desc) {
+  if (check_desc(desc) != NPD_OK) return 0;
+  return workspace_bytes_of(*desc, true);
+}
+
 npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logits, const void* teacher_dense,
                                const int32_t* teacher_idx, const float* teacher_val, const int32_t* labels,
                                const uint8_t* loss_mask, void* grad_out, float* kd_tok, float* nll_tok,
@@ -323,7 +329,8 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
         usable = false;
       }
       // bytes beyond those are used only where they are nobody else's
-      have = workspace_bytes >= 2 * need && !b.overlaps_any(range_of(workspace, 2 * need)) ? 2 * need : need;
+      const size_t more = workspace_bytes_of(*desc, true);
+      have = workspace_bytes >= more && !b.overlaps_any(range_of(workspace, more)) ? more : need;
     }
     a.ws = usable ? static_cast<uint32_t*>(workspace) : nullptr;
   }

@@ -20,6 +20,7 @@ namespace {
 
 struct Entry {
   decltype(&npd_workspace_bytes) workspace_bytes;
+  decltype(&npd_workspace_bytes_preferred) workspace_bytes_preferred;
   decltype(&npd_forward_scratch_bytes) forward_scratch_bytes;
   decltype(&npd_kd_loss_fwd_bwd) kd;
   decltype(&npd_kd_loss_forward) kd_forward;
@@ -190,22 +191,21 @@ PyObject* kd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         return call(lib.kd_forward, &d, sp, tp, ip, vp, labels, mask, kd_tok, nll, tnll, lse, status, own.data_ptr(), need, stream);
       }
     }
-    if (!ws && !no_workspace && g) {
-      const size_t need = 2 * lib.workspace_bytes(&d);  // (twice the least: shorter slices where they are faster)
-      if (need && ((ce != 0.0 && tau != 1.0) || (((uintptr_t)sp | (uintptr_t)(2 * d.student_stride)) & 15) != 0)) {
-        const at::Tensor own = scratch(need);
-        return call(lib.kd, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, own.data_ptr(), need, stream);
-      }
-      if (need) {  // the buffer that binding.workspace_for keeps
+    const size_t need = !ws && !no_workspace && g ? lib.workspace_bytes(&d) : 0;
+    if (need) {  // as binding._workspace
+      const size_t want = lib.workspace_bytes_preferred(&d);
+      at::Tensor w;  // (held through the call)
+      if (!((ce != 0.0 && tau != 1.0) || (((uintptr_t)sp | (uintptr_t)(2 * d.student_stride)) & 15) != 0)) {
         PyObject* key = PyLong_FromLong(s.get_device());
         PyObject* kept = key ? PyDict_GetItemWithError(workspaces, key) : nullptr;  // borrowed
         Py_XDECREF(key);
         if (!kept || !THPVariable_CheckExact(kept)) throw NotPlain();  // (Python makes it)
-        const at::Tensor w = THPVariable_Unpack(kept);  // (held through the call)
+        w = THPVariable_Unpack(kept);
         if (!w.is_cuda() || (size_t)w.numel() < need) throw NotPlain();
-        return call(lib.kd, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, w.data_ptr(), (size_t)w.nbytes(),
-                      stream);
       }
+      if (!w.defined() || (size_t)w.numel() < want) w = scratch(want);
+      return call(lib.kd, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, w.data_ptr(), (size_t)w.nbytes(),
+                    stream);
     }
     return call(lib.kd, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, ws ? ws->data_ptr() : nullptr,
                   ws ? (size_t)ws->numel() * ws->element_size() : 0, stream);
@@ -285,12 +285,13 @@ PyObject* policy_lag(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* bind(PyObject*, PyObject* args) {
   PyObject *stream, *kept, *addresses;
   if (!PyArg_ParseTuple(args, "OO!O!", &stream, &PyDict_Type, &kept, &PyTuple_Type, &addresses)) return nullptr;
-  void* p[8];
-  if (PyTuple_GET_SIZE(addresses) != 8) {
-    PyErr_SetString(PyExc_ValueError, "8 addresses");
+  constexpr int kEntries = 9;
+  void* p[kEntries];
+  if (PyTuple_GET_SIZE(addresses) != kEntries) {
+    PyErr_SetString(PyExc_ValueError, "9 addresses");
     return nullptr;
   }
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < kEntries; ++i) {
     p[i] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(addresses, i));
     if (!p[i]) {
       if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "a null address");
@@ -302,13 +303,14 @@ PyObject* bind(PyObject*, PyObject* args) {
   Py_XSETREF(raw_stream, stream);
   Py_XSETREF(workspaces, kept);
   lib.workspace_bytes = reinterpret_cast<decltype(lib.workspace_bytes)>(p[0]);
-  lib.forward_scratch_bytes = reinterpret_cast<decltype(lib.forward_scratch_bytes)>(p[1]);
-  lib.kd = reinterpret_cast<decltype(lib.kd)>(p[2]);
-  lib.kd_forward = reinterpret_cast<decltype(lib.kd_forward)>(p[3]);
-  lib.segment_reduce = reinterpret_cast<decltype(lib.segment_reduce)>(p[4]);
-  lib.delta_ifd = reinterpret_cast<decltype(lib.delta_ifd)>(p[5]);
-  lib.teacher_topk = reinterpret_cast<decltype(lib.teacher_topk)>(p[6]);
-  lib.policy_lag = reinterpret_cast<decltype(lib.policy_lag)>(p[7]);
+  lib.workspace_bytes_preferred = reinterpret_cast<decltype(lib.workspace_bytes_preferred)>(p[1]);
+  lib.forward_scratch_bytes = reinterpret_cast<decltype(lib.forward_scratch_bytes)>(p[2]);
+  lib.kd = reinterpret_cast<decltype(lib.kd)>(p[3]);
+  lib.kd_forward = reinterpret_cast<decltype(lib.kd_forward)>(p[4]);
+  lib.segment_reduce = reinterpret_cast<decltype(lib.segment_reduce)>(p[5]);
+  lib.delta_ifd = reinterpret_cast<decltype(lib.delta_ifd)>(p[6]);
+  lib.teacher_topk = reinterpret_cast<decltype(lib.teacher_topk)>(p[7]);
+  lib.policy_lag = reinterpret_cast<decltype(lib.policy_lag)>(p[8]);
   Py_RETURN_NONE;
 }
 

@@ -49,11 +49,14 @@ bool gang_path_applies(const KdArgs& a, int teacher_kind, bool want_grad) {
   return a.T * (int64_t)g <= 0x7fffffffLL;  // one workgroup per slice, 1-D grid
 }
 
+static size_t record_bytes(int64_t T, int g, int words_per_slice) {
+  return ((size_t)T * g * words_per_slice + kGangTailWords) * sizeof(uint32_t);
+}
 size_t gang_workspace_bytes(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1) {
   const int g = gang_size(V / 8, gang_k(teacher_kind, divergence), false);  // (the larger of the two counts)
   if (g < 2 || T * (int64_t)g > 0x7fffffffLL) return 0;
   if (g > kGangMax && gang_size(V / 8, gang_k(teacher_kind, divergence), true) > kGangMax) return 0;
-  return ((size_t)T * g * gang_words(lse1 ? 4 : 2) + kGangTailWords) * sizeof(uint32_t);
+  return record_bytes(T, g, gang_words(lse1 ? 4 : 2));
 }
 
 // Runs in front of every launch of a row-gang kernel: clears the scratch record (and the words behind it) to the
@@ -68,8 +71,8 @@ hipError_t clear_gang_record(uint32_t* ws, size_t words, hipStream_t stream) {
   return launch_kernel(gang_clear_kernel, dim3((unsigned)grid), dim3(256), 0, stream, ws, words);
 }
 
-// Shorter slices, for calls whose workspace has room for their record (at most twice the bytes a call asks for, so that
-// what a call runs does not depend on how much more it was given): groups per thread, 0: none.
+// Shorter slices, for calls whose workspace has room for their record (gang_workspace_preferred(), at most twice the bytes a
+// call asks for; what a call runs does not depend on how much more it was given): groups per thread, 0: none.
 //   5  calls of so few rows that all their slices run at once, and wait for the latency of each step of a slice.
 //      Measured (MI355X, all scored, us with the clearing launch, 10 groups / 5): dense, tau = 1 32 rows of 32,000 10.0 /
 //      8.5, 128 11.4 / 10.4, 64 rows of 50,304 11.8 / 10.9, 256 19.3 / 18.2, 32 of 100,352 12.3 / 10.9, 128 19.9 / 17.7, 64 of
@@ -85,6 +88,19 @@ static int fine_groups(int64_t T, int nvec, int teacher_kind, int divergence, bo
   return !lse1 && nvec > 4080 && nvec <= 5352 ? 7 : 0;
 }
 
+// `lse1` of the functions below: the sums at tau = 1 that a call takes, which is known at its launch; the two that size a
+// workspace have only its tau, and count the larger record.
+size_t gang_workspace_preferred(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1) {
+  const size_t least = gang_workspace_bytes(T, V, teacher_kind, divergence, lse1);
+  size_t best = least;
+  for (int sums = 0; least > 0 && sums <= (lse1 ? 1 : 0); ++sums) {
+    const int k = fine_groups(T, V / 8, teacher_kind, divergence, sums != 0);
+    const size_t bytes = k > 0 ? record_bytes(T, gang_slices(V / 8, k, false), gang_words(sums ? 4 : 2)) : 0;
+    if (bytes > best && bytes <= 2 * least) best = bytes;
+  }
+  return best;
+}
+
 template <int DIVK>
 static hipError_t launch_gang(const KdArgs& a, hipStream_t stream) {
   return launch_gang_dense<DIVK, DIVK == kSkewKl || DIVK == kSkewReverseKl ? kGangSkewK : kGangK>(a, stream);
@@ -98,11 +114,10 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
   int k = fine_groups(a.T, a.nvec_s, teacher_kind, a.divergence, a.need_lse1 != 0);
   if (k > 0) {
     const int g = gang_slices(a.nvec_s, k, on_lines);
-    const int words = gang_words(teacher_kind == kTopk || !a.need_lse1 ? 2 : 4);
-    const size_t bytes = ((size_t)a.T * g * words + kGangTailWords) * sizeof(uint32_t);
-    const size_t asked =
-        gang_workspace_bytes(a.T, a.V, teacher_kind, a.divergence, teacher_kind == kDense && a.c != kLog2e);
-    if (g >= 2 && bytes <= workspace_bytes && bytes <= 2 * asked)
+    const size_t bytes = record_bytes(a.T, g, gang_words(teacher_kind == kTopk || !a.need_lse1 ? 2 : 4));
+    const size_t preferred =
+        gang_workspace_preferred(a.T, a.V, teacher_kind, a.divergence, teacher_kind == kDense && a.c != kLog2e);
+    if (g >= 2 && bytes <= workspace_bytes && bytes <= preferred)
       a.gang = g;
     else
       k = 0;

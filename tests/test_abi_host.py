@@ -342,6 +342,74 @@ def test_calls_that_may_overlap_get_scratch_of_their_own(lib, monkeypatch, pitch
         assert devices == ["cuda", "cuda"]
 
 
+def test_workspace_that_a_call_prefers(lib):
+    """As much as the record of the shorter slices takes where a call has them, else the least."""
+    def ask(V, T, **kw):
+        d = _desc(vocab=V, n_tokens=T, student_stride=V, teacher_stride=V, **kw)
+        return lib.npd_workspace_bytes(ctypes.byref(d)), lib.npd_workspace_bytes_preferred(ctypes.byref(d))
+
+    assert ask(151936, 64) == (64 * 8 * 32 + 256, 64 * 15 * 32 + 256)
+    assert ask(151936, 64, tau=2.0) == (64 * 8 * 64 + 256, 64 * 15 * 64 + 256)
+    assert ask(36000, 10000, divergence=1) == (10000 * 2 * 32 + 256, 10000 * 3 * 32 + 256)
+    assert ask(40960, 64, teacher_kind=1, topk=8) == (64 * 3 * 32 + 256, 64 * 5 * 32 + 256)
+    for V, T, kw in ((151936, 32768, {}), (36000, 10000, dict(tau=2.0)), (65536, 64, dict(divergence=2, skew_alpha=0.1)),
+                     (151936, 64, dict(flags=4)), (151936, 64, dict(flags=1)), (4096, 64, {}), (151936, 64, dict(tau=-1.0))):
+        least, preferred = ask(V, T, **kw)
+        assert preferred == least, (V, T, kw)
+    for V in range(30624, 262144, 1499):
+        for T in (1, 63, 256, 700, 5000):
+            least, preferred = ask(V, T)
+            assert 0 < least <= preferred <= 2 * least
+
+
+def test_kept_workspace_is_replaced_only_where_it_does_not_do(lib, monkeypatch):
+    """A buffer of npd_workspace_bytes made before (for a graph's sake, say) stays; a call that prefers more has a block of its
+    own, or the kept one where there is no memory."""
+    seen, left = [], [True]
+
+    class Library:
+        npd_workspace_bytes = staticmethod(lib.npd_workspace_bytes)
+        npd_workspace_bytes_preferred = staticmethod(lib.npd_workspace_bytes_preferred)
+        npd_kd_loss_fwd_bwd = staticmethod(lambda *args: seen.append((args[13], args[14])) or 0)
+
+    monkeypatch.setattr(binding, "load", lambda: Library)
+    monkeypatch.setattr(binding, "_stream", lambda: None)
+    monkeypatch.setattr(binding, "_ptr", lambda t, dtype=None: None if t is None else t.data_ptr())
+    monkeypatch.setattr(binding, "_array", lambda name, t, n, dtype: None if t is None else t.data_ptr())
+    monkeypatch.setattr(binding, "_workspaces", {})
+    empty = torch.empty
+
+    def allocate(n, dtype, device):
+        if device == "cuda" and not left[0]:
+            raise torch.cuda.OutOfMemoryError("no memory")
+        return empty(n, dtype=dtype)
+
+    monkeypatch.setattr(binding.torch, "empty", allocate)
+    T, V = 10000, 36000
+    s = empty(1, dtype=torch.bfloat16).expand(T, V)
+    monkeypatch.setattr(binding, "_row_stride", lambda x: V)
+    d = _desc(vocab=V, n_tokens=T, student_stride=V, teacher_stride=V)
+    need = lib.npd_workspace_bytes(ctypes.byref(d))
+    want = lib.npd_workspace_bytes_preferred(ctypes.byref(d))
+    kept = binding.workspace_for(need, "cpu")
+    assert need <= kept.numel() < want
+    call = lambda **kw: binding.npd_kd_loss_fwd_bwd(s, torch.ones(T, dtype=torch.uint8), teacher_dense=s, grad_out=s, **kw)
+    call()
+    assert seen[-1][1] == want and binding._workspaces[0] is kept
+    left[0] = False
+    call()
+    assert seen[-1] == (kept.data_ptr(), need) and binding._workspaces[0] is kept
+    call(tau=2.0)                                           # the wider record: twice the least of before
+    assert seen[-1][1] > need and binding._workspaces[0] is not kept
+    binding._workspaces.clear()
+    kept = binding.workspace_for(1, "cpu")                  # of the smallest size: enough for every call of few rows
+    for T in range(1, 280, 31):
+        s = empty(1, dtype=torch.bfloat16).expand(T, V)
+        call = lambda **kw: binding.npd_kd_loss_fwd_bwd(s, torch.ones(T, dtype=torch.uint8), teacher_dense=s, grad_out=s, **kw)
+        call(tau=2.0)
+        assert seen[-1][0] == kept.data_ptr()
+
+
 def test_forward_only_calls_run_without_memory_for_their_scratch(monkeypatch):
     """The scratch of a forward-only call is optional: where it cannot be allocated, the call is made without."""
     calls = []
