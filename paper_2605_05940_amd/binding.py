@@ -7,12 +7,13 @@ fallback: without the built library these calls fail.
 import ctypes
 import importlib.util
 import os
+import warnings
 from typing import Optional
 
 import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-# NPD_LIB_PATH overrides the in-tree library (e.g. to try a differently tuned build)
+# NPD_LIB_PATH overrides the in-tree library (e.g. to try a differently tuned build, or an older one: version 118 and later)
 LIB_PATH = os.environ.get("NPD_LIB_PATH") or os.path.join(HERE, "libnpd.so")
 HOST_PATH = os.path.join(HERE, "npd_host.so")
 
@@ -47,8 +48,8 @@ class KdDesc(ctypes.Structure):
 
 
 _lib = None
-# native marshalling of the ordinary call (csrc/npd_host.cpp), there once the library is loaded; None without torch's raw
-# stream handles.  Its functions return libnpd's status, or -1 for a call that is left to the Python code below.
+# native marshalling of the ordinary call (csrc/npd_host.cpp), there once the library is loaded; None without it (the Python
+# code below makes every call then).  Its functions return libnpd's status, or -1 for a call that is left to the Python code.
 _host = None
 _vp = ctypes.c_void_p
 
@@ -70,16 +71,10 @@ def load() -> ctypes.CDLL:
         L.npd_kd_kernel_name.argtypes = [ctypes.POINTER(KdDesc)]
         L.npd_workspace_bytes.restype = ctypes.c_size_t
         L.npd_workspace_bytes.argtypes = [ctypes.POINTER(KdDesc)]
-        L.npd_workspace_bytes_preferred.restype = ctypes.c_size_t
-        L.npd_workspace_bytes_preferred.argtypes = [ctypes.POINTER(KdDesc)]
         L.npd_kd_loss_fwd_bwd.restype = ctypes.c_int
         L.npd_kd_loss_fwd_bwd.argtypes = [ctypes.POINTER(KdDesc)] + [_vp] * 13 + [ctypes.c_size_t, _vp]
         L.npd_kd_loss_fwd_bwd_noalloc.restype = ctypes.c_int
         L.npd_kd_loss_fwd_bwd_noalloc.argtypes = [ctypes.POINTER(KdDesc)] + [_vp] * 13
-        L.npd_forward_scratch_bytes.restype = ctypes.c_size_t
-        L.npd_forward_scratch_bytes.argtypes = [ctypes.POINTER(KdDesc)]
-        L.npd_kd_loss_forward.restype = ctypes.c_int
-        L.npd_kd_loss_forward.argtypes = [ctypes.POINTER(KdDesc)] + [_vp] * 12 + [ctypes.c_size_t, _vp]
         L.npd_segment_reduce.restype = ctypes.c_int
         L.npd_segment_reduce.argtypes = [ctypes.c_int64, ctypes.c_int32] + [_vp] * 9
         L.npd_delta_ifd_score.restype = ctypes.c_int
@@ -92,7 +87,17 @@ def load() -> ctypes.CDLL:
         L.npd_teacher_topk.restype = ctypes.c_int
         L.npd_teacher_topk.argtypes = ([ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32,
                                         ctypes.c_uint32] + [_vp] * 5)
-        _host = _load_host(L)
+        # entry points that a library of another build (NPD_LIB_PATH) may not have yet; its calls are made without them
+        newer = {"npd_forward_scratch_bytes": (ctypes.c_size_t, []),
+                 "npd_workspace_bytes_preferred": (ctypes.c_size_t, []),
+                 "npd_kd_loss_forward": (ctypes.c_int, [_vp] * 12 + [ctypes.c_size_t, _vp])}
+        here = os.path.realpath(LIB_PATH) == os.path.realpath(os.path.join(HERE, "libnpd.so"))
+        complete = here or all(hasattr(L, name) for name in newer)
+        for name, (result, more) in newer.items():
+            if complete or hasattr(L, name):
+                getattr(L, name).restype = result
+                getattr(L, name).argtypes = [ctypes.POINTER(KdDesc)] + more
+        _host = _load_host(L) if complete else None
         _lib = L
     return _lib
 
@@ -100,12 +105,14 @@ def load() -> ctypes.CDLL:
 def _load_host(L):
     if _raw_stream is None:
         return None
-    if not os.path.exists(HOST_PATH):
-        raise RuntimeError(f"{HOST_PATH} is not built: run `python -m paper_2605_05940_amd.build` "
-                           "(or __graft_entry__.build()) first")
-    spec = importlib.util.spec_from_file_location("npd_host", HOST_PATH)
-    host = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(host)
+    try:
+        spec = importlib.util.spec_from_file_location("npd_host", HOST_PATH)
+        host = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(host)
+    except (ImportError, OSError) as e:  # not built, or built against another torch
+        warnings.warn(f"{HOST_PATH} cannot be loaded ({e}): calls are marshalled by Python code, which is slower; "
+                      "`python -m paper_2605_05940_amd.build` builds it", RuntimeWarning)
+        return None
     entries = (L.npd_workspace_bytes, L.npd_workspace_bytes_preferred, L.npd_forward_scratch_bytes, L.npd_kd_loss_fwd_bwd,
                L.npd_kd_loss_forward, L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag)
     host.bind(_raw_stream, _workspaces, tuple(ctypes.cast(f, _vp).value for f in entries))
@@ -215,7 +222,7 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     L = load()
     scratch = None
     if workspace is None and not no_workspace and not noalloc and grad_out is None:
-        need = L.npd_forward_scratch_bytes(desc)
+        need = L.npd_forward_scratch_bytes(desc) if hasattr(L, "npd_forward_scratch_bytes") else 0
         if need:  # rows to be split over several workgroups; without the block they are not
             scratch = _own_block(need)
     elif workspace is None and not no_workspace and not noalloc:

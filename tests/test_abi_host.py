@@ -342,6 +342,66 @@ def test_calls_that_may_overlap_get_scratch_of_their_own(lib, monkeypatch, pitch
         assert devices == ["cuda", "cuda"]
 
 
+def _in_a_copy(tmp_path, code, library=None, host=None):
+    """Runs `code` with a copy of the package that has the given files as its libraries, and `library` as NPD_LIB_PATH."""
+    import shutil
+    import subprocess
+    import sys
+    pkg = tmp_path / "paper_2605_05940_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "binding.py", "build.py", "synth.py"):
+        shutil.copy(os.path.join(ROOT, "paper_2605_05940_amd", name), pkg)
+    (pkg / "libnpd.so").symlink_to(os.path.join(ROOT, "paper_2605_05940_amd", "libnpd.so"))
+    if host:
+        (pkg / "npd_host.so").write_bytes(host)
+    env = {k: v for k, v in os.environ.items() if k != "NPD_LIB_PATH"}
+    env.update(PYTHONPATH=str(tmp_path), **({"NPD_LIB_PATH": str(library)} if library else {}))
+    r = subprocess.run([sys.executable, "-W", "always", "-c", code], cwd=tmp_path, env=env, capture_output=True, text=True,
+                       timeout=300)
+    assert r.returncode == 0, r.stderr
+    return r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("host", [None, b"not a library"])
+def test_loads_without_the_native_marshalling(tmp_path, host):
+    """The Python code makes every call: a warning, no error."""
+    out = _in_a_copy(tmp_path, "from paper_2605_05940_amd import binding as b\n"
+                     "assert b.load().npd_version() >= 120 and b._host is None\n"
+                     "assert b.npd_workspace_bytes(64, 151936) > 0", host=host)
+    assert "RuntimeWarning" in out and "npd_host.so" in out
+
+
+def test_loads_a_library_without_the_newer_entry_points(tmp_path):
+    """NPD_LIB_PATH may name one that has no forward scratch and no preferred workspace: its calls are made as before."""
+    import subprocess
+    old = [n for n in binding.EXPORTS
+           if n not in ("npd_forward_scratch_bytes", "npd_kd_loss_forward", "npd_workspace_bytes_preferred")]
+    src = tmp_path / "old.c"
+    src.write_text("long last_ws;\n" + "".join(f"long {n}() {{ return 0; }}\n" for n in old
+                                                if n not in ("npd_kd_loss_fwd_bwd", "npd_workspace_bytes")) +
+                   "long npd_workspace_bytes() { return 777; }\n"
+                   "long npd_kd_loss_fwd_bwd(void *d, void *a, void *b, void *c, void *e, void *f, void *g, void *h, void *i,"
+                   " void *j, void *k, void *l, void *m, void *n, unsigned long bytes) { last_ws = n ? (long)bytes : -1;"
+                   " return 0; }\n")
+    lib = tmp_path / "libold.so"
+    subprocess.run(["gcc", "-shared", "-fPIC", "-w", "-o", str(lib), str(src)], check=True)
+    _in_a_copy(tmp_path, """
+import ctypes, torch
+from paper_2605_05940_amd import binding as b
+b._ptr = lambda t, dtype=None: None if t is None else t.data_ptr()
+b._array = lambda name, t, n, dtype: None if t is None else t.data_ptr()
+b._stream = lambda: None
+L = b.load()
+assert b._host is None and not hasattr(L, "npd_kd_loss_forward")
+s, m = torch.zeros((4, 64), dtype=torch.bfloat16), torch.ones(4, dtype=torch.uint8)
+last = ctypes.c_long.in_dll(L, "last_ws")
+b.npd_kd_loss_fwd_bwd(s, m, teacher_dense=s, kd_tok=torch.zeros(4))
+assert last.value == -1
+b.npd_kd_loss_fwd_bwd(s, m, teacher_dense=s, grad_out=s)
+assert last.value >= 777
+""", library=lib)
+
+
 def test_workspace_that_a_call_prefers(lib):
     """As much as the record of the shorter slices takes where a call has them, else the least."""
     def ask(V, T, **kw):
