@@ -249,7 +249,14 @@ hipError_t launch_policy_lag(int64_t T, int32_t S, const float* kl, const uint8_
                              float epsilon, float* seg_mean, int32_t* seg_count, float* batch_mean,
                              int32_t* batch_count, int32_t* exceeded, int32_t* status, hipStream_t stream) {
   constexpr int kSegs = kLagBlock / kSegBlock;
-  const int64_t seg_blocks = S > 0 && (seg_mean || seg_count) ? ((int64_t)S + kSegs - 1) / kSegs : 0;
+  int64_t seg_blocks = S > 0 && (seg_mean || seg_count) ? ((int64_t)S + kSegs - 1) / kSegs : 0;
+  // a grid has fewer than 2^32 threads: the last few numbers of samples that a launch of their own takes (2^24 - 1 of 256
+  // threads) leave no room for workgroup 0
+  if ((1 + seg_blocks) * kLagBlock > 0xffffffffLL) {
+    seg_blocks = 0;
+    const hipError_t e = launch_segment_reduce(T, S, kl, mask, cu, nullptr, seg_count, seg_mean, nullptr, status, stream);
+    if (e != hipSuccess) return e;
+  }
   return launch_kernel(policy_lag_kernel, dim3((unsigned)(1 + seg_blocks)), dim3(kLagBlock), 0, stream, T, S, kl, mask, cu,
                        epsilon, seg_mean, seg_count, batch_mean, batch_count, exceeded, status);
 }

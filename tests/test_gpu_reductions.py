@@ -61,3 +61,26 @@ def test_kept_pairs_of_one_workgroup_or_several(oracle, P):
     clear = np.abs(np.abs(np.nan_to_num(ref["delta"], nan=9.0)) - 0.3) > 1e-5    # fp32 and fp64 agree off the thresholds
     np.testing.assert_array_equal(zone.check().cpu().numpy()[clear], ref["zone"][clear])
     assert int(count.check().item()) == int(keep.check().sum().item())
+
+
+@pytest.mark.parametrize("S", [(1 << 24) - 9, (1 << 24) - 8, (1 << 24) - 1])
+def test_monitor_of_as_many_samples_as_a_grid_takes(S):
+    """Almost all of them empty; the last three and one in the middle are not."""
+    T = 64
+    cu = torch.zeros(S + 1, dtype=torch.int32, device=dev())
+    cu[S // 2:] += 10
+    cu[S - 2:] += 20
+    cu[S - 1:] += 15
+    cu[S:] += 9
+    x = torch.arange(T, device=dev(), dtype=torch.float32)
+    mask = torch.ones(T, dtype=torch.uint8, device=dev())
+    mean, count = Guarded(S, torch.float32), Guarded(S, torch.int32)
+    batch, n, status = (torch.zeros(1, dtype=t, device=dev()) for t in (torch.float32, torch.int32, torch.int32))
+    binding.npd_policy_lag(x, mask, cu, 0.1, seg_kl_mean=mean.t, seg_count=count.t, batch_kl_mean=batch, batch_count=n,
+                           dev_status=status)
+    torch.cuda.synchronize()
+    want_n, want = torch.zeros(S, dtype=torch.int32, device=dev()), torch.zeros(S, device=dev())
+    for i, a, b in ((S // 2 - 1, 0, 10), (S - 3, 10, 30), (S - 2, 30, 45), (S - 1, 45, 54)):
+        want_n[i], want[i] = b - a, (a + b - 1) / 2
+    assert torch.equal(count.check(), want_n) and torch.equal(mean.check(), want)      # (whole and half numbers: exact)
+    assert int(n.item()) == 54 and float(batch.item()) == 26.5 and int(status.item()) == 0
