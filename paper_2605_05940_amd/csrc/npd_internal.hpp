@@ -45,7 +45,7 @@ struct KdArgs {
 
 // Enqueues `kernel` and returns this launch's own status: the thread's pending HIP error (something an earlier call
 // of the application left behind) is neither reported as ours nor cleared.  Arguments are converted to the kernel's
-// parameter types.
+// parameter types.  A 1-D grid of 2^32 threads and more is refused here: the runtime would run it modulo 2^32.
 template <class T>
 struct launch_param {
   using type = T;
@@ -53,6 +53,7 @@ struct launch_param {
 template <class... Params>
 inline hipError_t launch_kernel(void (*kernel)(Params...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t stream,
                                 typename launch_param<Params>::type... params) {
+  if ((uint64_t)grid.x * block.x > 0xffffffffull) return hipErrorInvalidConfiguration;
   void* argv[] = {const_cast<void*>(static_cast<const void*>(&params))...};
   return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, argv, lds_bytes, stream);
 }

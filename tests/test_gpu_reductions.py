@@ -84,3 +84,14 @@ def test_monitor_of_as_many_samples_as_a_grid_takes(S):
         want_n[i], want[i] = b - a, (a + b - 1) / 2
     assert torch.equal(count.check(), want_n) and torch.equal(mean.check(), want)      # (whole and half numbers: exact)
     assert int(n.item()) == 54 and float(batch.item()) == 26.5 and int(status.item()) == 0
+
+
+def test_more_samples_than_a_grid_takes_are_refused():
+    S = 1 << 24
+    cu, mask = torch.zeros(S + 1, dtype=torch.int32, device=dev()), torch.ones(4, dtype=torch.uint8, device=dev())
+    count = torch.zeros(S, dtype=torch.int32, device=dev())
+    with pytest.raises(binding.NpdError) as e:
+        binding.npd_segment_reduce(None, mask, cu, seg_count=count)
+    assert e.value.status == 7
+    binding.npd_segment_reduce(None, mask, cu[:4], seg_count=count[:3])
+    torch.cuda.synchronize()
