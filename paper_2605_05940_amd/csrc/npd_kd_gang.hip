@@ -73,29 +73,57 @@ hipError_t clear_gang_record(uint32_t* ws, size_t words, hipStream_t stream) {
 
 // Shorter slices, for calls whose workspace has room for their record (gang_workspace_preferred(), at most twice the bytes a
 // call asks for; what a call runs does not depend on how much more it was given): groups per thread, 0: none.
-//   5  calls of so few rows that all their slices run at once, and wait for the latency of each step of a slice.
-//      Measured (MI355X, all scored, us with the clearing launch, 10 groups / 5): dense, tau = 1 32 rows of 32,000 10.0 /
-//      8.5, 128 11.4 / 10.4, 64 rows of 50,304 11.8 / 10.9, 256 19.3 / 18.2, 32 of 100,352 12.3 / 10.9, 128 19.9 / 17.7, 64 of
-//      151,936 15.4 / 14.9, 128 24.6 / 27.3; tau = 2 64 of 50,304 13.1 / 12.0; top-k 64 of 40,960 10.4 / 8.9
+// A compute unit works through the slices that fall to it; the fullest one has ceil(slices / 256) of them, so slices of
+// another length are judged by that number times their length (a ratio below: shorter slices / slices of 10 groups).
+//   5  calls of so few rows that all their slices are resident: five workgroups of 256 threads to a compute unit with sums
+//      at tau = 1 (up to 84 registers), six without (78).  They wait for the latency of each step of a slice, not for bytes.
+//      With sums at tau = 1 up to 1,280 slices, and to 1,400 where the ratio is at most 9 / 10; else up to 1,320, and to 1,400
+//      where the ratio is at most 1.
+//      Measured (MI355X, all scored, us of a call, 10 groups / 5), slices of five and ratio in brackets:
+//        tau = 1          32 rows of 32,000 10.0 / 8.5; 64 of 50,304 11.8 / 10.9, 264 [1,320, .90] 21.7 / 19.7; 184 of 65,536
+//                         [1,288, 1.14] 18.1 / 17.2, 188 [1,316, 1.14] 17.9 / 17.4; 86 of 151,936 [1,290, 1.07] 19.9 / 18.4, 93
+//                         [1,395, 1.07] 20.9 / 21.8, 128 [1,920] 24.6 / 27.3; 132 of 100,352 [1,320, 1.0] 20.9 / 19.6; 53 of
+//                         262,144 [1,378, 1.0] 21.5 / 21.8
+//        tau = 2, NLL     320 of 32,000 [1,280, 1.0] 19.6 / 17.9, 330 [1,320, 1.0] 19.7 / 21.3; 272 of 50,304 [1,360, .90] 23.7 /
+//                         23.3 (tau = 3 25.9 / 24.1); 188 of 65,536 [1,316, 1.14] 20.3 / 23.4; 88 of 151,936 [1,320, 1.07] 22.0 / 24.1
+//        top-k            322 of 32,000 [1,288, 1.0] 12.8 / 12.3, 340 [1,360, 1.0] 12.9 / 12.7; 50 of 262,144 [1,300, 1.0] 13.8 / 13.2
 //   7  tau = 1, rows that two slices of 10 groups fill to four fifths and more, or three to two thirds: one more workgroup
 //      per compute unit (94 registers), and no register left empty.  10,000 rows of 36,000 379 / 342, top-k (40 entries)
 //      281 / 248; of 40,960 395 / 386, 289 / 275 (32,000 308 / 306, 50,304 475 / 474; with sums at tau = 1 the registers
-//      do not allow that workgroup: 36,000 tau = 2 with a CE term 382 / 401)
-static int fine_groups(int64_t T, int nvec, int teacher_kind, int divergence, bool lse1) {
+//      do not allow that workgroup: 36,000 tau = 2 with a CE term 382 / 401).  Fewer rows: from 640 on (top-k 1,024), where
+//      a row has no more slices of seven groups than of ten, and where the ratio is below 1 (top-k: as above, and all
+//      resident, six to a compute unit).  Time of 10 groups over time of 7: dense 40,000 351 rows .94, 420 1.12, 512 .95, 600
+//      .97, 640 1.03, 1,024 1.02; 42,816 351 1.20; 33,000 351 1.07, 512 1.01; top-k 36,000 470 1.05, 560 .86, 768 .78, 1,024 1.06
+// (Rows that are not scored are not known here: their slices count like the others'.)
+constexpr int kMeasuredCus = 256;
+static int fine_groups(int64_t T, int nvec, int teacher_kind, int divergence, bool lse1, bool on_lines) {
   if (divergence != kForwardKl && divergence != kReverseKl) return 0;
-  const int g = gang_slices(nvec, 5, false);
-  if (g <= kGangMax && T * g <= 1400) return 5;
-  return !lse1 && nvec > 4080 && nvec <= 5352 ? 7 : 0;
+  const bool topk = teacher_kind == kTopk;
+  auto fullest = [&](int64_t slices) { return (T * slices + kMeasuredCus - 1) / kMeasuredCus; };
+  const int64_t gb = gang_slices(nvec, kGangK, on_lines);
+  int64_t g = gang_slices(nvec, 5, on_lines);
+  int64_t fine = fullest(g) * gb, base = fullest(gb) * g;  // their quotient is the ratio
+  if (g <= kGangMax && T * g <= 1400) {
+    if (T * g <= 5 * kMeasuredCus) return 5;
+    if (lse1 && !topk ? 10 * fine <= 9 * base : T * g <= 1320 || fine <= base) return 5;
+  }
+  if (lse1 || nvec <= 4080 || nvec > 5352) return 0;
+  g = gang_slices(nvec, 7, on_lines);
+  fine = fullest(g) * gb;
+  base = fullest(gb) * g;
+  const bool many = T >= (topk ? 1024 : 640) || g == gb;
+  const bool few = topk ? T * g <= 6 * kMeasuredCus && 14 * fine <= 15 * base : fine < base || nvec <= 4200;
+  return many || few ? 7 : 0;
 }
 
-// `lse1` of the functions below: the sums at tau = 1 that a call takes, which is known at its launch; the two that size a
-// workspace have only its tau, and count the larger record.
+// (Which sums at tau = 1 a call takes and where its gradient begins is known at its launch; here the largest record counts.)
 size_t gang_workspace_preferred(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1) {
   const size_t least = gang_workspace_bytes(T, V, teacher_kind, divergence, lse1);
   size_t best = least;
-  for (int sums = 0; least > 0 && sums <= (lse1 ? 1 : 0); ++sums) {
-    const int k = fine_groups(T, V / 8, teacher_kind, divergence, sums != 0);
-    const size_t bytes = k > 0 ? record_bytes(T, gang_slices(V / 8, k, false), gang_words(sums ? 4 : 2)) : 0;
+  for (int i = 0; least > 0 && i < (lse1 ? 4 : 2); ++i) {
+    const bool on_lines = i & 1, sums = i & 2;
+    const int k = fine_groups(T, V / 8, teacher_kind, divergence, sums, on_lines);
+    const size_t bytes = k > 0 ? record_bytes(T, gang_slices(V / 8, k, on_lines), gang_words(sums ? 4 : 2)) : 0;
     if (bytes > best && bytes <= 2 * least) best = bytes;
   }
   return best;
@@ -111,7 +139,7 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
   const bool on_lines = rows_on_lines(a);
   const int base = gang_size(a.nvec_s, gang_k(teacher_kind, a.divergence), on_lines);
   a.gang = base;
-  int k = fine_groups(a.T, a.nvec_s, teacher_kind, a.divergence, a.need_lse1 != 0);
+  int k = fine_groups(a.T, a.nvec_s, teacher_kind, a.divergence, a.need_lse1 != 0, on_lines);
   if (k > 0) {
     const int g = gang_slices(a.nvec_s, k, on_lines);
     const size_t bytes = record_bytes(a.T, g, gang_words(teacher_kind == kTopk || !a.need_lse1 ? 2 : 4));

@@ -416,6 +416,16 @@ def test_workspace_that_a_call_prefers(lib):
                      (151936, 64, dict(flags=4)), (151936, 64, dict(flags=1)), (4096, 64, {}), (151936, 64, dict(tau=-1.0))):
         least, preferred = ask(V, T, **kw)
         assert preferred == least, (V, T, kw)
+    # where shorter slices are the faster ones: by how many slices fall to the fullest compute unit, times their length
+    for V, T, kw, more in ((32000, 320, {}, True), (32000, 330, {}, True), (32000, 351, {}, False),
+                           (32000, 330, dict(tau=2.0), False), (65536, 128, {}, True),
+                           (65536, 194, {}, True), (65536, 189, {}, False), (65536, 189, dict(tau=2.0), False), (151936, 88, {}, True),
+                           (151936, 89, {}, False), (262144, 53, {}, True), (262144, 54, {}, False), (36000, 351, {}, False), (36000, 420, {}, True),
+                           (36000, 512, {}, False), (36000, 640, {}, True), (33600, 512, {}, True),
+                           (36000, 470, dict(teacher_kind=1, topk=8), True), (36000, 560, dict(teacher_kind=1, topk=8), False),
+                           (36000, 1024, dict(teacher_kind=1, topk=8), True)):
+        least, preferred = ask(V, T, **kw)
+        assert (preferred > least) == more, (V, T, kw)
     for V in range(30624, 262144, 1499):
         for T in (1, 63, 256, 700, 5000):
             least, preferred = ask(V, T)
