@@ -354,7 +354,8 @@ npd_status npd_kd_loss_forward(const npd_kd_desc* desc, const void* student_logi
                                       nullptr, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
   if (st != NPD_OK) return st;  // (also a descriptor that is not forward only: its gradient is missing)
   need = a.nvec_s > 0 ? forward_scratch_bytes_of(*desc) : 0;
-  bool split = need > 0 && scratch && scratch_bytes >= need && !misaligned(scratch, 16);
+  bool split = need > 0 && scratch && scratch_bytes >= need && !misaligned(scratch, 16) &&
+               npd::split_path_applies(a, desc->teacher_kind);
   if (split)
     split = !kd_buffers(*desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask, nullptr, kd_tok,
                         nll_tok, teacher_nll_tok, lse_tok, dev_status).overlaps_any(range_of(scratch, need));

@@ -85,8 +85,10 @@ hipError_t launch_solo_reverse(const KdArgs& a, hipStream_t stream);
 hipError_t launch_solo_skew(const KdArgs& a, hipStream_t stream);
 hipError_t launch_solo_forward_only(const KdArgs& a, hipStream_t stream);
 
-// forward-only calls whose rows are split over several workgroups (npd_kd_split.hip); 0 bytes: not split
+// forward-only calls whose rows are split over several workgroups (npd_kd_split.hip); 0 bytes: not split.  `lse1`: the call
+// may take sums at tau = 1 beside others; whether it does is known at its launch (split_path_applies)
 size_t split_scratch_bytes(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1);
+bool split_path_applies(const KdArgs& a, int teacher_kind);
 hipError_t launch_kd_split(const KdArgs& a, int teacher_kind, hipStream_t stream);
 
 // compute units of the current device (cached per device)

@@ -227,27 +227,36 @@ __global__ __launch_bounds__(kSplitThreads) void kd_split_merge_kernel(const KdA
 
 namespace {
 
-// Groups per thread, 0: not split.  Measured (MI355X, all scored, us, a workgroup per row / split):
-//   dense teacher, tau = 1   1 row of 151,936 19.0 / 5.9;  64 rows of 50,304 10.4 / 7.9, 151,936 21.3 / 11.6;  181 rows of
-//                            151,936 23.2 / 21.3;  256 rows of 50,304 12.1 / 13.1, 131,072 and more the same;  800 rows of
-//                            50,304 34.0 / 29.1;  6,000 rows of 50,304 188 / 180, 151,936 565 / 533
-//                            (32,000: 128 rows 8.4 / 8.2, 4,096 80.7 / 84.2)
-//   dense teacher, tau = 2, NLL wanted   128 rows of 151,936 33.4 / 23.2;  6,000 rows of 50,304 255 / 218, 151,936 792 / 633
-//   no teacher               64 rows of 65,536 6.9 / 6.2, 128 rows of 151,936 12.3 / 11.0, 4,096 of 262,144 339 / 323
-//                            (181 rows of 151,936 11.7 / 13.4, 1,024 of 200,000 63.9 / 66.1)
-// Four groups of a dense teacher per thread for few rows, eight for many (2,048 rows of 151,936 at tau = 2: 246 / 225).
-int split_groups(int64_t T, int nvec, bool dense) {
+// Groups per thread, 0: not split.  Four groups of a dense teacher for few rows, eight for many (2,048 rows of 151,936 at tau
+// = 2: 246 / 225 us).  Measured (MI355X, all scored, us, a workgroup per row / split; the dense kernel with a workgroup per row
+// runs two rows to a compute unit, so its time steps up behind every multiple of 512 rows):
+//   dense teacher, tau = 1   1 row of 151,936 20.0 / 6.7;  64 rows of 50,304 10.0 / 7.8, 151,936 21.1 / 11.9;  181 rows of
+//                            151,936 22.9 / 21.4;  256 rows of 50,304 12.1 / 13.1, 131,072 and more the same or less;  257 rows
+//                            of 50,304 16.3 / 14.8, 400 18.6 / 18.5, 440 .958 of the speed at 60,000, 512 19.8 / 21.3, 520
+//                            1.15, 700 .99 .. 1.06, 768 .974 .. 1.05, 800 32.3 / 29.5;  512 of 100,352 36.1 / 35.3;  6,000 rows of
+//                            50,304 182 / 182, 151,936 541 / 510  (32,000: 128 rows 8.4 / 8.2, 4,096 80.7 / 84.2)
+//   dense teacher, tau = 2, NLL wanted   128 rows of 151,936 33.4 / 23.2;  512 of 50,304 1.06;  6,000 rows of 50,304 255 / 218,
+//                            151,936 792 / 633
+//   no teacher               64 rows of 65,536 6.9 / 6.2, of 75,000 .952, of 90,000 1.06;  100 rows of 100,352 1.02, 112 .932, 128
+//                            8.7 / 9.6, of 116,000 1.03;  128 rows of 151,936 12.3 / 11.0;  240,000: 130 .. 256 rows .95 .. .98, 300
+//                            1.26, 500 .. 1,024 .97 .. .99, 2,000 1.02;  262,144: 181 rows 20.4 / 19.3, 256 .995, 1,000 .996, 4,096
+//                            339 / 323  (181 rows of 151,936 11.7 / 13.4, 1,024 of 200,000 63.9 / 66.1)
+int split_groups(int64_t T, int nvec, bool dense, bool lse1) {
   constexpr int kFew = 256;  // rows: one to a compute unit
   if (dense) {
     if (nvec <= 5120 || (T > kFew / 2 && T <= kFew && nvec < 16384)) return 0;
+    if (!lse1 && T > 432 && T <= 2 * kFew && nvec < 12288) return 0;
     return T <= kFew ? 4 : 8;
   }
-  return nvec >= 30000 || (T <= kFew / 2 && nvec >= 12288) || (T <= kFew / 4 && nvec >= 8192) ? 8 : 0;
+  if (nvec >= 32768) return 8;
+  if (nvec >= 30000) return T <= kFew / 2 || (T > kFew && T <= 448) || T > 1024 ? 8 : 0;
+  if (nvec >= 12288) return T <= 104 || (T <= kFew / 2 && nvec >= 14500) ? 8 : 0;
+  return nvec >= 8192 && T <= (nvec > 10240 ? 64 : 51) ? 8 : 0;
 }
 
 // slices of a row of nvec groups, 0: not split
-int split_slices(int64_t T, int nvec, bool dense) {
-  const int cap = split_groups(T, nvec, dense) * kSplitThreads;
+int split_slices(int64_t T, int nvec, bool dense, bool lse1) {
+  const int cap = split_groups(T, nvec, dense, lse1) * kSplitThreads;
   if (cap == 0) return 0;
   const int g = (nvec + cap - 1) / cap;
   return g >= 2 && g <= kSplitMax && T * (int64_t)g <= 0x7fffffffLL ? g : 0;
@@ -268,17 +277,21 @@ hipError_t launch_split(const KdArgs& a, hipStream_t stream) {
 size_t split_scratch_bytes(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1) {
   if ((teacher_kind != kDense && teacher_kind != kNone) || divergence != kForwardKl) return 0;
   const bool dense = teacher_kind == kDense;
-  const int g = split_slices(T, V / 8, dense);
+  const int g = split_slices(T, V / 8, dense, dense && lse1);
   return (size_t)T * g * split_words(dense, dense && lse1) * sizeof(float);
+}
+
+bool split_path_applies(const KdArgs& a, int teacher_kind) {
+  return split_slices(a.T, a.nvec_s, teacher_kind == kDense, teacher_kind == kDense && a.need_lse1) > 0;
 }
 
 hipError_t launch_kd_split(const KdArgs& a0, int teacher_kind, hipStream_t stream) {
   KdArgs a = a0;
   const bool dense = teacher_kind == kDense;
-  a.gang = split_slices(a.T, a.nvec_s, dense);
+  a.gang = split_slices(a.T, a.nvec_s, dense, dense && a.need_lse1);
   a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;
   if (!dense) return launch_split<8, false, false>(a, stream);
-  if (split_groups(a.T, a.nvec_s, true) == 4)
+  if (split_groups(a.T, a.nvec_s, true, a.need_lse1) == 4)
     return a.need_lse1 ? launch_split<4, true, true>(a, stream) : launch_split<4, true, false>(a, stream);
   return a.need_lse1 ? launch_split<8, true, true>(a, stream) : launch_split<8, true, false>(a, stream);
 }

@@ -579,6 +579,20 @@ def test_forward_scratch(lib):
     assert ask(teacher_stride=151937) == 0                                        # rows that drift apart: element by element
     assert ask(divergence=1) == ask(vocab=32768) == ask(tau=-1.0) == 0
     assert ask(teacher_kind=binding.NPD_TEACHER_TOPK, topk=8) == 0
+    # the lines of the rule: rows per compute unit, and rows whose kernel with a workgroup per row is as fast
+    none = binding.NPD_TEACHER_NONE
+    for V, T, kind, tau, split in ((50304, 128, 0, 1.0, True), (50304, 129, 0, 1.0, False), (50304, 256, 0, 1.0, False),
+                                   (131072, 129, 0, 1.0, True), (50304, 432, 0, 1.0, True), (50304, 433, 0, 1.0, False),
+                                   (50304, 512, 0, 1.0, False), (50304, 513, 0, 1.0, True), (50304, 512, 0, 2.0, True),
+                                   (100352, 512, 0, 1.0, True), (70000, 51, none, 1.0, True), (70000, 52, none, 1.0, False),
+                                   (90000, 64, none, 1.0, True), (90000, 65, none, 1.0, False), (100352, 104, none, 1.0, True),
+                                   (100352, 105, none, 1.0, False), (116000, 128, none, 1.0, True),
+                                   (116000, 129, none, 1.0, False), (240000, 128, none, 1.0, True),
+                                   (240000, 256, none, 1.0, False), (240000, 300, none, 1.0, True),
+                                   (240000, 449, none, 1.0, False), (240000, 1025, none, 1.0, True),
+                                   (262144, 256, none, 1.0, True)):
+        d = dict(vocab=V, n_tokens=T, student_stride=V, teacher_stride=V, teacher_kind=kind, tau=tau)
+        assert (ask(**d) > 0) == split, (V, T, kind, tau)
 
     def forward(d, grad_flags=F, kd=FAKE + 0x10000000, student=FAKE, scratch=None, n=0):
         return lib.npd_kd_loss_forward(ctypes.byref(d), student, FAKE + 0x4000000, None, None, None, FAKE + 0x8000000, kd,
