@@ -256,7 +256,9 @@ __device__ __forceinline__ int crossing_bin(const int* hist, int k, int& above) 
 
 // rank sort of n <= 1024 distinct words from src into sh.sorted (only ranks below k are kept): the rank of a word
 // is the number of larger words.  1024 threads split the n x n comparisons: thread (i, s) compares word i with
-// segment s of the list; lanes of a wave read the same word (broadcast).
+// segment s of the list; lanes of a wave read the same word (broadcast), eight of them requested together.  One at a time,
+// this loop was most of a long record's time, and depended on the code around it (64 rows of 1,001, k = 1,000, us: without the
+// wave's code in the kernel 60.6, with it 65.1, so 46.1; 64 of 65,600, k = 512, 42.2, 46.2, 27.4).
 __device__ __forceinline__ void rank_sort(TopkShared& sh, const unsigned long long* src, int n, int k, int tid) {
   int lg = 0;
   while ((1 << lg) < n) ++lg;
@@ -267,8 +269,12 @@ __device__ __forceinline__ void rank_sort(TopkShared& sh, const unsigned long lo
   if (i < n) {
     const unsigned long long w = src[i];
     const int j1 = min(n, (seg + 1) * chunk);
-    int c = 0;
-    for (int j = seg * chunk; j < j1; ++j) c += src[j] > w;
+    int c = 0, j = seg * chunk;
+    for (; j + 8 <= j1; j += 8) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) c += src[j + q] > w;
+    }
+    for (; j < j1; ++j) c += src[j] > w;
     if (c) atomicAdd(&sh.rank[i], c);
   }
   __syncthreads();
@@ -434,12 +440,20 @@ __global__ __launch_bounds__(kTB, 8) void teacher_topk_kernel(const TopkArgs a) 
 
 // ------------------------------------------------------------------------------------------------ one read
 // One 16-byte group of a row; 32-bit byte offsets keep the address in one VGPR next to the scalar row base.  `i` past the
-// row's groups: group 0 instead, to be left out by the caller.  No branch around a load, here or in the loop over full
-// windows below: the compiler cannot tell then how many loads are under way, and waits for all of them at every group
-// (MI355X, all scored, with / without the branches: 151,936 logits, k = 64, 1,024 rows 58.2 / 54.0 us, 4,096 205 / 195;
-// k = 256, 4,096 rows 268 / 234; 8 rows of 262,144 k = 10 21.9 / 17.0; where the memory is the limit, 8,192 rows of 262,144
-// k = 10, 649 / 668 with 512 threads; such calls take 1,024 threads, 646).
+// row's groups: nothing, or group 0, to be left out by the caller.
+// GUARDED: with branches around the loads, here and in the kernel's loop over windows.  The compiler cannot tell then how many
+// loads are under way, and waits for all of them at every group.  Without branches is faster (MI355X, all scored, us, with /
+// without: 151,936 logits, k = 64, 1,024 rows 58.2 / 54.0, 4,096 205 / 195; k = 256, 4,096 rows 268 / 234; 8 rows of 262,144,
+// k = 10, 21.9 / 17.0) except for many rows whose pitch is a multiple of 524,288 bytes, which all begin on the same memory
+// channel (4,000 rows of 262,144, k = 10, 512 threads 316 / 327, 1,024 threads 328; with a pitch of 262,208 322 / 313).
+template <bool GUARDED>
 __device__ __forceinline__ u32x4 load_group(const uint16_t* trow, int i, int nvec) {
+  if constexpr (GUARDED) {
+    u32x4 v = u32x4{0u, 0u, 0u, 0u};
+    if (i < nvec)
+      v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(trow) + (uint32_t)i * 16u));
+    return v;
+  }
   const uint32_t off = i < nvec ? (uint32_t)i * 16u : 0u;
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(trow) + off));
 }
@@ -500,7 +514,7 @@ __device__ __forceinline__ void collect_group(const u32x4& v, int i, int Lp, boo
 // W = register window (groups in flight per thread), S <= W = groups of the sample that gives the bound.
 // ngroups = ceil(nvec / kTB) >= 1 groups are visited in the order (g * step) mod ngroups, step < ngroups coprime to it.
 // RAGGED: rows begin anywhere inside a 16-byte group.
-template <int W, int S, bool RAGGED, int WAVES = 8>
+template <int W, int S, bool RAGGED, int WAVES, bool GUARDED>
 __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const TopkArgs a, int ngroups, int step) {
   __shared__ TopkShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -527,7 +541,7 @@ __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const T
   for (int j = 0; j < W; ++j) {
     const int i = visit(at_load);
     w[j] = u32x4{0u, 0u, 0u, 0u};
-    if (j < ngroups) w[j] = load_group(tvec, i, nvec);
+    if (j < ngroups) w[j] = load_group<GUARDED>(tvec, i, nvec);
   }
 
   // ---- one maximum per thread over the sample, in value order: the largest non-negative pattern if there is one,
@@ -551,7 +565,9 @@ __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const T
 
   bool slow = k > kTB;  // uniform
   if (!slow) {
-    // each wave reports its m-th largest thread maximum; NW m >= k elements of the row are >= the smallest report
+    // each wave reports its m-th largest thread maximum; NW m >= k elements of the row are >= the smallest report.  (Or a
+    // bound between that and the next one, which is found sooner; not where the list is nearly full: 257 rows of 32,768,
+    // k = 1,000, 132 us, and 177 with the one row whose list overflows for it.)
     const int m = (k + kTB / kWave - 1) / (kTB / kWave);
     int bhi = best, blo = best;
 #pragma unroll
@@ -560,7 +576,11 @@ __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const T
       blo = min(blo, __shfl_xor(blo, off, kWave));
     }
     const int x[1] = {best};
-    blo = wave_bound(x, m, 0, __builtin_amdgcn_readfirstlane(blo), __builtin_amdgcn_readfirstlane(bhi) + 1);
+    const int from = __builtin_amdgcn_readfirstlane(blo), to = __builtin_amdgcn_readfirstlane(bhi) + 1;
+    if (k > kWaveSortMax)  // uniform; (a slack that is a variable costs the others 2 .. 5 %)
+      blo = wave_bound(x, m, -1, from, to);
+    else
+      blo = wave_bound(x, m, 0, from, to);
     if (lane == 0) sh.wave_bound[wid] = blo;
   }
   if (tid == 0) sh.ncand = 0;
@@ -584,26 +604,36 @@ __global__ __launch_bounds__(kTB, WAVES) void teacher_topk_stream_kernel(const T
       collect_group(v, i, Lp, ordered, nvec, head, sh);
 #endif
     };
-    int left = ngroups;  // groups not tested yet; the first W of them are in the window
-    for (; left >= 2 * W; left -= W) {
+    if constexpr (GUARDED) {
+      for (int base = 0; base < ngroups; base += W) {
 #pragma unroll
-      for (int j = 0; j < W; ++j) {
-        test(w[j]);
-        w[j] = load_group(tvec, visit(at_load), nvec);
+        for (int j = 0; j < W; ++j) {
+          if (base + j < ngroups) test(w[j]);
+          if (base + j + W < ngroups) w[j] = load_group<true>(tvec, visit(at_load), nvec);
+        }
       }
-    }
-    const int more = left - W;  // groups behind the window, fewer than W (a load for nothing costs more here than the wait)
-    if (more > 0) {
+    } else {
+      int left = ngroups;  // groups not tested yet; the first W of them are in the window
+      for (; left >= 2 * W; left -= W) {
 #pragma unroll
-      for (int j = 0; j < W; ++j) {
-        test(w[j]);
-        if (j < more) w[j] = load_group(tvec, visit(at_load), nvec);
+        for (int j = 0; j < W; ++j) {
+          test(w[j]);
+          w[j] = load_group<false>(tvec, visit(at_load), nvec);
+        }
       }
-      left = more;
-    }
+      const int more = left - W;  // groups behind the window, fewer than W (a load for nothing costs more here than the wait)
+      if (more > 0) {
 #pragma unroll
-    for (int j = 0; j < W; ++j)
-      if (j < left) test(w[j]);
+        for (int j = 0; j < W; ++j) {
+          test(w[j]);
+          if (j < more) w[j] = load_group<false>(tvec, visit(at_load), nvec);
+        }
+        left = more;
+      }
+#pragma unroll
+      for (int j = 0; j < W; ++j)
+        if (j < left) test(w[j]);
+    }
 #if NPD_TOPK_GROUPS
     __syncthreads();
     const int ng = min(sh.ngroups, kGroupCap);
@@ -640,7 +670,7 @@ static bool rows_ragged(const TopkArgs& a) {
   return (reinterpret_cast<uintptr_t>(a.t) & 15u) != 0 || a.stride % 8 != 0;
 }
 
-template <int W, int S, int WAVES>
+template <int W, int S, int WAVES, bool GUARDED>
 static hipError_t launch_window(const TopkArgs& a, hipStream_t stream) {
   const int ngroups = (a.nvec + kTB - 1) / kTB;
   // visiting order: the first S groups spread over the row
@@ -650,25 +680,29 @@ static hipError_t launch_window(const TopkArgs& a, hipStream_t stream) {
     return launch_kernel(kernel, dim3((unsigned)a.T), dim3(kTB), 0, stream, a, ngroups,
                          step % ngroups == 0 ? 1 : step % ngroups);
   };
-  return rows_ragged(a) ? go(teacher_topk_stream_kernel<W, S, true, WAVES>)
-                : go(teacher_topk_stream_kernel<W, S, false, WAVES>);
+  return rows_ragged(a) ? go(teacher_topk_stream_kernel<W, S, true, WAVES, GUARDED>)
+                        : go(teacher_topk_stream_kernel<W, S, false, WAVES, GUARDED>);
 }
 // one-read kernel of this configuration; every row has kTB whole groups at least
 hipError_t launch_stream(const TopkArgs& a, hipStream_t stream) {
-  return launch_window<NPD_TOPK_WINDOW, NPD_TOPK_SAMPLE, 8>(a, stream);
+  return launch_window<NPD_TOPK_WINDOW, NPD_TOPK_SAMPLE, 8, false>(a, stream);
 }
-#if NPD_TOPK_ANY_SHAPE
-// few rows
-hipError_t launch_few(const TopkArgs& a, hipStream_t stream) {
-  const int ngroups = (a.nvec + kTB - 1) / kTB;
-  if (ngroups <= 8) return launch_window<8, 8, 4>(a, stream);
-  if (ngroups <= 12) return launch_window<12, 12, 4>(a, stream);
-  if (ngroups <= 16) return launch_window<16, 16, 4>(a, stream);
-  return launch_window<20, 20, 4>(a, stream);
+#if NPD_TOPK_GROUPS
+// rows that all begin on the same memory channel
+hipError_t launch_same_channel(const TopkArgs& a, hipStream_t stream) {
+  return launch_window<NPD_TOPK_WINDOW, NPD_TOPK_SAMPLE, 8, true>(a, stream);
 }
 #endif
-
 #if NPD_TOPK_ANY_SHAPE
+// few rows (of 9 .. 12 groups per thread: launch_stream's window holds as many, and k = 450 .. 512 of 65,600 took 5 .. 8 % longer)
+hipError_t launch_few(const TopkArgs& a, hipStream_t stream) {
+  const int ngroups = (a.nvec + kTB - 1) / kTB;
+  if (ngroups <= 8) return launch_window<8, 8, 4, false>(a, stream);
+  if (ngroups <= NPD_TOPK_WINDOW) return launch_stream(a, stream);
+  if (ngroups <= 16) return launch_window<16, 16, 4, false>(a, stream);
+  return launch_window<20, 20, 4, false>(a, stream);
+}
+
 hipError_t launch_any(const TopkArgs& a, hipStream_t stream) {
   return launch_kernel(teacher_topk_kernel, dim3((unsigned)a.T), dim3(kTB), 0, stream, a);
 }

@@ -3,7 +3,7 @@
 // and their values (the logits, or their log-softmax over the k).  Exact selection, integer bookkeeping only.
 //
 // One workgroup per token row, several per CU so that one row's ordering phase overlaps the others' streaming
-// (1024 threads, two per CU; for small k 512 threads, four per CU: npd_topk_kernels_512.hip).  Both kernels derive
+// (512 threads, four per CU: npd_topk_kernels_512.hip; or 1024 threads, two per CU or one: see launch_teacher_topk).  Both kernels derive
 // a lower bound L of the k-th largest logit from per-thread maxima and append every element >= L as a 64-bit
 // (key, ~id) word to an LDS list.  Up to 1,024 candidates are cut and ordered by one wave in its registers
 // (npd_topk_order.hpp); longer lists are cut at the k-th key with a two-level radix count and ordered by rank sort
@@ -36,13 +36,16 @@ namespace npd {
 
 namespace topk512 {
 hipError_t launch_stream(const TopkArgs& a, hipStream_t stream);  // npd_topk_kernels_512.hip
+hipError_t launch_same_channel(const TopkArgs& a, hipStream_t stream);
 }
 
 // Which kernel streams a long row.  Four 512-thread workgroups per CU (three rows stream while a fourth is in its ordering
 // phase) as long as their bound, from a sample of eight groups per thread, lets few enough groups pass, about k / 4 per chunk
 // of 512; else two of 1024 threads.  Up to a row per CU the second choice is one workgroup of 1024 threads with the whole
-// CU's registers, up to 20 groups in flight per thread and the bound from all of them.  Where memory alone is the limit
-// (k <= 64, many long rows) two workgroups of 1024 threads read a little faster.
+// CU's registers, up to 20 groups in flight per thread and the bound from all of them, if there are more than the others' 12.
+// Where memory alone is the limit (small k, many long rows) two workgroups of 1024 threads read a little faster: up to k = 64;
+// where that ends lies with the length (8,192 rows, 512 threads / two of 1024: 100,352 logits k = 72 251 / 254, 128 258 / 276;
+// 128,256 k = 72 321 / 316, 128 338 / 332; 200,064 k = 72 510 / 492).
 // Measured (MI355X, all scored, us, 512 threads / two of 1024 / one of 1024 per CU), k chunks in brackets:
 //   8 rows       65,600 k = 128 [2176] 11.7 / 13.3 / 13.3; 128,256 k = 64 [2048] 15.6 / - / 13.5; 262,144 k = 10 [640] 19.4 / 17.5 / 18.1
 //   256 rows     100,352 k = 10 [250] 14.4 / 15.1 / 15.6; 151,936 k = 10 [380] 18.1 / 18.5 / 20.8; 65,600 k = 256 [4352] 29.6 / 18.7 / 18.8
@@ -75,6 +78,8 @@ hipError_t launch_teacher_topk(int64_t T, int32_t V, int64_t stride, int32_t k, 
     const bool few = T <= kTopkFewRows, very_few = T <= kTopkFewRows / 2;
     const int64_t most = very_few && a.nvec > 12288 ? 1300 : few ? 2200 : T <= 512 ? 3250 : T < 3072 ? 3400 : 4400;
     const bool memory_bound = k <= 64 && a.nvec > 12288 && T * a.nvec > 100000000;
+    const bool same_channel = stride % 262144 == 0 && k <= 40 && T * a.nvec > 90000000;  // (see load_group)
+    if (same_channel) return topk512::launch_same_channel(a, stream);
     const bool threads512 = k <= kSmallK && passing <= most && !memory_bound && !(very_few && a.nvec > 20480);
     if (threads512) return topk512::launch_stream(a, stream);
     return few ? topk1024::launch_few(a, stream) : topk1024::launch_stream(a, stream);

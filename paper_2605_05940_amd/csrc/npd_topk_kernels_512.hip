@@ -1,4 +1,5 @@
-// The one-read top-k kernel with 512-thread workgroups, four per CU, for small k (see npd_topk_kernels.hip).
+// The one-read top-k kernel with 512-thread workgroups, four per CU (which calls: launch_teacher_topk in npd_topk_kernels.hip;
+// k <= 256).
 // 2048 candidates and 1024 groups per row keep a workgroup's LDS at 37 KB; rows that pass more take the exact slow path.
 #define NPD_TOPK_NS topk512
 #define NPD_TOPK_TB 512

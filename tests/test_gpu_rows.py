@@ -368,6 +368,41 @@ def test_teacher_topk_windows(oracle, V, T, k, off):
     _check_teacher_topk(oracle, V, V, off, k, T)
 
 
+# lists longer than one wave takes: k around 512, every element a candidate, records of up to 1,024 entries; one window and more
+@pytest.mark.parametrize("V,T,k", [
+    (1040, 40, 512), (1040, 40, 513), (1030, 12, 1024), (2048, 40, 300), (2056, 12, 257), (4096, 40, 512), (4100, 12, 512),
+    (4104, 12, 512), (8192, 12, 513), (8192, 12, 1024), (16400, 260, 700), (65600, 12, 500), (65600, 260, 1000),
+    (98304, 12, 513), (98312, 12, 512), (98312, 40, 600), (131080, 260, 513), (200008, 12, 1024), (262144, 12, 700),
+])
+@pytest.mark.parametrize("off", [0, 3])
+def test_teacher_topk_long_records(oracle, V, T, k, off):
+    _check_teacher_topk(oracle, V, V, off, k, T)
+
+
+@pytest.mark.parametrize("V,off,k,T", [(262144, 0, 10, 2747), (262144, 0, 10, 2746), (262131, 3, 40, 2760), (262144, 0, 41, 2760)])
+def test_teacher_topk_of_rows_on_one_memory_channel(oracle, V, off, k, T):
+    """Many rows with a pitch of 524,288 bytes: sixteen different ones over and over."""
+    n, pitch = 16, 262144
+    g = torch.Generator(device=dev()).manual_seed(V + k)
+    x = 3.0 * torch.randn((n, V), generator=g, device=dev())
+    x[1] = torch.randint(0, 3, (V,), generator=g, device=dev()).float()
+    x[2] = -x[2].abs() - 0.01
+    x[3] = torch.where(torch.rand(V, generator=g, device=dev()) < 0.5, 0.0, -0.0)
+    x[4, 0] = x[4, V - 1] = x[4, V // 2] = 50.0
+    _, t = _rows(T, V, pitch, off)
+    for r in range(0, T, n):
+        t[r:r + n].copy_(x[:min(n, T - r)])
+    mask = torch.ones(T, dtype=torch.uint8, device=dev())
+    idx, val = Guarded(T * k, torch.int32), Guarded(T * k, torch.float32)
+    print(f"[rows] teacher top-k V={V} off={off} k={k} T={T}", flush=True)
+    binding.npd_teacher_topk(t, k, topk_idx=idx.t.view(T, k), topk_val=val.t.view(T, k), loss_mask=mask, log_probs=False)
+    torch.cuda.synchronize()
+    ref = oracle.teacher_topk(synth.bf16_bits(x.to(torch.bfloat16)), k, np.ones(n, np.uint8), False)
+    at = np.arange(T) % n
+    np.testing.assert_array_equal(idx.check().cpu().numpy().reshape(T, k), ref["idx"][at])
+    np.testing.assert_array_equal(val.check().cpu().numpy().reshape(T, k), ref["val"][at].astype(np.float32))
+
+
 @pytest.mark.parametrize("T", [8, 300, 520])
 def test_teacher_topk_keys_of_both_signs(oracle, T):
     """Candidates that span so many keys that one does not fit 32 bits beside its id: fewer positive logits than k."""
