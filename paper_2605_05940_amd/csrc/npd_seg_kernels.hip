@@ -16,7 +16,8 @@ __global__ __launch_bounds__(kSegBlock) void fill_i32_kernel(int32_t* p, int64_t
 // b + t + TH, ... in order; `own` is called with every position.  What such a sum waits for is a chain of loads per position,
 // so up to kSumAhead positions' masks and values are requested together (values of positions that are not scored are read
 // and left out).  Measured (MI355X, in a graph): 4 samples of 8,192 positions 10.1 us one position at a time, 4.8 us so; 10
-// samples of 819 3.4 / 3.0.
+// samples of 819 3.4 / 3.0.  TWO: batches of two besides, for samples of one or two positions per thread (1,024 of 300 3.2, 3.5
+// in a batch of eight, 2.7 so; 16 of 300 2.9 and 2.4; the more code costs the others 0 .. 0.1 us, 4,096 of them 0.15).
 constexpr int kSumAhead = 8;
 template <int TH, int N, class Own>
 __device__ __forceinline__ void masked_sum_step(const float* __restrict__ x, const uint8_t* __restrict__ mask, int64_t p0,
@@ -39,16 +40,20 @@ __device__ __forceinline__ void masked_sum_step(const float* __restrict__ x, con
     n += (int)__popcll(__ballot(scored));  // of the wave
   }
 }
-template <int TH, class Own>
+template <int TH, bool TWO, class Own>
 __device__ __forceinline__ void masked_sum(const float* __restrict__ x, const uint8_t* __restrict__ mask, int64_t b, int64_t e,
                                            int tid, float& acc, int& n, Own own) {
   int64_t p = b;
-  for (; e - p > TH; p += kSumAhead * TH) masked_sum_step<TH, kSumAhead>(x, mask, p, e, tid, acc, n, own);
-  if (p < e) masked_sum_step<TH, 1>(x, mask, p, e, tid, acc, n, own);
+  for (; e - p > (TWO ? 2 : 1) * TH; p += kSumAhead * TH) masked_sum_step<TH, kSumAhead>(x, mask, p, e, tid, acc, n, own);
+  if (TWO && e - p > TH)
+    masked_sum_step<TH, 2>(x, mask, p, e, tid, acc, n, own);
+  else if (p < e)
+    masked_sum_step<TH, 1>(x, mask, p, e, tid, acc, n, own);
 }
 
 // One sample, by 256 threads of the workgroup (thread `tid` of them; `fred`, `ired`: their four words each).  All threads
 // of the workgroup call it alike: it holds the workgroup's barriers.  `seg` < 0: no sample, only the barriers.
+template <bool TWO>
 __device__ __forceinline__ void reduce_segment(int64_t T, int seg, int tid, const float* __restrict__ x,
                                                const uint8_t* __restrict__ mask, const int32_t* __restrict__ cu,
                                                float* seg_sum, int32_t* seg_count, float* seg_mean,
@@ -64,7 +69,7 @@ __device__ __forceinline__ void reduce_segment(int64_t T, int seg, int tid, cons
   }
   float acc = 0.0f;
   int n = 0;
-  masked_sum<kSegBlock>(x, mask, b, e, tid, acc, n, [&](int64_t p) {
+  masked_sum<kSegBlock, TWO>(x, mask, b, e, tid, acc, n, [&](int64_t p) {
     if (token_to_sample) token_to_sample[p] = seg;
   });
   // the 256 partials are folded by a fixed tree, the four wave totals in wave order
@@ -98,7 +103,7 @@ __global__ __launch_bounds__(kSegBlock) void segment_reduce_kernel(int64_t T, co
                                                                    int32_t* token_to_sample, int32_t* status) {
   __shared__ float fred[kSegBlock / kWave];
   __shared__ int ired[kSegBlock / kWave];
-  reduce_segment(T, blockIdx.x, threadIdx.x, x, mask, cu, seg_sum, seg_count, seg_mean, token_to_sample, status, fred, ired);
+  reduce_segment<true>(T, blockIdx.x, threadIdx.x, x, mask, cu, seg_sum, seg_count, seg_mean, token_to_sample, status, fred, ired);
 }
 
 hipError_t launch_segment_reduce(int64_t T, int32_t S, const float* values, const uint8_t* mask, const int32_t* cu,
@@ -212,7 +217,7 @@ __global__ __launch_bounds__(kLagBlock) void policy_lag_kernel(int64_t T, int32_
     constexpr int NW = kSegBlock / kWave;
     const int sub = threadIdx.x / kSegBlock;
     const int64_t seg = (int64_t)(blockIdx.x - 1) * (kLagBlock / kSegBlock) + sub;
-    reduce_segment(T, seg < S ? (int)seg : -1, threadIdx.x % kSegBlock, kl, mask, cu, nullptr, seg_count, seg_mean, nullptr,
+    reduce_segment<false>(T, seg < S ? (int)seg : -1, threadIdx.x % kSegBlock, kl, mask, cu, nullptr, seg_count, seg_mean, nullptr,
                    status, fred + sub * NW, ired + sub * NW);
     return;
   }
@@ -223,7 +228,7 @@ __global__ __launch_bounds__(kLagBlock) void policy_lag_kernel(int64_t T, int32_
   bad = __syncthreads_or(bad);
   float acc = 0.0f;
   int n = 0;
-  if (!bad && S > 0) masked_sum<kLagBlock>(kl, mask, cu[0], cu[S], threadIdx.x, acc, n, [](int64_t) {});
+  if (!bad && S > 0) masked_sum<kLagBlock, false>(kl, mask, cu[0], cu[S], threadIdx.x, acc, n, [](int64_t) {});
   constexpr int NW = kLagBlock / kWave;
   const int lane = threadIdx.x % kWave;
   acc = wave_sum_dpp(acc);

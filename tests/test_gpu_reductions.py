@@ -15,7 +15,8 @@ def _rel_bound(n, threads):
     return (n / threads + 22) * 2.0 ** -24
 
 
-@pytest.mark.parametrize("n", [1, 255, 256, 257, 511, 512, 513, 2048, 2049, 2304, 2305, 4609, 20000])
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 511, 512, 513, 1024, 1025, 2048, 2049, 2304, 2305, 2560, 2561, 3072, 3073, 4096,
+                               4097, 4609, 20000])
 def test_segments_around_the_batches(oracle, n):
     rng = np.random.default_rng(n)
     cu = np.array([0, n, n, n + 3, 2 * n + 3, 2 * n + 260], np.int32)
