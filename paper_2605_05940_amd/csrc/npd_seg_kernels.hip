@@ -176,7 +176,8 @@ hipError_t launch_delta_ifd(int32_t P, int32_t S, const float* ms, const float* 
                             const int32_t* pc, const int32_t* pu, float lo, float hi, uint32_t flags, float* ifd_s,
                             float* ifd_t, float* delta, uint8_t* zone, uint8_t* keep, int32_t* keep_count,
                             hipStream_t stream) {
-  if (P > 0 && P <= kIfdAlone) {
+  // (nothing to clear without a count: 600 and 1,024 pairs 2.8 us by workgroups of 256, 2.9 and 3.0 us by one)
+  if (P > 0 && P <= (keep_count ? kIfdAlone : kSegBlock)) {
     if (P <= kSegBlock)
       return launch_kernel(delta_ifd_kernel<kSegBlock, true>, dim3(1), dim3(kSegBlock), 0, stream, P, S, ms, mt, cnt, pc, pu,
                            lo, hi, flags, ifd_s, ifd_t, delta, zone, keep, keep_count);

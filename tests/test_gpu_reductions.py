@@ -62,6 +62,12 @@ def test_kept_pairs_of_one_workgroup_or_several(oracle, P):
     clear = np.abs(np.abs(np.nan_to_num(ref["delta"], nan=9.0)) - 0.3) > 1e-5    # fp32 and fp64 agree off the thresholds
     np.testing.assert_array_equal(zone.check().cpu().numpy()[clear], ref["zone"][clear])
     assert int(count.check().item()) == int(keep.check().sum().item())
+    kept = keep.check().clone()
+    zone.poison()
+    keep.poison()
+    binding.npd_delta_ifd_score(d(ms), d(mt), d(cnt), d(pc), d(pu), -0.3, 0.3, zone=zone.t, keep=keep.t)   # no count
+    assert torch.equal(keep.check(), kept)
+    np.testing.assert_array_equal(zone.check().cpu().numpy()[clear], ref["zone"][clear])
 
 
 @pytest.mark.parametrize("S", [(1 << 24) - 9, (1 << 24) - 8, (1 << 24) - 1])
