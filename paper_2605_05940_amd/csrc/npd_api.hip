@@ -329,7 +329,8 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
         usable = false;
       }
       // bytes beyond those are used only where they are nobody else's
-      const size_t more = workspace_bytes_of(*desc, true);
+      // (a call prefers at most twice the least)
+      const size_t more = workspace_bytes >= 2 * need ? 2 * need : workspace_bytes_of(*desc, true);
       have = workspace_bytes >= more && !b.overlaps_any(range_of(workspace, more)) ? more : need;
     }
     a.ws = usable ? static_cast<uint32_t*>(workspace) : nullptr;

@@ -143,9 +143,9 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
   if (k > 0) {
     const int g = gang_slices(a.nvec_s, k, on_lines);
     const size_t bytes = record_bytes(a.T, g, gang_words(teacher_kind == kTopk || !a.need_lse1 ? 2 : 4));
-    const size_t preferred =
-        gang_workspace_preferred(a.T, a.V, teacher_kind, a.divergence, teacher_kind == kDense && a.c != kLog2e);
-    if (g >= 2 && bytes <= workspace_bytes && bytes <= preferred)
+    const size_t least =
+        gang_workspace_bytes(a.T, a.V, teacher_kind, a.divergence, teacher_kind == kDense && a.c != kLog2e);
+    if (g >= 2 && bytes <= workspace_bytes && bytes <= 2 * least)
       a.gang = g;
     else
       k = 0;

@@ -26,13 +26,18 @@ static hipError_t launch_solo_dense(const KdArgs& a, hipStream_t stream) {
   }
 }
 
-// the shapes of the forward and the reverse KL
+// The shapes of the forward and the reverse KL.  Forward-only rows of up to 1,536 groups have one of six groups per thread: the
+// instances of eight take 101 .. 107 registers since they unpack with the matrix cores, four waves per SIMD, and those of six
+// 85 .. 91, five (MI355X, 16,384 rows, us, eight groups unpacked by shifts, five waves / by the matrix cores / six: 8,500 logits
+// 89.2 / 97.7 / 84.4, 10,500 101.6 / 108.5 / 99.1; 12,288 113.8 / 111.5 / 114.0).
 template <int DIVK, bool GRAD>
 static hipError_t launch_solo_two_sweeps(const KdArgs& a, hipStream_t stream) {
   if (a.nvec_s <= 64 * 2) return launch_solo_dense<64, 2, DIVK, GRAD>(a, stream);
   if (a.nvec_s <= 64 * 4) return launch_solo_dense<64, 4, DIVK, GRAD>(a, stream);
   if (a.nvec_s <= 128 * 4) return launch_solo_dense<128, 4, DIVK, GRAD>(a, stream);
   if (a.nvec_s <= 256 * 4) return launch_solo_dense<256, 4, DIVK, GRAD>(a, stream);
+  if constexpr (!GRAD)
+    if (a.nvec_s <= 256 * 6) return launch_solo_dense<256, 6, DIVK, GRAD>(a, stream);
   if (a.nvec_s <= 256 * 8) return launch_solo_dense<256, 8, DIVK, GRAD>(a, stream);
   if (a.nvec_s <= 256 * 10) return launch_solo_dense<256, 10, DIVK, GRAD>(a, stream);
   return launch_solo_dense<512, 8, DIVK, GRAD>(a, stream);

@@ -441,3 +441,19 @@ def test_masked_entries_among_finite_ones(oracle, V, div, tau, ce):
     got = _call(lay, s, t, y, V=V, pitch=V, offs=(0, 0, 0), div=div, tau=tau, ce=ce)
     compare_kd(got, ref, lay.loss_mask, lay.cu_seqlens, oracle, grad_scale=0.75 + ce * tau, tau=tau,
                amp_from_ref=div != "forward")
+
+
+# six groups per thread, the last one partly or fully there, and the first rows of eight; aligned and not
+@pytest.mark.parametrize("V,off", [(8200, 0), (10241, 3), (12285, 5), (12288, 0), (12291, 1), (12296, 0)])
+@pytest.mark.parametrize("tau", [1.0, 2.0, 3.0])
+def test_forward_only_rows_of_six_groups(oracle, V, off, tau):
+    w, lay, s, t, lab = _batch(V)
+    s, t = s.clone(), t.clone()
+    for r in range(1, s.shape[0], 2):                   # masked entries: one group of a thread is not finite
+        s[r, r::613] = t[r, r::613] = float("-inf")
+    y = lab.copy()
+    y[1::2] = 0
+    print(f"[rows] forward only V={V} off={off} tau={tau}", flush=True)
+    ref = _reference(oracle, lay, s, t, y, "forward", tau, 1.0, 0.0)
+    got = _call(lay, s, t, y, V=V, pitch=V, offs=(off, off, off), tau=tau, grad=False)
+    compare_kd(got, {n: ref[n] for n in ("kd", "nll_s", "nll_t", "lse_s")}, lay.loss_mask, lay.cu_seqlens, oracle)
