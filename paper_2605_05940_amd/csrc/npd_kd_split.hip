@@ -235,17 +235,22 @@ namespace {
 //                            of 50,304 16.3 / 14.8, 400 18.6 / 18.5, 440 .958 of the speed at 60,000, 512 19.8 / 21.3, 520
 //                            1.15, 700 .99 .. 1.06, 768 .974 .. 1.05, 800 32.3 / 29.5;  512 of 100,352 36.1 / 35.3;  6,000 rows of
 //                            50,304 182 / 182, 151,936 541 / 510  (32,000: 128 rows 8.4 / 8.2, 4,096 80.7 / 84.2)
-//   dense teacher, tau = 2, NLL wanted   128 rows of 151,936 33.4 / 23.2;  512 of 50,304 1.06;  6,000 rows of 50,304 255 / 218,
+//   dense teacher, tau = 2, both NLLs    128 rows of 151,936 33.4 / 23.2;  512 of 50,304 1.06;  6,000 rows of 50,304 255 / 218,
 //                            151,936 792 / 633
+//   the student's alone (speed; the other kernel then has less to do, this one as many instructions)   50,304: 512 rows .971,
+//                            600 1.09, 1,024 .98, 1,400 1.04, 1,536 .973, 6,000 .95;  100,352 512 1.02, 1,024 .96, 1,400 1.01, 6,000 .90;
+//                            41,000 6,000 1.05;  110,000 512 1.23, 6,000 1.34
 //   no teacher               64 rows of 65,536 6.9 / 6.2, of 75,000 .952, of 90,000 1.06;  100 rows of 100,352 1.02, 112 .932, 128
 //                            8.7 / 9.6, of 116,000 1.03;  128 rows of 151,936 12.3 / 11.0;  240,000: 130 .. 256 rows .95 .. .98, 300
 //                            1.26, 500 .. 1,024 .97 .. .99, 2,000 1.02;  262,144: 181 rows 20.4 / 19.3, 256 .995, 1,000 .996, 4,096
 //                            339 / 323  (181 rows of 151,936 11.7 / 13.4, 1,024 of 200,000 63.9 / 66.1)
-int split_groups(int64_t T, int nvec, bool dense, bool lse1) {
+enum Tau1Sums { kNoSums, kStudentSum, kBothSums };  // at tau = 1, beside others
+int split_groups(int64_t T, int nvec, bool dense, Tau1Sums sums) {
   constexpr int kFew = 256;  // rows: one to a compute unit
   if (dense) {
     if (nvec <= 5120 || (T > kFew / 2 && T <= kFew && nvec < 16384)) return 0;
-    if (!lse1 && T > 432 && T <= 2 * kFew && nvec < 12288) return 0;
+    if (sums != kBothSums && T > 432 && T <= 2 * kFew && nvec < 12288) return 0;
+    if (sums == kStudentSum && (T > 1400 || (T > 960 && T <= 4 * kFew)) && nvec >= 5500 && nvec < 13000) return 0;
     return T <= kFew ? 4 : 8;
   }
   if (nvec >= 32768) return 8;
@@ -255,8 +260,8 @@ int split_groups(int64_t T, int nvec, bool dense, bool lse1) {
 }
 
 // slices of a row of nvec groups, 0: not split
-int split_slices(int64_t T, int nvec, bool dense, bool lse1) {
-  const int cap = split_groups(T, nvec, dense, lse1) * kSplitThreads;
+int split_slices(int64_t T, int nvec, bool dense, Tau1Sums sums) {
+  const int cap = split_groups(T, nvec, dense, sums) * kSplitThreads;
   if (cap == 0) return 0;
   const int g = (nvec + cap - 1) / cap;
   return g >= 2 && g <= kSplitMax && T * (int64_t)g <= 0x7fffffffLL ? g : 0;
@@ -277,21 +282,25 @@ hipError_t launch_split(const KdArgs& a, hipStream_t stream) {
 size_t split_scratch_bytes(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1) {
   if ((teacher_kind != kDense && teacher_kind != kNone) || divergence != kForwardKl) return 0;
   const bool dense = teacher_kind == kDense;
-  const int g = split_slices(T, V / 8, dense, dense && lse1);
+  const int g = split_slices(T, V / 8, dense, dense && lse1 ? kBothSums : kNoSums);  // (split if any of them is)
   return (size_t)T * g * split_words(dense, dense && lse1) * sizeof(float);
 }
 
+static Tau1Sums tau1_sums(const KdArgs& a, bool dense) {
+  return !dense || !a.need_lse1 ? kNoSums : a.tnll ? kBothSums : kStudentSum;
+}
 bool split_path_applies(const KdArgs& a, int teacher_kind) {
-  return split_slices(a.T, a.nvec_s, teacher_kind == kDense, teacher_kind == kDense && a.need_lse1) > 0;
+  const bool dense = teacher_kind == kDense;
+  return split_slices(a.T, a.nvec_s, dense, tau1_sums(a, dense)) > 0;
 }
 
 hipError_t launch_kd_split(const KdArgs& a0, int teacher_kind, hipStream_t stream) {
   KdArgs a = a0;
   const bool dense = teacher_kind == kDense;
-  a.gang = split_slices(a.T, a.nvec_s, dense, dense && a.need_lse1);
+  a.gang = split_slices(a.T, a.nvec_s, dense, tau1_sums(a, dense));
   a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;
   if (!dense) return launch_split<8, false, false>(a, stream);
-  if (split_groups(a.T, a.nvec_s, true, a.need_lse1) == 4)
+  if (split_groups(a.T, a.nvec_s, true, tau1_sums(a, true)) == 4)
     return a.need_lse1 ? launch_split<4, true, true>(a, stream) : launch_split<4, true, false>(a, stream);
   return a.need_lse1 ? launch_split<8, true, true>(a, stream) : launch_split<8, true, false>(a, stream);
 }

@@ -122,3 +122,22 @@ def test_forward_only_call_with_no_memory_left_for_its_scratch(native, monkeypat
         used.clear()
     torch.cuda.synchronize()
     assert torch.equal(kd, want)
+
+
+@pytest.mark.parametrize("T,teacher_nll,split", [(1401, False, False), (1401, True, True), (600, False, True), (512, False, False)])
+def test_which_sums_at_tau_one_are_split(T, teacher_nll, split):
+    """The student's sum alone: many rows of a middling vocabulary stay whole (bit for bit as with no_workspace)."""
+    V = 65536
+    g = torch.Generator(device=dev()).manual_seed(T)
+    s, t = (torch.randn((T, V), generator=g, device=dev()).mul_(3).to(torch.bfloat16) for _ in range(2))
+    mask, lab = torch.ones(T, dtype=torch.uint8, device=dev()), torch.arange(T, dtype=torch.int32, device=dev())
+    out = {}
+    for n in (False, True):
+        kd, nll, tnll = (torch.empty(T, device=dev()) for _ in range(3))
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, labels=lab, tau=2.0, kd_tok=kd, nll_tok=nll,
+                                    teacher_nll_tok=tnll if teacher_nll else None, no_workspace=n)
+        out[n] = [kd, nll] + ([tnll] if teacher_nll else [])
+    torch.cuda.synchronize()
+    for a, b in zip(out[False], out[True]):
+        torch.testing.assert_close(a, b, rtol=2e-5, atol=2e-5)
+    assert all(torch.equal(a, b) for a, b in zip(out[False], out[True])) != split
