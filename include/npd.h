@@ -128,7 +128,9 @@ const char* npd_status_string(npd_status st);
  * workspace npd_workspace_bytes() asks for is given ("kd_gang_kernel": rows shared by several workgroups;
  * "kd_solo_kernel": the same kernels with a whole row to a workgroup, in a profile kd_gang_kernel and
  * kd_gang_topk_kernel too; "kd_cached_kernel", "kd_rows_kernel", "div_rows_kernel"; "" for an invalid desc): lets a
- * benchmark or profile say what it measured.  Static string.
+ * benchmark or profile say what it measured.  Static string.  Forward-only calls through npd_kd_loss_forward() with scratch
+ * run "kd_split_kernel" and "kd_split_merge_kernel" instead where npd_forward_scratch_bytes() is not 0 (with a temperature
+ * and labels: in most of these calls).
  */
 const char* npd_kd_kernel_name(const npd_kd_desc* desc);
 
@@ -215,7 +217,8 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
 /*
  * Forward-only calls (desc->flags with NPD_FLAG_FWD_ONLY) with scratch memory: arguments, results and errors are those of
  * npd_kd_loss_fwd_bwd without grad_out; rows that are too few to fill the GPU are split over several workgroups.
- * npd_forward_scratch_bytes() says how many bytes that takes: 0 where splitting gains nothing, or for an invalid desc.
+ * npd_forward_scratch_bytes() says how many bytes that takes: 0 where splitting gains nothing, or for an invalid desc.  (Which
+ * outputs are wanted is not known there: at tau != 1 it may ask for scratch that the call then makes no use of.)
  *
  *   scratch   device, >= npd_forward_scratch_bytes(desc) bytes, 16-byte aligned, contents meaningless before and after; two
  *             calls that may run at the same time need one each.  Optional: where it is NULL, too small, unaligned or

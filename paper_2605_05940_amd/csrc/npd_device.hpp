@@ -75,7 +75,7 @@ __device__ __forceinline__ s16x4 lane_identity(short one) {
   const int l = threadIdx.x & 3;
   return s16x4{l == 0 ? one : (short)0, l == 1 ? one : (short)0, l == 2 ? one : (short)0, l == 3 ? one : (short)0};
 }
-constexpr short kBf16One = 0x3f80, kBf16MinusOne = (short)0xbf80;
+constexpr short kBf16One = 0x3f80;
 __device__ __forceinline__ void mfma8(const uint4& v, const s16x4& m, const float c[8], float x[8]) {
   const uint2 lo = make_uint2(v.x, v.y), hi = make_uint2(v.z, v.w);
   const f32x4 a = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(m, __builtin_bit_cast(s16x4, lo), f32x4{c[0], c[1], c[2], c[3]}, 0, 0, 0);

@@ -594,9 +594,9 @@ def test_forward_scratch(lib):
         d = dict(vocab=V, n_tokens=T, student_stride=V, teacher_stride=V, teacher_kind=kind, tau=tau)
         assert (ask(**d) > 0) == split, (V, T, kind, tau)
 
-    def forward(d, grad_flags=F, kd=FAKE + 0x10000000, student=FAKE, scratch=None, n=0):
+    def forward(d, kd=FAKE + 0x10000000, student=FAKE):
         return lib.npd_kd_loss_forward(ctypes.byref(d), student, FAKE + 0x4000000, None, None, None, FAKE + 0x8000000, kd,
-                                       None, None, None, None, scratch, n, None)
+                                       None, None, None, None, None, 0, None)
 
     assert forward(_desc(**{**big, "flags": 0})) == E_NULL                        # a gradient call has no gradient here
     assert forward(_desc(**{**big, "tau": 0.0})) == E_VALUE

@@ -1,5 +1,7 @@
 """Forward-only calls whose rows are split over several workgroups, against the oracle and against the same call with a
 workgroup per row."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -12,17 +14,24 @@ pytestmark = pytest.mark.gpu
 
 def _scratch(T, V, teacher, tau):
     d = binding.KdDesc(T, V, teacher, V, V, 0, binding.NPD_FLAG_FWD_ONLY, tau, 1.0, 0.0, 0, 0.0)
-    import ctypes
     return binding.load().npd_forward_scratch_bytes(ctypes.byref(d))
 
 
 # slices of 1,024 groups of eight logits a tensor (up to 256 rows) or 2,048 (more, or no teacher): one more and one less than
-# a whole number of them, rows at any offset, last slices that hold edge elements alone
-@pytest.mark.parametrize("V,pitch,T", [
+# a whole number of them, rows at any offset, last slices that hold edge elements alone, the most slices a row may have (64)
+DENSE = [
     (40968, 40968, 24), (49152, 49152, 24), (49160, 49160, 24), (50003, 50003, 24), (65537, 65600, 20), (98305, 98305, 20),
-    (151936, 151936, 16), (262144, 262144, 8), (40976, 40976, 300), (49159, 49159, 280), (65544, 65544, 270),
-])
-@pytest.mark.parametrize("dense", [True, False])
+    (151936, 151936, 16), (262144, 262144, 8), (524288, 524288, 8), (40976, 40976, 300), (49159, 49159, 280),
+    (65544, 65544, 270),
+]
+ALONE = [
+    (65536, 65536, 24), (65544, 65544, 24), (81920, 81920, 24), (81931, 81931, 24), (98304, 98304, 100), (98305, 98408, 20),
+    (114696, 114696, 40), (151936, 151936, 16), (262144, 262144, 8), (1048576, 1048576, 8), (240003, 240003, 290),
+    (262151, 262151, 280),
+]
+
+
+@pytest.mark.parametrize("V,pitch,T,dense", [(*x, True) for x in DENSE] + [(*x, False) for x in ALONE])
 def test_split_rows(oracle, V, pitch, T, dense):
     w = synth.scaled(synth.config(1), n_rows=1, row_len=T, vocab=V, length_lo=4, length_hi=16)
     lay = synth.make_layout(w)
@@ -42,7 +51,7 @@ def test_split_rows(oracle, V, pitch, T, dense):
     lab[7] = V - 1
     lab[3:5] = 1                                                # (not a masked entry)
     labels = lab.cpu().numpy()
-    assert _scratch(T, V, binding.NPD_TEACHER_NONE if not dense else 0, 2.0) > 0 or not dense
+    assert _scratch(T, V, binding.NPD_TEACHER_NONE if not dense else 0, 1.0) > 0
     for tau in (1.0, 2.0) if dense else (1.0,):
         print(f"[split] V={V} pitch={pitch} T={T} dense={dense} tau={tau}", flush=True)
         got, one = (run_gpu_kd(s, mask, t=t if dense else None, labels=lab, tau=tau, want_grad=False, no_workspace=n)
@@ -141,3 +150,35 @@ def test_which_sums_at_tau_one_are_split(T, teacher_nll, split):
     for a, b in zip(out[False], out[True]):
         torch.testing.assert_close(a, b, rtol=2e-5, atol=2e-5)
     assert all(torch.equal(a, b) for a, b in zip(out[False], out[True])) != split
+
+
+def test_forward_entry_point_with_scratch_that_does_not_do():
+    """NULL, too small, unaligned or overlapping another argument: the same call without, and nothing else is written."""
+    T, V, L = 12, 65536, binding.load()
+    g = torch.Generator(device=dev()).manual_seed(11)
+    s, t = (torch.randn((T, V), generator=g, device=dev()).mul_(3).to(torch.bfloat16) for _ in range(2))
+    mask = torch.ones(T, dtype=torch.uint8, device=dev())
+    whole, split = torch.empty(T, device=dev()), torch.empty(T, device=dev())
+    binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, kd_tok=whole, no_workspace=True)
+    binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, kd_tok=split)
+    d = binding.KdDesc(T, V, 0, V, V, 0, binding.NPD_FLAG_FWD_ONLY, 1.0, 1.0, 0.0, 0, 0.0)
+    need = L.npd_forward_scratch_bytes(ctypes.byref(d))
+    block = torch.full((need + 256,), 7, dtype=torch.uint8, device=dev())    # its first words are kd_tok in one call
+    for name, kd, scratch, n, want in (("fits", None, 128, need, split), ("none", None, None, 0, whole),
+                                       ("too small", None, 128, need - 1, whole), ("unaligned", None, 132, need, whole),
+                                       ("overlaps kd_tok", block[64:64 + 4 * T].view(torch.float32), 0, need, whole),
+                                       ("touches kd_tok", block[64:64 + 4 * T].view(torch.float32), 128, need, split)):
+        block.fill_(7)
+        kd = torch.empty(T, device=dev()) if kd is None else kd
+        print(f"[split] scratch {name}", flush=True)
+        st = L.npd_kd_loss_forward(ctypes.byref(d), s.data_ptr(), t.data_ptr(), None, None, None, mask.data_ptr(), kd.data_ptr(),
+                                   None, None, None, None, None if scratch is None else block.data_ptr() + scratch, n,
+                                   binding._stream())
+        torch.cuda.synchronize()
+        assert st == 0 and torch.equal(kd, want), name
+        assert (block[:64] == 7).all() and (block[128 + need:] == 7).all(), name
+        if want is whole:
+            assert (block[128:] == 7).all(), name
+    # one slice more than a row may have
+    assert _scratch(8, 524288, 0, 1.0) > 0 and _scratch(8, 524296, 0, 1.0) == 0
+    assert _scratch(8, 1048576, binding.NPD_TEACHER_NONE, 1.0) > 0 and _scratch(8, 1048584, binding.NPD_TEACHER_NONE, 1.0) == 0
