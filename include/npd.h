@@ -94,7 +94,8 @@ enum {
 /* npd_delta_ifd_score flags */
 enum { NPD_IFD_REQUIRE_TEACHER_LE_1 = 1u };
 
-/* Largest vocabulary and number of positions one call takes (beyond: NPD_ERR_UNSUPPORTED). */
+/* Largest vocabulary and number of positions one call takes (beyond: NPD_ERR_UNSUPPORTED).  A launch takes fewer than 2^32
+   threads: calls of so many rows or samples that theirs would be more (from 2^24 with 256 threads each) are NPD_ERR_HIP. */
 #define NPD_MAX_VOCAB (1 << 26)
 #define NPD_MAX_TOKENS 0x7fffffffLL
 

@@ -5,7 +5,8 @@ import torch
 from paper_2605_05940_amd import binding
 from gpu_util import dev
 
-CALLS = ("kd", "kd_bad_aligned", "kd_ce_tau2", "kd_topk", "forward", "forward_split", "segments", "lag", "ifd", "topk")
+CALLS = ("kd", "kd_bad_aligned", "kd_ce_tau2", "kd_inplace", "kd_workspace", "kd_no_workspace", "kd_kept_too_small", "kd_topk",
+         "forward", "forward_split", "forward_alone", "segments", "segments_no_values", "lag", "ifd", "ifd_all", "topk")
 
 
 def _call(name, T=24, V=65536):
@@ -19,7 +20,15 @@ def _call(name, T=24, V=65536):
     mask = (torch.rand(T, generator=g, device=dev()) < 0.8).to(torch.uint8)
     lab = torch.randint(0, V, (T,), generator=g, device=dev(), dtype=torch.int32)
     cu = torch.tensor([0, 5, 9, T], dtype=torch.int32, device=dev())
-    if name in ("kd", "kd_bad_aligned", "kd_ce_tau2"):
+    if name in ("kd_inplace", "kd_workspace", "kd_no_workspace", "kd_kept_too_small"):
+        n = 2 * binding.npd_workspace_bytes(T, V)
+        out = dict(grad_out=s if name == "kd_inplace" else torch.zeros_like(s), kd_tok=f(T))
+        ws = torch.empty(n, dtype=torch.uint8, device=dev()) if name == "kd_workspace" else None
+        if name == "kd_kept_too_small":                    # (enough for the call, less than it prefers: a block of its own)
+            binding._workspaces[0] = torch.empty(n // 2, dtype=torch.uint8, device=dev())
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, skew_alpha=0.5, workspace=ws,
+                                    no_workspace=name == "kd_no_workspace", **out)
+    elif name in ("kd", "kd_bad_aligned", "kd_ce_tau2"):
         out = dict(grad_out=torch.zeros((T, pitch), dtype=torch.bfloat16, device=dev())[:, :V], kd_tok=f(T), nll_tok=f(T),
                    teacher_nll_tok=f(T), lse_tok=f(T), dev_status=torch.zeros(1, dtype=torch.int32, device=dev()))
         ce = dict(tau=2.0, ce_grad_scale=0.25) if name == "kd_ce_tau2" else dict(divergence=1)
@@ -31,6 +40,12 @@ def _call(name, T=24, V=65536):
     elif name in ("forward", "forward_split"):
         out = dict(kd_tok=f(T), nll_tok=f(T))
         binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, labels=lab, **out)
+    elif name == "forward_alone":
+        out = dict(nll_tok=f(T), lse_tok=f(T))
+        binding.npd_kd_loss_fwd_bwd(s, mask, labels=lab, **out)
+    elif name == "segments_no_values":
+        out = dict(seg_count=i(3), dev_status=torch.zeros(1, dtype=torch.int32, device=dev()))
+        binding.npd_segment_reduce(None, mask, cu, **out)
     elif name == "segments":
         out = dict(seg_sum=f(3), seg_count=i(3), seg_mean=f(3), token_to_sample=i(T))
         binding.npd_segment_reduce(s[:, 0].float(), mask, cu, **out)
@@ -41,6 +56,10 @@ def _call(name, T=24, V=65536):
         out = dict(delta=f(2), keep=torch.zeros(2, dtype=torch.uint8, device=dev()), keep_count=i(1))
         ones = torch.tensor([1.0, 2.0, 1.5], device=dev())
         binding.npd_delta_ifd_score(ones, ones * 1.5, cu[1:], cu[:2] * 0, cu[:2] * 0 + 1, 0.0, 0.8, **out)
+    elif name == "ifd_all":
+        out = dict(ifd_student=f(2), ifd_teacher=f(2), delta=f(2), zone=torch.zeros(2, dtype=torch.uint8, device=dev()))
+        ones = torch.tensor([1.0, 2.0, 1.5], device=dev())
+        binding.npd_delta_ifd_score(ones, ones * 1.5, cu[1:], cu[:2] * 0, cu[:2] * 0 + 1, -1.0, 0.8, flags=1, **out)
     else:
         out = dict(topk_idx=i(T, 7), topk_val=f(T, 7))
         binding.npd_teacher_topk(t, 7, loss_mask=mask, log_probs=False, **out)
