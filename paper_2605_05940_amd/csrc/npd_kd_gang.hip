@@ -91,8 +91,8 @@ hipError_t clear_gang_record(uint32_t* ws, size_t words, hipStream_t stream) {
 //      per compute unit (94 registers), and no register left empty.  10,000 rows of 36,000 379 / 342, top-k (40 entries)
 //      281 / 248; of 40,960 395 / 386, 289 / 275 (32,000 308 / 306, 50,304 475 / 474; with sums at tau = 1 the registers
 //      do not allow that workgroup: 36,000 tau = 2 with a CE term 382 / 401).  Fewer rows: from 640 on (top-k 1,024), where
-//      a row has no more slices of seven groups than of ten, and where the ratio is below 1 (top-k: as above, and all
-//      resident, six to a compute unit).  Time of 10 groups over time of 7: dense 40,000 351 rows .94, 420 1.12, 512 .95, 600
+//      a row has no more slices of seven groups than of ten, and where the ratio is below 1, or rows are hardly longer than
+//      the shortest of these (top-k: where it is at most 15 / 14 and all slices are resident, six to a compute unit).  Time of 10 groups over time of 7: dense 40,000 351 rows .94, 420 1.12, 512 .95, 600
 //      .97, 640 1.03, 1,024 1.02; 42,816 351 1.20; 33,000 351 1.07, 512 1.01; top-k 36,000 470 1.05, 560 .86, 768 .78, 1,024 1.06
 // (Rows that are not scored are not known here: their slices count like the others'.)
 constexpr int kMeasuredCus = 256;
