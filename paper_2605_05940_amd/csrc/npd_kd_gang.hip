@@ -13,7 +13,8 @@ int set_gang_spin_limit(int polls) {
 
 constexpr int kGangK = 10;      // 128-bit groups per thread and tensor: 80 of a thread's 128 registers hold its slice
 constexpr int kGangTopkK = 10;  // top-k teacher: groups per thread of the student row alone
-constexpr int kGangSkewK = 6;   // skew forms: the slice is kept as two fp32 values per element from sweep 2 on
+constexpr int kGangSkewK = 6;   // skew forms: the slice is kept as two fp32 values per element from sweep 1 on
+constexpr int kGangSkewLongK = 7;  // the same with two of the groups in LDS, see skew_long_slices
 
 static int gang_k(int teacher_kind, int divergence) {
   if (teacher_kind == kTopk) return kGangTopkK;
@@ -129,9 +130,16 @@ size_t gang_workspace_preferred(int64_t T, int32_t V, int teacher_kind, int dive
   return best;
 }
 
-template <int DIVK>
-static hipError_t launch_gang(const KdArgs& a, hipStream_t stream) {
-  return launch_gang_dense<DIVK, DIVK == kSkewKl || DIVK == kSkewReverseKl ? kGangSkewK : kGangK>(a, stream);
+// Skew forms in longer slices (a record of fewer words than the call has asked for): where that makes them fewer, and the
+// slices of six groups are more than are resident at once (1,024, and a call leaves out the rows that are not scored); with
+// exponentials of their own at tau = 1 always, where six groups spill 13 registers.  Time of 6 groups over time of 7 (MI355X):
+// fewer slices 26,624 1.13, 28,672 1.11, 40,960 1.08, 50,304 1.06, 128,256 1.09, 262,144 1.08; as many 22,528 .998, 32,000 .996,
+// 18,432 .98; rows of 65,536, six tenths scored: 200 rows .94, 228 .95, 240 1.10, 300 1.16; 330 of 40,960 .89, 366 1.08; nine
+// slices against eight, 209 of 106,439 .98; 119 of 50,304 .92, 39 of 151,936 .95; tau = 3 with a CE term 1.07 .. 1.13, 119 rows of 50,304 .993.
+static bool skew_long_slices(const KdArgs& a, bool on_lines) {
+  const int64_t g = gang_slices(a.nvec_s, kGangSkewK, on_lines), g_long = gang_slices(a.nvec_s, kGangSkewLongK, on_lines);
+  if (g_long < 2) return false;
+  return l1_mode(a) == kL1Own || (g_long < g && (a.T * g > 4096 || (a.T * g > 1400 && 7 * g_long <= 6 * g)));
 }
 
 hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_bytes, hipStream_t stream) {
@@ -139,6 +147,9 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
   const bool on_lines = rows_on_lines(a);
   const int base = gang_size(a.nvec_s, gang_k(teacher_kind, a.divergence), on_lines);
   a.gang = base;
+  const bool skew = a.divergence == kSkewKl || a.divergence == kSkewReverseKl;
+  const bool skew_long = skew && skew_long_slices(a, on_lines);
+  if (skew_long) a.gang = gang_slices(a.nvec_s, kGangSkewLongK, on_lines);
   int k = fine_groups(a.T, a.nvec_s, teacher_kind, a.divergence, a.need_lse1 != 0, on_lines);
   if (k > 0) {
     const int g = gang_slices(a.nvec_s, k, on_lines);
@@ -160,10 +171,13 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
   if (k > 0) return launch_gang_fine(a, k, teacher_kind, stream);
   if (teacher_kind == kTopk) return launch_gang_topk<kGangTopkK>(a, stream);
   switch (a.divergence) {
-    case kReverseKl: return launch_gang<kReverseKl>(a, stream);
-    case kSkewKl: return launch_gang<kSkewKl>(a, stream);
-    case kSkewReverseKl: return launch_gang<kSkewReverseKl>(a, stream);
-    default: return launch_gang<kForwardKl>(a, stream);
+    case kReverseKl: return launch_gang_dense<kReverseKl, kGangK>(a, stream);
+    case kSkewKl:
+      return skew_long ? launch_gang_dense<kSkewKl, kGangSkewLongK>(a, stream) : launch_gang_dense<kSkewKl, kGangSkewK>(a, stream);
+    case kSkewReverseKl:
+      return skew_long ? launch_gang_dense<kSkewReverseKl, kGangSkewLongK>(a, stream)
+                       : launch_gang_dense<kSkewReverseKl, kGangSkewK>(a, stream);
+    default: return launch_gang_dense<kForwardKl, kGangK>(a, stream);
   }
 }
 

@@ -211,6 +211,13 @@ __device__ __forceinline__ int64_t solo_row() {
   if constexpr (solo_rows(TH) == 1) return blockIdx.x;
   return (int64_t)blockIdx.x * solo_rows(TH) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 }
+// Groups per thread whose two fp32 values per pair of logits the skew forms keep in registers: the first two of a shared row's
+// slice of seven are in LDS (16 KB each, four workgroups to a compute unit).  What these calls wait for is two exchanges per
+// slice, and longer slices are fewer of them.  Measured (MI355X, 8,192 x 151,936, us, six groups in registers / five and two
+// in LDS): skew KL 1234 / 1153, skew reverse KL 1264 / 1181, with a CE term at tau = 2 1342 / 1273; six in registers of seven
+// or eight spill (1,423, 1,342); three workgroups of ten or eleven groups 1,169, 1,166; five groups 1,290, four with a fifth
+// workgroup 1,353.
+__host__ __device__ constexpr int skew_in_registers(int k, bool solo) { return !solo && k == 7 ? 5 : k; }
 // waves per SIMD a kernel is compiled for: what its registers of data leave room for
 __host__ __device__ constexpr int gang_waves(int data_registers) { return data_registers <= 32 ? 6 : 4; }
 // orders a wave's or workgroup's earlier LDS accesses before its later ones
@@ -300,6 +307,8 @@ kd_gang_kernel(const KdArgs a) {
   __shared__ uint32_t xch[SOLO ? 1 : kGangMax * W];
   __shared__ uint32_t xch2[SKEW && !SOLO ? kGangMax * 2 : 1];
   __shared__ int gave_up;
+  constexpr int KR = skew_in_registers(K, SOLO), KL = SKEW ? K - KR : 0;  // groups [0, KL) of the skew forms' cache: LDS
+  __shared__ float4 more[KL > 0 ? KL * 4 * TH : 1];
 
   const int G = SOLO ? 1 : a.gang;
   const int64_t row = SOLO ? solo_row<TH>() : (int64_t)(blockIdx.x / (unsigned)G);
@@ -400,7 +409,40 @@ kd_gang_kernel(const KdArgs a) {
   // its sum is inside the range up to 94 bits above the first group's largest logit.
   const bool ref_of_all = SOLO || a.ragged || (LSE1 && a.cscale != 0.0f);  // uniform
   const float kRefBias = ref_of_all ? 0.0f : (L1 == kL1Square ? 44.0f : (SKEW ? 64.0f : 100.0f));
-  float cp[SKEW ? K : 1][8], cv[SKEW ? K : 1][8];
+  float cp[SKEW ? KR : 1][8], cv[SKEW ? KR : 1][8];
+  auto cache_get = [&](int k, float (&p)[8], float (&v)[8]) __attribute__((always_inline)) {
+    if (k >= KL) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        p[j] = cp[k - KL][j];
+        v[j] = cv[k - KL][j];
+      }
+    } else {  // (a thread reads its own words only: no barrier)
+      const float4* m = more + k * 4 * TH + tid;
+      const float4 w[4] = {m[0], m[TH], m[2 * TH], m[3 * TH]};
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        p[4 * j] = w[j].x; p[4 * j + 1] = w[j].y; p[4 * j + 2] = w[j].z; p[4 * j + 3] = w[j].w;
+        v[4 * j] = w[2 + j].x; v[4 * j + 1] = w[2 + j].y; v[4 * j + 2] = w[2 + j].z; v[4 * j + 3] = w[2 + j].w;
+      }
+    }
+  };
+  auto cache_put = [&](int k, const float (&p)[8], const float (&v)[8]) __attribute__((always_inline)) {
+    if (k >= KL) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        cp[k - KL][j] = p[j];
+        cv[k - KL][j] = v[j];
+      }
+    } else {
+      float4* m = more + k * 4 * TH + tid;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        m[j * TH] = make_float4(p[4 * j], p[4 * j + 1], p[4 * j + 2], p[4 * j + 3]);
+        m[(2 + j) * TH] = make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
+      }
+    }
+  };
   if (ng > tid) {  // (threads without a group keep their empty partials)
     float fs, ft;
     if (ref_of_all) {
@@ -430,6 +472,7 @@ kd_gang_kernel(const KdArgs a) {
   const s16x4 identity = lane_identity(kBf16One);
   const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
   auto add_group = [&](const float (&xs)[8], const float (&xt)[8], const float (&d)[8], int k) __attribute__((always_inline)) {
+    float p[8], v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const float es = exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
@@ -440,10 +483,8 @@ kd_gang_kernel(const KdArgs a) {
         acc[0].a = __builtin_fmaf(es, MFMA ? d[j] : xs[j] - xt[j], acc[0].a);
       else if constexpr (!SKEW)
         acc[1].a = __builtin_fmaf(et, MFMA ? d[j] : xt[j] - xs[j], acc[1].a);
-      if constexpr (SKEW) {
-        cp[k][j] = es;
-        cv[k][j] = et;
-      }
+      p[j] = es;
+      v[j] = et;
       if constexpr (L1 == kL1Square) {
         acc[2].z = __builtin_fmaf(es, es, acc[2].z);
         acc[3].z = __builtin_fmaf(et, et, acc[3].z);
@@ -453,6 +494,7 @@ kd_gang_kernel(const KdArgs a) {
         if (lse1_t) acc[3].z += exp2_fast(__builtin_fmaf(xt[j], kLog2e, -acc[3].r));
       }
     }
+    if constexpr (SKEW) cache_put(k, p, v);
   };
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -500,14 +542,15 @@ kd_gang_kernel(const KdArgs a) {
       if constexpr (SKEW) {  // the exponentials again, against the references the careful form ended with
 #pragma unroll
         for (int k = 0; k < K; ++k) {  // (every group, also those past the slice's end: all of the cache is rewritten)
-          float xs[8], xt[8];
+          float xs[8], xt[8], p[8], v[8];
           unpack8(sreg[k], xs);
           unpack8(treg[k], xt);
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            cp[k][j] = exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
-            cv[k][j] = exp2_fast(__builtin_fmaf(xt[j], c, -acc[1].r));
+            p[j] = exp2_fast(__builtin_fmaf(xs[j], c, -acc[0].r));
+            v[j] = exp2_fast(__builtin_fmaf(xt[j], c, -acc[1].r));
           }
+          cache_put(k, p, v);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -646,8 +689,11 @@ kd_gang_kernel(const KdArgs a) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (k < n_mine) {
+        float p[8], v[8];
+        cache_get(k, p, v);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) skew_terms<DIVK>(cp[k][j] * fs, cv[k][j] * ft, ks, dsum, usum, cp[k][j], cv[k][j]);
+        for (int j = 0; j < 8; ++j) skew_terms<DIVK>(p[j] * fs, v[j] * ft, ks, dsum, usum, p[j], v[j]);
+        cache_put(k, p, v);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -825,11 +871,12 @@ kd_gang_kernel(const KdArgs a) {
 #pragma unroll
       for (int k = K - 1; k >= 0; --k) {
         const uint4 vs = ld_group<GB>(rs, voff, k, true, true);
-        float xs[8], gv[8];
+        float xs[8], gv[8], p[8], v[8];
         unpack8(vs, xs);
+        cache_get(k, p, v);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          gv[j] = add_ce_own(__builtin_fmaf(cv[k][j], ks.Av, ks.B * cp[k][j]), xs[j], kf.p);
+          gv[j] = add_ce_own(__builtin_fmaf(v[j], ks.Av, ks.B * p[j]), xs[j], kf.p);
         uint4 o = make_uint4(pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3]), pack_bf16(gv[4], gv[5]), pack_bf16(gv[6], gv[7]));
         if (k == k_y) patch_label(o);  // uniform
         if (k < n_mine) store(k, o);
@@ -838,13 +885,14 @@ kd_gang_kernel(const KdArgs a) {
     } else {
 #pragma unroll
       for (int k = K - 1; k >= 0; --k) {
-        float gv[8];
+        float gv[8], p[8], v[8];
+        cache_get(k, p, v);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           if constexpr (L1 == kL1Square)  // (ks.C = 0 without a CE term)
-            gv[j] = __builtin_fmaf(cv[k][j], ks.Av, __builtin_fmaf(ks.C, cp[k][j], ks.B) * cp[k][j]);
+            gv[j] = __builtin_fmaf(v[j], ks.Av, __builtin_fmaf(ks.C, p[j], ks.B) * p[j]);
           else
-            gv[j] = __builtin_fmaf(cv[k][j], ks.Av, ks.B * cp[k][j]);
+            gv[j] = __builtin_fmaf(v[j], ks.Av, ks.B * p[j]);
         }
         uint4 o = make_uint4(pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3]), pack_bf16(gv[4], gv[5]), pack_bf16(gv[6], gv[7]));
         if (k == k_y) patch_label(o);  // uniform

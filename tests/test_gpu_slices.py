@@ -84,3 +84,40 @@ def test_slices_of_every_length(oracle, V, pitch, T, what):
     # what runs does not depend on how much more than twice the least a call is given
     for name in ("more", "binding"):
         assert all(torch.equal(a, b) for a, b in zip(bits[name], bits["twice"])), name
+
+
+@pytest.mark.parametrize("V,pitch,T,tau,ce", [
+    # slices of seven groups, two of them in LDS: fewer than of six, and more than 1,400 of those ...
+    (26624, 26624, 470, 1.0, 0.0), (28675, 28675, 470, 1.0, 0.25), (26632, 26640, 470, 2.0, 0.25),
+    # ... or sums at tau = 1 of their own, any number: two slices, a last slice of one group, 32 slices of six groups
+    (18344, 18344, 12, 3.0, 0.25), (28560, 28576, 12, 3.0, 0.0), (42819, 42819, 12, 3.0, 0.25), (391168, 391168, 4, 3.0, 0.25),
+])
+@pytest.mark.parametrize("div", ["skew", "skew_reverse"])
+def test_skew_slices_with_groups_in_lds(oracle, V, pitch, T, tau, ce, div):
+    w = synth.scaled(synth.config(1), n_rows=1, row_len=T, vocab=V, length_lo=4, length_hi=min(9, T))
+    lay = synth.make_layout(w)
+    mask_np = lay.loss_mask.copy()
+    mask_np[:3] = 1
+    g = torch.Generator(device=dev()).manual_seed(V + T)
+    s, t, grad = (torch.empty((T, pitch), dtype=torch.bfloat16, device=dev())[:, :V] for _ in range(3))
+    s.copy_(3.0 * torch.randn((T, V), generator=g, device=dev()))
+    t.copy_(0.8 * s.float() + 1.5 * torch.randn((T, V), generator=g, device=dev()))
+    # waves that sum once more in the careful form: logits far above the first group's, entries of probability 0
+    s[1, V // 2] = 420.0
+    t[1, V // 2 + 300] = 400.0
+    s[2, V - 70:] = float("-inf")
+    t[2, V - 70:] = float("-inf")
+    lab = np.minimum(lay.labels, V - 71).astype(np.int32)
+    ref = oracle.div_dense(synth.bf16_bits(s.contiguous()), synth.bf16_bits(t.contiguous()), div, 0.1, labels=lab, mask=mask_np,
+                           tau=tau, grad_scale=0.75, ce_grad_scale=ce)
+    grad.fill_(float("nan"))
+    kd, nll = (torch.full((T,), -1.0, device=dev()) for _ in range(2))
+    status = torch.zeros(1, dtype=torch.int32, device=dev())
+    print(f"[skew slices] V={V} pitch={pitch} T={T} tau={tau} {div}", flush=True)
+    binding.npd_kd_loss_fwd_bwd(s, torch.from_numpy(mask_np).to(dev()), teacher_dense=t, labels=torch.from_numpy(lab).to(dev()),
+                                tau=tau, grad_scale=0.75, ce_grad_scale=ce, divergence=2 if div == "skew" else 3, skew_alpha=0.1,
+                                grad_out=grad, kd_tok=kd, nll_tok=nll, dev_status=status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    got = dict(kd=kd.cpu().numpy().astype(np.float64), grad=grad.float().cpu().numpy().astype(np.float64))
+    compare_kd(got, ref, mask_np, None, oracle, grad_scale=0.75 + ce * tau, tau=tau, amp_from_ref=True)
