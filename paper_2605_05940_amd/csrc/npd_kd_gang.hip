@@ -21,8 +21,8 @@ static int gang_k(int teacher_kind, int divergence) {
   return divergence == kSkewKl || divergence == kSkewReverseKl ? kGangSkewK : kGangK;
 }
 
-// Slices per row.  A workgroup holds up to k * 256 groups; slices are sized to 8 groups less, because a slice is moved
-// by up to 7 groups so that it begins on a 128-byte boundary of memory (see launch_kd_gang).
+// Slices per row.  A workgroup holds up to k * 256 groups; slices are sized to 8 groups less, because boundaries are moved
+// by up to 7 groups so that they are 128-byte boundaries of memory (see launch_kd_gang).
 // `on_lines`: every row of the launch begins on a 128-byte boundary, no boundary is ever moved and a slice may be as
 // long as a workgroup holds (V = 102,400: 5 full slices instead of 6).
 static int gang_slices(int nvec, int k, bool on_lines) {
@@ -161,9 +161,10 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
     else
       k = 0;
   }
-  // Slices are multiples of 8 groups = 128 bytes long, and the kernels move every boundary inside a row down to the
-  // next 128-byte boundary of the gradient row's address (by 0 .. 7 groups: a row whose pitch is not a multiple of 128
-  // bytes begins anywhere): no cache line is then shared by two workgroups of a row -- measured +2.4 points of the HBM
+  // Slices that are one run of groups (`DEALT` in npd_kd_gang.hpp says which are not) are multiples of 8 groups = 128 bytes long,
+  // and the kernels move every boundary inside a row, of runs and of pieces, down to the next 128-byte boundary of the gradient
+  // row's address (by 0 .. 7 groups: a row whose pitch is not a multiple of 128 bytes begins anywhere): no cache line is then
+  // shared by two workgroups of a row -- measured +2.4 points of the HBM
   // peak on 32,768 x 151,936, +2.5 on 262,144 logits in place, +3.6 with a top-k teacher; a row pitch of 16 bytes more than
   // 151,936 logits: +4.
   a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;

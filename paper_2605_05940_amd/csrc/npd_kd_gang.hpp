@@ -1,6 +1,6 @@
 // Row-gang variant of the fused KD loss + gradient kernel (gfx950): a token row is shared by G short-lived
-// workgroups of 256 threads, each of which owns one contiguous slice of the row (up to K 128-bit groups per thread
-// and tensor) and keeps it in registers from the first sweep to the gradient write -- nothing is read twice, whatever
+// workgroups of 256 threads, each of which owns a slice of the row (up to K 128-bit groups per thread and tensor, in pieces
+// of 4 KB that are dealt to the row's workgroups in turn) and keeps it in registers from the first sweep to the gradient write -- nothing is read twice, whatever
 // the vocabulary.  The G partial log-sum-exps of a row meet through a small scratch record in device memory:
 //
 //   sweep 1 over the slice -> workgroup partials (r, z, a) -> posted to scratch[row][slice]
@@ -9,8 +9,8 @@
 //
 // Why: the memory system of this GPU gives a mix of two reads and one write 6.7 TB/s when the chip sweeps memory
 // front to back, every row is read completely before it is written and no cache line is shared by two workgroups,
-// against 5.7 TB/s when each compute unit works on a row of its own.  Consecutive workgroups are consecutive slices
-// (which begin on 128-byte boundaries of the row), four workgroups run per compute unit (one row's wait and arithmetic
+// against 5.7 TB/s when each compute unit works on a row of its own.  Consecutive workgroups take consecutive pieces
+// (which begin on 128-byte boundaries of the row) and write them side by side, four workgroups run per compute unit (one row's wait and arithmetic
 // overlap three other slices' memory traffic), and the workgroups of rows that are not scored zero-fill their slices
 // in the same address order.
 //
@@ -122,7 +122,7 @@ __device__ __forceinline__ float pk_max_value(uint32_t m) {
   return bf16_one((uint16_t)(lo > hi ? lo : hi));
 }
 
-// Largest logit of a thread's n >= 1 groups, whatever their signs, with v_pk_max_f16: fp16 patterns are sign and
+// Largest logit of a thread's groups (mine(k); at least one; FIRST: not always the first), whatever their signs, with v_pk_max_f16: fp16 patterns are sign and
 // magnitude like bf16 ones, so their order is the same.  The patterns it takes for NaN are magnitudes of more than
 // 2^121: infinities and NaN, which it passes over while the other operand is a number.  Where there is nothing else the
 // result is far below every logit: sums against it are 0 if all logits are -inf and show an anomaly otherwise.  (Written
@@ -132,18 +132,24 @@ __device__ __forceinline__ uint32_t pk_max_bf16(uint32_t a, uint32_t b) {
   asm("v_pk_max_f16 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
   return d;
 }
-template <int K>
-__device__ __forceinline__ float thread_max(const uint4 (&v)[K], int n) {
-  constexpr uint32_t kNothing = 0xff80ff80u;  // a pair of -inf, for the groups behind the thread's last
+template <bool FIRST, int K, class Mine>
+__device__ __forceinline__ float thread_max(const uint4 (&v)[K], Mine mine) {
+  constexpr uint32_t kNothing = 0xff80ff80u;  // a pair of -inf, for the groups that are not the thread's
   uint32_t m = kNothing;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const uint32_t g = pk_max_bf16(pk_max_bf16(v[k].x, v[k].y), pk_max_bf16(v[k].z, v[k].w));
-    m = k == 0 ? g : pk_max_bf16(m, k < n ? g : kNothing);
+    const uint32_t w = (k == 0 && !FIRST) || mine(k) ? g : kNothing;
+    m = k == 0 ? w : pk_max_bf16(m, w);
   }
   const float lo = bf16_lo(m), hi = bf16_hi(m);
   const float x = lo > hi ? lo : hi;
   return fabsf(x) < 2.6e36f ? x : -3.0e38f;
+}
+// ... of its first n >= 1 groups
+template <int K>
+__device__ __forceinline__ float thread_max(const uint4 (&v)[K], int n) {
+  return thread_max<false>(v, [&](int k) __attribute__((always_inline)) { return k < n; });
 }
 
 __device__ __forceinline__ void gang_post(uint32_t* p, float v) {
@@ -188,16 +194,19 @@ inline int l1_mode(const KdArgs& a) {
 // words of scratch per slice: 3 per partial log-sum-exp, rounded up to a power of two
 __host__ __device__ constexpr int gang_words(int ns) { return ns == 2 ? 8 : 16; }
 
-// Zero-fills the groups [g0, g0 + ng) of a gradient row, ng <= K * 256: what the workgroup of a slice does when its
-// row is not scored.  With slices that begin on 128-byte boundaries these short-lived workgroups, started in address
-// order among those of the scored rows, fill as fast as a separate fill pass (and save that pass).
-template <int K, int TH = kGangThreads>
-__device__ __forceinline__ void gang_zero_slice(uint16_t* grow, int g0, int ng, int tid) {
+// Zero-fills the share of slice `slice` of a gradient row's nvec groups: what a workgroup does when its row is not scored.
+// Pieces of TH groups are dealt to the G workgroups in turn (`shift`: groups the pieces begin in front of the row), so that
+// those that run side by side write side by side: (MI355X, rows that are not scored alone, TB/s, a run of up to 2,560 groups to
+// each workgroup / this) 151,936 logits 5.35 / 5.9, 32,000 5.38 / 5.5, 50,003 4.83 / 5.3.
+template <int K, int TH>
+__device__ __forceinline__ void gang_zero_slice(uint16_t* grow, int nvec, int shift, int slice, int G, int tid) {
   const u32x4 z = {0, 0, 0, 0};
-  u32x4* p = reinterpret_cast<u32x4*>(grow) + g0;
+  u32x4* p = reinterpret_cast<u32x4*>(grow);
 #pragma unroll
-  for (int k = 0; k < K; ++k)
-    if (k * TH + tid < ng) __builtin_nontemporal_store(z, p + k * TH + tid);
+  for (int k = 0; k < K; ++k) {
+    const int i = (k * G + slice) * TH - shift + tid;
+    if (i >= 0 && i < nvec) __builtin_nontemporal_store(z, p + i);
+  }
 }
 
 // The same kernels with a row to a workgroup (SOLO: no exchange, no workspace) take rows that fit one: TH threads of K
@@ -320,15 +329,24 @@ kd_gang_kernel(const KdArgs a) {
   uint16_t* grow = GRAD ? a.g + row * a.s_stride : nullptr;
   const RowSplit sp = row_split(a.s + row * a.s_stride, V, true);  // all dense rows at one offset from a 16-byte boundary
   const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;
-  // This workgroup owns groups [g0, g1) -- the last slice also the edge elements of the row.  Boundaries inside the row
-  // are moved down to the next 128-byte boundary of the gradient row's address (by `shift` groups), so that no cache
-  // line is shared by two workgroups of a row; a slice is at most 7 groups longer than a.gang_groups for it.
+  // The row's groups are dealt to its workgroups in pieces of TH groups (4 KB): piece k of slice `slice` is piece k G + slice of
+  // the row.  Pieces begin on 128-byte boundaries of the gradient row's address (the first one is up to 7 groups shorter for
+  // it), so that no cache line is shared by two workgroups.  A row's workgroups come out of the exchange together and write
+  // side by side so.  Measured (MI355X, us, every workgroup one run of groups / this, both with the late label below):
+  // 4,096 x 151,936 at tau = 2 with a CE term 446.9 / 435.6, 8,192 x 50,003 358.5 / 350.0, 16,384 x 32,000 reverse KL 458 / 451,
+  // 6,001 x 65,536 355.8 / 348.2, 32,768 x 151,936 3,827 / 3,807; with all rows scored 32,000 506 / 495, 151,936 the same.
+  // The skew forms with exponentials of their own at tau = 1, whose registers are full, take one run of gang_groups (up to 7
+  // more) with the same boundaries (4,096 x 65,536 at tau = 3 with a CE term: 301, in pieces 315).
+  // Group idx0 + k * step is the thread's k-th, if it is below `end`.  The last slice also owns the edge elements of the row.
+  constexpr bool DEALT = !SOLO && !(SKEW && L1 == kL1Own);
   const bool last = SOLO || slice == G - 1;
-  const int shift = (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
-  const int b0 = slice * a.gang_groups - shift, b1 = b0 + a.gang_groups;
-  const int g0 = slice == 0 ? 0 : (b0 < nvec ? b0 : nvec);
-  const int g1 = last ? nvec : (b1 < nvec ? b1 : nvec);
-  const int ng = g1 > g0 ? g1 - g0 : 0;
+  const int shift = SOLO ? 0 : (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
+  const int run = slice * a.gang_groups - shift;
+  const int first = DEALT ? slice * TH - shift : SOLO || slice == 0 ? 0 : (run < nvec ? run : nvec);
+  const int step = DEALT ? G * TH : TH;
+  const int end = DEALT || last ? nvec : (run + a.gang_groups < nvec ? run + a.gang_groups : nvec);
+  const int idx0 = first + tid;  // < 0: in front of the row (k = 0 of slice 0)
+  auto mine = [&](int k) __attribute__((always_inline)) { return idx0 < end - k * step && (!DEALT || k > 0 || idx0 >= 0); };
 
   if (!a.mask[row]) {  // not scored: scalars 0, the slice of the gradient row zero-filled, logits never read
     if (slice == 0 && tid == 0) {
@@ -338,7 +356,7 @@ kd_gang_kernel(const KdArgs a) {
       if (a.lse) a.lse[row] = 0.0f;
     }
     if constexpr (GRAD) {
-      gang_zero_slice<K, TH>(grow + head, g0, ng, tid);
+      gang_zero_slice<K, TH>(grow + head, nvec, shift, slice, G, tid);
       if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
     }
     return;
@@ -350,36 +368,56 @@ kd_gang_kernel(const KdArgs a) {
   const bool lse1_t = LSE1 && a.tnll != nullptr;
   if (!SOLO && tid == 0) gave_up = 0;  // ordered before its use by the barrier of the workgroup's merge
 
-  // The slice as a buffer: all of a thread's groups are requested at once, unconditionally (a predicate around a load
-  // makes the compiler wait for it on the spot); groups past the slice's end read as zero and are never used.  The thread
-  // owns its first n_mine groups (one comparison per group; masks kept for both sweeps were spilled).
-  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
-  const __amdgpu_buffer_rsrc_t rt = row_rsrc(trow + head + (size_t)g0 * 8, ng);
-  const int voff = tid * 16;
-  const int n_mine = (ng - tid + TH - 1) / TH;  // groups of this thread
+  // The row as a buffer: all of a thread's groups are requested at once, unconditionally (a predicate around a load
+  // makes the compiler wait for it on the spot); groups that are not the row's read as zero and are never used.
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head, end);
+  const __amdgpu_buffer_rsrc_t rt = row_rsrc(trow + head, end);
+  const int voff = idx0 * 16;
+  auto load = [&](const __amdgpu_buffer_rsrc_t& r, int k) __attribute__((always_inline)) {
+    return !DEALT ? ld_group<GB>(r, voff, k, true, true) : ld_group<0>(r, voff + k * step * 16, 0, true, true);
+  };
   uint4 sreg[K], treg[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    sreg[k] = ld_group<GB>(rs, voff, k, true, true);
-    treg[k] = ld_group<GB>(rt, voff, k, true, true);
+    sreg[k] = load(rs, k);
+    treg[k] = load(rt, k);
   }
 
-  // the label logits belong to the slice that holds them (it reads them before it can overwrite them in place)
-  int y = -1;
+  // The label logits belong to the slice that holds them (it reads them before it can overwrite them in place).  They arrive
+  // behind the slice's groups, so that converting them at once would wait for all of those before the first is summed
+  // (64 x 151,936 18.1 / 17.8 us, 32 x 32,000 12.6 / 12.3, 4,096 x 151,936 at tau = 2 451.6 / 446.9 us so, in a graph).
+  int y = -1, k_own = -1, thread_y = 0;  // piece and thread of the label's group; -1: an edge element
   bool own_y = false;
-  float s_y = 0.0f, t_y = 0.0f;
+  uint32_t s_y_bits = 0, t_y_bits = 0;
   if (a.labels) {
     y = a.labels[row];
     if ((unsigned)y < (unsigned)V) {
       const int gy = sp.group_of(y);
-      own_y = gy >= 0 ? gy >= g0 && gy < g1 : last;
+      if (gy >= 0) {
+        const unsigned at = (unsigned)(gy + (DEALT ? shift : -first)), piece = at / TH;
+        k_own = (int)(DEALT ? piece / (unsigned)G : piece);
+        thread_y = (int)(at % TH);
+        own_y = DEALT ? (int)(piece - (unsigned)(k_own * G)) == slice : gy >= first && gy < end;
+      } else {
+        own_y = last;
+      }
       if (own_y) {
-        s_y = bf16_one(srow[y]);
-        t_y = bf16_one(trow[y]);
+        s_y_bits = srow[y];
+        t_y_bits = trow[y];
+        if constexpr (SKEW) asm volatile("" : "+v"(s_y_bits), "+v"(t_y_bits));  // (their registers are full: waited for here)
       }
     }
   }
   const bool bad_label = a.labels && (unsigned)y >= (unsigned)V;  // uniform
+  // The edge elements of the row, with the last slice: a latency more behind its sums if they are read there (64 x 50,003 15.4 /
+  // 15.2 us; skew forms do, their registers are full)
+  uint32_t s_e_bits = 0, t_e_bits = 0;
+  auto read_edges = [&]() __attribute__((always_inline)) {
+    const int e = sp.edge_elem(tid);
+    s_e_bits = srow[e];
+    t_e_bits = trow[e];
+  };
+  if (!SKEW && last && tid < n_edge) read_edges();
 
   Lse acc[NS];
 #pragma unroll
@@ -443,14 +481,19 @@ kd_gang_kernel(const KdArgs a) {
       }
     }
   };
-  if (ng > tid) {  // (threads without a group keep their empty partials)
+  if (mine(0) || (DEALT && mine(1))) {  // (threads without a group keep their empty partials)
     float fs, ft;
     if (ref_of_all) {
-      fs = thread_max(sreg, n_mine);
-      ft = thread_max(treg, n_mine);
+      fs = thread_max<DEALT>(sreg, mine);
+      ft = thread_max<DEALT>(treg, mine);
     } else {
-      fs = pk_max_value(pk_max_group(sreg[0]));
-      ft = pk_max_value(pk_max_group(treg[0]));
+      uint32_t ms = pk_max_group(sreg[0]), mt = pk_max_group(treg[0]);
+      if (DEALT && idx0 < 0) {
+        ms = pk_max_group(sreg[1]);
+        mt = pk_max_group(treg[1]);
+      }
+      fs = pk_max_value(ms);
+      ft = pk_max_value(mt);
     }
     acc[0].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f));
     acc[1].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(ft, c, kRefBias), -1.0e30f));
@@ -500,7 +543,7 @@ kd_gang_kernel(const KdArgs a) {
   for (int k = 0; k < K; ++k) {
     float xs[8], xt[8], d[8] = {};
     if constexpr (MFMA) {
-      if (k * TH + wave0 < ng) {  // uniform: a group for the wave's first lane at least
+      if (first + wave0 < end - k * step) {  // uniform: a group for the wave's first lane at least
         unpack8_mfma(sreg[k], identity, xs);
         unpack8_mfma(treg[k], identity, xt);
         const s16x4 minus = identity ^ (short)0x8000;
@@ -508,9 +551,9 @@ kd_gang_kernel(const KdArgs a) {
           mfma8(treg[k], minus, xs, d);
         else
           mfma8(sreg[k], minus, xt, d);
-        if (k < n_mine) add_group(xs, xt, d, k);
+        if (mine(k)) add_group(xs, xt, d, k);
       }
-    } else if (k < n_mine) {
+    } else if (mine(k)) {
       unpack8(sreg[k], xs);
       unpack8(treg[k], xt);
       add_group(xs, xt, d, k);
@@ -530,13 +573,13 @@ kd_gang_kernel(const KdArgs a) {
       if constexpr (SKEW) {  // the packed logits are gone: fetched again (rare; they are still in a cache)
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          sreg[k] = ld_group<GB>(rs, voff, k, true, true);
-          treg[k] = ld_group<GB>(rt, voff, k, true, true);
+          sreg[k] = load(rs, k);
+          treg[k] = load(rt, k);
         }
       }
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        if (k < n_mine) accum8<kDense, LSE1, REV>(sreg[k], treg[k], c, lse1_t, acc);
+        if (mine(k)) accum8<kDense, LSE1, REV>(sreg[k], treg[k], c, lse1_t, acc);
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (SKEW) {  // the exponentials again, against the references the careful form ended with
@@ -557,10 +600,11 @@ kd_gang_kernel(const KdArgs a) {
     }
   }
   const float r_s_thread = acc[0].r, r_t_thread = acc[1].r;  // what this thread's cached exponentials refer to
+  // the conversions stay here: behind the sums, and in front of this workgroup's post (rows in place)
+  if constexpr (!SKEW) asm volatile("" : "+v"(s_y_bits), "+v"(t_y_bits), "+v"(s_e_bits), "+v"(t_e_bits));
   if (last && tid < n_edge) {
-    const int e = sp.edge_elem(tid);
-    const float xs = bf16_one(srow[e]);
-    const float xt = bf16_one(trow[e]);
+    if constexpr (SKEW) read_edges();
+    const float xs = bf16_lo(s_e_bits), xt = bf16_lo(t_e_bits);
     if constexpr (REV) {
       acc[1].add1(xt, c);
       acc[0].add1_cross(xs, xs - xt, c);
@@ -659,6 +703,7 @@ kd_gang_kernel(const KdArgs a) {
     }
   }
 
+  const float s_y = bf16_lo(s_y_bits), t_y = bf16_lo(t_y_bits);
   const float Ls = acc[0].log2_sum();
   const float Lt = acc[1].log2_sum();
   const float lse1_s = __fmul_rn(LSE1 ? acc[NS - 2].log2_sum() : Ls, kLn2);
@@ -688,7 +733,7 @@ kd_gang_kernel(const KdArgs a) {
     const float fs = exp2_fast(r_s_thread - ks.Rs) * ks.izs, ft = exp2_fast(r_t_thread - ks.Rt) * ks.izt;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      if (k < n_mine) {
+      if (mine(k)) {
         float p[8], v[8];
         cache_get(k, p, v);
 #pragma unroll
@@ -698,9 +743,9 @@ kd_gang_kernel(const KdArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
     if (last && tid < n_edge) {
-      const int e = sp.edge_elem(tid);
+      read_edges();
       float p, v;
-      skew_cache<DIVK>(bf16_one(srow[e]), bf16_one(trow[e]), ks, dsum, usum, p, v);
+      skew_cache<DIVK>(bf16_lo(s_e_bits), bf16_lo(t_e_bits), ks, dsum, usum, p, v);
     }
     // workgroup totals, second post / wait, row totals -- plain sums in a fixed order
     dsum = wave_sum_dpp(dsum);
@@ -777,16 +822,16 @@ kd_gang_kernel(const KdArgs a) {
 
   if constexpr (!GRAD) return;
   // ---- sweep 2: the gradient of the slice, from the registers, last group first
-  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (size_t)g0 * 16;
+  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (int64_t)first * 16;
   auto store = [&](int k, const uint4& o) {  // the group's base is uniform, the thread adds tid * 16
     const u32x4 w = {o.x, o.y, o.z, o.w};
-    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gslice + (size_t)k * GB) + tid);
+    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gslice + (size_t)k * (step * 16)) + tid);
   };
   if (timeout || (ce && bad_label)) {  // uniform: the row cannot be differentiated
     const uint4 qnan = make_uint4(0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u);
 #pragma unroll
     for (int k = 0; k < K; ++k)
-      if (k < n_mine) store(k, qnan);
+      if (mine(k)) store(k, qnan);
     if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0x7fc0;
     return;
   }
@@ -806,10 +851,9 @@ kd_gang_kernel(const KdArgs a) {
     if constexpr (LSE1 && (REV || SKEW)) gy = add_ce_own(gy, s_y, kf.p);
     const uint32_t b16 = one_bf16(gy - a.cscale);
     y_tail = (uint16_t)b16;
-    if (sp.group_of(y) >= 0) {
-      const int yg = sp.group_of(y) - g0;  // group of the slice
-      k_y = yg / TH;
-      if (yg - k_y * TH == tid) {
+    if (k_own >= 0) {
+      k_y = k_own;
+      if (thread_y == tid) {
         const int j = (y - head) & 7;
         const uint32_t keep = (j & 1) ? 0x0000ffffu : 0xffff0000u, bits = (j & 1) ? b16 << 16 : b16;
         if ((j >> 1) == 0) { y_keep.x = keep; y_bits.x = bits; }
@@ -827,7 +871,8 @@ kd_gang_kernel(const KdArgs a) {
   };
   if (last && tid < n_edge) {
     const int e = sp.edge_elem(tid);
-    const float xs = bf16_one(srow[e]), xt = bf16_one(trow[e]);
+    if constexpr (SKEW) read_edges();
+    const float xs = bf16_lo(s_e_bits), xt = bf16_lo(t_e_bits);
     float ge;
     if constexpr (SKEW)
       ge = skew_grad<DIVK>(xs, xt, ks);
@@ -847,12 +892,12 @@ kd_gang_kernel(const KdArgs a) {
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
       if constexpr (MFMA)
-        if (k * TH + wave0 >= ng) continue;  // uniform
+        if (first + wave0 >= end - k * step) continue;  // uniform
       opaque(sreg[k]);
       opaque(treg[k]);
       uint4 o = grad8<kDense, FORM, DIVK, M>(sreg[k], treg[k], kf, identity);
       if (k == k_y) patch_label(o);  // uniform
-      if (k < n_mine) store(k, o);
+      if (mine(k)) store(k, o);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -870,7 +915,7 @@ kd_gang_kernel(const KdArgs a) {
                        // not overwritten it yet, and no other one does)
 #pragma unroll
       for (int k = K - 1; k >= 0; --k) {
-        const uint4 vs = ld_group<GB>(rs, voff, k, true, true);
+        const uint4 vs = load(rs, k);
         float xs[8], gv[8], p[8], v[8];
         unpack8(vs, xs);
         cache_get(k, p, v);
@@ -879,7 +924,7 @@ kd_gang_kernel(const KdArgs a) {
           gv[j] = add_ce_own(__builtin_fmaf(v[j], ks.Av, ks.B * p[j]), xs[j], kf.p);
         uint4 o = make_uint4(pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3]), pack_bf16(gv[4], gv[5]), pack_bf16(gv[6], gv[7]));
         if (k == k_y) patch_label(o);  // uniform
-        if (k < n_mine) store(k, o);
+        if (mine(k)) store(k, o);
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
@@ -896,7 +941,7 @@ kd_gang_kernel(const KdArgs a) {
         }
         uint4 o = make_uint4(pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3]), pack_bf16(gv[4], gv[5]), pack_bf16(gv[6], gv[7]));
         if (k == k_y) patch_label(o);  // uniform
-        if (k < n_mine) store(k, o);
+        if (mine(k)) store(k, o);
         __builtin_amdgcn_sched_barrier(0);
       }
     }

@@ -82,7 +82,7 @@ kd_gang_topk_kernel(const KdArgs a) {
       if (a.lse) a.lse[row] = 0.0f;
     }
     if constexpr (GRAD) {
-      gang_zero_slice<K, TH>(grow + head, g0, ng, tid);
+      gang_zero_slice<K, TH>(grow + head, nvec, SOLO ? 0 : shift, slice, G, tid);
       if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
     }
     return;

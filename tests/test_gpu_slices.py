@@ -121,3 +121,73 @@ def test_skew_slices_with_groups_in_lds(oracle, V, pitch, T, tau, ce, div):
     assert int(status.item()) == 0
     got = dict(kd=kd.cpu().numpy().astype(np.float64), grad=grad.float().cpu().numpy().astype(np.float64))
     compare_kd(got, ref, mask_np, None, oracle, grad_scale=0.75 + ce * tau, tau=tau, amp_from_ref=True)
+
+
+@pytest.mark.parametrize("V,pitch,T", [
+    # four slices of four pieces of 256 groups: full, one group more and less, the last piece begun by the shift alone
+    (32768, 32768, 12), (32776, 32776, 12), (32760, 32768, 12), (32747, 32752, 12), (32768, 32776, 12),
+    (61440, 61448, 12), (40928, 40936, 290),
+])
+@pytest.mark.parametrize("what", ["forward", "forward_tau2", "reverse", "skew", "skew_tau3", "topk"])
+def test_pieces_dealt_to_the_slices(oracle, V, pitch, T, what):
+    if T > 100 and what in ("skew_tau3", "topk"):
+        pytest.skip("short rows cover it")
+    w = synth.scaled(synth.config(1), n_rows=1, row_len=T, vocab=V, length_lo=4, length_hi=9)
+    lay = synth.make_layout(w)
+    mask_np = lay.loss_mask.copy()
+    mask_np[:9] = 1
+    g = torch.Generator(device=dev()).manual_seed(V + pitch)
+    s, t, grad = (torch.empty((T, pitch), dtype=torch.bfloat16, device=dev())[:, :V] for _ in range(3))
+    s.copy_(3.0 * torch.randn((T, V), generator=g, device=dev()))
+    t.copy_(0.8 * s.float() + 1.5 * torch.randn((T, V), generator=g, device=dev()))
+    # No logit near 0 in some rows, most of the probability at the ends of pieces' first threads: a thread whose first group lies
+    # in front of the row must not take that group for its reference.  (200, not 1,500: a top-k loss is a sum of differences of
+    # logits times log2(e) and normalisers, three roundings of half of 2^-15 at 289, 3.2e-5 in all; at 2,164 they are 2.5e-4,
+    # beyond the bar for positions whose loss is small.)
+    for x in (s, t):
+        x[2:9] -= 200.0
+        for j in range(1, V // 2048):
+            x[2:9, 8 * (256 * j - 7):8 * 256 * j] += 12.0
+    # labels and support positions around the beginnings of pieces, whatever the shift
+    edges = sorted({min(max(0, 8 * (256 * j - r) + d), V - 1) for j in range(0, V // 2048 + 1, 3) for r in (0, 3, 7) for d in (-1, 0)} |
+                   {V - 1})
+    lab = np.array([edges[(5 * i) % len(edges)] for i in range(T)], np.int32)
+    sb, tb = synth.bf16_bits(s.contiguous()), synth.bf16_bits(t.contiguous())
+    tau = 3.0 if what == "skew_tau3" else 2.0 if what == "forward_tau2" else 1.0
+    ce = 0.25 if T < 100 else 0.0
+    kw = dict(tau=tau, grad_scale=0.75, ce_grad_scale=ce)
+    div = what.split("_")[0]
+    if what == "topk":
+        k = 24
+        idx = torch.topk(t.float(), k, dim=1)[1].to(torch.int32)
+        for r in range(T):
+            have = edges[r % 3::max(3, len(edges) // 12)][:12]
+            rest = [int(i) for i in idx[r].tolist() if int(i) not in have][:k - len(have)]
+            idx[r] = torch.tensor(have + rest, dtype=torch.int32)
+        val = t.float().gather(1, idx.long()).contiguous()
+        ref = oracle.kd_topk(sb, idx.cpu().numpy(), val.cpu().numpy(), lab, mask_np, **kw)
+        teacher = dict(teacher_idx=idx, teacher_val=val)
+    elif div == "forward":
+        ref = oracle.kd_dense(sb, tb, lab, mask_np, **kw)
+        teacher = dict(teacher_dense=t)
+    else:
+        ref = oracle.div_dense(sb, tb, div, 0.1, labels=lab, mask=mask_np, **kw)
+        teacher = dict(teacher_dense=t, divergence=1 if div == "reverse" else 2, skew_alpha=0.1)
+    print(f"[pieces] V={V} pitch={pitch} T={T} {what}", flush=True)
+    out = {}
+    for in_place in (False, True):
+        grad.fill_(float("nan"))
+        if in_place:
+            grad.copy_(s)
+        kd = torch.full((T,), -1.0, device=dev())
+        status = torch.zeros(1, dtype=torch.int32, device=dev())
+        binding.npd_kd_loss_fwd_bwd(grad if in_place else s, torch.from_numpy(mask_np).to(dev()),
+                                    labels=torch.from_numpy(lab).to(dev()), grad_out=grad, kd_tok=kd, dev_status=status, **kw,
+                                    **teacher)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0
+        got = dict(kd=kd.cpu().numpy().astype(np.float64), grad=grad.float().cpu().numpy().astype(np.float64))
+        compare_kd(got, ref, mask_np, None, oracle, grad_scale=0.75 + ce * tau, tau=tau, amp_from_ref=div in ("reverse", "skew"),
+                   folded=True)
+        out[in_place] = grad.contiguous().view(torch.int16).clone()
+    assert torch.equal(out[False], out[True])
