@@ -5,8 +5,7 @@ namespace npd {
 
 hipError_t launch_gang_fine(const KdArgs& a, int k, int teacher_kind, hipStream_t stream) {
   if (k == 7) {  // no sums at tau = 1
-    if (teacher_kind == kTopk) return launch_gang_kernel(a, 8, kd_gang_topk_kernel<7, kL1None>, stream,
-                                                         (size_t)topk_lds_words(kGangThreads, 7, a.k, false) * sizeof(uint32_t));
+    if (teacher_kind == kTopk) return launch_gang_topk_sums<7, kL1None>(a, stream);
     if (a.divergence == kReverseKl)
       return launch_gang_kernel(a, gang_words(2), kd_gang_kernel<7, kDense, kL1None, kReverseKl>, stream);
     return launch_gang_kernel(a, gang_words(2), kd_gang_kernel<7, kDense, kL1None, kForwardKl>, stream);

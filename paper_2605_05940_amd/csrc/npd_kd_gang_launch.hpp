@@ -24,13 +24,18 @@ static hipError_t launch_gang_dense(const KdArgs& a, hipStream_t stream) {
   }
 }
 
+template <int K, int L1>
+static hipError_t launch_gang_topk_sums(const KdArgs& a, hipStream_t stream) {
+  const size_t lds = (size_t)topk_lds_words(kGangThreads, K, a.k, true) * sizeof(uint32_t);
+  if (a.ragged) return launch_gang_kernel(a, 8, kd_gang_topk_kernel<K, L1, kGangThreads, false, true, true>, stream, lds);
+  return launch_gang_kernel(a, 8, kd_gang_topk_kernel<K, L1>, stream, lds);
+}
 template <int K>
 static hipError_t launch_gang_topk(const KdArgs& a, hipStream_t stream) {
-  const size_t lds = (size_t)topk_lds_words(kGangThreads, K, a.k, false) * sizeof(uint32_t);
   switch (l1_mode(a)) {
-    case kL1None: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<K, kL1None>, stream, lds);
-    case kL1Square: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<K, kL1Square>, stream, lds);
-    default: return launch_gang_kernel(a, 8, kd_gang_topk_kernel<K, kL1Own>, stream, lds);
+    case kL1None: return launch_gang_topk_sums<K, kL1None>(a, stream);
+    case kL1Square: return launch_gang_topk_sums<K, kL1Square>(a, stream);
+    default: return launch_gang_topk_sums<K, kL1Own>(a, stream);
   }
 }
 

@@ -4,9 +4,9 @@
 // log-sum-exps exchanged through the scratch record -- with these differences:
 //   - only the student row is dense: one read and one write per logit;
 //   - every workgroup of a row reads the row's whole top-k record (k ids + k values, a few hundred bytes): the teacher's
-//     normaliser over the k values is computed by each of them, the support positions that fall into its own slice
-//     are patched after its dense stores (final values from fp32, rounded once), and slice 0 also gathers the student
-//     logits of all k support positions for kd_tok;
+//     normaliser over the k values is computed by each of them, the support positions that fall into its own slice get
+//     their final values (from fp32, rounded once), and slice 0 also gathers the student logits of all k support
+//     positions for kd_tok;
 //   - every student logit a workgroup needs from outside its registers (support positions, the label) is fetched
 //     before the workgroup posts its partial sum, i.e. before any workgroup of the row can overwrite the row in place.
 #pragma once
@@ -17,23 +17,26 @@ namespace npd {
 // SOLO, TH, GRAD: as in npd_kd_gang.hpp; the forward-only SOLO form also takes calls without a teacher (k = 0).
 // Dynamic LDS: topk_lds_words per row of the workgroup.
 //
-// SOLO puts the final values of the support positions into the groups before they are stored: each group of the row has
+// The final values of the support positions are put into the groups before they are stored: each group of the workgroup has
 // a list of them in LDS that the threads build with exchanges (its order does not matter: the ids are distinct).
-// Stored behind the dense values they cost a wait for the whole workgroup's stores and k partial lines per row, which
-// dominates short rows (65,536 rows of 4,096, k = 64: 412 us, with lists 255 us).  On shared rows the k positions are
-// few per slice; they are stored behind the dense values there.
+// Stored behind the dense values they cost a wait for the whole workgroup's stores, the ids once more and k partial lines per
+// row (MI355X, us, so / with lists: 65,536 rows of 4,096, k = 64, one workgroup each 412 / 255; shared rows, with the record
+// requested in front of the slice's logits and its support logits gathered behind them, k = 64: 8,192 of 50,304 263 / 258,
+// of 36,000 194 / 184, 4,096 of 65,536 159 / 152, 64 of 151,936 16.0 / 15.5; k = 250, 8,192 of 128,256 681 / 625;
+// k = 1,000, 4,096 of 151,936 542 / 496).
 constexpr int kMaxEdges = 16;
 __host__ __device__ constexpr int topk_lds_words(int th, int groups, int k, bool lists) {
   return (lists ? th * groups + kMaxEdges + k : 0) + (k + 1) / 2;
 }
 
-template <int K, int L1, int TH = kGangThreads, bool SOLO = false, bool GRAD = true>
+template <int K, int L1, int TH = kGangThreads, bool SOLO = false, bool GRAD = true, bool DEALT = false>
 __global__ __launch_bounds__(gang_block(TH, SOLO), SOLO && K <= 8 ? 8 : 6) void
 kd_gang_topk_kernel(const KdArgs a) {
   static_assert(SOLO || (TH == kGangThreads && GRAD), "shared rows: gradient calls, 256 threads");
+  static_assert(!SOLO || !DEALT, "one workgroup takes the whole row");
   constexpr int GB = TH * 16;
   constexpr bool LSE1 = L1 != kL1None;
-  constexpr bool LIST = SOLO && GRAD;
+  constexpr bool LIST = GRAD;
   constexpr int NS = LSE1 ? 2 : 1;  // student / tau, student at tau = 1
   constexpr int NW3 = NS * 3;
   constexpr int W = 8;              // words of scratch per slice
@@ -65,15 +68,18 @@ kd_gang_topk_kernel(const KdArgs a) {
   uint16_t* grow = GRAD ? a.g + row * a.s_stride : nullptr;
   const RowSplit sp = row_split(a.s + row * a.s_stride, V, true);  // all dense rows at one offset from a 16-byte boundary
   const int head = sp.head, nvec = sp.nvec, n_edge = V - nvec * 8;
-  // This workgroup owns groups [g0, g1) -- the last slice also the edge elements of the row.  Boundaries inside the row
-  // are moved down to the next 128-byte boundary of the gradient row's address (by `shift` groups), so that no cache
-  // line is shared by two workgroups of a row; a slice is at most 7 groups longer than a.gang_groups for it.
+  // Slices: one run of gang_groups (up to 7 more), or, DEALT (rows that begin inside a 16-byte group), pieces of TH groups dealt to
+  // the row's workgroups in turn; boundaries as in npd_kd_gang.hpp.  Measured (MI355X, us, k = 64, runs / pieces): 8,192 x 50,003
+  // 268 / 261; aligned rows of 151,936 at tau = 2 726 / 733, 4,096 of 262,144 567 / 569, of 65,536 152 / 151.  Group
+  // idx0 + k * step is the thread's k-th, if it is below `end`.  The last slice also owns the edge elements of the row.
   const bool last = SOLO || slice == G - 1;
-  const int shift = (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
-  const int b0 = slice * a.gang_groups - shift, b1 = b0 + a.gang_groups;
-  const int g0 = slice == 0 ? 0 : (b0 < nvec ? b0 : nvec);
-  const int g1 = last ? nvec : (b1 < nvec ? b1 : nvec);
-  const int ng = g1 > g0 ? g1 - g0 : 0;
+  const int shift = SOLO ? 0 : (int)((reinterpret_cast<uintptr_t>(grow + head) >> 4) & 7u);
+  const int run = slice * a.gang_groups - shift;
+  const int first_group = DEALT ? slice * TH - shift : SOLO || slice == 0 ? 0 : (run < nvec ? run : nvec);
+  const int step = DEALT ? G * TH : TH;
+  const int end = DEALT || last ? nvec : (run + a.gang_groups < nvec ? run + a.gang_groups : nvec);
+  const int idx0 = first_group + tid;  // < 0: in front of the row (k = 0 of slice 0)
+  auto mine = [&](int k) __attribute__((always_inline)) { return idx0 < end - k * step && (!DEALT || k > 0 || idx0 >= 0); };
 
   if (!a.mask[row]) {  // not scored: scalars 0, the slice of the gradient row zero-filled, logits never read
     if (slice == 0 && tid == 0) {
@@ -82,7 +88,7 @@ kd_gang_topk_kernel(const KdArgs a) {
       if (a.lse) a.lse[row] = 0.0f;
     }
     if constexpr (GRAD) {
-      gang_zero_slice<K, TH>(grow + head, nvec, SOLO ? 0 : shift, slice, G, tid);
+      gang_zero_slice<K, TH>(grow + head, nvec, shift, slice, G, tid);
       if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0;
     }
     return;
@@ -92,51 +98,48 @@ kd_gang_topk_kernel(const KdArgs a) {
   const float c = a.c;
   if (TH > kWave && tid == 0) gave_up = y_hit_row = 0;  // ordered before their use by the barrier below
 
-  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head + (size_t)g0 * 8, ng);
-  const int voff = tid * 16;
-  const int n_mine = (ng - tid + TH - 1) / TH;  // groups of this thread
-  uint4 sreg[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) sreg[k] = ld_group<GB>(rs, voff, k, true, true);
-
-  // the elements of groups [g0, g1) are this workgroup's (the last slice also owns the edge elements)
-  auto owns = [&](int e) {
-    const int ge = sp.group_of(e);
-    return ge >= 0 ? ge >= g0 && ge < g1 : last;
-  };
-  int y = -1;
-  bool own_y = false;
-  float s_y = 0.0f;
-  if (a.labels) {
-    y = a.labels[row];
-    own_y = (unsigned)y < (unsigned)V && owns(y);
-    if (own_y) s_y = bf16_one(srow[y]);
-  }
-  const bool bad_label = a.labels && (unsigned)y >= (unsigned)V;  // uniform
-
-  // ---- the row's top-k record: the teacher's normaliser over the k values, the range check of the ids, and the
-  // student logits at the support positions this workgroup will need (its own; all of them in slice 0)
+  // ---- the row's top-k record: entries tid, tid + TH, ...; the first (for k <= TH the only one) is kept in registers and
+  // requested in front of the slice (what is loaded behind it arrives behind it)
   const int32_t* irow = a.tidx + row * (int64_t)k_top;
   const float* vrow = a.tval + row * (int64_t)k_top;
-  Lse tt;
-  tt.init();
-  int bad_index = 0;
-  // entries tid, tid + TH, ...; the first (for k <= TH the only one) is kept in registers
   const bool has_entry = tid < k_top;
   const int id_first = has_entry ? irow[tid] : 0;
   const float v_first = has_entry ? vrow[tid] : 0.0f;
-  auto each_entry = [&](auto&& f) {
-    if (has_entry) f(tid, id_first, v_first);
-    for (int j = tid + TH; j < k_top; j += TH) f(j, irow[j], vrow[j]);
+  __builtin_amdgcn_sched_barrier(0);
+
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(srow + head, end);
+  const int voff = idx0 * 16;
+  uint4 sreg[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    sreg[k] = !DEALT ? ld_group<GB>(rs, voff, k, true, true) : ld_group<0>(rs, voff + k * step * 16, 0, true, true);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // place of element e among this workgroup's: k * TH + thread of its group, behind K * TH the edge elements (the last slice's);
+  // -1: another workgroup's
+  auto place = [&](int e) __attribute__((always_inline)) {
+    const int ge = sp.group_of(e);
+    if (ge < 0) return last ? K * TH + (e < head ? e : e - nvec * 8) : -1;
+    if constexpr (SOLO) return ge;
+    if constexpr (!DEALT) return ge >= first_group && ge < end ? ge - first_group : -1;
+    const unsigned at = (unsigned)(ge + shift), piece = at / TH, k = piece / (unsigned)G;
+    return (int)(piece - k * (unsigned)G) == slice ? (int)(k * TH + at % TH) : -1;
   };
-  each_entry([&](int j, int id, float v) {
-    tt.add1(v, c);
-    if ((unsigned)id >= (unsigned)V) {
-      bad_index = 1;
-    } else if (slice == 0 || owns(id)) {
-      sup_s[j] = srow[id];
-    }
-  });
+  // student logits from outside the registers: the label's, and those at the support positions this workgroup will need
+  // (its own; all of them in slice 0)
+  int y = -1, place_y = -1;
+  uint32_t s_y_bits = 0;
+  if (a.labels) {
+    y = a.labels[row];
+    if ((unsigned)y < (unsigned)V) place_y = place(y);
+    if (place_y >= 0) s_y_bits = srow[y];
+  }
+  const bool own_y = place_y >= 0;
+  const bool bad_label = a.labels && (unsigned)y >= (unsigned)V;  // uniform
+  auto needs = [&](int id) __attribute__((always_inline)) { return (unsigned)id < (unsigned)V && (slice == 0 || place(id) >= 0); };
+  uint32_t sup_first = 0, s_e_bits = 0;
+  if (has_entry && needs(id_first)) sup_first = srow[id_first];
+  if (last && tid < n_edge) s_e_bits = srow[sp.edge_elem(tid)];
 
   // ---- sweep 1 over the student slice (see npd_kd_gang.hpp: fixed reference from the first group, careful re-run
   // of a wave whose sums show an anomaly)
@@ -145,8 +148,10 @@ kd_gang_topk_kernel(const KdArgs a) {
   for (int i = 0; i < 4; ++i) acc[i].init();
   const bool ref_of_all = SOLO || a.ragged || (LSE1 && a.cscale != 0.0f);  // see npd_kd_gang.hpp
   const float kRefBias = ref_of_all ? 0.0f : (L1 == kL1Square ? 44.0f : 100.0f);  // see npd_kd_gang.hpp
-  if (ng > tid) {
-    const float fs = ref_of_all ? thread_max(sreg, n_mine) : pk_max_value(pk_max_group(sreg[0]));
+  if (mine(0) || (DEALT && mine(1))) {
+    uint32_t ms = pk_max_group(sreg[0]);
+    if (DEALT && idx0 < 0) ms = pk_max_group(sreg[1]);
+    const float fs = ref_of_all ? thread_max<DEALT>(sreg, mine) : pk_max_value(ms);
     acc[0].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, c, kRefBias), -1.0e30f));
     if constexpr (L1 == kL1Own) acc[2].r = __builtin_rintf(__builtin_fmaxf(__builtin_fmaf(fs, kLog2e, kRefBias), -1.0e30f));
     if constexpr (L1 == kL1Square) acc[2].r = 2.0f * acc[0].r;
@@ -154,7 +159,7 @@ kd_gang_topk_kernel(const KdArgs a) {
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    if (k < n_mine) {
+    if (mine(k)) {
       float xs[8];
       unpack8(sreg[k], xs);
 #pragma unroll
@@ -176,7 +181,7 @@ kd_gang_topk_kernel(const KdArgs a) {
       acc[2].init();
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        if (k < n_mine) {
+        if (mine(k)) {
           float xs[8];
           unpack8(sreg[k], xs);
           acc[0].add8(xs, c);
@@ -186,11 +191,28 @@ kd_gang_topk_kernel(const KdArgs a) {
       }
     }
   }
+  // the conversions stay here: behind the sums, and in front of this workgroup's post (rows in place)
+  asm volatile("" : "+v"(s_y_bits), "+v"(sup_first), "+v"(s_e_bits));
+  const float s_y = bf16_lo(s_y_bits);
   if (last && tid < n_edge) {
-    const float xs = bf16_one(srow[sp.edge_elem(tid)]);
+    const float xs = bf16_lo(s_e_bits);
     acc[0].add1(xs, c);
     if constexpr (LSE1) acc[2].add1(xs, kLog2e);
   }
+
+  // ---- the teacher's normaliser over the k values, the range check of the ids, the gathered support logits
+  Lse tt;
+  tt.init();
+  int bad_index = 0;
+  auto each_entry = [&](auto&& f) {
+    if (has_entry) f(tid, id_first, v_first);
+    for (int j = tid + TH; j < k_top; j += TH) f(j, irow[j], vrow[j]);
+  };
+  each_entry([&](int j, int id, float v) {
+    tt.add1(v, c);
+    if ((unsigned)id >= (unsigned)V) bad_index = 1;
+    if (needs(id)) sup_s[j] = j == tid ? (uint16_t)sup_first : srow[id];
+  });
 
   // ---- wave totals, workgroup totals, post, wait, row totals (student); workgroup totals of the teacher's k values
   const int lane = tid & (kWave - 1), wid = tid / kWave;
@@ -284,8 +306,8 @@ kd_gang_topk_kernel(const KdArgs a) {
   int y_hit = 0;
   if (!bad_index) {
     each_entry([&](int j, int id, float v) {
-      const bool mine = owns(id);
-      if (slice == 0 || mine) {
+      const int at = place(id);
+      if (slice == 0 || at >= 0) {
         const float b = v * c;
         const float sj = bf16_one(sup_s[j]);
         if (slice == 0) {
@@ -293,7 +315,7 @@ kd_gang_topk_kernel(const KdArgs a) {
           const float lps = __builtin_fmaf(sj, c, -Ls);
           part_kd = __builtin_fmaf(exp2_fast(lpt), __builtin_fmaxf(lpt - lps, -3.4028234663852886e38f) * kLn2, part_kd);
         }
-        if (GRAD && mine) {
+        if (GRAD && at >= 0) {
           float gj = grad_pair_elem(sj, b, kf.p);
           if (ce && id == y) {
             gj -= a.cscale;
@@ -301,9 +323,7 @@ kd_gang_topk_kernel(const KdArgs a) {
           }
           sup_s[j] = one_bf16(gj);  // this thread read sup_s[j] above: no other thread touches entry j before the barrier
           if constexpr (LIST) {
-            const int ge = sp.group_of(id);
-            const int list = ge >= 0 ? ge : K * TH + (id < head ? id : id - nvec * 8);
-            link[j] = atomicExch(&first[list], (uint32_t)(j + 1)) | ((uint32_t)((id - head) & 7) << 16);
+            link[j] = atomicExch(&first[at], (uint32_t)(j + 1)) | ((uint32_t)((id - head) & 7) << 16);
           }
         }
       }
@@ -347,16 +367,16 @@ kd_gang_topk_kernel(const KdArgs a) {
 
   if constexpr (!GRAD) return;
   // ---- sweep 2: dense part p_S * weights from the registers, then the support positions of this slice
-  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (size_t)g0 * 16;
+  uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (int64_t)first_group * 16;
   auto store = [&](int k, const uint4& o) {
     const u32x4 w = {o.x, o.y, o.z, o.w};
-    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gslice + (size_t)k * GB) + tid);
+    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gslice + (size_t)k * (step * 16)) + tid);
   };
   if (timeout || bad_index || (ce && bad_label)) {  // uniform: the row cannot be differentiated
     const uint4 qnan = make_uint4(0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u);
 #pragma unroll
     for (int k = 0; k < K; ++k)
-      if (k < n_mine) store(k, qnan);
+      if (mine(k)) store(k, qnan);
     if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0x7fc0;
     return;
   }
@@ -368,10 +388,9 @@ kd_gang_topk_kernel(const KdArgs a) {
   if (patch_y) {
     const uint32_t b16 = one_bf16(grad_student_elem(s_y, kf.p) - a.cscale);
     y_tail = (uint16_t)b16;
-    if (sp.group_of(y) >= 0) {
-      const int yg = sp.group_of(y) - g0;
-      k_y = yg / TH;
-      if (yg - k_y * TH == tid) {
+    if (place_y < K * TH) {
+      k_y = place_y / TH;
+      if (place_y % TH == tid) {
         const int j = (y - head) & 7;
         const uint32_t keep = (j & 1) ? 0x0000ffffu : 0xffff0000u, bits = (j & 1) ? b16 << 16 : b16;
         if ((j >> 1) == 0) { y_keep.x = keep; y_bits.x = bits; }
@@ -403,7 +422,7 @@ kd_gang_topk_kernel(const KdArgs a) {
     constexpr int FORM = decltype(form)::value;
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
-      if (k < n_mine) {
+      if (mine(k)) {
         opaque(sreg[k]);
         uint4 o = grad8<kTopk, FORM>(sreg[k], sreg[k], kf);
         if (k == k_y) patch_label(o);  // uniform
@@ -423,21 +442,13 @@ kd_gang_topk_kernel(const KdArgs a) {
     walk(std::integral_constant<int, kPrecise>{});
   if (last && tid < n_edge) {
     const int e = sp.edge_elem(tid);
-    uint16_t o = one_bf16(grad_student_elem(bf16_one(srow[e]), kf.p));
+    uint16_t o = one_bf16(grad_student_elem(bf16_lo(s_e_bits), kf.p));
     if (patch_y && e == y) o = y_tail;
     if constexpr (LIST) {
       const uint32_t j1 = first[K * TH + tid];
       if (j1 != 0) o = sup_s[j1 - 1];
     }
     grow[e] = o;
-  }
-  if constexpr (!LIST) {
-    // the support positions get their final values once the stores of the whole workgroup are ordered before them
-    __syncthreads();
-    for (int j = tid; j < k_top; j += TH) {
-      const int id = irow[j];
-      if (owns(id)) grow[id] = sup_s[j];
-    }
   }
 }
 
