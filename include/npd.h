@@ -153,6 +153,13 @@ size_t npd_workspace_bytes(const npd_kd_desc* desc);
 size_t npd_workspace_bytes_preferred(const npd_kd_desc* desc);
 
 /*
+ * Bytes of a workspace that the caller keeps from call to call for npd_kd_loss_fwd_bwd_kept on
+ * `stream` (host call): 0 where that entry point does not serve the call -- no workspace is used,
+ * or the stream is being captured (a replay would repeat the call's number, see there).
+ */
+size_t npd_kept_workspace_bytes(const npd_kd_desc* desc, void* stream);
+
+/*
  * The fused KD loss of one packed batch: for every scored position p (Alg. 1,
  * "Compute Probs" / "Compute KD Loss"; Eq. 2; L_CE of Eq. 1):
  *
@@ -214,6 +221,23 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
                                const uint8_t* loss_mask, void* grad_out, float* kd_tok, float* nll_tok,
                                float* teacher_nll_tok, float* lse_tok, int32_t* dev_status, void* workspace,
                                size_t workspace_bytes, void* stream);
+
+/*
+ * The same call on a workspace that needs no clearing launch in front of the kernel: its words
+ * carry a number that every call of this entry point takes anew.
+ *   workspace        device, >= npd_kept_workspace_bytes(desc, stream) bytes (not 0), 256-byte
+ *                    aligned; zero before its first use and written since then by nothing but
+ *                    calls of this entry point, which must be ordered on one stream
+ * Not for streams under capture.  Results are those of npd_kd_loss_fwd_bwd with the workspace
+ * npd_workspace_bytes_preferred() asks for, bit by bit.
+ */
+npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student_logits,
+                                    const void* teacher_dense, const int32_t* teacher_idx,
+                                    const float* teacher_val, const int32_t* labels,
+                                    const uint8_t* loss_mask, void* grad_out, float* kd_tok,
+                                    float* nll_tok, float* teacher_nll_tok, float* lse_tok,
+                                    int32_t* dev_status, void* workspace, size_t workspace_bytes,
+                                    void* stream);
 
 /*
  * Forward-only calls (desc->flags with NPD_FLAG_FWD_ONLY) with scratch memory: arguments, results and errors are those of

@@ -29,7 +29,8 @@ NOALLOC_WORKSPACE_BYTES = 16 << 20   # NPD_NOALLOC_WORKSPACE_BYTES
 EXPORTS = ("npd_version", "npd_status_string", "npd_workspace_bytes", "npd_kd_loss_fwd_bwd",
            "npd_segment_reduce", "npd_delta_ifd_score", "npd_teacher_topk", "npd_debug_gang_spin_limit",
            "npd_kd_loss_fwd_bwd_noalloc", "npd_policy_lag", "npd_segment_ppl", "npd_kd_kernel_name",
-           "npd_forward_scratch_bytes", "npd_kd_loss_forward", "npd_workspace_bytes_preferred")
+           "npd_forward_scratch_bytes", "npd_kd_loss_forward", "npd_workspace_bytes_preferred",
+           "npd_kept_workspace_bytes", "npd_kd_loss_fwd_bwd_kept")
 
 
 class NpdError(RuntimeError):
@@ -90,7 +91,9 @@ def load() -> ctypes.CDLL:
         # entry points that a library of another build (NPD_LIB_PATH) may not have yet; its calls are made without them
         newer = {"npd_forward_scratch_bytes": (ctypes.c_size_t, []),
                  "npd_workspace_bytes_preferred": (ctypes.c_size_t, []),
-                 "npd_kd_loss_forward": (ctypes.c_int, [_vp] * 12 + [ctypes.c_size_t, _vp])}
+                 "npd_kd_loss_forward": (ctypes.c_int, [_vp] * 12 + [ctypes.c_size_t, _vp]),
+                 "npd_kept_workspace_bytes": (ctypes.c_size_t, [_vp]),
+                 "npd_kd_loss_fwd_bwd_kept": (ctypes.c_int, [_vp] * 13 + [ctypes.c_size_t, _vp])}
         here = os.path.realpath(LIB_PATH) == os.path.realpath(os.path.join(HERE, "libnpd.so"))
         complete = here or all(hasattr(L, name) for name in newer)
         for name, (result, more) in newer.items():
@@ -114,7 +117,8 @@ def _load_host(L):
                       "`python -m paper_2605_05940_amd.build` builds it", RuntimeWarning)
         return None
     entries = (L.npd_workspace_bytes, L.npd_workspace_bytes_preferred, L.npd_forward_scratch_bytes, L.npd_kd_loss_fwd_bwd,
-               L.npd_kd_loss_forward, L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag)
+               L.npd_kd_loss_forward, L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag,
+               L.npd_kept_workspace_bytes, L.npd_kd_loss_fwd_bwd_kept)
     host.bind(_raw_stream, _workspaces, tuple(ctypes.cast(f, _vp).value for f in entries))
     return host
 

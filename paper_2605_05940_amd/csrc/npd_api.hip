@@ -91,6 +91,11 @@ bool any_alias(const Range* in, int n_in, const Range* out, int n_out) {
 Range opt_range(const void* p, size_t bytes) { return p ? range_of(p, bytes) : Range{0, 0}; }
 
 
+// Numbers of the launches on records that are not cleared: each is taken once in the life of the process, so no word that an
+// earlier launch left can be taken for one of a later launch.  When they run out such calls are refused.
+std::atomic<uint64_t> gang_launches{0};
+constexpr uint64_t kLastTag = 0xffffffffu;
+
 constexpr int kMaxDevices = 64;
 std::atomic<void*> noalloc_scratch_ptr[kMaxDevices];  // zero-initialised
 
@@ -262,7 +267,7 @@ npd_status check_kd_call(const npd_kd_desc* desc, const void* student_logits, co
 
 extern "C" {
 
-int npd_version(void) { return 120; }
+int npd_version(void) { return 121; }
 
 const char* npd_status_string(npd_status st) {
   switch (st) {
@@ -337,6 +342,40 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
   }
   const bool want_grad = !(desc->flags & NPD_FLAG_FWD_ONLY);
   const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, have, static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
+}
+
+size_t npd_kept_workspace_bytes(const npd_kd_desc* desc, void* stream) {
+  if (check_desc(desc) != NPD_OK) return 0;
+  const size_t want = workspace_bytes_of(*desc, true);
+  if (want == 0 || gang_launches.load(std::memory_order_relaxed) >= kLastTag) return 0;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) != hipSuccess) return 0;
+  return capture == hipStreamCaptureStatusNone ? 2 * want : 0;
+}
+
+npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student_logits, const void* teacher_dense,
+                                    const int32_t* teacher_idx, const float* teacher_val, const int32_t* labels,
+                                    const uint8_t* loss_mask, void* grad_out, float* kd_tok, float* nll_tok,
+                                    float* teacher_nll_tok, float* lse_tok, int32_t* dev_status, void* workspace,
+                                    size_t workspace_bytes, void* stream) {
+  npd::KdArgs a{};
+  size_t need = 0;
+  const npd_status st = check_kd_call(desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
+                                      grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
+  if (st != NPD_OK) return st;
+  const size_t want = workspace_bytes_of(*desc, true);
+  if (want == 0 || !workspace || workspace_bytes < 2 * want || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
+    return NPD_ERR_WORKSPACE;
+  if (kd_buffers(*desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask, grad_out, kd_tok, nll_tok,
+                 teacher_nll_tok, lse_tok, dev_status).overlaps_any(range_of(workspace, 2 * want)))
+    return NPD_ERR_ALIAS;
+  const uint64_t tag = gang_launches.fetch_add(1, std::memory_order_relaxed) + 1;
+  if (tag > kLastTag) return NPD_ERR_UNSUPPORTED;
+  a.ws = static_cast<uint32_t*>(workspace);
+  a.tag = (uint32_t)tag;
+  const bool want_grad = !(desc->flags & NPD_FLAG_FWD_ONLY);
+  const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, want, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
 }
 

@@ -11,8 +11,11 @@
 #include <Python.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <ATen/ops/zeros.h>
 #include <c10/core/impl/VirtualGuardImpl.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <vector>
 
 #include "../../include/npd.h"
 
@@ -28,6 +31,8 @@ struct Entry {
   decltype(&npd_delta_ifd_score) delta_ifd;
   decltype(&npd_teacher_topk) teacher_topk;
   decltype(&npd_policy_lag) policy_lag;
+  decltype(&npd_kept_workspace_bytes) kept_bytes;
+  decltype(&npd_kd_loss_fwd_bwd_kept) kd_kept;
 };
 Entry lib;                            // written by bind() under the interpreter lock, before any call
 PyObject* raw_stream = nullptr;       // torch's current raw stream of a device index
@@ -103,6 +108,45 @@ void* current_stream() {
 // exception leaves the call to the Python code, which knows what runs without)
 at::Tensor scratch(size_t bytes) {
   return at::empty({(int64_t)bytes}, at::TensorOptions().dtype(at::kByte).device(current_device()));
+}
+
+// Records of the calls that clear none (npd_kd_loss_fwd_bwd_kept): one per device and stream, so that calls on different
+// streams share none and a record goes back to the pool of the stream that it was used on.  Written under the interpreter
+// lock.  At most kRecords of at most kRecordBytes; other calls clear a record as before.
+struct Record {
+  c10::DeviceIndex device;
+  void* stream;
+  at::Tensor bytes;
+};
+constexpr size_t kRecords = 8, kRecordBytes = 32u << 20, kRecordLeast = 1u << 18;
+std::vector<Record>& records() {
+  static auto* all = new std::vector<Record>;  // (not destroyed behind the runtime's own end)
+  return *all;
+}
+// undefined: none to be had
+at::Tensor record_of(size_t bytes, void* stream) {
+  const c10::Device device = current_device();
+  Record* r = nullptr;
+  for (Record& x : records())
+    if (x.device == device.index() && x.stream == stream) r = &x;
+  if (r && (size_t)r->bytes.numel() >= bytes) return r->bytes;
+  if (bytes > kRecordBytes || (!r && records().size() >= kRecords)) return at::Tensor();
+  const int64_t n = (int64_t)(bytes > kRecordLeast ? bytes : kRecordLeast);
+  at::Tensor t;
+  try {
+    t = at::zeros({n}, at::TensorOptions().dtype(at::kByte).device(device));
+  } catch (const std::exception&) {  // no memory: the call as before
+    return at::Tensor();
+  }
+  if (r)
+    r->bytes = t;
+  else
+    records().push_back(Record{device.index(), stream, t});
+  return t;
+}
+PyObject* release(PyObject*, PyObject*) {
+  records().clear();
+  Py_RETURN_NONE;
 }
 
 // A call into libnpd, without the interpreter lock: a launch may wait for room in its queue.
@@ -193,6 +237,12 @@ PyObject* kd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     }
     const size_t need = !ws && !no_workspace && g ? lib.workspace_bytes(&d) : 0;
     if (need) {  // as binding._workspace
+      if (const size_t bytes = s.get_device() == current_device().index() ? lib.kept_bytes(&d, stream) : 0) {
+        const at::Tensor kept = record_of(bytes, stream);  // (held through the call)
+        if (kept.defined())
+          return call(lib.kd_kept, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, kept.data_ptr(),
+                      (size_t)kept.numel(), stream);
+      }
       const size_t want = lib.workspace_bytes_preferred(&d);
       at::Tensor w;  // (held through the call)
       if (!((ce != 0.0 && tau != 1.0) || (((uintptr_t)sp | (uintptr_t)(2 * d.student_stride)) & 15) != 0)) {
@@ -285,10 +335,10 @@ PyObject* policy_lag(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* bind(PyObject*, PyObject* args) {
   PyObject *stream, *kept, *addresses;
   if (!PyArg_ParseTuple(args, "OO!O!", &stream, &PyDict_Type, &kept, &PyTuple_Type, &addresses)) return nullptr;
-  constexpr int kEntries = 9;
+  constexpr int kEntries = 11;
   void* p[kEntries];
   if (PyTuple_GET_SIZE(addresses) != kEntries) {
-    PyErr_SetString(PyExc_ValueError, "9 addresses");
+    PyErr_SetString(PyExc_ValueError, "11 addresses");
     return nullptr;
   }
   for (int i = 0; i < kEntries; ++i) {
@@ -311,6 +361,8 @@ PyObject* bind(PyObject*, PyObject* args) {
   lib.delta_ifd = reinterpret_cast<decltype(lib.delta_ifd)>(p[6]);
   lib.teacher_topk = reinterpret_cast<decltype(lib.teacher_topk)>(p[7]);
   lib.policy_lag = reinterpret_cast<decltype(lib.policy_lag)>(p[8]);
+  lib.kept_bytes = reinterpret_cast<decltype(lib.kept_bytes)>(p[9]);
+  lib.kd_kept = reinterpret_cast<decltype(lib.kd_kept)>(p[10]);
   Py_RETURN_NONE;
 }
 
@@ -321,6 +373,7 @@ PyMethodDef methods[] = {
     {"delta_ifd", reinterpret_cast<PyCFunction>(delta_ifd), METH_FASTCALL, nullptr},
     {"teacher_topk", reinterpret_cast<PyCFunction>(teacher_topk), METH_FASTCALL, nullptr},
     {"policy_lag", reinterpret_cast<PyCFunction>(policy_lag), METH_FASTCALL, nullptr},
+    {"release", release, METH_NOARGS, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "npd_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -40,6 +40,7 @@ struct KdArgs {
   uint32_t* ws;          // scratch record, gang_workspace_bytes() or split_scratch_bytes() bytes
   int32_t gang;          // slices (workgroups) per row
   int32_t gang_groups;   // 128-bit groups per slice
+  uint32_t tag;          // != 0: the record needs no clearing, its words carry this number (npd_kd_gang.hpp)
   int32_t spin_limit;    // polls before a waiting workgroup gives up
 };
 

@@ -60,7 +60,7 @@ size_t gang_workspace_bytes(int64_t T, int32_t V, int teacher_kind, int divergen
   return record_bytes(T, g, gang_words(lse1 ? 4 : 2));
 }
 
-// Runs in front of every launch of a row-gang kernel: clears the scratch record (and the words behind it) to the
+// Runs in front of the launch of a row-gang kernel whose record carries no numbers (KdArgs::tag): clears the scratch record (and the words behind it) to the
 // pattern no posted word takes.
 __global__ __launch_bounds__(256) void gang_clear_kernel(uint32_t* ws, size_t words) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) ws[i] = kGangEmpty;

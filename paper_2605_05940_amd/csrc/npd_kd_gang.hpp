@@ -14,9 +14,11 @@
 // overlap three other slices' memory traffic), and the workgroups of rows that are not scored zero-fill their slices
 // in the same address order.
 //
-// The exchange needs no fence: every posted word is a 32-bit atomic store that carries its own validity (the
-// scratch record is cleared to a pattern no posted word takes, by a fill kernel enqueued in front of each launch),
-// and consumers poll those words with atomic loads at device scope.  Forward progress: a workgroup waits only for
+// The exchange needs no fence: every posted word is an atomic store that carries its own validity, and consumers poll those
+// words with atomic loads at device scope.  Either the scratch record is cleared to a pattern no posted word takes, by a fill
+// kernel enqueued in front of each launch, and words are 32 bits; or (KdArgs::tag) words are 64 bits, the upper half a number
+// that no earlier launch on this record has had, and there is no launch in front (a record that was zero once and has been used
+// by such launches alone; the fill and its gap take 2.4 us of a small call, 5 us of a large one).  Forward progress: a workgroup waits only for
 // workgroups of smaller or neighbouring index (the other slices of its own row), a workgroup never waits before it
 // has posted, and workgroups start in index order, so the lowest unfinished row always has all its workgroups
 // resident or next to start.  Every wait is bounded all the same: a workgroup that gives up marks its row NaN, sets
@@ -152,31 +154,44 @@ __device__ __forceinline__ float thread_max(const uint4 (&v)[K], int n) {
   return thread_max<false>(v, [&](int k) __attribute__((always_inline)) { return k < n; });
 }
 
-__device__ __forceinline__ void gang_post(uint32_t* p, float v) {
+__device__ __forceinline__ void gang_post(uint32_t* ws, size_t at, float v, uint32_t tag) {
   uint32_t w = __builtin_bit_cast(uint32_t, v);
+  if (tag != 0) {  // uniform
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(ws) + at, (uint64_t)tag << 32 | w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
   if (w == kGangEmpty) w = 0x7fc00000u;  // another NaN
-  __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(ws + at, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Waits for a posted word.  Gives up after `spin_limit` polls, or -- looked at every 256th poll -- as soon as any
-// workgroup of the launch has given up (the word *abandon, cleared with the record): once one wait has run out, no
+// Waits for posted word `at`.  Gives up after `spin_limit` polls, or -- looked at every 256th poll -- as soon as any
+// workgroup of the launch has given up (word `abandon` behind the record, posted then): once one wait has run out, no
 // other workgroup spends its own limit, so a launch whose workgroups cannot see each other ends within seconds
-// however many rows it has.  Returns the word, or kGangEmpty with *gave_up set.
+// however many rows it has.  Returns the word, or anything with *gave_up set.
 constexpr int kGangTailWords = 64;  // words behind the record; word 0: a workgroup has given up
-__device__ __forceinline__ uint32_t gang_wait(const uint32_t* p, uint32_t* abandon, int spin_limit, int* gave_up) {
+__device__ __forceinline__ bool gang_look(const uint32_t* ws, size_t at, uint32_t tag, uint32_t& w) {
+  if (tag != 0) {  // uniform
+    const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(ws) + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    w = (uint32_t)v;
+    return (uint32_t)(v >> 32) == tag;
+  }
+  w = __hip_atomic_load(ws + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return w != kGangEmpty;
+}
+__device__ __forceinline__ uint32_t gang_wait(uint32_t* ws, size_t at, size_t abandon, uint32_t tag, int spin_limit, int* gave_up) {
   int spins = 0;
   while (true) {
-    const uint32_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (v != kGangEmpty) return v;
+    uint32_t w, given_up;
+    if (gang_look(ws, at, tag, w)) return w;
     ++spins;
     if (spins > spin_limit) {
-      __hip_atomic_store(abandon, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      gang_post(ws, abandon, 1.0f, tag);
       *gave_up = 1;
-      return v;
+      return w;
     }
-    if ((spins & 255) == 0 && __hip_atomic_load(abandon, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 1u) {
+    if ((spins & 255) == 0 && gang_look(ws, abandon, tag, given_up)) {
       *gave_up = 1;
-      return v;
+      return w;
     }
     __builtin_amdgcn_s_sleep(8);
   }
@@ -630,8 +645,8 @@ kd_gang_kernel(const KdArgs a) {
       wave_merge_rescaled<false>(acc[i]);
   }
   bool timeout = false;
-  uint32_t* rec = nullptr;
-  uint32_t* abandon = nullptr;
+  const size_t rec = SOLO ? 0 : (size_t)blockIdx.x * W;      // words of scratch[row][slice]
+  const size_t abandon = SOLO ? 0 : (size_t)gridDim.x * W;  // behind the record
   if constexpr (NWV > 1) {
     if (lane == 0) {
 #pragma unroll
@@ -658,8 +673,6 @@ kd_gang_kernel(const KdArgs a) {
 
   }
   if constexpr (!SOLO) {
-    rec = a.ws + (size_t)blockIdx.x * W;  // scratch[row][slice]
-    abandon = a.ws + (size_t)gridDim.x * W;  // behind the record
     if (tid < NW3) {
       float v = acc[0].r;
 #pragma unroll
@@ -668,14 +681,14 @@ kd_gang_kernel(const KdArgs a) {
         if (tid == i * 3 + 1) v = acc[i].z;
         if (tid == i * 3 + 2) v = acc[i].a;
       }
-      gang_post(rec + tid, v);
+      gang_post(a.ws, rec + tid, v, a.tag);
     }
     {
-      const uint32_t* rrow = a.ws + (size_t)row * G * W;
+      const size_t rrow = (size_t)row * G * W;
       const int nw = G * NW3;
       for (int w = tid; w < nw; w += TH) {
         const int s = w / NW3, f = w - s * NW3;
-        xch[s * W + f] = gang_wait(rrow + s * W + f, abandon, a.spin_limit, &gave_up);
+        xch[s * W + f] = gang_wait(a.ws, rrow + s * W + f, abandon, a.tag, a.spin_limit, &gave_up);
       }
     }
     __syncthreads();
@@ -761,12 +774,12 @@ kd_gang_kernel(const KdArgs a) {
       usum = wave_sum_dpp(lane < NWV ? red[NWV + lane] : 0.0f);
     }
     if constexpr (!SOLO) {
-      if (tid < 2) gang_post(rec + NW3 + tid, tid == 0 ? dsum : usum);
+      if (tid < 2) gang_post(a.ws, rec + NW3 + tid, tid == 0 ? dsum : usum, a.tag);
       {
-        const uint32_t* rrow = a.ws + (size_t)row * G * W;
+        const size_t rrow = (size_t)row * G * W;
         for (int w = tid; w < 2 * G; w += TH) {
           const int s = w >> 1, f = w & 1;
-          xch2[w] = gang_wait(rrow + s * W + NW3 + f, abandon, a.spin_limit, &gave_up);
+          xch2[w] = gang_wait(a.ws, rrow + s * W + NW3 + f, abandon, a.tag, a.spin_limit, &gave_up);
         }
       }
       __syncthreads();

@@ -10,8 +10,10 @@ hipError_t clear_gang_record(uint32_t* ws, size_t words, hipStream_t stream);  /
 template <class Kernel>
 static hipError_t launch_gang_kernel(const KdArgs& a, int words_per_slice, Kernel kernel, hipStream_t stream,
                                      size_t lds_bytes = 0) {
-  const hipError_t e = clear_gang_record(a.ws, (size_t)a.T * a.gang * words_per_slice + kGangTailWords, stream);
-  if (e != hipSuccess) return e;
+  if (a.tag == 0) {
+    const hipError_t e = clear_gang_record(a.ws, (size_t)a.T * a.gang * words_per_slice + kGangTailWords, stream);
+    if (e != hipSuccess) return e;
+  }
   return launch_kernel(kernel, dim3((unsigned)(a.T * a.gang)), dim3(kGangThreads), lds_bytes, stream, a);
 }
 

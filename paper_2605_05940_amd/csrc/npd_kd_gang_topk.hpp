@@ -258,8 +258,7 @@ kd_gang_topk_kernel(const KdArgs a) {
 
   bool timeout = false;
   if constexpr (!SOLO) {
-    uint32_t* rec = a.ws + (size_t)blockIdx.x * W;
-    uint32_t* abandon = a.ws + (size_t)gridDim.x * W;  // behind the record
+    const size_t abandon = (size_t)gridDim.x * W;  // behind the record
     if (tid < NW3) {
       float v = st[0].r;
 #pragma unroll
@@ -268,14 +267,14 @@ kd_gang_topk_kernel(const KdArgs a) {
         if (tid == i * 3 + 1) v = st[i].z;
         if (tid == i * 3 + 2) v = 0.0f;
       }
-      gang_post(rec + tid, v);
+      gang_post(a.ws, (size_t)blockIdx.x * W + tid, v, a.tag);
     }
     {
-      const uint32_t* rrow = a.ws + (size_t)row * G * W;
+      const size_t rrow = (size_t)row * G * W;
       const int nw = G * NW3;
       for (int w = tid; w < nw; w += TH) {
         const int s = w / NW3, f = w - s * NW3;
-        xch[s * W + f] = gang_wait(rrow + s * W + f, abandon, a.spin_limit, &gave_up);
+        xch[s * W + f] = gang_wait(a.ws, rrow + s * W + f, abandon, a.tag, a.spin_limit, &gave_up);
       }
     }
     __syncthreads();

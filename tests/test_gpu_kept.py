@@ -1,0 +1,166 @@
+"""Gradient calls whose scratch record is kept and not cleared: its words carry a number that each launch takes anew.  Whatever
+an earlier call left in the record, the results are those of a call on a workspace of its own, bit by bit."""
+import ctypes
+
+import pytest
+import torch
+
+from gpu_util import dev
+from paper_2605_05940_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+CASES = {  # rows, vocabulary, what: records of 8 and 16 words per slice, of 2 .. 8 slices per row, a second exchange
+    "few": (24, 40960, dict()), "few_tau2": (24, 40960, dict(tau=2.0, ce_grad_scale=0.25)), "reverse": (300, 50304, dict(divergence=1)),
+    "odd": (40, 50003, dict(ce_grad_scale=0.25)), "skew": (40, 36000, dict(divergence=2, skew_alpha=0.1)),
+    "skew_tau3": (40, 36000, dict(divergence=3, skew_alpha=0.1, tau=3.0)), "topk": (24, 65536, "topk"), "long": (500, 65536, dict()),
+}
+
+
+def _inputs(name):
+    T, V, kw = CASES[name]
+    g = torch.Generator(device=dev()).manual_seed(T + V)
+    s = (3.0 * torch.randn((T, V), generator=g, device=dev())).to(torch.bfloat16)
+    t = (0.8 * s.float() + 1.5 * torch.randn((T, V), generator=g, device=dev())).to(torch.bfloat16)
+    mask = (torch.rand(T, generator=g, device=dev()) < 0.8).to(torch.uint8)
+    lab = torch.randint(0, V, (T,), generator=g, device=dev(), dtype=torch.int32)
+    if kw == "topk":
+        val, idx = torch.topk(t.float(), 24, dim=1)
+        kw = dict(teacher_idx=idx.to(torch.int32).contiguous(), teacher_val=val.contiguous())
+    else:
+        kw = dict(kw, teacher_dense=t)
+    return s, mask, dict(kw, labels=lab)
+
+
+def _out(s):
+    return (torch.full_like(s, float("nan")), torch.full((s.shape[0],), -1.0, device=dev()),
+            torch.full((s.shape[0],), -1.0, device=dev()), torch.zeros(1, dtype=torch.int32, device=dev()))
+
+
+def _call(s, mask, kw, out, workspace=None):
+    binding.npd_kd_loss_fwd_bwd(s, mask, grad_out=out[0], kd_tok=out[1], nll_tok=out[2], dev_status=out[3], workspace=workspace, **kw)
+
+
+def _same(got, want):
+    return all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, want))
+
+
+@pytest.fixture(scope="module")
+def reference():
+    """Inputs, and the results on a workspace that the call clears."""
+    all_of = {}
+    for name in CASES:
+        s, mask, kw = _inputs(name)
+        want = _out(s)
+        _call(s, mask, kw, want, torch.full((8 << 20,), 0xab, dtype=torch.uint8, device=dev()))
+        all_of[name] = s, mask, kw, want
+    torch.cuda.synchronize()
+    return all_of
+
+
+@pytest.fixture
+def fresh():
+    binding.load()
+    assert binding._host is not None
+    torch.cuda.synchronize()
+    binding._host.release()
+    yield
+    torch.cuda.synchronize()
+    binding._host.release()
+
+
+def test_calls_of_all_kinds_on_one_record(reference, fresh):
+    order = list(CASES) + list(CASES)[::-1] + ["few", "long", "few", "skew", "few_tau2", "topk"] * 3
+    for name in order:
+        s, mask, kw, want = reference[name]
+        got = _out(s)
+        print(f"[kept] {name}", flush=True)
+        _call(s, mask, kw, got)
+        torch.cuda.synchronize()
+        assert _same(got, want), name
+    base = torch.cuda.memory_allocated()
+    binding._host.release()                                # the record goes back
+    assert torch.cuda.memory_allocated() < base
+
+
+def test_streams_share_no_record(reference, fresh):
+    streams = [torch.cuda.Stream() for _ in range(11)]      # more than have a record: the others clear one of their own or wait
+    names = ["odd", "few_tau2"]                            # (calls that bring no kept workspace: any streams)
+    torch.cuda.synchronize()
+    got = []
+    for i, st in enumerate(streams):
+        with torch.cuda.stream(st):
+            for name in names:
+                s, mask, kw, _ = reference[name]
+                got.append((name, _out(s)))
+                _call(s, mask, kw, got[-1][1])
+    torch.cuda.synchronize()
+    for name, out in got:
+        assert _same(out, reference[name][3]), name
+
+
+def test_capture_takes_no_kept_record(reference, fresh):
+    s, mask, kw, want = reference["few"]
+    s2, mask2, kw2, want2 = reference["reverse"]
+    got, other = _out(s), _out(s2)
+    _call(s, mask, kw, got)                                # (the record and the kept workspace are there)
+    binding.workspace_for(1 << 20, dev())
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        _call(s, mask, kw, got)
+    for _ in range(4):
+        for x in got[:3]:
+            x.fill_(-3.0)
+        graph.replay()
+        _call(s2, mask2, kw2, other)                       # the program's own call between the replays
+        torch.cuda.synchronize()
+        assert _same(got, want) and _same(other, want2)
+
+
+def test_a_call_that_gave_up_leaves_nothing_behind(reference, fresh):
+    s, mask, kw, want = reference["reverse"]
+    lib = binding.load()
+    got = _out(s)
+    lib.npd_debug_gang_spin_limit(1)                       # (waits that end at once: the rows are marked and the kernel exits)
+    try:
+        _call(s, mask, kw, got)
+        torch.cuda.synchronize()
+    finally:
+        lib.npd_debug_gang_spin_limit(0)
+    assert int(got[3].item()) in (0, 8)
+    for name in ("reverse", "few", "reverse"):
+        s, mask, kw, want = reference[name]
+        got = _out(s)
+        _call(s, mask, kw, got)
+        torch.cuda.synchronize()
+        assert _same(got, want), name
+
+
+def test_what_the_entry_point_refuses(reference):
+    lib = binding.load()
+    s, mask, kw, want = reference["few"]
+    T, V = s.shape
+    d = binding.KdDesc(T, V, binding.NPD_TEACHER_DENSE_BF16, V, V, 0, 0, 1.0, 1.0, 0.0, 0, 0.0)
+    stream = torch.cuda.current_stream().cuda_stream
+    need = lib.npd_kept_workspace_bytes(ctypes.byref(d), stream)
+    assert need == 2 * lib.npd_workspace_bytes_preferred(ctypes.byref(d)) > 0
+    short = binding.KdDesc(T, 1024, binding.NPD_TEACHER_DENSE_BF16, V, V, 0, 0, 1.0, 1.0, 0.0, 0, 0.0)
+    none = binding.KdDesc(T, V, binding.NPD_TEACHER_DENSE_BF16, V, V, 0, 4, 1.0, 1.0, 0.0, 0, 0.0)
+    assert lib.npd_kept_workspace_bytes(ctypes.byref(short), stream) == lib.npd_kept_workspace_bytes(ctypes.byref(none), stream) == 0
+    got = _out(s)
+    ws = torch.zeros(need + 512, dtype=torch.uint8, device=dev())
+
+    def call(desc, at, size, grad):
+        return lib.npd_kd_loss_fwd_bwd_kept(ctypes.byref(desc), s.data_ptr(), kw["teacher_dense"].data_ptr(), None, None,
+                                            kw["labels"].data_ptr(), mask.data_ptr(), grad, got[1].data_ptr(), got[2].data_ptr(),
+                                            None, None, got[3].data_ptr(), at, size, stream)
+
+    assert call(d, ws.data_ptr(), need - 1, got[0].data_ptr()) == 6 and call(d, None, need, got[0].data_ptr()) == 6
+    assert call(d, ws.data_ptr() + 4, need, got[0].data_ptr()) == 6 and call(none, ws.data_ptr(), need, got[0].data_ptr()) == 6
+    assert call(d, got[0].data_ptr(), need, got[0].data_ptr()) == 4
+    torch.cuda.synchronize()
+    assert (ws == 0).all() and (got[1] == -1.0).all()       # nothing was enqueued
+    assert call(d, ws.data_ptr(), need, got[0].data_ptr()) == 0
+    torch.cuda.synchronize()
+    assert _same(got, want) and (ws[need:] == 0).all()
