@@ -154,8 +154,9 @@ size_t npd_workspace_bytes_preferred(const npd_kd_desc* desc);
 
 /*
  * Bytes of a workspace that the caller keeps from call to call for npd_kd_loss_fwd_bwd_kept on
- * `stream` (host call): 0 where that entry point does not serve the call -- no workspace is used,
- * or the stream is being captured (a replay would repeat the call's number, see there).
+ * `stream` (host call): 0 where that entry point does not serve the call -- no workspace is used
+ * (forward-only calls: rows are not split, or are more than 512), or the stream is being captured
+ * (a replay would repeat the call's number, see there).
  */
 size_t npd_kept_workspace_bytes(const npd_kd_desc* desc, void* stream);
 
@@ -223,13 +224,14 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
                                size_t workspace_bytes, void* stream);
 
 /*
- * The same call on a workspace that needs no clearing launch in front of the kernel: its words
- * carry a number that every call of this entry point takes anew.
+ * The same call on a workspace that needs no clearing launch in front of the kernel (forward-only
+ * calls: no merging launch behind it): its words carry a number that every call of this entry
+ * point takes anew.
  *   workspace        device, >= npd_kept_workspace_bytes(desc, stream) bytes (not 0), 256-byte
  *                    aligned; zero before its first use and written since then by nothing but
  *                    calls of this entry point, which must be ordered on one stream
  * Not for streams under capture.  Results are those of npd_kd_loss_fwd_bwd with the workspace
- * npd_workspace_bytes_preferred() asks for, bit by bit.
+ * npd_workspace_bytes_preferred() asks for, of npd_kd_loss_forward with its scratch, bit by bit.
  */
 npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student_logits,
                                     const void* teacher_dense, const int32_t* teacher_idx,

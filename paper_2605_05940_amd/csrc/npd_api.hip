@@ -139,6 +139,12 @@ size_t forward_scratch_bytes_of(const npd_kd_desc& d) {
   return npd::split_scratch_bytes(d.n_tokens, d.vocab, d.teacher_kind, d.divergence, d.tau != 1.0f);
 }
 
+// bytes of the record that a call keeps (npd_kd_loss_fwd_bwd_kept), 0: it does not
+size_t kept_bytes_of(const npd_kd_desc& d) {
+  if (d.flags & NPD_FLAG_FWD_ONLY) return npd::split_kept_bytes(d.n_tokens, forward_scratch_bytes_of(d));
+  return 2 * workspace_bytes_of(d, true);
+}
+
 // Every input and output buffer of a KD call as a byte range (empty for arguments that are absent).
 struct KdBuffers {
   Range in[6];   // student logits, dense teacher, top-k ids, top-k values, labels, loss mask
@@ -347,11 +353,11 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
 
 size_t npd_kept_workspace_bytes(const npd_kd_desc* desc, void* stream) {
   if (check_desc(desc) != NPD_OK) return 0;
-  const size_t want = workspace_bytes_of(*desc, true);
-  if (want == 0 || gang_launches.load(std::memory_order_relaxed) >= kLastTag) return 0;
+  const size_t bytes = kept_bytes_of(*desc);
+  if (bytes == 0 || gang_launches.load(std::memory_order_relaxed) >= kLastTag) return 0;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) != hipSuccess) return 0;
-  return capture == hipStreamCaptureStatusNone ? 2 * want : 0;
+  return capture == hipStreamCaptureStatusNone ? bytes : 0;
 }
 
 npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student_logits, const void* teacher_dense,
@@ -364,18 +370,27 @@ npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student
   const npd_status st = check_kd_call(desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask,
                                       grad_out, kd_tok, nll_tok, teacher_nll_tok, lse_tok, dev_status, &a, &need);
   if (st != NPD_OK) return st;
-  const size_t want = workspace_bytes_of(*desc, true);
-  if (want == 0 || !workspace || workspace_bytes < 2 * want || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
+  const size_t bytes = kept_bytes_of(*desc);
+  if (bytes == 0 || !workspace || workspace_bytes < bytes || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
     return NPD_ERR_WORKSPACE;
   if (kd_buffers(*desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask, grad_out, kd_tok, nll_tok,
-                 teacher_nll_tok, lse_tok, dev_status).overlaps_any(range_of(workspace, 2 * want)))
+                 teacher_nll_tok, lse_tok, dev_status).overlaps_any(range_of(workspace, bytes)))
     return NPD_ERR_ALIAS;
   const uint64_t tag = gang_launches.fetch_add(1, std::memory_order_relaxed) + 1;
   if (tag > kLastTag) return NPD_ERR_UNSUPPORTED;
   a.ws = static_cast<uint32_t*>(workspace);
   a.tag = (uint32_t)tag;
   const bool want_grad = !(desc->flags & NPD_FLAG_FWD_ONLY);
-  const hipError_t e = npd::launch_kd(a, desc->teacher_kind, want_grad, want, static_cast<hipStream_t>(stream));
+  const hipStream_t on = static_cast<hipStream_t>(stream);
+  hipError_t e;
+  if (want_grad) {
+    e = npd::launch_kd(a, desc->teacher_kind, true, bytes / 2, on);
+  } else if (a.nvec_s > 0 && npd::split_path_applies(a, desc->teacher_kind)) {
+    e = npd::launch_kd_split(a, desc->teacher_kind, on);
+  } else {
+    a.ws = nullptr;
+    e = npd::launch_kd(a, desc->teacher_kind, false, 0, on);
+  }
   return e == hipSuccess ? NPD_OK : NPD_ERR_HIP;
 }
 

@@ -231,7 +231,14 @@ PyObject* kd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!ws && !no_workspace && !g) {
       const size_t need = lib.forward_scratch_bytes(&d);
       if (need) {
+        // (first: without memory for it the call runs whole, whatever earlier calls have kept, and so gives the same bits)
         const at::Tensor own = scratch(need);
+        if (const size_t bytes = s.get_device() == current_device().index() ? lib.kept_bytes(&d, stream) : 0) {
+          const at::Tensor kept = record_of(bytes, stream);  // (held through the call)
+          if (kept.defined())
+            return call(lib.kd_kept, &d, sp, tp, ip, vp, labels, mask, nullptr, kd_tok, nll, tnll, lse, status, kept.data_ptr(),
+                        (size_t)kept.numel(), stream);
+        }
         return call(lib.kd_forward, &d, sp, tp, ip, vp, labels, mask, kd_tok, nll, tnll, lse, status, own.data_ptr(), need, stream);
       }
     }

@@ -77,6 +77,7 @@ size_t gang_workspace_preferred(int64_t T, int32_t V, int teacher_kind, int dive
 hipError_t launch_kd_gang(const KdArgs& a, int teacher_kind, size_t workspace_bytes, hipStream_t stream);
 hipError_t launch_gang_fine(const KdArgs& a, int k, int teacher_kind, hipStream_t stream);  // npd_kd_gang_fine.hip
 int set_gang_spin_limit(int polls);  // returns the previous limit; <= 0 restores the default
+int gang_spin_limit();
 
 // the row-gang kernels with a row to a workgroup, for rows that fit one (npd_kd_solo*.hip); no workspace
 bool solo_path_applies(const KdArgs& a, int teacher_kind, bool want_grad);
@@ -90,6 +91,8 @@ hipError_t launch_solo_forward_only(const KdArgs& a, hipStream_t stream);
 // may take sums at tau = 1 beside others; whether it does is known at its launch (split_path_applies)
 size_t split_scratch_bytes(int64_t T, int32_t V, int teacher_kind, int divergence, bool lse1);
 bool split_path_applies(const KdArgs& a, int teacher_kind);
+// bytes of a kept record (KdArgs::tag) for a call of that scratch; 0: not with one
+size_t split_kept_bytes(int64_t T, size_t scratch_bytes);
 hipError_t launch_kd_split(const KdArgs& a, int teacher_kind, hipStream_t stream);
 
 // compute units of the current device (cached per device)

@@ -11,6 +11,8 @@ int set_gang_spin_limit(int polls) {
   return g_spin_limit.exchange(polls > 0 ? polls : kGangSpinLimitDefault, std::memory_order_relaxed);
 }
 
+int gang_spin_limit() { return g_spin_limit.load(std::memory_order_relaxed); }
+
 constexpr int kGangK = 10;      // 128-bit groups per thread and tensor: 80 of a thread's 128 registers hold its slice
 constexpr int kGangTopkK = 10;  // top-k teacher: groups per thread of the student row alone
 constexpr int kGangSkewK = 6;   // skew forms: the slice is kept as two fp32 values per element from sweep 1 on
@@ -168,7 +170,7 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
   // peak on 32,768 x 151,936, +2.5 on 262,144 logits in place, +3.6 with a top-k teacher; a row pitch of 16 bytes more than
   // 151,936 logits: +4.
   a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;
-  a.spin_limit = g_spin_limit.load(std::memory_order_relaxed);
+  a.spin_limit = gang_spin_limit();
   if (k > 0) return launch_gang_fine(a, k, teacher_kind, stream);
   if (teacher_kind == kTopk) return launch_gang_topk<kGangTopkK>(a, stream);
   switch (a.divergence) {

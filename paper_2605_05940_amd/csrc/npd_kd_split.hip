@@ -5,7 +5,9 @@
 // Why: with a workgroup per row a row takes as long as one compute unit needs for it, which is its vector instructions
 // (17 us for the 151,936 pairs of logits of a dense teacher) behind the latency of its first loads; rows that are
 // fewer than the compute units leave the others idle, and the last rows of many leave most of them idle.  A slice is read,
-// summed once and gone; nothing waits for another workgroup.  The second launch costs about 2.5 us.
+// summed once and gone; nothing waits for another workgroup.  The second launch costs about 2.5 us: calls of few rows on a kept
+// record whose words carry the launch's number (KdArgs::tag, npd_kd_gang.hpp) have none, the last slice of a row waits for the
+// others' partials and merges them (forward progress and bounded waits as there).
 #include "npd_kd_gang.hpp"
 
 namespace npd {
@@ -22,16 +24,53 @@ constexpr int split_words(bool dense, bool lse1) { return split_sums(dense, lse1
 
 }  // namespace
 
-// K: groups per thread and tensor; a slice is a.gang_groups <= K * 256 groups long.
-template <int K, bool DENSE, bool LSE1>
+// A row's scalars from its totals (one lane).
+template <bool DENSE, bool LSE1>
+__device__ __forceinline__ void split_row_scalars(const KdArgs& a, int64_t row, int y, float s_y, float t_y,
+                                                  Lse (&acc)[split_sums(DENSE, LSE1)], bool timeout) {
+  constexpr int NS = split_sums(DENSE, LSE1);
+  const float nanv = __builtin_nanf("");
+  const float Ls = acc[0].log2_sum();
+  const float lse1_s = timeout ? nanv : __fmul_rn(LSE1 ? acc[NS == 4 ? 2 : 0].log2_sum() : Ls, kLn2);
+  float lse1_t = 0.0f;
+  if constexpr (DENSE) {
+    lse1_t = timeout ? nanv : __fmul_rn(LSE1 ? acc[NS == 4 ? 3 : 1].log2_sum() : acc[1].log2_sum(), kLn2);
+    const float lse_diff = ((acc[0].r - acc[1].r) + (acc[0].log2_z() - acc[1].log2_z())) * kLn2;  // lse_S - lse_T at tau
+    const float kd = (acc[1].a / acc[1].z) * a.inv_tau + lse_diff;
+    if (a.kd) a.kd[row] = timeout ? nanv : kd < 0.0f ? 0.0f : kd;
+  }
+  if (a.lse) a.lse[row] = lse1_s;
+  const bool bad_label = a.labels && (unsigned)y >= (unsigned)a.V;
+  if (a.nll) a.nll[row] = bad_label ? nanv : __fsub_rn(lse1_s, s_y);
+  if (a.tnll) a.tnll[row] = bad_label ? nanv : __fsub_rn(lse1_t, t_y);
+  int flags = timeout ? 8 : 0;                            // NPD_DEV_GANG_TIMEOUT
+  if (bad_label && (a.nll || a.tnll)) flags |= 1;         // NPD_DEV_BAD_LABEL
+  if (flags && a.status) atomicOr(a.status, flags);
+}
+__device__ __forceinline__ void split_row_zeros(const KdArgs& a, int64_t row) {
+  if (a.kd) a.kd[row] = 0.0f;
+  if (a.nll) a.nll[row] = 0.0f;
+  if (a.tnll) a.tnll[row] = 0.0f;
+  if (a.lse) a.lse[row] = 0.0f;
+}
+
+// K: groups per thread and tensor; a slice is a.gang_groups <= K * 256 groups long.  ONE: the only launch of the call.
+template <int K, bool DENSE, bool LSE1, bool ONE>
 __global__ __launch_bounds__(kSplitThreads, 4) void kd_split_kernel(const KdArgs a) {
   constexpr int TH = kSplitThreads, GB = TH * 16, NS = split_sums(DENSE, LSE1), W = split_words(DENSE, LSE1);
   constexpr int NWV = TH / kWave;
   __shared__ float red[NS * 3 * NWV];
+  __shared__ uint32_t xch[ONE ? kSplitMax * W : 1];
+  __shared__ int gave_up;
   const int G = a.gang;
   const int64_t row = blockIdx.x / (unsigned)G;
   const int slice = (int)(blockIdx.x - (unsigned)(row * G));
-  if (!a.mask[row]) return;  // (the second kernel writes its zeros)
+  const bool merges = ONE && slice == G - 1;  // uniform
+  if (!a.mask[row]) {  // (the second kernel writes its zeros, where there is one)
+    if (merges && threadIdx.x == 0) split_row_zeros(a, row);
+    return;
+  }
+  if (ONE && threadIdx.x == 0) gave_up = 0;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
   const int V = a.V;
   const uint16_t* srow = a.s + row * a.s_stride;
@@ -53,6 +92,15 @@ __global__ __launch_bounds__(kSplitThreads, 4) void kd_split_kernel(const KdArgs
   for (int k = 0; k < K; ++k) {
     sreg[k] = ld_group<GB>(rs, voff, k, true, true);
     if constexpr (DENSE) treg[k] = ld_group<GB>(rt, voff, k, true, true);
+  }
+  int y = -1;
+  uint32_t s_y = 0, t_y = 0;
+  if (merges && a.labels) {
+    y = a.labels[row];
+    if ((unsigned)y < (unsigned)V) {
+      s_y = srow[y];
+      if constexpr (DENSE) t_y = trow[y];
+    }
   }
   Lse acc[NS];
 #pragma unroll
@@ -150,8 +198,7 @@ __global__ __launch_bounds__(kSplitThreads, 4) void kd_split_kernel(const KdArgs
     }
   }
   __syncthreads();
-  if (wid > 0) return;
-  float* rec = reinterpret_cast<float*>(a.ws) + (size_t)blockIdx.x * W;
+  if (!merges && wid > 0) return;
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     acc[i].init();
@@ -161,11 +208,45 @@ __global__ __launch_bounds__(kSplitThreads, 4) void kd_split_kernel(const KdArgs
       acc[i].a = red[(i * 3 + 2) * NWV + lane];
     }
     wave_merge_rescaled<true, merge_lanes(NWV)>(acc[i]);
+  }
+  if constexpr (!ONE) {
     if (lane == 0) {
-      rec[i * 3 + 0] = acc[i].r;
-      rec[i * 3 + 1] = acc[i].z;
-      rec[i * 3 + 2] = acc[i].a;
+      float* rec = reinterpret_cast<float*>(a.ws) + (size_t)blockIdx.x * W;
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        rec[i * 3 + 0] = acc[i].r;
+        rec[i * 3 + 1] = acc[i].z;
+        rec[i * 3 + 2] = acc[i].a;
+      }
     }
+  } else {
+    float v = acc[0].r;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (lane == i * 3 + 0) v = acc[i].r;
+      if (lane == i * 3 + 1) v = acc[i].z;
+      if (lane == i * 3 + 2) v = acc[i].a;
+    }
+    if (!merges) {
+      if (lane < W) gang_post(a.ws, (size_t)blockIdx.x * W + lane, v, a.tag);
+      return;
+    }
+    if (wid == 0 && lane < W) xch[slice * W + lane] = __builtin_bit_cast(uint32_t, v);
+    for (int w = tid; w < slice * W; w += TH)
+      xch[w] = gang_wait(a.ws, (size_t)row * G * W + w, (size_t)gridDim.x * W, a.tag, a.spin_limit, &gave_up);
+    __syncthreads();
+    if (wid > 0) return;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      acc[i].init();
+      if (lane < G) {
+        acc[i].r = __builtin_bit_cast(float, xch[lane * W + i * 3 + 0]);
+        acc[i].z = __builtin_bit_cast(float, xch[lane * W + i * 3 + 1]);
+        acc[i].a = __builtin_bit_cast(float, xch[lane * W + i * 3 + 2]);
+      }
+      wave_merge_rescaled<true>(acc[i]);
+    }
+    if (lane == 0) split_row_scalars<DENSE, LSE1>(a, row, y, bf16_lo(s_y), bf16_lo(t_y), acc, gave_up != 0);
   }
 }
 
@@ -177,12 +258,7 @@ __global__ __launch_bounds__(kSplitThreads) void kd_split_merge_kernel(const KdA
   const int64_t row = (int64_t)blockIdx.x * (kSplitThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (row >= a.T) return;
   if (!a.mask[row]) {
-    if (lane == 0) {
-      if (a.kd) a.kd[row] = 0.0f;
-      if (a.nll) a.nll[row] = 0.0f;
-      if (a.tnll) a.tnll[row] = 0.0f;
-      if (a.lse) a.lse[row] = 0.0f;
-    }
+    if (lane == 0) split_row_zeros(a, row);
     return;
   }
   int y = -1;
@@ -207,22 +283,7 @@ __global__ __launch_bounds__(kSplitThreads) void kd_split_merge_kernel(const KdA
   }
 #pragma unroll
   for (int i = 0; i < NS; ++i) wave_merge_rescaled<true>(acc[i]);
-  if (lane != 0) return;
-  const float Ls = acc[0].log2_sum();
-  const float lse1_s = __fmul_rn(LSE1 ? acc[NS == 4 ? 2 : 0].log2_sum() : Ls, kLn2);
-  float lse1_t = 0.0f;
-  if constexpr (DENSE) {
-    lse1_t = __fmul_rn(LSE1 ? acc[NS == 4 ? 3 : 1].log2_sum() : acc[1].log2_sum(), kLn2);
-    const float lse_diff = ((acc[0].r - acc[1].r) + (acc[0].log2_z() - acc[1].log2_z())) * kLn2;  // lse_S - lse_T at tau
-    const float kd = (acc[1].a / acc[1].z) * a.inv_tau + lse_diff;
-    if (a.kd) a.kd[row] = kd < 0.0f ? 0.0f : kd;
-  }
-  if (a.lse) a.lse[row] = lse1_s;
-  const bool bad_label = a.labels && (unsigned)y >= (unsigned)a.V;
-  const float nanv = __builtin_nanf("");
-  if (a.nll) a.nll[row] = bad_label ? nanv : __fsub_rn(lse1_s, s_y);
-  if (a.tnll) a.tnll[row] = bad_label ? nanv : __fsub_rn(lse1_t, t_y);
-  if (bad_label && (a.nll || a.tnll) && a.status) atomicOr(a.status, 1);  // NPD_DEV_BAD_LABEL
+  if (lane == 0) split_row_scalars<DENSE, LSE1>(a, row, y, s_y, t_y, acc, false);
 }
 
 namespace {
@@ -259,6 +320,12 @@ int split_groups(int64_t T, int nvec, bool dense, Tau1Sums sums) {
   return nvec >= 8192 && T <= (nvec > 10240 ? 64 : 51) ? 8 : 0;
 }
 
+// Rows up to which a call on a kept record is one launch: a workgroup that waits keeps its place on a compute unit from the
+// slices behind it, and the second launch counts for less the longer the first is.  Measured (MI355X, us of the loss and the
+// monitor's reduction, dense teacher, seven tenths scored, two launches / one): 16 rows of 151,936 12.2 / 9.9, 256 25.6 / 24.1,
+// 64 of 50,304 12.1 / 9.8, 400 of 100,352 27.6 / 26.2;  700 of 151,936 51.6 / 52.1, 5,000 305 / 311, of 50,304 112 / 121.
+constexpr int64_t kSplitOneLaunchRows = 512;
+
 // slices of a row of nvec groups, 0: not split
 int split_slices(int64_t T, int nvec, bool dense, Tau1Sums sums) {
   const int cap = split_groups(T, nvec, dense, sums) * kSplitThreads;
@@ -269,8 +336,9 @@ int split_slices(int64_t T, int nvec, bool dense, Tau1Sums sums) {
 
 template <int K, bool DENSE, bool LSE1>
 hipError_t launch_split(const KdArgs& a, hipStream_t stream) {
-  const hipError_t e =
-      launch_kernel(kd_split_kernel<K, DENSE, LSE1>, dim3((unsigned)(a.T * a.gang)), dim3(kSplitThreads), 0, stream, a);
+  const dim3 grid((unsigned)(a.T * a.gang));
+  if (a.tag != 0) return launch_kernel(kd_split_kernel<K, DENSE, LSE1, true>, grid, dim3(kSplitThreads), 0, stream, a);
+  const hipError_t e = launch_kernel(kd_split_kernel<K, DENSE, LSE1, false>, grid, dim3(kSplitThreads), 0, stream, a);
   if (e != hipSuccess) return e;
   constexpr int rows = kSplitThreads / kWave;
   return launch_kernel(kd_split_merge_kernel<DENSE, LSE1>, dim3((unsigned)((a.T + rows - 1) / rows)), dim3(kSplitThreads), 0,
@@ -286,6 +354,10 @@ size_t split_scratch_bytes(int64_t T, int32_t V, int teacher_kind, int divergenc
   return (size_t)T * g * split_words(dense, dense && lse1) * sizeof(float);
 }
 
+size_t split_kept_bytes(int64_t T, size_t scratch_bytes) {
+  return T <= kSplitOneLaunchRows && scratch_bytes > 0 ? 2 * (scratch_bytes + kGangTailWords * sizeof(uint32_t)) : 0;
+}
+
 static Tau1Sums tau1_sums(const KdArgs& a, bool dense) {
   return !dense || !a.need_lse1 ? kNoSums : a.tnll ? kBothSums : kStudentSum;
 }
@@ -299,6 +371,7 @@ hipError_t launch_kd_split(const KdArgs& a0, int teacher_kind, hipStream_t strea
   const bool dense = teacher_kind == kDense;
   a.gang = split_slices(a.T, a.nvec_s, dense, tau1_sums(a, dense));
   a.gang_groups = ((a.nvec_s + a.gang - 1) / a.gang + 7) / 8 * 8;
+  a.spin_limit = gang_spin_limit();
   if (!dense) return launch_split<8, false, false>(a, stream);
   if (split_groups(a.T, a.nvec_s, true, tau1_sums(a, true)) == 4)
     return a.need_lse1 ? launch_split<4, true, true>(a, stream) : launch_split<4, true, false>(a, stream);

@@ -63,10 +63,11 @@ def fresh():
     binding.load()
     assert binding._host is not None
     torch.cuda.synchronize()
-    binding._host.release()
+    host = binding._host
+    host.release()
     yield
     torch.cuda.synchronize()
-    binding._host.release()
+    host.release()
 
 
 def test_calls_of_all_kinds_on_one_record(reference, fresh):
@@ -164,3 +165,35 @@ def test_what_the_entry_point_refuses(reference):
     assert call(d, ws.data_ptr(), need, got[0].data_ptr()) == 0
     torch.cuda.synchronize()
     assert _same(got, want) and (ws[need:] == 0).all()
+
+
+@pytest.mark.parametrize("T,V,pitch,what", [
+    (1, 50304, 50304, "tau1"), (24, 65536, 65536, "tau2"), (40, 50003, 50003, "tau1"), (60, 151936, 151936, "none"), (130, 131080, 131088, "tau2"),
+    (512, 100352, 100352, "tau1"), (513, 100352, 100352, "tau1"), (3, 524288, 524288, "tau1"),
+])
+def test_forward_only_in_one_launch(T, V, pitch, what, fresh, monkeypatch):
+    g = torch.Generator(device=dev()).manual_seed(T + V)
+    s, t = ((3.0 * torch.randn((T, pitch), generator=g, device=dev())).to(torch.bfloat16)[:, :V] for _ in range(2))
+    if T > 2:
+        s[1, V // 3] = 300.0                               # waves that sum once more in the careful form
+        t[2, 5:900] = float("-inf")
+    mask = (torch.rand(T, generator=g, device=dev()) < 0.8).to(torch.uint8)
+    mask[0] = 1
+    lab = torch.randint(5000, V, (T,), generator=g, device=dev(), dtype=torch.int32)
+    if T > 4:
+        lab[4], mask[4] = V, 1                             # a label out of range
+    results = []
+    for native in (True, True, False):
+        if not native:
+            monkeypatch.setattr(binding, "_host", None)
+        out = [torch.full((T,), -1.0, device=dev()) for _ in range(4)]
+        status = torch.zeros(1, dtype=torch.int32, device=dev())
+        kw = dict(labels=lab, nll_tok=out[0], lse_tok=out[1], dev_status=status)
+        if what != "none":
+            kw.update(teacher_dense=t, kd_tok=out[2], teacher_nll_tok=out[3], tau=2.0 if what == "tau2" else 1.0)
+        print(f"[kept] forward only T={T} V={V} {what} native={native}", flush=True)
+        binding.npd_kd_loss_fwd_bwd(s, mask, **kw)
+        torch.cuda.synchronize()
+        results.append(out + [status])
+    assert _same(results[0], results[2]) and _same(results[1], results[2])
+    assert int(results[0][4].item()) == (1 if T > 4 else 0)
