@@ -187,7 +187,9 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
     a uint8 tensor of at least ``npd_workspace_bytes`` bytes, better of ``npd_workspace_bytes_preferred``; if it is None one
     is taken from ``workspace_for`` (a per-device tensor that this module keeps and grows) or, with a CE term at tau != 1, for
     rows that are not 16-byte aligned and for calls that prefer more than is kept, allocated for the call.  Forward-only calls
-    allocate a block of their own where splitting rows pays, and run without it where there is no memory for it.  Blocks of a
+    allocate a block of their own where splitting rows pays, and run without it where there is no memory for it.  With the
+    native marshalling, calls outside captures run on a record that it keeps per device and stream instead, with the same results
+    (``npd_kd_loss_fwd_bwd_kept``; eight of 32 MB at most, given back by ``_host.release()``).  Blocks of a
     call go back to torch's allocator when it returns, so a capture that is not ``torch.cuda.graph``'s should set
     ``no_workspace`` (``NPD_FLAG_NO_WORKSPACE``: no scratch memory at all) or bring a workspace.  ``noalloc`` calls
     ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in scratch array; no workspace argument).
