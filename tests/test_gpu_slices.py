@@ -191,3 +191,49 @@ def test_pieces_dealt_to_the_slices(oracle, V, pitch, T, what):
                    folded=True)
         out[in_place] = grad.contiguous().view(torch.int16).clone()
     assert torch.equal(out[False], out[True])
+
+
+@pytest.mark.parametrize("V,pitch,T,what", [
+    (30624, 30624, 8192, "forward"), (30631, 30632, 8191, "forward"), (50003, 50003, 5462, "forward"), (56007, 56007, 5462, "forward"),
+    (56008, 56064, 5462, "forward"), (26000, 26000, 5470, "skew"), (45000, 45000, 5470, "topk"), (45003, 45003, 5470, "topk"),
+])
+def test_zeros_around_a_few_scored_rows(oracle, V, pitch, T, what):
+    """Many rows that are not scored around a few that are: every group and edge of theirs is zeroed, and nothing else."""
+    g = torch.Generator(device=dev()).manual_seed(V + T)
+    s, t = (torch.zeros((T, pitch), dtype=torch.bfloat16, device=dev())[:, :V] for _ in range(2))
+    grad = torch.full((T, pitch), float("nan"), dtype=torch.bfloat16, device=dev())[:, :V]
+    rows = [0, 1, T // 2, T - 2]
+    x = 3.0 * torch.randn((len(rows), V), generator=g, device=dev())
+    s[rows] = x.to(torch.bfloat16)
+    t[rows] = (0.8 * x + 1.5 * torch.randn(x.shape, generator=g, device=dev())).to(torch.bfloat16)
+    mask = torch.zeros(T, dtype=torch.uint8, device=dev())
+    mask[rows] = 1
+    kw = {}
+    ones = np.ones(len(rows), np.uint8)
+    lab = np.zeros(len(rows), np.int32)
+    sb, tb = synth.bf16_bits(s[rows].contiguous()), synth.bf16_bits(t[rows].contiguous())
+    if what == "topk":
+        idx = torch.arange(9, dtype=torch.int32, device=dev()).repeat(T, 1)
+        val = torch.zeros((T, 9), device=dev())
+        val[rows], i = torch.topk(t[rows].float(), 9, dim=1)
+        idx[rows] = i.to(torch.int32)
+        kw.update(teacher_idx=idx, teacher_val=val)
+        ref = oracle.kd_topk(sb, idx[rows].cpu().numpy(), val[rows].cpu().numpy(), lab, ones, tau=1.0, grad_scale=0.75)
+    else:
+        kw.update(teacher_dense=t)
+        if what == "skew":
+            kw.update(divergence=2, skew_alpha=0.1)
+            ref = oracle.div_dense(sb, tb, "skew", 0.1, labels=lab, mask=ones, tau=1.0, grad_scale=0.75)
+        else:
+            ref = oracle.kd_dense(sb, tb, lab, ones, tau=1.0, grad_scale=0.75)
+    kd = torch.full((T,), -1.0, device=dev())
+    print(f"[zeros] V={V} pitch={pitch} T={T} {what}", flush=True)
+    binding.npd_kd_loss_fwd_bwd(s, mask, grad_scale=0.75, grad_out=grad, kd_tok=kd, **kw)
+    torch.cuda.synchronize()
+    off = mask == 0
+    assert all((grad[i:i + 512][off[i:i + 512]].view(torch.int16) == 0).all() for i in range(0, T, 512)) and (kd[off] == 0).all()
+    if pitch > V:                                          # the padding between rows is nobody's
+        whole = grad.as_strided((T - 1, pitch - V), (pitch, 1), V)
+        assert torch.isnan(whole.float()).all()
+    got = dict(kd=kd[rows].cpu().numpy().astype(np.float64), grad=grad[rows].float().cpu().numpy().astype(np.float64))
+    compare_kd(got, ref, ones, None, oracle, grad_scale=0.75, amp_from_ref=what == "skew")
