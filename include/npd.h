@@ -230,8 +230,9 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
  *   workspace        device, >= npd_kept_workspace_bytes(desc, stream) bytes (not 0), 256-byte
  *                    aligned; zero before its first use and written since then by nothing but
  *                    calls of this entry point, which must be ordered on one stream
- * Not for streams under capture.  Results are those of npd_kd_loss_fwd_bwd with the workspace
- * npd_workspace_bytes_preferred() asks for, of npd_kd_loss_forward with its scratch, bit by bit.
+ * A stream under capture is NPD_ERR_UNSUPPORTED, with nothing enqueued.  Results are those of
+ * npd_kd_loss_fwd_bwd with the workspace npd_workspace_bytes_preferred() asks for, of
+ * npd_kd_loss_forward with its scratch, bit by bit.
  */
 npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student_logits,
                                     const void* teacher_dense, const int32_t* teacher_idx,

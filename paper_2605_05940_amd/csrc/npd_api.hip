@@ -145,6 +145,13 @@ size_t kept_bytes_of(const npd_kd_desc& d) {
   return 2 * workspace_bytes_of(d, true);
 }
 
+// What is enqueued on the stream runs once: it is not being captured (a replay would repeat the numbers of its launches and take
+// the words of the replay before for its own).
+bool runs_once(void* stream) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+}
+
 // Every input and output buffer of a KD call as a byte range (empty for arguments that are absent).
 struct KdBuffers {
   Range in[6];   // student logits, dense teacher, top-k ids, top-k values, labels, loss mask
@@ -355,9 +362,7 @@ size_t npd_kept_workspace_bytes(const npd_kd_desc* desc, void* stream) {
   if (check_desc(desc) != NPD_OK) return 0;
   const size_t bytes = kept_bytes_of(*desc);
   if (bytes == 0 || gang_launches.load(std::memory_order_relaxed) >= kLastTag) return 0;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) != hipSuccess) return 0;
-  return capture == hipStreamCaptureStatusNone ? bytes : 0;
+  return runs_once(stream) ? bytes : 0;
 }
 
 npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student_logits, const void* teacher_dense,
@@ -376,6 +381,7 @@ npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student
   if (kd_buffers(*desc, student_logits, teacher_dense, teacher_idx, teacher_val, labels, loss_mask, grad_out, kd_tok, nll_tok,
                  teacher_nll_tok, lse_tok, dev_status).overlaps_any(range_of(workspace, bytes)))
     return NPD_ERR_ALIAS;
+  if (!runs_once(stream)) return NPD_ERR_UNSUPPORTED;
   const uint64_t tag = gang_launches.fetch_add(1, std::memory_order_relaxed) + 1;
   if (tag > kLastTag) return NPD_ERR_UNSUPPORTED;
   a.ws = static_cast<uint32_t*>(workspace);

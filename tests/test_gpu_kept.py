@@ -167,6 +167,40 @@ def test_what_the_entry_point_refuses(reference):
     assert _same(got, want) and (ws[need:] == 0).all()
 
 
+@pytest.mark.parametrize("flags", [0, binding.NPD_FLAG_FWD_ONLY])
+def test_the_entry_point_refuses_a_stream_under_capture(reference, flags):
+    """A replay would repeat the number of the call.  Nothing is enqueued: what the capture holds besides replays as it should."""
+    lib = binding.load()
+    s, mask, kw, _ = reference["topk"]                     # (its rows; the teacher: the student)
+    T, V = s.shape
+    side = torch.cuda.Stream()
+    d = binding.KdDesc(T, V, binding.NPD_TEACHER_DENSE_BF16, V, V, 0, flags, 1.0, 1.0, 0.0, 0, 0.0)
+    need = lib.npd_kept_workspace_bytes(ctypes.byref(d), side.cuda_stream)
+    assert need > 0
+    ws = torch.zeros(need, dtype=torch.uint8, device=dev())
+    got = _out(s)
+    count = torch.zeros(1, device=dev())
+    args = (ctypes.byref(d), s.data_ptr(), s.data_ptr(), None, None, kw["labels"].data_ptr(), mask.data_ptr(),
+            None if flags else got[0].data_ptr(), got[1].data_ptr(), got[2].data_ptr(), None, None, got[3].data_ptr(),
+            ws.data_ptr(), need, side.cuda_stream)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        count.add_(1.0)
+        asked = lib.npd_kept_workspace_bytes(ctypes.byref(d), side.cuda_stream)
+        status = lib.npd_kd_loss_fwd_bwd_kept(*args)
+        count.add_(1.0)
+    assert (asked, status) == (0, 5)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+    assert count.item() == 6.0 and (ws == 0).all() and (got[1] == -1.0).all() and (got[2] == -1.0).all()
+    with torch.cuda.stream(side):
+        assert lib.npd_kd_loss_fwd_bwd_kept(*args) == 0    # the same call beside a capture
+    torch.cuda.synchronize()
+    assert (got[1] != -1.0).all()
+
+
 @pytest.mark.parametrize("T,V,pitch,what", [
     (1, 50304, 50304, "tau1"), (24, 65536, 65536, "tau2"), (40, 50003, 50003, "tau1"), (60, 151936, 151936, "none"), (130, 131080, 131088, "tau2"),
     (512, 100352, 100352, "tau1"), (513, 100352, 100352, "tau1"), (3, 524288, 524288, "tau1"),
