@@ -112,7 +112,7 @@ at::Tensor scratch(size_t bytes) {
 
 // Records of the calls that clear none (npd_kd_loss_fwd_bwd_kept): one per device and stream, so that calls on different
 // streams share none and a record goes back to the pool of the stream that it was used on.  Written under the interpreter
-// lock.  At most kRecords of at most kRecordBytes; other calls clear a record as before.
+// lock.  At most kRecords of at most kRecordBytes; other calls clear a block of their own.
 struct Record {
   c10::DeviceIndex device;
   void* stream;
@@ -243,16 +243,17 @@ PyObject* kd(PyObject*, PyObject* const* a, Py_ssize_t n) {
       }
     }
     const size_t need = !ws && !no_workspace && g ? lib.workspace_bytes(&d) : 0;
-    if (need) {  // as binding._workspace
+    if (need) {
+      const size_t want = lib.workspace_bytes_preferred(&d);
+      at::Tensor w;  // (held through the call)
       if (const size_t bytes = s.get_device() == current_device().index() ? lib.kept_bytes(&d, stream) : 0) {
         const at::Tensor kept = record_of(bytes, stream);  // (held through the call)
         if (kept.defined())
           return call(lib.kd_kept, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, kept.data_ptr(),
                       (size_t)kept.numel(), stream);
-      }
-      const size_t want = lib.workspace_bytes_preferred(&d);
-      at::Tensor w;  // (held through the call)
-      if (!((ce != 0.0 && tau != 1.0) || (((uintptr_t)sp | (uintptr_t)(2 * d.student_stride)) & 15) != 0)) {
+        w = scratch(want);  // (calls on other streams, and graphs that are replayed, may use the buffer below meanwhile)
+      } else if (!((ce != 0.0 && tau != 1.0) || (((uintptr_t)sp | (uintptr_t)(2 * d.student_stride)) & 15) != 0)) {
+        // as binding._workspace
         PyObject* key = PyLong_FromLong(s.get_device());
         PyObject* kept = key ? PyDict_GetItemWithError(workspaces, key) : nullptr;  // borrowed
         Py_XDECREF(key);

@@ -85,8 +85,8 @@ def test_calls_of_all_kinds_on_one_record(reference, fresh):
 
 
 def test_streams_share_no_record(reference, fresh):
-    streams = [torch.cuda.Stream() for _ in range(11)]      # more than have a record: the others clear one of their own or wait
-    names = ["odd", "few_tau2"]                            # (calls that bring no kept workspace: any streams)
+    streams = [torch.cuda.Stream() for _ in range(11)]      # more than have a record: the others clear one of their own
+    names = ["odd", "few_tau2", "reverse", "few", "topk", "skew"]
     torch.cuda.synchronize()
     got = []
     for i, st in enumerate(streams):
@@ -98,6 +98,52 @@ def test_streams_share_no_record(reference, fresh):
     torch.cuda.synchronize()
     for name, out in got:
         assert _same(out, reference[name][3]), name
+
+
+class _Watched:
+    """The native marshalling with entry points that note the scratch they are given (`seen`: entry point, address, bytes,
+    stream) and launch nothing."""
+
+    def __init__(self, lib, host):
+        kd = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * 14, ctypes.c_size_t, ctypes.c_void_p)
+        self.seen = []
+        self.calls = tuple(kd(lambda *a, name=name: self.seen.append((name, a[13], a[14], a[15])) or 0)
+                           for name in ("cleared", "kept"))
+        real = (lib.npd_workspace_bytes, lib.npd_workspace_bytes_preferred, lib.npd_forward_scratch_bytes, lib.npd_kd_loss_fwd_bwd,
+                lib.npd_kd_loss_forward, lib.npd_segment_reduce, lib.npd_delta_ifd_score, lib.npd_teacher_topk, lib.npd_policy_lag,
+                lib.npd_kept_workspace_bytes, lib.npd_kd_loss_fwd_bwd_kept)
+        self.host = host
+        self.real = tuple(ctypes.cast(f, ctypes.c_void_p).value for f in real)
+
+    def __enter__(self):
+        to = list(self.real)
+        to[3], to[10] = (ctypes.cast(f, ctypes.c_void_p).value for f in self.calls)
+        self.host.bind(binding._raw_stream, binding._workspaces, tuple(to))
+        return self
+
+    def __exit__(self, *_):
+        self.host.bind(binding._raw_stream, binding._workspaces, self.real)
+
+
+def test_no_stream_uses_the_scratch_of_another(fresh):
+    """Calls that once took the buffer kept per device too: with a record, with none to be had (more bytes than one may have),
+    beside a graph that holds that buffer."""
+    streams = [torch.cuda.Stream() for _ in range(11)]
+    buffer = binding.workspace_for(64 << 20, dev())
+    s = torch.empty((24, 40960), dtype=torch.bfloat16, device=dev())
+    wide = torch.empty((140000, 32000), dtype=torch.bfloat16, device=dev())   # 2 x 140,000 slices of 16 words of 64 bits: 36 MB
+    with _Watched(binding.load(), binding._host) as w:
+        for x, kw in ((s, dict()), (s, dict(divergence=1)), (wide, dict(tau=2.0))):
+            mask, out = torch.ones(x.shape[0], dtype=torch.uint8, device=dev()), torch.empty(x.shape[0], device=dev())
+            del w.seen[:]
+            for st in streams:
+                with torch.cuda.stream(st):
+                    binding.npd_kd_loss_fwd_bwd(x, mask, teacher_dense=x, grad_out=x, kd_tok=out, **kw)
+            assert [st.cuda_stream for st in streams] == [call[3] for call in w.seen]
+            ranges = sorted((at, at + n) for _, at, n, _ in w.seen) + [(1 << 63, 0)]
+            assert all(a[1] <= b[0] for a, b in zip(ranges, ranges[1:])), [call[0] for call in w.seen]
+            assert all(e <= buffer.data_ptr() or b >= buffer.data_ptr() + buffer.numel() for b, e in ranges[:-1])
+        assert {call[0] for call in w.seen} == {"cleared"}
 
 
 def test_capture_takes_no_kept_record(reference, fresh):
