@@ -12,6 +12,7 @@
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <ATen/ops/zeros.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/VirtualGuardImpl.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -104,11 +105,18 @@ void* current_stream() {
   return s;
 }
 
-// scratch of one call: from torch's stream-ordered allocator, reused only behind the call on its stream (no memory: its
-// exception leaves the call to the Python code, which knows what runs without)
-at::Tensor scratch(size_t bytes) {
-  return at::empty({(int64_t)bytes}, at::TensorOptions().dtype(at::kByte).device(current_device()));
+// Memory for the kernels, whatever mode the caller has on: a tensor made under one may be a fake or a wrapped one without memory,
+// and code of the mode would run here.  (No memory: its exception.)
+at::Tensor memory(size_t bytes, bool zero) {
+  const c10::impl::ForceDispatchKeyGuard plain(c10::DispatchKeySet(c10::DispatchKey::BackendSelect),
+                                               c10::default_excluded_set | c10::autograd_dispatch_keyset_with_ADInplaceOrView);
+  const auto options = at::TensorOptions().dtype(at::kByte).device(current_device());
+  return zero ? at::zeros({(int64_t)bytes}, options) : at::empty({(int64_t)bytes}, options);
 }
+
+// scratch of one call: from torch's stream-ordered allocator, reused only behind the call on its stream (no memory: the
+// exception leaves the call to the Python code, which knows what runs without)
+at::Tensor scratch(size_t bytes) { return memory(bytes, false); }
 
 // Records of the calls that clear none (npd_kd_loss_fwd_bwd_kept): one per device and stream, so that calls on different
 // streams share none and a record goes back to the pool of the stream that it was used on.  Written under the interpreter
@@ -123,25 +131,27 @@ std::vector<Record>& records() {
   static auto* all = new std::vector<Record>;  // (not destroyed behind the runtime's own end)
   return *all;
 }
+Record* find_record(c10::DeviceIndex device, void* stream) {
+  for (Record& x : records())
+    if (x.device == device && x.stream == stream) return &x;
+  return nullptr;
+}
 // undefined: none to be had
 at::Tensor record_of(size_t bytes, void* stream) {
-  const c10::Device device = current_device();
-  Record* r = nullptr;
-  for (Record& x : records())
-    if (x.device == device.index() && x.stream == stream) r = &x;
-  if (r && (size_t)r->bytes.numel() >= bytes) return r->bytes;
-  if (bytes > kRecordBytes || (!r && records().size() >= kRecords)) return at::Tensor();
-  const int64_t n = (int64_t)(bytes > kRecordLeast ? bytes : kRecordLeast);
+  const c10::DeviceIndex device = current_device().index();
+  const Record* have = find_record(device, stream);
+  if (have && (size_t)have->bytes.numel() >= bytes) return have->bytes;
+  if (bytes > kRecordBytes || (!have && records().size() >= kRecords)) return at::Tensor();
   at::Tensor t;
   try {
-    t = at::zeros({n}, at::TensorOptions().dtype(at::kByte).device(device));
+    t = memory(bytes > kRecordLeast ? bytes : kRecordLeast, true);
   } catch (const std::exception&) {  // no memory: the call as before
     return at::Tensor();
   }
-  if (r)
+  if (Record* r = find_record(device, stream))  // (looked up anew: an observer of the allocator may have let another thread run)
     r->bytes = t;
   else
-    records().push_back(Record{device.index(), stream, t});
+    records().push_back(Record{device, stream, t});
   return t;
 }
 PyObject* release(PyObject*, PyObject*) {

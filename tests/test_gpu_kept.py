@@ -100,6 +100,54 @@ def test_streams_share_no_record(reference, fresh):
         assert _same(out, reference[name][3]), name
 
 
+def _under_fake_tensors(f):
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    with FakeTensorMode(allow_non_fake_inputs=True):
+        f()
+
+
+def _under_grad(f):
+    def g(x):
+        f()
+        return x.sum()
+    torch.func.grad(g)(torch.ones(3, device=dev()))
+
+
+def _under_vmap(f):
+    def g(x):
+        f()
+        return x + 1.0
+    torch.func.vmap(g)(torch.ones(3, device=dev()))
+
+
+@pytest.mark.parametrize("under", [_under_fake_tensors, _under_grad, _under_vmap])
+def test_scratch_is_memory_whatever_mode_is_on(reference, fresh, monkeypatch, under):
+    """Tensors made under such a mode have none; a record made there would stand in the way of all later calls."""
+    s, mask, kw, want = reference["few"]
+    x = torch.randn((513, 100352), generator=torch.Generator(device=dev()).manual_seed(3), device=dev()).to(torch.bfloat16)
+    ones, status = torch.ones(513, dtype=torch.uint8, device=dev()), []
+    first, second = (torch.full((513,), -1.0, device=dev()) for _ in range(2))
+    host = binding._host
+
+    class Watched:
+        @staticmethod
+        def kd(*a):
+            status.append(host.kd(*a))
+            return status[-1]
+
+    monkeypatch.setattr(binding, "_host", Watched)
+    got = _out(s)
+    under(lambda: _call(s, mask, kw, got))
+    under(lambda: binding.npd_kd_loss_fwd_bwd(x, ones, lse_tok=first))     # (two launches, a block of its own)
+    torch.cuda.synchronize()
+    assert _same(got, want)
+    got = _out(s)
+    _call(s, mask, kw, got)
+    binding.npd_kd_loss_fwd_bwd(x, ones, lse_tok=second)
+    torch.cuda.synchronize()
+    assert _same(got, want) and _same([first], [second]) and status == [0] * 4
+
+
 class _Watched:
     """The native marshalling with entry points that note the scratch they are given (`seen`: entry point, address, bytes,
     stream) and launch nothing."""
