@@ -16,6 +16,7 @@
 #include <c10/core/impl/VirtualGuardImpl.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "../../include/npd.h"
@@ -120,7 +121,9 @@ at::Tensor scratch(size_t bytes) { return memory(bytes, false); }
 
 // Records of the calls that clear none (npd_kd_loss_fwd_bwd_kept): one per device and stream, so that calls on different
 // streams share none and a record goes back to the pool of the stream that it was used on.  Written under the interpreter
-// lock.  At most kRecords of at most kRecordBytes; other calls clear a block of their own.
+// lock, the one used last at the end.  At most kRecords of at most kRecordBytes: a call on another stream takes the place of the
+// one that has been idle longest (a new record costs a launch that zeroes it, as much as clearing one for the call); calls that
+// need more clear a block of their own.
 struct Record {
   c10::DeviceIndex device;
   void* stream;
@@ -131,9 +134,14 @@ std::vector<Record>& records() {
   static auto* all = new std::vector<Record>;  // (not destroyed behind the runtime's own end)
   return *all;
 }
+// the record of a stream, moved to the end; nullptr: it has none
 Record* find_record(c10::DeviceIndex device, void* stream) {
-  for (Record& x : records())
-    if (x.device == device && x.stream == stream) return &x;
+  auto& all = records();
+  for (auto x = all.begin(); x != all.end(); ++x) {
+    if (x->device != device || x->stream != stream) continue;
+    std::rotate(x, x + 1, all.end());
+    return &all.back();
+  }
   return nullptr;
 }
 // undefined: none to be had
@@ -141,17 +149,20 @@ at::Tensor record_of(size_t bytes, void* stream) {
   const c10::DeviceIndex device = current_device().index();
   const Record* have = find_record(device, stream);
   if (have && (size_t)have->bytes.numel() >= bytes) return have->bytes;
-  if (bytes > kRecordBytes || (!have && records().size() >= kRecords)) return at::Tensor();
+  if (bytes > kRecordBytes) return at::Tensor();
   at::Tensor t;
   try {
     t = memory(bytes > kRecordLeast ? bytes : kRecordLeast, true);
   } catch (const std::exception&) {  // no memory: the call as before
     return at::Tensor();
   }
-  if (Record* r = find_record(device, stream))  // (looked up anew: an observer of the allocator may have let another thread run)
+  auto& all = records();
+  if (Record* r = find_record(device, stream)) {  // (looked up anew: an observer of the allocator may have let another thread run)
     r->bytes = t;
-  else
-    records().push_back(Record{device, stream, t});
+  } else {
+    if (all.size() >= kRecords) all.erase(all.begin());
+    all.push_back(Record{device, stream, t});
+  }
   return t;
 }
 PyObject* release(PyObject*, PyObject*) {

@@ -85,7 +85,7 @@ def test_calls_of_all_kinds_on_one_record(reference, fresh):
 
 
 def test_streams_share_no_record(reference, fresh):
-    streams = [torch.cuda.Stream() for _ in range(11)]      # more than have a record: the others clear one of their own
+    streams = [torch.cuda.Stream() for _ in range(11)]      # more than have a record at a time
     names = ["odd", "few_tau2", "reverse", "few", "topk", "skew"]
     torch.cuda.synchronize()
     got = []
@@ -192,6 +192,30 @@ def test_no_stream_uses_the_scratch_of_another(fresh):
             assert all(a[1] <= b[0] for a, b in zip(ranges, ranges[1:])), [call[0] for call in w.seen]
             assert all(e <= buffer.data_ptr() or b >= buffer.data_ptr() + buffer.numel() for b, e in ranges[:-1])
         assert {call[0] for call in w.seen} == {"cleared"}
+
+
+def test_streams_that_come_later_have_a_record_too(fresh):
+    """Of the stream that has been idle longest; no more than eight are held."""
+    s = torch.empty((24, 40960), dtype=torch.bfloat16, device=dev())
+    mask, out = torch.ones(24, dtype=torch.uint8, device=dev()), torch.empty(24, device=dev())
+    streams = [torch.cuda.Stream() for _ in range(20)]
+    base = torch.cuda.memory_allocated()
+    with _Watched(binding.load(), binding._host) as w:
+        def call(st):
+            with torch.cuda.stream(st):
+                binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=s, grad_out=s, kd_tok=out)
+            return w.seen[-1][:2]
+
+        at = {st: call(st) for st in streams[:8]}
+        assert call(streams[0]) == at[streams[0]]           # (used: the second is the one that is idle longest)
+        for st in streams[8:]:
+            assert call(st)[0] == "kept"
+            assert call(streams[0]) == at[streams[0]]
+        assert {name for name, _ in at.values()} == {"kept"}
+        held = torch.cuda.memory_allocated() - base
+        assert held == 8 << 18                              # (the least that a record has)
+    binding._host.release()
+    assert torch.cuda.memory_allocated() == base
 
 
 def test_capture_takes_no_kept_record(reference, fresh):
