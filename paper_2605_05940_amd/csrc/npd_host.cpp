@@ -129,7 +129,8 @@ struct Record {
   void* stream;
   at::Tensor bytes;
 };
-constexpr size_t kRecords = 8, kRecordBytes = 32u << 20, kRecordLeast = 1u << 18;
+constexpr size_t kRecords = 8, kRecordTail = 512, kRecordLeast = 1u << 18;  // (the tail: 64 words behind those of the slices)
+constexpr size_t kRecordBytes = (32u << 20) + kRecordTail;
 std::vector<Record>& records() {
   static auto* all = new std::vector<Record>;  // (not destroyed behind the runtime's own end)
   return *all;

@@ -218,6 +218,16 @@ def test_streams_that_come_later_have_a_record_too(fresh):
     assert torch.cuda.memory_allocated() == base
 
 
+def test_sizes_of_records(fresh):
+    """The longest is of 2^22 words, and the 64 behind them do not count."""
+    x = torch.empty((131073, 32000), dtype=torch.bfloat16, device=dev())
+    mask, out = torch.ones(131073, dtype=torch.uint8, device=dev()), torch.empty(131073, device=dev())
+    with _Watched(binding.load(), binding._host) as w:
+        for T in (131072, 131073):                          # two slices of 16 words each
+            binding.npd_kd_loss_fwd_bwd(x[:T], mask[:T], teacher_dense=x[:T], grad_out=x[:T], kd_tok=out[:T], tau=2.0)
+        assert [name for name, *_ in w.seen] == ["kept", "cleared"]
+
+
 def test_capture_takes_no_kept_record(reference, fresh):
     s, mask, kw, want = reference["few"]
     s2, mask2, kw2, want2 = reference["reverse"]
