@@ -129,8 +129,15 @@ struct Record {
   void* stream;
   at::Tensor bytes;
 };
-constexpr size_t kRecords = 8, kRecordTail = 512, kRecordLeast = 1u << 18;  // (the tail: 64 words behind those of the slices)
-constexpr size_t kRecordBytes = (32u << 20) + kRecordTail;
+constexpr size_t kRecords = 8, kRecordTail = 512;  // (bytes behind the slices' words: 64 words)
+constexpr size_t kRecordBytes = (32u << 20) + kRecordTail, kRecordLeast = (1u << 18) + kRecordTail;
+// bytes of a record for a call that needs `bytes`: a power of two of words, so that batches that get longer by little do not make
+// a new one each
+size_t record_bytes(size_t bytes) {
+  size_t n = kRecordLeast;
+  while (n < bytes) n = 2 * (n - kRecordTail) + kRecordTail;
+  return n;
+}
 std::vector<Record>& records() {
   static auto* all = new std::vector<Record>;  // (not destroyed behind the runtime's own end)
   return *all;
@@ -153,7 +160,7 @@ at::Tensor record_of(size_t bytes, void* stream) {
   if (bytes > kRecordBytes) return at::Tensor();
   at::Tensor t;
   try {
-    t = memory(bytes > kRecordLeast ? bytes : kRecordLeast, true);
+    t = memory(record_bytes(bytes), true);
   } catch (const std::exception&) {  // no memory: the call as before
     return at::Tensor();
   }

@@ -213,19 +213,21 @@ def test_streams_that_come_later_have_a_record_too(fresh):
             assert call(streams[0]) == at[streams[0]]
         assert {name for name, _ in at.values()} == {"kept"}
         held = torch.cuda.memory_allocated() - base
-        assert held == 8 << 18                              # (the least that a record has)
+        assert held == 8 * ((1 << 18) + 512)                # (the least that a record has)
     binding._host.release()
     assert torch.cuda.memory_allocated() == base
 
 
 def test_sizes_of_records(fresh):
-    """The longest is of 2^22 words, and the 64 behind them do not count."""
+    """Batches that get longer by little share one; the longest is of 2^22 words, and the 64 behind them do not count."""
     x = torch.empty((131073, 32000), dtype=torch.bfloat16, device=dev())
     mask, out = torch.ones(131073, dtype=torch.uint8, device=dev()), torch.empty(131073, device=dev())
     with _Watched(binding.load(), binding._host) as w:
-        for T in (131072, 131073):                          # two slices of 16 words each
+        for T in list(range(1000, 1500, 50)) + [131072, 131073]:     # two slices of 16 words each
             binding.npd_kd_loss_fwd_bwd(x[:T], mask[:T], teacher_dense=x[:T], grad_out=x[:T], kd_tok=out[:T], tau=2.0)
-        assert [name for name, *_ in w.seen] == ["kept", "cleared"]
+        assert len({(at, n) for _, at, n, _ in w.seen[:10]}) <= 2
+        assert [name for name, *_ in w.seen] == ["kept"] * 11 + ["cleared"]
+        assert w.seen[10][2] == 2 * 4 * ((1 << 22) + 64)
 
 
 def test_capture_takes_no_kept_record(reference, fresh):
