@@ -385,6 +385,7 @@ PyObject* bind(PyObject*, PyObject* args) {
       return nullptr;
     }
   }
+  records().clear();  // (another library counts its calls anew: what they left could pass for words of its first ones)
   Py_INCREF(stream);
   Py_INCREF(kept);
   Py_XSETREF(raw_stream, stream);

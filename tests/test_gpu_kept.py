@@ -230,6 +230,18 @@ def test_sizes_of_records(fresh):
         assert w.seen[10][2] == 2 * 4 * ((1 << 22) + 64)
 
 
+def test_another_library_finds_no_record_of_the_last_one(fresh):
+    """Each library counts its own calls: a record that stayed would hold words with the numbers of the next one's calls."""
+    lib, host = binding.load(), binding._host
+    s = torch.empty((24, 40960), dtype=torch.bfloat16, device=dev())
+    t, mask, out = torch.empty_like(s), torch.ones(24, dtype=torch.uint8, device=dev()), torch.empty(24, device=dev())
+    base = torch.cuda.memory_allocated()
+    with _Watched(lib, host) as w:
+        binding.npd_kd_loss_fwd_bwd(s, mask, teacher_dense=t, grad_out=s, kd_tok=out)
+        assert w.seen[0][0] == "kept" and torch.cuda.memory_allocated() > base
+    assert torch.cuda.memory_allocated() == base
+
+
 def test_capture_takes_no_kept_record(reference, fresh):
     s, mask, kw, want = reference["few"]
     s2, mask2, kw2, want2 = reference["reverse"]
