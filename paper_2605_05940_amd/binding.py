@@ -88,19 +88,20 @@ def load() -> ctypes.CDLL:
         L.npd_teacher_topk.restype = ctypes.c_int
         L.npd_teacher_topk.argtypes = ([ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32,
                                         ctypes.c_uint32] + [_vp] * 5)
-        # entry points that a library of another build (NPD_LIB_PATH) may not have yet; its calls are made without them
+        # entry points that a library of another build (NPD_LIB_PATH) may not have yet; its calls are made without them, by
+        # native code if it has those of the first group
         newer = {"npd_forward_scratch_bytes": (ctypes.c_size_t, []),
                  "npd_workspace_bytes_preferred": (ctypes.c_size_t, []),
-                 "npd_kd_loss_forward": (ctypes.c_int, [_vp] * 12 + [ctypes.c_size_t, _vp]),
-                 "npd_kept_workspace_bytes": (ctypes.c_size_t, [_vp]),
-                 "npd_kd_loss_fwd_bwd_kept": (ctypes.c_int, [_vp] * 13 + [ctypes.c_size_t, _vp])}
+                 "npd_kd_loss_forward": (ctypes.c_int, [_vp] * 12 + [ctypes.c_size_t, _vp])}
+        newest = {"npd_kept_workspace_bytes": (ctypes.c_size_t, [_vp]),
+                  "npd_kd_loss_fwd_bwd_kept": (ctypes.c_int, [_vp] * 13 + [ctypes.c_size_t, _vp])}
         here = os.path.realpath(LIB_PATH) == os.path.realpath(os.path.join(HERE, "libnpd.so"))
-        complete = here or all(hasattr(L, name) for name in newer)
-        for name, (result, more) in newer.items():
-            if complete or hasattr(L, name):
+        native = here or all(hasattr(L, name) for name in newer)
+        for name, (result, more) in {**newer, **newest}.items():
+            if here or hasattr(L, name):
                 getattr(L, name).restype = result
                 getattr(L, name).argtypes = [ctypes.POINTER(KdDesc)] + more
-        _host = _load_host(L) if complete else None
+        _host = _load_host(L) if native else None
         _lib = L
     return _lib
 
@@ -116,10 +117,11 @@ def _load_host(L):
         warnings.warn(f"{HOST_PATH} cannot be loaded ({e}): calls are marshalled by Python code, which is slower; "
                       "`python -m paper_2605_05940_amd.build` builds it", RuntimeWarning)
         return None
-    entries = (L.npd_workspace_bytes, L.npd_workspace_bytes_preferred, L.npd_forward_scratch_bytes, L.npd_kd_loss_fwd_bwd,
-               L.npd_kd_loss_forward, L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag,
-               L.npd_kept_workspace_bytes, L.npd_kd_loss_fwd_bwd_kept)
-    host.bind(_raw_stream, _workspaces, tuple(ctypes.cast(f, _vp).value for f in entries))
+    entries = [L.npd_workspace_bytes, L.npd_workspace_bytes_preferred, L.npd_forward_scratch_bytes, L.npd_kd_loss_fwd_bwd,
+               L.npd_kd_loss_forward, L.npd_segment_reduce, L.npd_delta_ifd_score, L.npd_teacher_topk, L.npd_policy_lag]
+    kept = [getattr(L, name, None) for name in ("npd_kept_workspace_bytes", "npd_kd_loss_fwd_bwd_kept")]
+    addresses = [ctypes.cast(f, _vp).value for f in entries + (kept if all(kept) else [])]
+    host.bind(_raw_stream, _workspaces, tuple(addresses + [0] * (11 - len(addresses))))
     return host
 
 

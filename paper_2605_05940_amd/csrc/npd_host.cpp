@@ -33,7 +33,7 @@ struct Entry {
   decltype(&npd_delta_ifd_score) delta_ifd;
   decltype(&npd_teacher_topk) teacher_topk;
   decltype(&npd_policy_lag) policy_lag;
-  decltype(&npd_kept_workspace_bytes) kept_bytes;
+  decltype(&npd_kept_workspace_bytes) kept_bytes;  // null with a library that has no calls on kept records
   decltype(&npd_kd_loss_fwd_bwd_kept) kd_kept;
 };
 Entry lib;                            // written by bind() under the interpreter lock, before any call
@@ -173,6 +173,10 @@ at::Tensor record_of(size_t bytes, void* stream) {
   }
   return t;
 }
+// bytes of the record that a call on `logits` runs on, 0: on none
+size_t kept_bytes(const at::Tensor& logits, const npd_kd_desc& d, void* stream) {
+  return lib.kept_bytes && logits.get_device() == current_device().index() ? lib.kept_bytes(&d, stream) : 0;
+}
 PyObject* release(PyObject*, PyObject*) {
   records().clear();
   Py_RETURN_NONE;
@@ -262,7 +266,7 @@ PyObject* kd(PyObject*, PyObject* const* a, Py_ssize_t n) {
       if (need) {
         // (first: without memory for it the call runs whole, whatever earlier calls have kept, and so gives the same bits)
         const at::Tensor own = scratch(need);
-        if (const size_t bytes = s.get_device() == current_device().index() ? lib.kept_bytes(&d, stream) : 0) {
+        if (const size_t bytes = kept_bytes(s, d, stream)) {
           const at::Tensor kept = record_of(bytes, stream);  // (held through the call)
           if (kept.defined())
             return call(lib.kd_kept, &d, sp, tp, ip, vp, labels, mask, nullptr, kd_tok, nll, tnll, lse, status, kept.data_ptr(),
@@ -275,7 +279,7 @@ PyObject* kd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (need) {
       const size_t want = lib.workspace_bytes_preferred(&d);
       at::Tensor w;  // (held through the call)
-      if (const size_t bytes = s.get_device() == current_device().index() ? lib.kept_bytes(&d, stream) : 0) {
+      if (const size_t bytes = kept_bytes(s, d, stream)) {
         const at::Tensor kept = record_of(bytes, stream);  // (held through the call)
         if (kept.defined())
           return call(lib.kd_kept, &d, sp, tp, ip, vp, labels, mask, gp, kd_tok, nll, tnll, lse, status, kept.data_ptr(),
@@ -368,11 +372,12 @@ PyObject* policy_lag(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// bind(raw_stream, workspaces, addresses): `addresses` of libnpd's entry points in the order of Entry
+// bind(raw_stream, workspaces, addresses): `addresses` of libnpd's entry points in the order of Entry; 0 for both of the last two:
+// a library without them
 PyObject* bind(PyObject*, PyObject* args) {
   PyObject *stream, *kept, *addresses;
   if (!PyArg_ParseTuple(args, "OO!O!", &stream, &PyDict_Type, &kept, &PyTuple_Type, &addresses)) return nullptr;
-  constexpr int kEntries = 11;
+  constexpr int kEntries = 11, kRequired = 9;
   void* p[kEntries];
   if (PyTuple_GET_SIZE(addresses) != kEntries) {
     PyErr_SetString(PyExc_ValueError, "11 addresses");
@@ -380,8 +385,9 @@ PyObject* bind(PyObject*, PyObject* args) {
   }
   for (int i = 0; i < kEntries; ++i) {
     p[i] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(addresses, i));
-    if (!p[i]) {
-      if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "a null address");
+    if (!p[i] && PyErr_Occurred()) return nullptr;
+    if (i < kRequired ? !p[i] : !p[i] != !p[kRequired]) {
+      PyErr_SetString(PyExc_ValueError, "a null address");
       return nullptr;
     }
   }

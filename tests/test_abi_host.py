@@ -402,6 +402,34 @@ assert last.value >= 777
 """, library=lib)
 
 
+def test_native_marshalling_of_a_library_without_kept_records(tmp_path):
+    """NPD_LIB_PATH may name one whose calls all clear their record: native code makes them all the same."""
+    import subprocess
+    src = tmp_path / "old.c"
+    src.write_text("".join(f"long {n}() {{ return 0; }}\n" for n in binding.EXPORTS if "kept" not in n))
+    lib = tmp_path / "libold.so"
+    subprocess.run(["gcc", "-shared", "-fPIC", "-w", "-o", str(lib), str(src)], check=True)
+    with open(binding.HOST_PATH, "rb") as f:
+        host = f.read()
+    out = _in_a_copy(tmp_path, """
+import torch
+from paper_2605_05940_amd import binding as b
+L = b.load()
+assert b._host is not None and not hasattr(L, "npd_kd_loss_fwd_bwd_kept")
+s = torch.zeros((4, 64), dtype=torch.bfloat16)
+assert b._host.kd(s) == -1
+good = (b._raw_stream, {}, (1,) * 9 + (0, 0))
+b._host.bind(*good)
+for bad in ((1,) * 9, (1,) * 8 + (0, 0, 0), (1,) * 9 + (1, 0), (1,) * 9 + (0, 1)):
+    try:
+        b._host.bind(b._raw_stream, {}, bad)
+    except ValueError:
+        continue
+    raise AssertionError(bad)
+""", library=lib, host=host)
+    assert "RuntimeWarning" not in out
+
+
 def test_workspace_that_a_call_prefers(lib):
     """As much as the record of the shorter slices takes where a call has them, else the least."""
     def ask(V, T, **kw):

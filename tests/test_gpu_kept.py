@@ -242,6 +242,28 @@ def test_another_library_finds_no_record_of_the_last_one(fresh):
     assert torch.cuda.memory_allocated() == base
 
 
+def test_a_library_without_kept_records(reference, fresh):
+    """The native marshalling makes its calls on workspaces that they clear."""
+    w = _Watched(binding.load(), binding._host)
+    binding.workspace_for(1 << 20, dev())
+    binding._host.bind(binding._raw_stream, binding._workspaces, w.real[:9] + (0, 0))
+    try:
+        base = torch.cuda.memory_allocated()
+        for name in CASES:
+            s, mask, kw, want = reference[name]
+            got = _out(s)
+            _call(s, mask, kw, got)
+            torch.cuda.synchronize()
+            assert _same(got, want), name
+        s, mask, kw, _ = reference["topk"]
+        nll = torch.empty(s.shape[0], device=dev())
+        binding.npd_kd_loss_fwd_bwd(s, mask, labels=kw["labels"], nll_tok=nll)
+        del got, nll
+        assert torch.cuda.memory_allocated() == base        # (no record)
+    finally:
+        binding._host.bind(binding._raw_stream, binding._workspaces, w.real)
+
+
 def test_capture_takes_no_kept_record(reference, fresh):
     s, mask, kw, want = reference["few"]
     s2, mask2, kw2, want2 = reference["reverse"]
