@@ -186,15 +186,17 @@ def npd_kd_loss_fwd_bwd(student_logits: torch.Tensor, loss_mask: torch.Tensor, *
 
     The teacher kind follows from which teacher tensors are given; ``grad_out is None`` means forward
     only; ``grad_out`` sharing storage with ``student_logits`` means the in-place gradient.  ``workspace``:
-    a uint8 tensor of at least ``npd_workspace_bytes`` bytes, better of ``npd_workspace_bytes_preferred``; if it is None one
-    is taken from ``workspace_for`` (a per-device tensor that this module keeps and grows) or, with a CE term at tau != 1, for
-    rows that are not 16-byte aligned and for calls that prefer more than is kept, allocated for the call.  Forward-only calls
-    allocate a block of their own where splitting rows pays, and run without it where there is no memory for it.  With the
-    native marshalling, calls outside captures run on a record that it keeps per device and stream instead, with the same results
-    (``npd_kd_loss_fwd_bwd_kept``; eight of 32 MB at most, given back by ``_host.release()``).  Blocks of a
-    call go back to torch's allocator when it returns, so a capture that is not ``torch.cuda.graph``'s should set
-    ``no_workspace`` (``NPD_FLAG_NO_WORKSPACE``: no scratch memory at all) or bring a workspace.  ``noalloc`` calls
-    ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in scratch array; no workspace argument).
+    a uint8 tensor of at least ``npd_workspace_bytes`` bytes, better of ``npd_workspace_bytes_preferred``.  If it is None the
+    native marshalling takes a record that it keeps per device and stream (``npd_kd_loss_fwd_bwd_kept``; eight of 32 MB at
+    most, given back by ``release_records``), or for calls that need more a block allocated for the call.  Under capture, and
+    where the Python code makes the call, one is taken from ``workspace_for`` (a per-device tensor that this module keeps and
+    grows, for calls ordered on one stream) or, with a CE term at tau != 1, for rows that are not 16-byte aligned and for calls
+    that prefer more than is kept, allocated for the call; the results are the same.  Forward-only calls allocate a block of
+    their own where splitting rows pays (those of up to 512 rows are one launch on such a record), and run without it where
+    there is no memory for it.  Blocks of a call go back to torch's allocator when it returns, so a capture that is not
+    ``torch.cuda.graph``'s should set ``no_workspace`` (``NPD_FLAG_NO_WORKSPACE``: no scratch memory at all) or bring a
+    workspace.  ``noalloc`` calls ``npd_kd_loss_fwd_bwd_noalloc`` instead (the library's built-in scratch array; no workspace
+    argument).
     """
     if _host is not None and not noalloc:
         st = _host.kd(student_logits, loss_mask, teacher_dense, teacher_idx, teacher_val, labels, tau, grad_scale,
@@ -302,6 +304,13 @@ def workspace_for(n_bytes: int, device) -> Optional[torch.Tensor]:
         ws = torch.empty(max(n_bytes, _KEPT_BYTES), dtype=torch.uint8, device=device)
         _workspaces[key] = ws
     return ws
+
+
+def release_records() -> None:
+    """Give the scratch records that the native marshalling keeps (one per device and stream, eight of 32 MB at most) back to
+    torch's allocator.  Calls that are under way keep theirs; later ones make new ones."""
+    if _host is not None:
+        _host.release()
 
 
 def npd_workspace_bytes(n_tokens: int, vocab: int, teacher_kind: int = NPD_TEACHER_DENSE_BF16, topk: int = 0,

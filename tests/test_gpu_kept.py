@@ -63,7 +63,7 @@ def fresh():
     binding.load()
     assert binding._host is not None
     torch.cuda.synchronize()
-    host = binding._host
+    host = binding._host                                   # (a test may replace it)
     host.release()
     yield
     torch.cuda.synchronize()
@@ -80,7 +80,7 @@ def test_calls_of_all_kinds_on_one_record(reference, fresh):
         torch.cuda.synchronize()
         assert _same(got, want), name
     base = torch.cuda.memory_allocated()
-    binding._host.release()                                # the record goes back
+    binding.release_records()                              # the record goes back
     assert torch.cuda.memory_allocated() < base
 
 
@@ -214,7 +214,7 @@ def test_streams_that_come_later_have_a_record_too(fresh):
         assert {name for name, _ in at.values()} == {"kept"}
         held = torch.cuda.memory_allocated() - base
         assert held == 8 * ((1 << 18) + 512)                # (the least that a record has)
-    binding._host.release()
+    binding.release_records()
     assert torch.cuda.memory_allocated() == base
 
 
