@@ -144,6 +144,15 @@ static bool skew_long_slices(const KdArgs& a, bool on_lines) {
   return l1_mode(a) == kL1Own || (g_long < g && (a.T * g > 4096 || (a.T * g > 1400 && 7 * g_long <= 6 * g)));
 }
 
+template <int DIVK>
+static hipError_t launch_gang_skew(const KdArgs& a, bool long_slices, hipStream_t stream) {
+  if (long_slices) return launch_gang_dense<DIVK, kGangSkewLongK>(a, stream);
+  // (rows that are shared have 2,292 groups at least, two long slices: kL1Own never comes here)
+  if (l1_mode(a) == kL1Square)
+    return launch_gang_kernel(a, gang_words(4), kd_gang_kernel<kGangSkewK, kDense, kL1Square, DIVK>, stream);
+  return launch_gang_kernel(a, gang_words(2), kd_gang_kernel<kGangSkewK, kDense, kL1None, DIVK>, stream);
+}
+
 hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_bytes, hipStream_t stream) {
   KdArgs a = a0;
   const bool on_lines = rows_on_lines(a);
@@ -175,11 +184,8 @@ hipError_t launch_kd_gang(const KdArgs& a0, int teacher_kind, size_t workspace_b
   if (teacher_kind == kTopk) return launch_gang_topk<kGangTopkK>(a, stream);
   switch (a.divergence) {
     case kReverseKl: return launch_gang_dense<kReverseKl, kGangK>(a, stream);
-    case kSkewKl:
-      return skew_long ? launch_gang_dense<kSkewKl, kGangSkewLongK>(a, stream) : launch_gang_dense<kSkewKl, kGangSkewK>(a, stream);
-    case kSkewReverseKl:
-      return skew_long ? launch_gang_dense<kSkewReverseKl, kGangSkewLongK>(a, stream)
-                       : launch_gang_dense<kSkewReverseKl, kGangSkewK>(a, stream);
+    case kSkewKl: return launch_gang_skew<kSkewKl>(a, skew_long, stream);
+    case kSkewReverseKl: return launch_gang_skew<kSkewReverseKl>(a, skew_long, stream);
     default: return launch_gang_dense<kForwardKl, kGangK>(a, stream);
   }
 }
