@@ -36,7 +36,6 @@ kd_gang_topk_kernel(const KdArgs a) {
   static_assert(!SOLO || !DEALT, "one workgroup takes the whole row");
   constexpr int GB = TH * 16;
   constexpr bool LSE1 = L1 != kL1None;
-  constexpr bool LIST = GRAD;
   constexpr int NS = LSE1 ? 2 : 1;  // student / tau, student at tau = 1
   constexpr int NW3 = NS * 3;
   constexpr int W = 8;              // words of scratch per slice
@@ -56,10 +55,10 @@ kd_gang_topk_kernel(const KdArgs a) {
   // LDS of the row: per group (and per edge element) the first of its support positions (entry + 1, 0: none), per entry
   // the next one of the same group (same encoding, low half) and its element of the group (high half); the student
   // logits at the support positions (bf16 bits), later their final gradient values
-  uint32_t* first = topk_rows + (solo_rows(TH) > 1 ? (threadIdx.x / TH) * topk_lds_words(TH, K, k_top, LIST) : 0);
+  uint32_t* first = topk_rows + (solo_rows(TH) > 1 ? (threadIdx.x / TH) * topk_lds_words(TH, K, k_top, GRAD) : 0);
   uint32_t* link = first + K * TH + kMaxEdges;
-  uint16_t* sup_s = reinterpret_cast<uint16_t*>(LIST ? link + k_top : first);
-  if constexpr (LIST) {  // ordered before their use by the barrier below
+  uint16_t* sup_s = reinterpret_cast<uint16_t*>(GRAD ? link + k_top : first);
+  if constexpr (GRAD) {  // ordered before their use by the barrier below
 #pragma unroll
     for (int k = 0; k < K; ++k) first[k * TH + tid] = 0;
     if (tid < kMaxEdges) first[K * TH + tid] = 0;
@@ -321,14 +320,12 @@ kd_gang_topk_kernel(const KdArgs a) {
             y_hit = 1;
           }
           sup_s[j] = one_bf16(gj);  // this thread read sup_s[j] above: no other thread touches entry j before the barrier
-          if constexpr (LIST) {
-            link[j] = atomicExch(&first[at], (uint32_t)(j + 1)) | ((uint32_t)((id - head) & 7) << 16);
-          }
+          link[j] = atomicExch(&first[at], (uint32_t)(j + 1)) | ((uint32_t)((id - head) & 7) << 16);
         }
       }
     });
   }
-  if constexpr (LIST && NWV == 1) row_sync<TH>();  // the lists before their readers (else: the barrier below)
+  if constexpr (GRAD && NWV == 1) row_sync<TH>();  // the lists before their readers (else: the barrier below)
   float kd = wave_sum_dpp(part_kd);
   bool y_in_support = __builtin_amdgcn_ballot_w64(y_hit != 0) != 0;  // the label is one of the support positions
   if constexpr (NWV > 1) {
@@ -365,7 +362,7 @@ kd_gang_topk_kernel(const KdArgs a) {
   }
 
   if constexpr (!GRAD) return;
-  // ---- sweep 2: dense part p_S * weights from the registers, then the support positions of this slice
+  // ---- sweep 2: dense part p_S * weights from the registers, the label's and the support positions' values put in, one store
   uint8_t* gslice = reinterpret_cast<uint8_t*>(grow + head) + (int64_t)first_group * 16;
   auto store = [&](int k, const uint4& o) {
     const u32x4 w = {o.x, o.y, o.z, o.w};
@@ -379,7 +376,7 @@ kd_gang_topk_kernel(const KdArgs a) {
     if (last && tid < n_edge) grow[sp.edge_elem(tid)] = 0x7fc0;
     return;
   }
-  // the label position of the composite loss, unless it is one of the support positions (patched with them)
+  // the label position of the composite loss, unless it is one of the support positions (put in with them)
   int k_y = -1;
   uint4 y_keep = make_uint4(~0u, ~0u, ~0u, ~0u), y_bits = make_uint4(0, 0, 0, 0);
   uint16_t y_tail = 0;
@@ -425,7 +422,7 @@ kd_gang_topk_kernel(const KdArgs a) {
         opaque(sreg[k]);
         uint4 o = grad8<kTopk, FORM>(sreg[k], sreg[k], kf);
         if (k == k_y) patch_label(o);  // uniform
-        if constexpr (LIST) patch_support(o, first[k * TH + tid]);
+        patch_support(o, first[k * TH + tid]);
         store(k, o);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -443,10 +440,8 @@ kd_gang_topk_kernel(const KdArgs a) {
     const int e = sp.edge_elem(tid);
     uint16_t o = one_bf16(grad_student_elem(bf16_lo(s_e_bits), kf.p));
     if (patch_y && e == y) o = y_tail;
-    if constexpr (LIST) {
-      const uint32_t j1 = first[K * TH + tid];
-      if (j1 != 0) o = sup_s[j1 - 1];
-    }
+    const uint32_t j1 = first[K * TH + tid];
+    if (j1 != 0) o = sup_s[j1 - 1];
     grow[e] = o;
   }
 }
