@@ -302,6 +302,62 @@ def test_a_call_that_gave_up_leaves_nothing_behind(reference, fresh):
         assert _same(got, want), name
 
 
+@pytest.mark.parametrize("route", ["kept", "cleared", "forward"])
+@pytest.mark.parametrize("what", ["forward", "skew", "topk"])
+def test_rows_that_gave_up_are_marked(fresh, route, what):
+    """With a limit of one poll (the waits end at once and the kernel exits) every value is what it should be or NaN, and if there
+    is NaN the flag says so; the next call with the default limit is exact.  Gradient calls on a kept record, on a workspace
+    that the call clears, and forward-only calls in one launch."""
+    T, V = 384, 151936
+    if route == "forward" and what != "forward":
+        pytest.skip("one launch: forward KL and no teacher")
+    g = torch.Generator(device=dev()).manual_seed(23)
+    s = torch.randn((T, V), generator=g, device=dev()).mul_(3.0).to(torch.bfloat16)
+    mask = (torch.rand(T, generator=g, device=dev()) < 0.8).to(torch.uint8)
+    kw = dict(labels=torch.randint(0, V, (T,), generator=g, device=dev(), dtype=torch.int32))
+    t = torch.randn((T, V), generator=g, device=dev()).add_(s).to(torch.bfloat16)
+    if what == "topk":
+        val, idx = torch.topk(t[:, :4096].float(), 24, dim=1)
+        kw.update(teacher_idx=idx.to(torch.int32), teacher_val=val)
+    else:
+        kw.update(teacher_dense=t, **(dict(divergence=2, skew_alpha=0.1) if what == "skew" else {}))
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device=dev()) if route == "cleared" else None
+    lib = binding.load()
+
+    def run():
+        out = [torch.full((T,), -1.0, device=dev()) for _ in range(3)]
+        out.append(torch.full((T,), -1.0, device=dev()) if route == "forward" else torch.full_like(s, float("nan")))
+        status = torch.zeros(1, dtype=torch.int32, device=dev())
+        last = dict(teacher_nll_tok=out[3]) if route == "forward" else dict(grad_out=out[3])
+        binding.npd_kd_loss_fwd_bwd(s, mask, kd_tok=out[0], nll_tok=out[1], lse_tok=out[2], dev_status=status, workspace=ws, **last,
+                                    **kw)
+        torch.cuda.synchronize()
+        return out, int(status.item())
+
+    with _Watched(lib, binding._host) as w:                 # the route that the call takes
+        run()
+        assert w.seen[-1][0] == ("cleared" if route == "cleared" else "kept")
+    good, status = run()
+    assert status == 0 and not any(torch.isnan(x).any() for x in good)
+    lib.npd_debug_gang_spin_limit(1)
+    try:
+        hurried, status = run()
+    finally:
+        lib.npd_debug_gang_spin_limit(0)
+    gave_up = [torch.isnan(x) for x in hurried]
+    for x, y, nan in zip(hurried, good, gave_up):
+        assert (nan | (x == y)).all()
+        assert not nan[mask == 0].any()                     # rows that are not scored wait for nothing
+    rows = sum(int(n.any(dim=1).sum() if n.dim() == 2 else n.sum()) for n in gave_up)
+    print(f"[gave up] {route} {what}: status {status}, {rows} rows and scalars", flush=True)
+    assert status == (8 if rows else 0)
+    if route == "forward":                                  # one workgroup writes the scalars of a row
+        assert all((n == gave_up[0]).all() for n in gave_up)
+    for _ in range(2):
+        again, status = run()
+        assert status == 0 and _same(again, good)
+
+
 def test_what_the_entry_point_refuses(reference):
     lib = binding.load()
     s, mask, kw, want = reference["few"]
