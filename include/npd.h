@@ -136,9 +136,10 @@ const char* npd_status_string(npd_status st);
 const char* npd_kd_kernel_name(const npd_kd_desc* desc);
 
 /*
- * Testing aid: how many times a workgroup of the row-gang kernels polls for the other workgroups of its row before
- * it gives up (NPD_DEV_GANG_TIMEOUT).  polls <= 0 restores the default (about a second).  Returns the previous
- * value.  A tiny limit lets a test reach the give-up path while every kernel still ends normally.  Process-wide.
+ * Testing aid: how many times a workgroup that waits for the other workgroups of its row polls before it gives up
+ * (NPD_DEV_GANG_TIMEOUT): the row-gang kernels, and forward-only calls of npd_kd_loss_fwd_bwd_kept().  polls <= 0 restores
+ * the default (about a second).  Returns the previous value.  A tiny limit lets a test reach the give-up path while every
+ * kernel still ends normally.  Process-wide.
  */
 int npd_debug_gang_spin_limit(int polls);
 
@@ -232,7 +233,9 @@ npd_status npd_kd_loss_fwd_bwd(const npd_kd_desc* desc, const void* student_logi
  *                    calls of this entry point, which must be ordered on one stream
  * A stream under capture is NPD_ERR_UNSUPPORTED, with nothing enqueued.  Results are those of
  * npd_kd_loss_fwd_bwd with the workspace npd_workspace_bytes_preferred() asks for, of
- * npd_kd_loss_forward with its scratch, bit by bit.
+ * npd_kd_loss_forward with its scratch, bit by bit.  Forward-only calls wait for the other workgroups
+ * of a row here (those of npd_kd_loss_forward do not): a wait that runs out makes the row's scalars NaN
+ * and sets NPD_DEV_GANG_TIMEOUT, as in gradient calls.
  */
 npd_status npd_kd_loss_fwd_bwd_kept(const npd_kd_desc* desc, const void* student_logits,
                                     const void* teacher_dense, const int32_t* teacher_idx,

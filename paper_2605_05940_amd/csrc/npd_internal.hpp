@@ -37,7 +37,8 @@ struct KdArgs {
   int32_t divergence;  // Divergence
   float alpha;         // skew coefficient
   // row-gang kernels (npd_kd_gang.hpp), split rows (npd_kd_split.hip)
-  uint32_t* ws;          // scratch record, gang_workspace_bytes() or split_scratch_bytes() bytes
+  uint32_t* ws;          // scratch record, gang_workspace_bytes() or split_scratch_bytes() bytes; with a tag twice as many, as its
+                         // words are 64 bits, and for split rows kGangTailWords words more (a gang's record always has them)
   int32_t gang;          // slices (workgroups) per row
   int32_t gang_groups;   // 128-bit groups per slice
   uint32_t tag;          // != 0: the record needs no clearing, its words carry this number (npd_kd_gang.hpp)

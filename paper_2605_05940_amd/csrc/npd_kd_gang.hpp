@@ -307,7 +307,9 @@ __device__ __forceinline__ float skew_grad(float xs, float xt, const SkewCoef& k
   return __builtin_fmaf(v, k.Av, k.B * p);
 }
 
-// K: groups per thread and tensor a workgroup holds (a slice has at most a.gang_groups + 7 <= K * 256 - 1 groups).
+// K: groups per thread and tensor a workgroup holds.  A slice that is one run has at most a.gang_groups + shift <= K * 256 groups;
+// dealt pieces cover the nvec + shift <= G * K * 256 groups from the boundary that the first one begins on (shift: 0 where all
+// rows begin on 128-byte boundaries, else up to 7 groups, for which every slice is sized to 8 groups less).
 // L1: what is summed at tau = 1 beside the sums at tau -- 0 nothing (tau = 1, or no such output wanted), kL1Own with
 // exponentials of their own, kL1Square (tau = 2) from squares of the exponentials at tau.  Measured (MI355X, 4,096 x
 // 151,936, dense teacher, composite loss at tau = 2): one workgroup per row, both sweeps from memory 738 us; shared

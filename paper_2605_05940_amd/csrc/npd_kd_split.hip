@@ -5,9 +5,9 @@
 // Why: with a workgroup per row a row takes as long as one compute unit needs for it, which is its vector instructions
 // (17 us for the 151,936 pairs of logits of a dense teacher) behind the latency of its first loads; rows that are
 // fewer than the compute units leave the others idle, and the last rows of many leave most of them idle.  A slice is read,
-// summed once and gone; nothing waits for another workgroup.  The second launch costs about 2.5 us: calls of few rows on a kept
-// record whose words carry the launch's number (KdArgs::tag, npd_kd_gang.hpp) have none, the last slice of a row waits for the
-// others' partials and merges them (forward progress and bounded waits as there).
+// summed once and gone; with two launches nothing waits for another workgroup.  The second launch costs about 2.5 us: calls of few
+// rows on a kept record whose words carry the launch's number (KdArgs::tag, npd_kd_gang.hpp) have none, there the last slice of a
+// row waits for the others' partials and merges them (forward progress and bounded waits as in npd_kd_gang.hpp).
 #include "npd_kd_gang.hpp"
 
 namespace npd {
